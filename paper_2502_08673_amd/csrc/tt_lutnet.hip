@@ -59,9 +59,9 @@ constexpr int kCopyRows = 8;  // rows per wave with their loads in flight togeth
 // `stride` bytes at dst, each element ANDed with its column's entry of
 // colmask (when given).  Wave w takes rows w, w + waves, ... and lane l the
 // columns l, l + 64, ...; a wave issues kCopyRows rows' loads before its
-// first LDS store.
+// first LDS store.  Rows up to `pad` are filled with zeros.
 template <typename T>
-__device__ __forceinline__ void rows_to_lds(const T* src, int rows, int per_row, uint8_t* dst, int stride,
+__device__ __forceinline__ void rows_to_lds(const T* src, int rows, int pad, int per_row, uint8_t* dst, int stride,
                                             const T* colmask) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
@@ -70,7 +70,7 @@ __device__ __forceinline__ void rows_to_lds(const T* src, int rows, int per_row,
     const int c = c0 + lane;
     const bool cok = c < per_row;
     const T m = colmask && cok ? colmask[c] : (T)~T(0);
-    for (int r0 = wave; r0 < rows; r0 += nw * kCopyRows) {
+    for (int r0 = wave; r0 < pad; r0 += nw * kCopyRows) {
       T v[kCopyRows];
 #pragma unroll
       for (int u = 0; u < kCopyRows; ++u) {
@@ -80,7 +80,7 @@ __device__ __forceinline__ void rows_to_lds(const T* src, int rows, int per_row,
 #pragma unroll
       for (int u = 0; u < kCopyRows; ++u) {
         const int r = r0 + u * nw;
-        if (cok && r < rows) reinterpret_cast<T*>(dst + r * stride)[c] = (T)(v[u] & m);
+        if (cok && r < pad) reinterpret_cast<T*>(dst + r * stride)[c] = (T)(v[u] & m);
       }
     }
   }
@@ -130,7 +130,9 @@ __global__ __launch_bounds__(kNetThreads) void lutnet_fused_kernel(NetArgs a, co
   const long s0 = (long)blockIdx.x * kNetSamples;
   const int ns = (int)min((long)kNetSamples, (long)a.batch - s0);
   // the samples' input rows into LDS, each code reduced to the digits its
-  // readers take when they all take the same number (then no reader masks)
+  // readers take when they all take the same number (then no reader masks).
+  // Every lane looks tables up, so the rows past the batch are zeros: what
+  // LDS held before would index past the tables.
   if (a.sample) {
     // drawn: bytes 8m .. 8m + 7 of row r are the bytes of output
     // (first + s0 + r) Q + m + 1 of the stream, masked per column.  With
@@ -145,8 +147,10 @@ __global__ __launch_bounds__(kNetThreads) void lutnet_fused_kernel(NetArgs a, co
     if (sub < RP) {
       uint64_t mk0 = 0;
       if (m0 < Q && 8 * m0 + 8 <= a.n_inputs) mk0 = *reinterpret_cast<const uint64_t*>(a.in_mask + 8 * m0);
-      for (int r = wave * RP + sub; r < ns; r += nwaves * RP)
+      for (int r = wave * RP + sub; r < kNetSamples; r += nwaves * RP)
         for (int m = m0; m < Q; m += 64) {
+          // (rows past the batch take the draws that would follow: masked
+          // as the others are, and not kept)
           const uint64_t z = splitmix64_at(smp.seed, (smp.first + (uint64_t)(s0 + r)) * (uint64_t)Q + m + 1);
           uint8_t* dst = sig + r * a.stride + 8 * m;
           if (8 * m + 8 <= a.n_inputs) {
@@ -159,10 +163,10 @@ __global__ __launch_bounds__(kNetThreads) void lutnet_fused_kernel(NetArgs a, co
         }
     }
   } else if ((a.n_inputs & 3) == 0 && ((uintptr_t)a.inputs & 3) == 0) {
-    rows_to_lds<uint32_t>(reinterpret_cast<const uint32_t*>(a.inputs + s0 * a.n_inputs), ns, a.n_inputs / 4, sig,
-                          a.stride, reinterpret_cast<const uint32_t*>(a.in_mask));
+    rows_to_lds<uint32_t>(reinterpret_cast<const uint32_t*>(a.inputs + s0 * a.n_inputs), ns, kNetSamples,
+                          a.n_inputs / 4, sig, a.stride, reinterpret_cast<const uint32_t*>(a.in_mask));
   } else {
-    rows_to_lds<uint8_t>(a.inputs + s0 * a.n_inputs, ns, a.n_inputs, sig, a.stride, a.in_mask);
+    rows_to_lds<uint8_t>(a.inputs + s0 * a.n_inputs, ns, kNetSamples, a.n_inputs, sig, a.stride, a.in_mask);
   }
   if (threadIdx.x < kNetSamples) sig[threadIdx.x * a.stride + a.n_inputs + a.n] = 0;
   __syncthreads();

@@ -263,3 +263,39 @@ def test_sample_rejects_a_per_level_network():
         count = torch.zeros(1, dtype=torch.int32, device="cuda")
         with pytest.raises(tt.TTError):
             net.sample({}, 1, 0, 64, None, None, count)
+
+
+@pytest.mark.parametrize("batch", [1, 29, 63, 349])
+@pytest.mark.parametrize("P", [92, 93])
+def test_ragged_batch_lanes_stay_inside_the_tables(batch, P):
+    """Blocks with fewer samples than lanes: the lanes past the batch look
+    tables up as well, so their signal rows must hold codes and not what LDS
+    held before (an enumeration with full int8 weights, whose mask tables
+    fill it, runs first).  Inputs in range, so that no read masks its code;
+    evaluation and sampling."""
+    dirty = random_neurons(seed=641, n=600, F=(4, 4), b=(4, 4), o=(3, 3), max_fb=16)
+    ddesc = tt.descriptors(dirty)
+    dtotal = tt.layout(ddesc)
+    dtab = device_tables(dtotal)
+    ns = random_neurons(seed=642, n=102, F=(5, 5), b=(2, 2), o=(2, 2), max_fb=10, wmax=7, bias_max=8)
+    rng = np.random.default_rng(643)
+    fanin = np.full((len(ns), 8), -1, np.int32)
+    for i in range(len(ns)):
+        fanin[i, :5] = rng.integers(0, P + i, size=5)
+    inputs = rng.integers(0, 4, size=(batch, P)).astype(np.uint8)
+    tt.enumerate(ddesc, dtab, total_words=dtotal)
+    got = run(ns, fanin, P, inputs)
+    assert np.array_equal(got, lutnet.evaluate(ns, [f[:5] for f in fanin], P, inputs))
+    desc = tt.descriptors(ns)
+    total = tt.layout(desc)
+    tables = device_tables(total)
+    tt.enumerate(desc, tables, total_words=total)
+    tt.enumerate(ddesc, dtab, total_words=dtotal)
+    found = torch.zeros((batch, P), dtype=torch.uint8, device="cuda")
+    draw = torch.zeros(batch, dtype=torch.int64, device="cuda")
+    count = torch.zeros(1, dtype=torch.int32, device="cuda")
+    with tt.Lutnet(desc, fanin, P, tables, total) as net:
+        net.sample({}, 5, 0, batch, found, draw, count)  # no targets: every draw is kept, none past the batch
+        torch.cuda.synchronize()
+    assert int(count.item()) == batch
+    assert sorted(draw.cpu().tolist()) == list(range(batch))
