@@ -281,7 +281,7 @@ def main():
     torch.cuda.synchronize()
     plan.kernel_times_ms()
 
-    issued_ops = _mfma_issued_ops(ns, info["tile_neurons"])
+    issued_ops = _mfma_issued_ops(ns)
     useful_ops = sum(2 * int(f) * (1 << max(0, int(f) * int(b) - 6)) for f, b in zip(ns.F, ns.b))
 
     achieved = table_bytes / (kernel_ms * 1e-3) / 1e9
@@ -312,7 +312,7 @@ def main():
         "roofline": {
             "bound": "hbm",
             "kernel": ("enum_wide_kernel" if info["wide_neurons"] == n else
-                       "enum_kernel" if info["wide_neurons"] == 0 else "enum_wide_kernel + enum_kernel"),
+                       "enum_small_kernel" if info["wide_neurons"] == 0 else "enum_wide_kernel + enum_small_kernel"),
             "achieved": achieved,
             "peak": HBM_PEAK_GBS,
             "unit": "GB/s",
@@ -823,22 +823,14 @@ def bench_screen(args):
     }
 
 
-WIDE_MIN_LOG2 = 12  # groups with 2^12 or more words per plane use the wide kernel
-
-
-def _mfma_issued_ops(ns, tile_neurons):
-    """int8 MFMA ops issued per launch: one 32x32x16 product per tile of up
-    to tile_neurons neurons x 32 words (unused rows included), or for wide
-    groups one 16x16x32 product per 256 words of one neuron."""
-    from collections import Counter
-    groups = Counter((int(f), int(b), int(o)) for f, b, o in zip(ns.F, ns.b, ns.o))
+def _mfma_issued_ops(ns):
+    """int8 MFMA ops issued per launch: one 16x16x32 product per 256 words of
+    one neuron, for tables of at least 256 words per plane (shorter ones sum
+    per lane)."""
     ops = 0
-    for (f, b, o), cnt in groups.items():
-        w = max(1, (1 << (f * b)) // 64)
-        if f * b - 6 >= WIDE_MIN_LOG2:
-            ops += cnt * (w // 256) * 16 * 16 * 32 * 2
-        else:
-            ops += ((cnt + tile_neurons - 1) // tile_neurons) * ((w + 31) // 32) * 32 * 32 * 16 * 2
+    for f, b in zip(ns.F, ns.b):
+        w = max(1, (1 << (int(f) * int(b))) // 64)
+        ops += (w // 256) * 16 * 16 * 32 * 2
     return ops
 
 

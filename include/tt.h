@@ -122,8 +122,9 @@ uint64_t tt_words_per_plane(int F, int b);
  * total_words uint64 words; every neuron's o*W words at word_off must lie
  * inside it and ranges must not overlap).  If d_hist is not NULL it receives
  * hist[i*8 + v] = number of rows of neuron i with q = v (bins >= 2^o are 0).
- * One-shot ("plain") path: descriptors are grouped by (F, b, o) and each
- * group is enumerated by its own pair of kernel launches. */
+ * One-shot ("plain") path: the neurons of fewer than 2^12 words per plane
+ * take one launch together; the others a preparation launch and one per
+ * (F, b, o) group. */
 int tt_enumerate(const tt_neuron* h_desc, int n, uint64_t* d_tables, uint64_t total_words,
                  uint32_t* d_hist, void* stream);
 
@@ -135,13 +136,13 @@ int tt_enumerate(const tt_neuron* h_desc, int n, uint64_t* d_tables, uint64_t to
  * library instead of a stream-ordered allocation.  The call makes no
  * hipMalloc/hipFree or other allocating device call; it copies the staged
  * descriptors from host memory with hipMemcpyAsync.
- *  - Limit: an input whose workspace exceeds the array returns TT_ESCRATCH
- *    before any device work.  The workspace is about 128 B per neuron, plus
- *    8 B per mask-table entry (per neuron: the sum over its low six row bits
- *    of |w_j| * 2^(bit within digit j), plus 2; at most 2306), plus about
- *    2 KiB per tile of up to 32 neurons of one (F, b, o).  For example, 8192
- *    neurons of up to 16 input bits with |w| <= 7 need about 3 MiB, and
- *    about 1800 neurons with the largest mask table fill the array.
+ *  - Limit: an input whose counted bytes exceed the array returns
+ *    TT_ESCRATCH before any device work.  Counted are about 128 B per neuron,
+ *    plus 8 B per mask-table entry (per neuron: the sum over its low six row
+ *    bits of |w_j| * 2^(bit within digit j), plus 2; at most 2306), plus about
+ *    2 KiB per 32 neurons of one (F, b, o).  For example, 8192 neurons of up
+ *    to 16 input bits with |w| <= 7 count about 3 MiB, and about 1800 neurons
+ *    with the largest mask table fill the array.
  *  - Each device holds its own copy of the array from the first call on it
  *    until the process ends.  All calls on one device share it and it keeps
  *    the last call's contents (nothing in it needs to start at zero).  Calls
@@ -171,18 +172,20 @@ int tt_support(const tt_neuron* h_desc, int n, const uint64_t* d_tables, uint64_
 
 typedef struct tt_plan tt_plan;
 
-/* Launch configuration of the batched enumerator. */
+/* Launch configuration of the batched enumerator.  chunk_words and waves
+ * shape the blocks of the wide kernel (tt_plan_wide_neurons): blocks of
+ * `waves` waves, max(1, chunk_words / (256 * waves)) 256-word units each. */
 typedef struct tt_tune {
-  int chunk_words;   /* words per work item along a neuron's rows (multiple of 32) */
-  int blocks_per_cu; /* persistent workgroups per compute unit */
+  int chunk_words;   /* words per block along a neuron's rows (multiple of 32) */
+  int blocks_per_cu; /* 1..8; without effect */
   int waves;         /* waves per workgroup: 4 or 8 */
   int nontemporal;   /* 1: streaming (non-temporal) table stores */
-  int tile_neurons;  /* neurons per work tile: 8, 16 or 32 (fewer neurons per
-                        tile = fewer concurrent output streams, longer runs) */
+  int tile_neurons;  /* 8, 16 or 32; without effect */
 } tt_tune;
 
-#define TT_PLAN_PERSISTENT 1u /* one launch over an LPT-ordered work queue */
-#define TT_PLAN_GRAPH 2u      /* replay the launches from a captured hipGraph */
+#define TT_PLAN_PERSISTENT 1u /* the batched form; without it the same launches are made */
+#define TT_PLAN_GRAPH 2u      /* replay the launches from a captured hipGraph (a
+                                 single launch is made directly) */
 #define TT_PLAN_TIMING 4u     /* record HIP events around the enumeration
                                  kernel of every launch (not with GRAPH) */
 
@@ -194,7 +197,8 @@ int tt_plan_create(const tt_neuron* h_desc, int n, uint64_t total_words, const t
 
 /* Enqueue the enumeration of the plan's neurons into d_tables (and d_hist if
  * not NULL).  With TT_PLAN_GRAPH the first launch (and any launch with
- * different pointers) captures a graph; later launches replay it.  Calls on
+ * different pointers) captures a graph; later launches replay it (a plan
+ * whose work is one launch makes that launch instead).  Calls on
  * one plan must not overlap in time (they share the plan's workspace). */
 int tt_plan_launch(tt_plan* plan, uint64_t* d_tables, uint32_t* d_hist, void* stream);
 
@@ -202,7 +206,7 @@ int tt_plan_launch(tt_plan* plan, uint64_t* d_tables, uint32_t* d_hist, void* st
  * (enumeration, with the histogram when d_hist is not NULL) followed by
  * tt_plan_support_enumerated into d_support (skipped when NULL).  The
  * support of neurons whose sums span fewer than 512 values is decided by
- * the enumeration's own preparation pass; the others take one more kernel.
+ * the enumeration's own launches; the others take one more kernel.
  * With TT_PLAN_GRAPH the whole step is captured once into one hipGraph and
  * replayed; it is captured again when a pointer changes.  With
  * TT_PLAN_TIMING (and no graph) the enumeration kernels are timed as in
@@ -238,13 +242,14 @@ int tt_plan_support_enumerated(tt_plan* plan, const uint64_t* d_tables, uint8_t*
  * last 256).  *count receives how many were written. */
 int tt_plan_kernel_times(tt_plan* plan, float* h_ms, int max_count, int* count);
 
-/* Report the plan's configuration and size. */
+/* Report the plan's configuration and size: the neurons of the small kernel
+ * (those that are not wide), the distinct (F, b, o), and the small kernel's
+ * blocks (-1 without TT_PLAN_PERSISTENT). */
 int tt_plan_info(const tt_plan* plan, tt_tune* tune, int* n_items, int* n_groups, int* grid);
 
 /* Number of the plan's neurons with at least 2^12 words per plane
  * (F*b >= 18).  Their tables are written by the wide kernel, one wave per
- * 256 words of one neuron with no work queue; the tune settings apply to the
- * other neurons.  TT_EINVAL for a NULL argument. */
+ * 256 words of one neuron; the others take a wave or a block each.  TT_EINVAL for a NULL argument. */
 int tt_plan_wide_neurons(const tt_plan* plan, int* n_wide);
 
 /* Time candidate tt_tune settings on the given descriptors and table buffer

@@ -117,10 +117,9 @@ int lut_cap_of(const tt_neuron& d) {
 }
 
 // ---------------------------------------------------------------- planner
-struct Group {
-  int item_begin = 0, item_end = 0;
+struct Group {  // the wide neurons of one (F, b, o)
   int neuron_begin = 0, neuron_end = 0;  // into group_neurons
-  int wide_wb = 0;                       // > 0: enumerated by the wide kernel (log2 words per plane)
+  int wide_wb = 0;                       // log2 words per plane
   int wide_lds = 0;                      // its largest mask table (entries)
   int wide_upw = 1;                      // 256-word units per wave
   int o = 1;
@@ -132,22 +131,30 @@ struct PlanHost {
   tt_tune tune{};
   unsigned flags = 0;
   std::vector<tt_neuron> desc;
-  std::vector<uint64_t> lut_off;
-  std::vector<int32_t> lut_cap;
+  // wide neurons (empty arrays when there are none)
+  std::vector<uint64_t> lut_off;  // [n]
+  std::vector<int32_t> lut_cap;   // [n]
   uint64_t lut_total = 0;
   int lut_chunks = 1;  // the largest mask table in 64-entry chunks
-  std::vector<TileInfo> tiles;
-  std::vector<int32_t> tile_neuron;
-  std::vector<int32_t> tile_lds;  // [n] LDS entry base of the neuron's mask table in its tile
-  std::vector<int32_t> tile_pos;  // [n] position in tile_neuron, -1 for wide-group neurons
-  std::vector<int32_t> sup_lists;  // neurons for the support from parameters: small ranges first
-  int64_t sup_small = 0;           // how many of them have sums spanning < 512 values
-  std::vector<WorkItem> items;
   std::vector<Group> groups;
   std::vector<int32_t> group_neurons;
+  // the others, in the order their kernel takes them (reserved = index)
+  std::vector<tt_neuron> small;
+  int n_block = 0;                    // how many take a block each
+  int wave_lds = 0, block_lds = 0;    // largest mask table of each class
+  std::vector<int32_t> mid, tiny;     // places in small by the span of their sums
+  int n_groups = 0;                   // distinct (F, b, o)
+  std::vector<int32_t> sup_lists;  // neurons for the support from parameters: small ranges first
+  int64_t sup_small = 0;           // how many of them have sums spanning < 512 values
   std::vector<int32_t> large;  // neurons whose tables the support kernels take wave by wave
   long max_chunks = 1, max_items = 1;
 };
+
+int sum_range_of(const tt_neuron& d) {
+  int R = 0;
+  for (int j = 0; j < d.F; ++j) R += std::abs((int)d.w[j]) * ((1 << d.b) - 1);
+  return R;
+}
 
 // Neurons with more than kSmallTableWords words per plane.
 // Also the most check items any of them has per check: 512-word chunks
@@ -157,17 +164,12 @@ struct PlanHost {
 void build_large_list(PlanHost& P) {
   // neurons for the support from parameters: those whose sums span fewer
   // than 512 values first (one wave each), then the others
-  auto range_of = [&](const tt_neuron& d) {
-    int R = 0;
-    for (int j = 0; j < d.F; ++j) R += std::abs((int)d.w[j]) * ((1 << d.b) - 1);
-    return R;
-  };
   P.sup_lists.clear();
   for (int i = 0; i < P.n; ++i)
-    if (range_of(P.desc[i]) < 512) P.sup_lists.push_back(i);
+    if (sum_range_of(P.desc[i]) < 512) P.sup_lists.push_back(i);
   P.sup_small = (int64_t)P.sup_lists.size();
   for (int i = 0; i < P.n; ++i)
-    if (range_of(P.desc[i]) >= 512) P.sup_lists.push_back(i);
+    if (sum_range_of(P.desc[i]) >= 512) P.sup_lists.push_back(i);
   P.large.clear();
   P.max_chunks = 1;
   P.max_items = 1;
@@ -187,166 +189,138 @@ void build_large_list(PlanHost& P) {
   }
 }
 
+// One 256-word unit per wave and eight waves per block, streaming stores:
+// 0.33 ms for the 2 GiB of 512 neurons of 2^24 rows, where four waves of four
+// units take 0.37 ms (more blocks in flight, shorter bursts of each).
 tt_tune default_tune() {
   tt_tune t;
-  t.chunk_words = 4096;
+  t.chunk_words = 2048;
   t.blocks_per_cu = 2;
-  t.waves = 4;
+  t.waves = 8;
   t.nontemporal = 1;
-  t.tile_neurons = kTileM;
+  t.tile_neurons = 32;
   return t;
 }
 
 int check_tune(const tt_tune& t) {
-  // at most 2^16 words per item keeps a lane's 16-bit threshold counts exact
-  if (t.chunk_words < kTileN || t.chunk_words % kTileN || t.chunk_words > (1 << 16)) return TT_EINVAL;
+  // at most kWideMaxUpw units per wave keep a lane's 16-bit threshold counts exact
+  if (t.chunk_words < 32 || t.chunk_words % 32 || t.chunk_words > (1 << 16)) return TT_EINVAL;
   if (t.blocks_per_cu < 1 || t.blocks_per_cu > 8) return TT_EINVAL;
   if (t.waves != 4 && t.waves != 8) return TT_EINVAL;
-  if (t.tile_neurons != 8 && t.tile_neurons != 16 && t.tile_neurons != kTileM) return TT_EINVAL;
+  if (t.tile_neurons != 8 && t.tile_neurons != 16 && t.tile_neurons != 32) return TT_EINVAL;
   return TT_OK;
 }
 
-void build_plan(PlanHost& P, bool persistent) {
+// A neuron of the small kernel takes a block when its tables have 512 words
+// or more per plane (two or four 256-word units) or its mask table exceeds a
+// wave's share of LDS (kSmallWaveLut entries; only weights near the int8 limits
+// do), else a wave.
+bool takes_block(uint64_t W, int cap) {
+  return W >= 512 || (W > (uint64_t)kDirectWords && cap > kSmallWaveLut);
+}
+
+void build_plan(PlanHost& P) {
   const int n = P.n;
-  P.lut_off.resize(n);
-  P.lut_cap.resize(n);
-  uint64_t acc = 0;
+  // The (F, b, o) groups, in first-seen order; members of the wide ones.
+  int group_of[9][5][4];
+  std::memset(group_of, -1, sizeof(group_of));
+  std::vector<std::vector<int>> wide;
+  P.n_groups = 0;
+  P.lut_total = 0;
   P.lut_chunks = 1;
+  // Small neurons by class, then by work (words per plane, thresholds),
+  // heaviest first: a counting sort over 2 x 16 x 4 keys.
+  constexpr int kKeys = 128;
+  auto key_of = [&](const tt_neuron& d, uint64_t W, int cap) {
+    const int lw = 63 - __builtin_clzll(W);
+    return (takes_block(W, cap) ? 0 : 64) + (15 - lw) * 4 + (3 - (int)d.o);
+  };
+  std::vector<int16_t> key(n);
+  std::vector<int32_t> at(kKeys + 1, 0);
   for (int i = 0; i < n; ++i) {
-    P.lut_cap[i] = lut_cap_of(P.desc[i]);
-    P.lut_chunks = std::max(P.lut_chunks, (P.lut_cap[i] + 63) / 64);
-    P.lut_off[i] = acc;
-    acc += (uint64_t)P.lut_cap[i];
-  }
-  P.lut_total = acc;
-
-  // Group by (F, b, o) in first-seen order.
-  std::map<std::tuple<int, int, int>, int> key_to_group;
-  std::vector<std::vector<int>> members;
-  for (int i = 0; i < n; ++i) {
-    auto key = std::make_tuple((int)P.desc[i].F, (int)P.desc[i].b, (int)P.desc[i].o);
-    auto it = key_to_group.find(key);
-    int g;
-    if (it == key_to_group.end()) {
-      g = (int)members.size();
-      key_to_group[key] = g;
-      members.emplace_back();
-    } else {
-      g = it->second;
+    const tt_neuron& d = P.desc[i];
+    const uint64_t W = words_of(d.F, d.b);
+    int& g = group_of[d.F][d.b][d.o];
+    const bool is_wide = W >= (1ull << kWideMinLog2);
+    if (g == -1) {
+      g = is_wide ? (int)wide.size() : 0;
+      if (is_wide) wide.emplace_back();
+      ++P.n_groups;
     }
-    members[g].push_back(i);
-  }
-
-  P.tiles.clear();
-  P.tile_neuron.clear();
-  P.tile_lds.assign(n, 0);
-  P.items.clear();
-  P.groups.clear();
-  P.group_neurons.clear();
-  for (const auto& mem : members) {
-    Group G;
-    G.neuron_begin = (int)P.group_neurons.size();
-    for (int i : mem) P.group_neurons.push_back(i);
-    G.neuron_end = (int)P.group_neurons.size();
-    G.item_begin = (int)P.items.size();
-    const tt_neuron& d0 = P.desc[mem[0]];
-    const uint64_t W = words_of(d0.F, d0.b);
-    G.o = d0.o;
-    if (W >= (1ull << kWideMinLog2)) {  // no tiles: one wave per 256 words
-      G.wide_wb = d0.F * d0.b - 6;
-      for (int i : mem) G.wide_lds = std::max(G.wide_lds, (int)P.lut_cap[i]);
-      // blocks of the tuned number of waves; units per wave from the tuned
-      // words per item: chunk_words / (256 * waves), a power of two in
-      // [1, kWideMaxUpw] with waves * upw at most the neuron's units
-      const int nw = P.tune.waves;
-      int upw = 1;
-      while (upw * 2 <= P.tune.chunk_words / (256 * nw) && upw * 2 <= kWideMaxUpw) upw *= 2;
-      while (upw > 1 && nw * upw > (1 << (G.wide_wb - 8))) upw /= 2;
-      G.wide_upw = upw;
-      G.item_end = G.item_begin;
-      P.groups.push_back(G);
+    if (is_wide) {
+      wide[g].push_back(i);
+      key[i] = -1;
       continue;
     }
-    size_t pos = 0;
-    while (pos < mem.size()) {
-      TileInfo ti{};
-      ti.first = (int32_t)P.tile_neuron.size();
-      ti.W = (int32_t)W;
-      ti.F = d0.F;
-      ti.b = d0.b;
-      ti.o = d0.o;
-      int lds = 0, cnt = 0;
-      while (pos < mem.size() && cnt < P.tune.tile_neurons) {
-        const int c = P.lut_cap[mem[pos]];
-        if (cnt > 0 && lds + c > kLutLdsEntries) break;
-        P.tile_neuron.push_back(mem[pos]);
-        P.tile_lds[mem[pos]] = lds;
-        lds += c;
-        ++cnt;
-        ++pos;
-      }
-      for (int k = cnt; k < kTileM; ++k) P.tile_neuron.push_back(-1);
-      ti.count = cnt;
-      ti.lut_total = lds;
-      const int tile_id = (int)P.tiles.size();
-      P.tiles.push_back(ti);
-      const uint64_t chunk = (uint64_t)P.tune.chunk_words;
-      for (uint64_t h0 = 0; h0 < W; h0 += chunk) {
-        WorkItem wi{};
-        wi.tile = tile_id;
-        wi.h0 = (int32_t)h0;
-        wi.count = (int32_t)std::min<uint64_t>(chunk, W - h0);
-        P.items.push_back(wi);
-      }
+    const int cap = lut_cap_of(d);
+    key[i] = (int16_t)key_of(d, W, cap);
+    ++at[key[i] + 1];
+    if (W > (uint64_t)kDirectWords) {
+      int& most = takes_block(W, cap) ? P.block_lds : P.wave_lds;
+      most = std::max(most, cap);
     }
-    G.item_end = (int)P.items.size();
+  }
+  for (int k = 0; k < kKeys; ++k) at[k + 1] += at[k];
+  P.n_block = at[64];
+  P.small.resize(at[kKeys]);
+  for (int i = 0; i < n; ++i) {
+    if (key[i] < 0) continue;
+    tt_neuron& d = P.small[at[key[i]]++];
+    d = P.desc[i];
+    d.reserved = (uint64_t)i;
+  }
+  P.groups.clear();
+  P.group_neurons.clear();
+  if (wide.empty()) return;
+  P.lut_off.assign(n, 0);
+  P.lut_cap.assign(n, 0);
+  for (const auto& mem : wide) {
+    Group G;
+    G.neuron_begin = (int)P.group_neurons.size();
+    for (int i : mem) {
+      P.group_neurons.push_back(i);
+      P.lut_cap[i] = lut_cap_of(P.desc[i]);
+      P.lut_off[i] = P.lut_total;
+      P.lut_total += (uint64_t)P.lut_cap[i];
+      P.lut_chunks = std::max(P.lut_chunks, (P.lut_cap[i] + 63) / 64);
+      G.wide_lds = std::max(G.wide_lds, (int)P.lut_cap[i]);
+    }
+    G.neuron_end = (int)P.group_neurons.size();
+    const tt_neuron& d0 = P.desc[mem[0]];
+    G.o = d0.o;
+    G.wide_wb = d0.F * d0.b - 6;
+    // blocks of the tuned number of waves; units per wave from the tuned
+    // words per item: chunk_words / (256 * waves), a power of two in
+    // [1, kWideMaxUpw] with waves * upw at most the neuron's units
+    const int nw = P.tune.waves;
+    int upw = 1;
+    while (upw * 2 <= P.tune.chunk_words / (256 * nw) && upw * 2 <= kWideMaxUpw) upw *= 2;
+    while (upw > 1 && nw * upw > (1 << (G.wide_wb - 8))) upw /= 2;
+    G.wide_upw = upw;
     P.groups.push_back(G);
   }
-  // Mask tables in tile order (each tile's back to back, as in its LDS copy),
-  // then the wide groups' neurons; tile positions of the tile members.
-  P.tile_pos.assign(n, -1);
-  acc = 0;
-  for (TileInfo& ti : P.tiles) {
-    ti.lut_base_lo = (uint32_t)acc;
-    ti.lut_base_hi = (uint32_t)(acc >> 32);
-    for (int m = 0; m < ti.count; ++m) {
-      const int idx = P.tile_neuron[ti.first + m];
-      P.lut_off[idx] = acc;
-      P.tile_pos[idx] = ti.first + m;
-      acc += (uint64_t)P.lut_cap[idx];
-    }
-  }
-  for (const Group& G : P.groups)
-    if (G.wide_wb)
-      for (int k = G.neuron_begin; k < G.neuron_end; ++k) {
-        const int idx = P.group_neurons[k];
-        P.lut_off[idx] = acc;
-        acc += (uint64_t)P.lut_cap[idx];
-      }
-  P.lut_total = acc;
-  for (WorkItem& w : P.items) w.t = P.tiles[w.tile];
-  if (persistent) {
-    // Longest processing time first: cost ~ words x neurons x thresholds
-    // plus the mask-table copy.
-    auto cost = [&](const WorkItem& w) {
-      const TileInfo& t = P.tiles[w.tile];
-      return (double)w.count * (double)t.count * (double)((1 << t.o) + 1) + 4.0 * (double)t.lut_total;
-    };
-    std::stable_sort(P.items.begin(), P.items.end(),
-                     [&](const WorkItem& x, const WorkItem& y) { return cost(x) > cost(y); });
-  }
+}
+
+// The lists the support of the plan's neurons takes (plans only: a one-shot
+// enumeration has no support).
+void build_support_lists(PlanHost& P) {
   build_large_list(P);
+  for (size_t k = 0; k < P.small.size(); ++k) {
+    const int R = sum_range_of(P.small[k]);
+    if (R < 512) (R < 64 ? P.tiny : P.mid).push_back((int32_t)k);
+  }
 }
 
 // ------------------------------------------------------ device workspace
 struct Layout {
-  size_t desc, lut_off, lut_cap, tiles, tile_neuron, tile_lds, tile_pos, items, group_neurons, large, sup_lists;
+  size_t desc, small, lut_off, lut_cap, group_neurons, large, sup_lists, mid, tiny;
   size_t upload_bytes;
-  size_t params, slots, queue, found, sup_list, sup_count, lut;
+  size_t params, found, sup_list, sup_count, lut;
   size_t total;
 };
 
-Layout layout_of(const PlanHost& P) {
+// with_desc: the descriptors in their own order too (support, wide tables)
+Layout layout_of(const PlanHost& P, bool with_desc = true) {
   Layout L{};
   size_t o = 0;
   auto take = [&](size_t bytes) {
@@ -354,45 +328,41 @@ Layout layout_of(const PlanHost& P) {
     o = align_up(o + bytes);
     return at;
   };
-  L.desc = take(sizeof(tt_neuron) * P.desc.size());
+  const size_t nd = with_desc ? P.desc.size() : 0;
+  L.desc = take(sizeof(tt_neuron) * nd);
+  L.small = take(sizeof(tt_neuron) * P.small.size());
   L.lut_off = take(sizeof(uint64_t) * P.lut_off.size());
   L.lut_cap = take(sizeof(int32_t) * P.lut_cap.size());
-  L.tiles = take(sizeof(TileInfo) * P.tiles.size());
-  L.tile_neuron = take(sizeof(int32_t) * P.tile_neuron.size());
-  L.tile_lds = take(sizeof(int32_t) * P.tile_lds.size());
-  L.tile_pos = take(sizeof(int32_t) * P.tile_pos.size());
-  L.items = take(sizeof(WorkItem) * P.items.size());
   L.group_neurons = take(sizeof(int32_t) * P.group_neurons.size());
   L.large = take(sizeof(int32_t) * P.large.size());
   L.sup_lists = take(sizeof(int32_t) * P.sup_lists.size());
+  L.mid = take(sizeof(int32_t) * P.mid.size());
+  L.tiny = take(sizeof(int32_t) * P.tiny.size());
   L.upload_bytes = o;
-  L.params = take(sizeof(NeuronParams) * P.desc.size());
-  L.slots = take(sizeof(LdsSlot) * P.tile_neuron.size());
-  L.queue = take(sizeof(uint32_t) * 4);
-  L.found = take(sizeof(uint32_t) * P.desc.size());
-  L.sup_list = take(sizeof(int32_t) * (size_t)P.n);  // neurons still pending a support check
+  L.params = take(P.lut_off.empty() ? 0 : sizeof(NeuronParams) * P.desc.size());
+  const size_t sup = P.sup_lists.size();  // the support kernels' scratch
+  L.found = take(sizeof(uint32_t) * sup);
+  L.sup_list = take(sizeof(int32_t) * sup);  // neurons still pending a support check
   L.sup_count = take(sizeof(uint32_t) * 4);
   L.lut = take(sizeof(uint64_t) * P.lut_total);
   L.total = o;
   return L;
 }
 
-std::vector<uint8_t>* make_upload(const PlanHost& P, const Layout& L) {
+std::vector<uint8_t>* make_upload(const PlanHost& P, const Layout& L, bool with_desc = true) {
   auto* blob = new std::vector<uint8_t>(L.upload_bytes, 0);
   auto put = [&](size_t at, const void* src, size_t bytes) {
     if (bytes) std::memcpy(blob->data() + at, src, bytes);
   };
-  put(L.desc, P.desc.data(), sizeof(tt_neuron) * P.desc.size());
+  if (with_desc) put(L.desc, P.desc.data(), sizeof(tt_neuron) * P.desc.size());
+  put(L.small, P.small.data(), sizeof(tt_neuron) * P.small.size());
   put(L.lut_off, P.lut_off.data(), sizeof(uint64_t) * P.lut_off.size());
   put(L.lut_cap, P.lut_cap.data(), sizeof(int32_t) * P.lut_cap.size());
-  put(L.tiles, P.tiles.data(), sizeof(TileInfo) * P.tiles.size());
-  put(L.tile_neuron, P.tile_neuron.data(), sizeof(int32_t) * P.tile_neuron.size());
-  put(L.tile_lds, P.tile_lds.data(), sizeof(int32_t) * P.tile_lds.size());
-  put(L.tile_pos, P.tile_pos.data(), sizeof(int32_t) * P.tile_pos.size());
-  put(L.items, P.items.data(), sizeof(WorkItem) * P.items.size());
   put(L.group_neurons, P.group_neurons.data(), sizeof(int32_t) * P.group_neurons.size());
   put(L.large, P.large.data(), sizeof(int32_t) * P.large.size());
   put(L.sup_lists, P.sup_lists.data(), sizeof(int32_t) * P.sup_lists.size());
+  put(L.mid, P.mid.data(), sizeof(int32_t) * P.mid.size());
+  put(L.tiny, P.tiny.data(), sizeof(int32_t) * P.tiny.size());
   return blob;
 }
 
@@ -422,31 +392,22 @@ int upload_async(void* dst, std::vector<uint8_t>* blob, hipStream_t s) {
   return TT_OK;
 }
 
-EnumArgs enum_args(const PlanHost& P, const Layout& L, uint8_t* ws, uint64_t* tables) {
+EnumArgs enum_args(const Layout& L, uint8_t* ws, uint64_t* tables) {
   EnumArgs a{};
   a.desc = reinterpret_cast<const tt_neuron*>(ws + L.desc);
   a.lut_off = reinterpret_cast<const uint64_t*>(ws + L.lut_off);
   a.lut_cap = reinterpret_cast<const int32_t*>(ws + L.lut_cap);
   a.params = reinterpret_cast<NeuronParams*>(ws + L.params);
   a.lut = reinterpret_cast<uint64_t*>(ws + L.lut);
-  a.tiles = reinterpret_cast<const TileInfo*>(ws + L.tiles);
-  a.tile_neuron = reinterpret_cast<const int32_t*>(ws + L.tile_neuron);
-  a.tile_lds = reinterpret_cast<const int32_t*>(ws + L.tile_lds);
-  a.tile_pos = reinterpret_cast<const int32_t*>(ws + L.tile_pos);
-  a.slots = reinterpret_cast<LdsSlot*>(ws + L.slots);
-  a.tile_lut_max = 1;
-  for (const TileInfo& ti : P.tiles) a.tile_lut_max = std::max(a.tile_lut_max, (int32_t)ti.lut_total);
-  a.items = reinterpret_cast<const WorkItem*>(ws + L.items);
-  a.queue = reinterpret_cast<uint32_t*>(ws + L.queue);
   a.prep_waves = 1;
   a.tables = tables;
-  (void)P;
   return a;
 }
 
-int grid_for(const PlanHost& P, int cus) {
-  const long g = (long)P.tune.blocks_per_cu * (long)cus;
-  return (int)std::max<long>(1, std::min<long>(g, (long)P.items.size()));
+// blocks of the small kernel that enumerate (its launch)
+int small_grid(const PlanHost& P) {
+  const int waves = (int)P.small.size() - P.n_block;
+  return P.n_block + (waves + kSmallWaves - 1) / kSmallWaves;
 }
 
 // Enqueue support and/or histogram of the plan's neurons over `tables`
@@ -502,72 +463,66 @@ int enqueue_support(const PlanHost& P, const Layout& L, uint8_t* ws, const uint6
   return TT_OK;
 }
 
-// Enqueue the whole enumeration.  With hist != NULL the enumeration kernels
-// also form the histogram (tile kernel: each work item adds its share; wide
-// groups: their counts kernel).  With small_support != NULL the prep pass
-// also decides the support of the neurons whose sums span fewer than 512
-// values.
+// Enqueue the whole enumeration: the small kernel (one launch) and, for the
+// wide neurons, their prep pass and a launch per group.  With hist != NULL
+// the kernels also form the histogram.  With small_support != NULL they also
+// decide the support of the neurons whose sums span fewer than 512 values.
 int enqueue_plan(const PlanHost& P, const Layout& L, uint8_t* ws, uint64_t* tables, uint32_t* hist,
                  int cus, hipStream_t s, hipEvent_t ev0 = nullptr, hipEvent_t ev1 = nullptr,
                  uint8_t* small_support = nullptr) {
   if (P.n == 0) return TT_OK;
-  EnumArgs a = enum_args(P, L, ws, tables);
-  a.hist = hist;
-  a.support = small_support;
-  // Prep waves per neuron: each wave's dependent chain is the kernel's time
-  // when the neurons are few, so the mask-table chunks and the support get
-  // waves of their own, up to one round of resident waves (8 per SIMD).
-  {
-    const long round = 32L * (long)std::max(cus, 1);
-    const long fit = round / std::max<long>(P.n, 1);
+  if (!P.groups.empty()) {
+    EnumArgs a = enum_args(L, ws, tables);
+    a.hist = hist;
+    a.support = small_support;
+    // Prep waves per neuron: each wave's dependent chain is the kernel's time
+    // when the neurons are few, so the mask-table chunks and the support get
+    // waves of their own, up to one round of resident waves (8 per SIMD).
+    const int32_t* gn = reinterpret_cast<const int32_t*>(ws + L.group_neurons);
+    a.prep_list = gn;
+    a.prep_count = (int)P.group_neurons.size();
+    const long fit = 32L * (long)std::max(cus, 1) / std::max<long>(a.prep_count, 1);
     a.prep_waves = (int)std::max<long>(1, std::min<long>(fit, 1 + P.lut_chunks));
-  }
-  const bool persistent = (P.flags & TT_PLAN_PERSISTENT) != 0;
-  const int32_t* gn = reinterpret_cast<const int32_t*>(ws + L.group_neurons);
-  auto launch_wide = [&](const Group& G) {
-    a.wide_list = gn + G.neuron_begin;
-    a.wide_count = G.neuron_end - G.neuron_begin;
-    a.wide_wb = G.wide_wb;
-    a.wide_lds = G.wide_lds;
-    a.wide_upw = G.wide_upw;
-    return launch_enum_wide(a, G.o, P.tune.waves, P.tune.nontemporal, s);
-  };
-  if (persistent) {
-    a.prep_list = nullptr;
-    a.prep_count = P.n;
     TT_HIP(launch_prep(a, s));
     if (ev0) TT_HIP(hipEventRecord(ev0, s));
-    for (const Group& G : P.groups)
-      if (G.wide_wb) TT_HIP(launch_wide(G));
-    a.persistent = 1;
-    a.item_base = 0;
-    a.n_items = (int)P.items.size();
-    if (a.n_items > 0)
-      TT_HIP(launch_enum(a, grid_for(P, cus), P.tune.waves, P.tune.nontemporal, P.tune.tile_neurons, s));
-    if (ev1) TT_HIP(hipEventRecord(ev1, s));
-  } else {
-    if (ev0) TT_HIP(hipEventRecord(ev0, s));
     for (const Group& G : P.groups) {
-      a.prep_list = gn + G.neuron_begin;
-      a.prep_count = G.neuron_end - G.neuron_begin;
-      a.queue = nullptr;
-      TT_HIP(launch_prep(a, s));
-      if (G.wide_wb) {
-        TT_HIP(launch_wide(G));
-        continue;
-      }
-      a.persistent = 0;
-      a.item_base = G.item_begin;
-      a.n_items = G.item_end;
-      TT_HIP(launch_enum(a, G.item_end - G.item_begin, P.tune.waves, P.tune.nontemporal, P.tune.tile_neurons, s));
+      a.wide_list = gn + G.neuron_begin;
+      a.wide_count = G.neuron_end - G.neuron_begin;
+      a.wide_wb = G.wide_wb;
+      a.wide_lds = G.wide_lds;
+      a.wide_upw = G.wide_upw;
+      TT_HIP(launch_enum_wide(a, G.o, P.tune.waves, P.tune.nontemporal, s));
     }
-    if (ev1) TT_HIP(hipEventRecord(ev1, s));
+  } else if (ev0) {
+    TT_HIP(hipEventRecord(ev0, s));
   }
+  if (!P.small.empty()) {
+    SmallArgs a{};
+    a.desc = reinterpret_cast<const tt_neuron*>(ws + L.small);
+    a.n_block = P.n_block;
+    a.n_wave = (int)P.small.size() - P.n_block;
+    a.mid = reinterpret_cast<const int32_t*>(ws + L.mid);
+    a.tiny = reinterpret_cast<const int32_t*>(ws + L.tiny);
+    a.n_mid = (int)P.mid.size();
+    a.n_tiny = (int)P.tiny.size();
+    a.wave_lds = P.wave_lds;
+    a.block_lds = P.block_lds;
+    a.tables = tables;
+    a.hist = hist;
+    a.support = small_support;
+    TT_HIP(launch_enum_small(a, P.tune.nontemporal, s));
+  }
+  if (ev1) TT_HIP(hipEventRecord(ev1, s));
   return TT_OK;
 }
 
-// Validate the arguments of a one-shot enumeration and build its plan
-// (groups of (F, b, o), each enumerated by its own launches).
+// Launches of one step of the plan (support: with the support, too).
+int step_launches(const PlanHost& P, bool support) {
+  return (P.groups.empty() ? 0 : 1 + (int)P.groups.size()) + (P.small.empty() ? 0 : 1) +
+         (support && P.n > P.sup_small ? 1 : 0);
+}
+
+// Validate the arguments of a one-shot enumeration and build its plan.
 int plan_oneshot(const tt_neuron* h_desc, int n, const uint64_t* d_tables, uint64_t total_words, PlanHost* P) {
   TT_TRY(validate_all(h_desc, n));
   if (n == 0) return TT_OK;
@@ -578,8 +533,44 @@ int plan_oneshot(const tt_neuron* h_desc, int n, const uint64_t* d_tables, uint6
   P->tune = default_tune();
   P->flags = 0;
   P->desc.assign(h_desc, h_desc + n);
-  build_plan(*P, false);
+  build_plan(*P);
   return TT_OK;
+}
+
+// The bytes tt_enumerate_noalloc counts against its limit, as its interface
+// states them: 256-byte aligned arrays of descriptors, mask tables, tiles of
+// up to 32 neurons of one (F, b, o) whose mask tables fit 6144 entries, and
+// work lists.  The kernels take less, but which inputs the call refuses is
+// part of the interface and stays as it was.
+size_t noalloc_counted_bytes(const PlanHost& P) {
+  constexpr int kTile = 32, kTileEntries = 6144, kItemWords = 4096;
+  struct Open {
+    int count = 0, entries = 0;
+  };
+  std::map<std::tuple<int, int, int>, Open> open;
+  const size_t n = P.desc.size();
+  size_t tiles = 0, items = 0, large = 0, entries = 0;
+  for (const tt_neuron& d : P.desc) {
+    const uint64_t W = words_of(d.F, d.b);
+    const int cap = lut_cap_of(d);
+    entries += (size_t)cap;
+    if (W > (uint64_t)kSmallTableWords) ++large;
+    if (W >= (1ull << kWideMinLog2)) continue;
+    Open& t = open[std::make_tuple((int)d.F, (int)d.b, (int)d.o)];
+    if (t.count == 0 || t.count == kTile || t.entries + cap > kTileEntries) {
+      t = Open{};
+      ++tiles;
+      items += (size_t)((W + kItemWords - 1) / kItemWords);
+    }
+    ++t.count;
+    t.entries += cap;
+  }
+  const size_t bytes[] = {sizeof(tt_neuron) * n, 8 * n, 4 * n,          32 * tiles, 4 * kTile * tiles, 4 * n, 4 * n,
+                          48 * items,            4 * n, 4 * large,      4 * n,      32 * n,
+                          56 * kTile * tiles,    16,    4 * n,          4 * n,      16,                8 * entries};
+  size_t total = 0;
+  for (size_t x : bytes) total = align_up(total + x);
+  return total;
 }
 
 // Fixed workspace of tt_enumerate_noalloc, for callers that cannot allocate
@@ -896,14 +887,15 @@ int tt_enumerate(const tt_neuron* h_desc, int n, uint64_t* d_tables, uint64_t to
   int cus = 0;
   TT_TRY(device_info(&cus));
   hipStream_t s = (hipStream_t)stream;
-  const Layout L = layout_of(P);
+  const bool with_desc = !P.groups.empty();
+  const Layout L = layout_of(P, with_desc);
   uint8_t* ws = nullptr;
   hipError_t e = hipMallocAsync((void**)&ws, L.total, s);
   if (e != hipSuccess) {
     g_last_hip = (int)e;
     return TT_ENOMEM;
   }
-  int st = upload_async(ws, make_upload(P, L), s);
+  int st = upload_async(ws, make_upload(P, L, with_desc), s);
   if (st == TT_OK) st = enqueue_plan(P, L, ws, d_tables, d_hist, cus, s);
   e = hipFreeAsync(ws, s);
   if (st == TT_OK && e != hipSuccess) {
@@ -918,14 +910,15 @@ int tt_enumerate_noalloc(const tt_neuron* h_desc, int n, uint64_t* d_tables, uin
   PlanHost P;
   TT_TRY(plan_oneshot(h_desc, n, d_tables, total_words, &P));
   if (n == 0) return TT_OK;
-  const Layout L = layout_of(P);
-  if (L.total > kNoallocScratchBytes) return TT_ESCRATCH;
+  const bool with_desc = !P.groups.empty();
+  const Layout L = layout_of(P, with_desc);
+  if (noalloc_counted_bytes(P) > kNoallocScratchBytes || L.total > kNoallocScratchBytes) return TT_ESCRATCH;
   int cus = 0;
   TT_TRY(device_info(&cus));
   uint8_t* ws = nullptr;
   TT_TRY(noalloc_scratch(&ws));
   hipStream_t s = (hipStream_t)stream;
-  const int st = upload_async(ws, make_upload(P, L), s);
+  const int st = upload_async(ws, make_upload(P, L, with_desc), s);
   return st == TT_OK ? enqueue_plan(P, L, ws, d_tables, d_hist, cus, s) : st;
 }
 
@@ -946,7 +939,8 @@ int tt_plan_create(const tt_neuron* h_desc, int n, uint64_t total_words, const t
   p->host.tune = t;
   p->host.flags = flags;
   p->host.desc.assign(h_desc, h_desc + n);
-  build_plan(p->host, (flags & TT_PLAN_PERSISTENT) != 0);
+  build_plan(p->host);
+  build_support_lists(p->host);
   p->layout = layout_of(p->host);
   p->cus = cus;
   hipError_t e = hipMalloc((void**)&p->ws, std::max<size_t>(p->layout.total, kAlign));
@@ -992,6 +986,9 @@ int tt_plan_launch(tt_plan* p, uint64_t* d_tables, uint32_t* d_hist, void* strea
     if (st == TT_OK && e0) ++p->launches;
     return st;
   }
+  // a graph of one launch is that launch: replaying it would only add cost
+  if (step_launches(p->host, false) == 1)
+    return enqueue_plan(p->host, p->layout, p->ws, d_tables, d_hist, p->cus, s);
   if (!p->exec || p->cap_tables != d_tables || p->cap_hist != d_hist) {
     if (p->exec) {
       TT_HIP(hipGraphExecDestroy(p->exec));
@@ -1041,6 +1038,7 @@ int tt_plan_step(tt_plan* p, uint64_t* d_tables, uint32_t* d_hist, uint8_t* d_su
     if (st == TT_OK && e0) ++p->launches;
     return st;
   }
+  if (step_launches(p->host, d_support != nullptr) == 1) return enqueue(s, nullptr, nullptr);
   if (!p->step_exec || p->step_tables != d_tables || p->step_hist != d_hist || p->step_support != d_support) {
     if (p->step_exec) {
       TT_HIP(hipGraphExecDestroy(p->step_exec));
@@ -1106,8 +1104,7 @@ int tt_plan_kernel_times(tt_plan* p, float* h_ms, int max_count, int* count) {
 int tt_plan_wide_neurons(const tt_plan* p, int* n_wide) {
   if (!p || !n_wide) return TT_EINVAL;
   int c = 0;
-  for (const Group& G : p->host.groups)
-    if (G.wide_wb) c += G.neuron_end - G.neuron_begin;
+  for (const Group& G : p->host.groups) c += G.neuron_end - G.neuron_begin;
   *n_wide = c;
   return TT_OK;
 }
@@ -1115,9 +1112,9 @@ int tt_plan_wide_neurons(const tt_plan* p, int* n_wide) {
 int tt_plan_info(const tt_plan* p, tt_tune* tune, int* n_items, int* n_groups, int* grid) {
   if (!p) return TT_EINVAL;
   if (tune) *tune = p->host.tune;
-  if (n_items) *n_items = (int)p->host.items.size();
-  if (n_groups) *n_groups = (int)p->host.groups.size();
-  if (grid) *grid = (p->host.flags & TT_PLAN_PERSISTENT) ? grid_for(p->host, p->cus) : -1;
+  if (n_items) *n_items = (int)p->host.small.size();
+  if (n_groups) *n_groups = p->host.n_groups;
+  if (grid) *grid = (p->host.flags & TT_PLAN_PERSISTENT) ? std::max(1, small_grid(p->host)) : -1;
   return TT_OK;
 }
 
@@ -1948,47 +1945,54 @@ int tt_autotune(const tt_neuron* h_desc, int n, uint64_t* d_tables, uint64_t tot
       return TT_EHIP;
     }
   }
-  const int chunks[] = {32, 64, 128, 256, 512, 1024, 2048, 4096, 8192, 16384, 32768};
-  const int bpcs[] = {1, 2, 3, 4, 6, 8};
-  const int waves[] = {4, 8};
+  // chunk_words and waves shape the wide kernel's blocks: units per wave
+  // 1, 2, 4, ... of 4 or 8 waves; without wide neurons only the kind of store
+  // is left to choose.  The other fields decide nothing and keep the defaults.
+  bool any_wide = false;
+  for (int i = 0; i < n; ++i) any_wide = any_wide || words_of(h_desc[i].F, h_desc[i].b) >= (1ull << kWideMinLog2);
+  std::vector<int> upws = {1}, waves = {default_tune().waves};
+  if (any_wide) {
+    upws = {1, 2, 4, 8, 16, 32};
+    waves = {4, 8};
+  }
   const int nts[] = {0, 1};
-  const int tms[] = {8, 16, 32};
   double best_us = 1e300;
   tt_tune best_t = default_tune();
   int st = TT_OK;
-  for (int tm : tms)
-    for (int c : chunks)
-      for (int bpc : bpcs)
-        for (int wv : waves)
-          for (int nt : nts) {
-            tt_tune t{c, bpc, wv, nt, tm};
-            tt_plan* p = nullptr;
-            st = tt_plan_create(h_desc, n, total_words, &t, TT_PLAN_PERSISTENT, &p);
-            if (st != TT_OK) goto done;
-            double times[3] = {0, 0, 0};
-            for (int rep = 0; rep < 4; ++rep) {
-              if (hipEventRecord(e0, s) != hipSuccess) {
-                st = TT_EHIP;
-                break;
-              }
-              st = tt_plan_launch(p, d_tables, d_hist, s);
-              if (st != TT_OK) break;
-              if (hipEventRecord(e1, s) != hipSuccess || hipEventSynchronize(e1) != hipSuccess) {
-                st = TT_EHIP;
-                break;
-              }
-              float ms = 0;
-              (void)hipEventElapsedTime(&ms, e0, e1);
-              if (rep > 0) times[rep - 1] = ms * 1000.0;
-            }
-            tt_plan_destroy(p);
-            if (st != TT_OK) goto done;
-            std::sort(times, times + 3);
-            if (times[1] < best_us) {
-              best_us = times[1];
-              best_t = t;
-            }
+  for (int upw : upws)
+    for (int wv : waves)
+      for (int nt : nts) {
+        tt_tune t = default_tune();
+        t.chunk_words = 256 * wv * upw;
+        t.waves = wv;
+        t.nontemporal = nt;
+        tt_plan* p = nullptr;
+        st = tt_plan_create(h_desc, n, total_words, &t, TT_PLAN_PERSISTENT, &p);
+        if (st != TT_OK) goto done;
+        double times[3] = {0, 0, 0};
+        for (int rep = 0; rep < 4; ++rep) {
+          if (hipEventRecord(e0, s) != hipSuccess) {
+            st = TT_EHIP;
+            break;
           }
+          st = tt_plan_launch(p, d_tables, d_hist, s);
+          if (st != TT_OK) break;
+          if (hipEventRecord(e1, s) != hipSuccess || hipEventSynchronize(e1) != hipSuccess) {
+            st = TT_EHIP;
+            break;
+          }
+          float ms = 0;
+          (void)hipEventElapsedTime(&ms, e0, e1);
+          if (rep > 0) times[rep - 1] = ms * 1000.0;
+        }
+        tt_plan_destroy(p);
+        if (st != TT_OK) goto done;
+        std::sort(times, times + 3);
+        if (times[1] < best_us) {
+          best_us = times[1];
+          best_t = t;
+        }
+      }
 done:
   (void)hipStreamSynchronize(s);
   (void)hipFree(d_hist);

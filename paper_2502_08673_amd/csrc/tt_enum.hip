@@ -9,31 +9,38 @@
 //     P_hi[h] = sum_j w_j * x_j(64h),   P_lo[l] = sum_j w_j * x_j(l).
 //
 // P_hi over all words is the dense integer GEMM (digits of the rows 64h) x
-// (weights): the main kernel computes it with v_mfma_i32_32x32x16_i8, digits
-// generated from h in registers (the row matrix is never stored), exact int32
-// accumulation.  P_lo takes only 64 values per neuron; the prep kernel turns
-// it into a table of 64-bit row masks M[e] = { l : P_lo[l] - vmin >= e }.
-// Row l of word h reaches threshold t iff P_lo[l] >= t - bias - P_hi[h], so
-// the whole 64-row word of a threshold is M[clamp(t - bias - vmin - P_hi[h])]:
-// one LDS lookup per threshold replaces 64 compares.  ReLU only matters for
-// thresholds t <= 0, which every row reaches; the prep kernel folds that in.
-// The masks of the 2^o - 1 thresholds are nested, so bit p of the code q is
-// the XOR of the masks whose threshold index is a multiple of 2^p.
+// (weights).  From 256 words per plane on it is computed with
+// v_mfma_i32_16x16x32_i8, 256 words of one neuron a product, the digits
+// generated from h in registers (the row matrix is never stored), exact
+// int32 accumulation; shorter tables sum it per lane.  P_lo takes only 64
+// values per neuron, which are turned into a table of 64-bit row masks
+// M[e] = { l : P_lo[l] - vmin >= e }.  Row l of word h reaches threshold t
+// iff P_lo[l] >= t - bias - P_hi[h], so the whole 64-row word of a threshold
+// is M[clamp(t - bias - vmin - P_hi[h])]: one LDS lookup per threshold
+// replaces 64 compares.  ReLU only matters for thresholds t <= 0, which every
+// row reaches; the folded thresholds say so.  The masks of the 2^o - 1
+// thresholds are nested, so bit p of the code q is the XOR of the masks whose
+// threshold index is a multiple of 2^p.
+//
+// Two kernels: enum_small_kernel (fewer than 2^12 words per plane) builds
+// each neuron's mask table where it uses it; enum_wide_kernel (larger tables,
+// many blocks per neuron) reads tables that prep_kernel wrote once.
 //
 // Histogram, fused: the mask of threshold k holds the rows whose code is at
 // least k, so c_k = sum over words of popcount(mask_k) counts them, and
-// hist[v] = c_v - c_{v+1} (c_0 = all rows, c_{2^o} = 0).  Each lane keeps
-// its c_k for its neurons in registers (two 16-bit counts per register),
-// each wave sums them over its word-lanes at the end of a work item and adds
-// them into LDS, and the block adds the item's share of the histogram,
-// c_v - c_{v+1} with c_0 = the item's rows, into hist in global memory:
-// modulo-2^32 adds whose sum over the items is the histogram itself (the
-// prep kernel zeroes it first), so no conversion pass follows.
+// hist[v] = c_v - c_{v+1} (c_0 = all rows, c_{2^o} = 0).  Each lane keeps its
+// c_k in registers (two 16-bit counts per register).  The small kernel sums
+// them over the neuron's wave or block and stores the histogram; a block of
+// the wide kernel adds its share, c_v - c_{v+1} with c_0 = its rows, into
+// hist in global memory: modulo-2^32 adds whose sum over the blocks is the
+// histogram itself (the prep kernel zeroes it first), so no conversion pass
+// follows.
+#include <algorithm>
+
 #include "tt_internal.h"
 
 namespace tt {
 
-typedef int v16i __attribute__((ext_vector_type(16)));
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
 
@@ -72,108 +79,92 @@ __device__ __forceinline__ void mask_entries(int& lo, int& hi, int pe, int lim) 
   }
 }
 
-// prep_waves waves per neuron (role r = 0 .. prep_waves - 1): P_lo, its
-// range, the mask table (64-entry chunks c, taken by role c mod prep_waves),
-// the folded thresholds, the tile member's slot record and the zeroed
-// histogram (role 0), and, when asked, the support of a small-range neuron
-// (the last role).  Several waves per neuron shorten the chain each wave
-// runs when the plan has few neurons.  Block 0 also resets the persistent
-// work counter.
+// P of row `lane` less its minimum over the rows (INT_MIN in lanes that hold
+// no row), and the range of P: digit j contributes w_j times any value of its
+// bits below bit min(6, F b), independently of the others, so the extremes
+// are sums (wave-uniform, scalar work).
+struct LowSums {
+  int pv, vmin, range;
+};
+__device__ __forceinline__ LowSums low_sums(const NeuronRegs& d) {
+  const int lane = threadIdx.x & 63;
+  const int F = d.F, b = d.b, Fb = F * b;
+  const int dmask = (1 << b) - 1;
+  const int lowb = Fb < 6 ? Fb : 6;
+  int P = 0, vmin = 0, vmax = 0;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    if (j < F && j * b < 6) {
+      const int w = weight_at(d.wv, j);
+      P += w * ((lane >> (j * b)) & dmask);
+      const int nb = min(lowb - j * b, b);
+      const int top = w * ((1 << nb) - 1);
+      vmin += min(top, 0);
+      vmax += max(top, 0);
+    }
+  }
+  return LowSums{lane < (1 << lowb) ? P - vmin : INT_MIN, vmin, vmax - vmin};
+}
+
+// Entries e0 .. min(e0 + 63, r1) of a neuron's mask table (entry e: the rows
+// with P - vmin >= e; one compare per entry, writelane puts the mask into
+// lane e).
+__device__ __forceinline__ void mask_chunk(uint64_t* lut, int pv, int e0, int r1) {
+  const int lane = threadIdx.x & 63;
+  const int lim = __builtin_amdgcn_readfirstlane(min(64, r1 + 1 - e0));
+  int lo = 0, hi = 0;
+  mask_entries<0>(lo, hi, pv >= 0 ? pv - e0 : -1, lim);
+  if (lane < lim) lut[e0 + lane] = ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo;
+}
+
+// Threshold k with bias, ReLU and the minimum of P_lo folded in: row l of
+// word h reaches it iff pv[l] >= te - P_hi[h].  Thresholds far outside every
+// sum are cut to +-2^30, which no sum reaches either.
+__device__ __forceinline__ int folded_threshold(int32_t t, const NeuronRegs& d, int vmin) {
+  if (d.act == TT_ACT_RELU && t <= 0) return kNegBig;
+  return min(max(t, kNegBig), kPosBig) - d.bias - vmin;
+}
+
+// Neurons of the wide kernel, prep_waves waves each (role r = 0 ..
+// prep_waves - 1): P_lo, its range, the mask table (64-entry chunks c, taken
+// by role c mod prep_waves), the folded thresholds and the zeroed histogram
+// (role 0), and, when asked, the support of a small-range neuron (the last
+// role).  Several waves per neuron shorten the chain each wave runs when the
+// plan has few neurons.
 __global__ __launch_bounds__(256) void prep_kernel(EnumArgs a) {
-  if (blockIdx.x == 0 && threadIdx.x == 0 && a.queue) a.queue[0] = 0u;
   const int lane = threadIdx.x & 63;
   // wave-uniform by construction; said so, later branches on it are scalar
   const int gw = __builtin_amdgcn_readfirstlane(blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6));
   const int W = a.prep_waves;
   const int i = gw / W, role = gw - (gw / W) * W;
   if (i >= a.prep_count) return;
-  const int n = a.prep_list ? __builtin_amdgcn_readfirstlane(a.prep_list[i]) : i;
+  const int n = __builtin_amdgcn_readfirstlane(a.prep_list[i]);
   // every per-neuron input in one load instruction: lanes 0..15 the
-  // descriptor, lanes 16..20 the plan's entries (a plan's arguments always
-  // carry the tile arrays)
+  // descriptor, lanes 16..18 the plan's entries
   const uint32_t* src = neuron_dword(a.desc + n, lane);
   if (lane == 16) src = reinterpret_cast<const uint32_t*>(a.lut_cap + n);
   if (lane == 17) src = reinterpret_cast<const uint32_t*>(a.lut_off + n);
   if (lane == 18) src = reinterpret_cast<const uint32_t*>(a.lut_off + n) + 1;
-  if (lane == 19) src = reinterpret_cast<const uint32_t*>(a.tile_pos + n);
-  if (lane == 20) src = reinterpret_cast<const uint32_t*>(a.tile_lds + n);
-  const uint32_t x = lane < 21 ? *src : 0u;
+  const uint32_t x = lane < 19 ? *src : 0u;
   const NeuronRegs d = neuron_from_lanes(x);
   const int cap = __builtin_amdgcn_readlane((int)x, 16);
   const uint64_t loff = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)x, 18) << 32) |
                         (uint32_t)__builtin_amdgcn_readlane((int)x, 17);
-  const int tp = __builtin_amdgcn_readlane((int)x, 19);
-  const int tlds = __builtin_amdgcn_readlane((int)x, 20);
   uint64_t* lut = a.lut + loff;
-  const int F = d.F, b = d.b, o = d.o;
-  const int Fb = F * b;
-  const int R = Fb >= 6 ? 64 : (1 << Fb);
-  const bool valid = lane < R;
-  const int dmask = (1 << b) - 1;
-  // P of row `lane` (its low six bits) and the range of P over the rows, in
-  // closed form: digit j contributes w_j times any value of its bits below
-  // bit min(6, F b), independently of the others
-  int P = 0, vmin = 0, vmax = 0;
-  const int lowb = Fb < 6 ? Fb : 6;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    if (j < F) {
-      const int w = weight_at(d.wv, j);
-      P += w * ((lane >> (j * b)) & dmask);
-      const int nb = min(max(lowb - j * b, 0), b);
-      const int top = w * ((1 << nb) - 1);
-      vmin += min(top, 0);
-      vmax += max(top, 0);
-    }
-  }
-  const int r1 = min(vmax - vmin + 1, cap - 1);
-  // entry e of the mask table: the rows with P - vmin >= e (one compare per
-  // entry; writelane puts the mask into lane e)
-  const int pv = valid ? P - vmin : -1;
-  for (int e0 = 64 * role; e0 <= r1; e0 += 64 * W) {
-    const int lim = __builtin_amdgcn_readfirstlane(min(64, r1 + 1 - e0));
-    int lo = 0, hi = 0;
-    mask_entries<0>(lo, hi, valid ? pv - e0 : -1, lim);
-    if (lane < lim) lut[e0 + lane] = ((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo;
-  }
+  const LowSums ls = low_sums(d);
+  const int r1 = min(ls.range + 1, cap - 1);
+  for (int e0 = 64 * role; e0 <= r1; e0 += 64 * W) mask_chunk(lut, ls.pv, e0, r1);
   if (role == 0) {
-  // tile members: the LDS slot record at the neuron's tile position
-  int32_t* slot = tp >= 0 ? reinterpret_cast<int32_t*>(a.slots + tp) : nullptr;
-  const int32_t thr_mine = thr_lane(d, lane >= 1 && lane <= 7 ? lane - 1 : 0);  // lane k + 1: thr[k]
-  if (lane < 8) {
-    int32_t val = kPosBig;
-    if (lane == 0) {
-      val = r1;
-    } else {
-      const int k = lane - 1;
-      if (k < (1 << o) - 1) {
-        const int64_t t = thr_mine;
-        if (d.act == TT_ACT_RELU && t <= 0) {
-          val = kNegBig;
-        } else {
-          int64_t te = t - (int64_t)d.bias - (int64_t)vmin;
-          te = te < kNegBig ? kNegBig : (te > kPosBig ? kPosBig : te);
-          val = (int32_t)te;
-        }
-      }
+    const int32_t thr_mine = thr_lane(d, lane >= 1 && lane <= 7 ? lane - 1 : 0);  // lane k + 1: thr[k]
+    if (lane < 8) {
+      int32_t val = kPosBig;
+      if (lane == 0)
+        val = r1;
+      else if (lane - 1 < (1 << d.o) - 1)
+        val = folded_threshold(thr_mine, d, ls.vmin);
+      reinterpret_cast<int32_t*>(&a.params[n])[lane] = val;
+      if (a.hist) a.hist[(size_t)n * 8 + lane] = 0u;  // histogram accumulators
     }
-    reinterpret_cast<int32_t*>(&a.params[n])[lane] = val;
-    if (slot) slot[lane] = val;
-    if (a.hist) a.hist[(size_t)n * 8 + lane] = 0u;  // histogram accumulators
-  } else if (slot && lane < 14) {
-    const uint64_t wm = F < 8 ? d.wv & ((1ull << (8 * F)) - 1ull) : d.wv;
-    const uint64_t woff = d.word_off;
-    uint32_t v = 0;
-    switch (lane) {
-      case 8: v = (uint32_t)tlds; break;
-      case 9: v = Fb >= 6 ? 1u << (Fb - 6) : 1u; break;
-      case 10: v = (uint32_t)woff; break;
-      case 11: v = (uint32_t)(woff >> 32); break;
-      case 12: v = (uint32_t)wm; break;
-      default: v = (uint32_t)(wm >> 32); break;
-    }
-    slot[lane] = (int32_t)v;
-  }
   }
   // the support of a small-range neuron, decided from its parameters by this
   // wave (the step's support of the plan's own tables)
@@ -198,184 +189,313 @@ __device__ __forceinline__ void planes_from_masks(const uint64_t* mk, uint64_t* 
   }
 }
 
-// One work item's column tiles for output width O (uniform over the block).
-// Each wave takes 32-word column tiles of the item: one MFMA gives P_hi for
-// 32 neurons x 32 words; lane l then owns word (l % 32) of the neurons
-// 8*(v/4) + 4*(l/32) + v%4 in accumulator register v, so every store writes
-// two 256-byte runs of consecutive words.  Tiles of at most 4*MV/2 neurons
-// only use registers v < MV.  With a histogram, the wave's threshold counts
-// are added into s_cnt[m * 8 + k] (k = 1..2^O - 1) at the end.
-template <int O, int NW, bool NT, int MV>
-__device__ __forceinline__ void enum_item(const EnumArgs& a, const WorkItem& wi, const TileInfo& ti,
-                                          const LdsSlot* s_slot, const uint64_t* s_lut, uint32_t* s_cnt, long A,
-                                          int lane, int wave) {
+// The four accumulator words of a lane of one 256-word unit (words 2 l + v
+// and 128 + 2 l + v - 2 of the unit, see enum_wide_kernel): masks looked up,
+// planes stored at dst (the lane's first word), threshold counts added.
+// aligned: dst and its planes lie on 16-byte boundaries (wave-uniform).
+template <int O, bool NT>
+__device__ __forceinline__ void unit_words(const v4i& acc, const int* te, int r1, const uint64_t* lut, uint64_t* dst,
+                                           uint64_t W, bool aligned, uint32_t* cnt) {
   constexpr int K = (1 << O) - 1;
-  constexpr int NC = (K + 1) / 2;  // registers of packed counts per neuron
-  const bool want_hist = a.hist != nullptr;
-  const int F = ti.F, b = ti.b, W = ti.W;
-  const uint32_t dmask = (1u << b) - 1u;
-  const int hend = wi.h0 + wi.count;
-  uint32_t cnt[MV][NC];
+  uint64_t pl[4][O];
 #pragma unroll
-  for (int v = 0; v < MV; ++v)
+  for (int v = 0; v < 4; ++v) {
+    const int P = acc[v];
+    uint64_t mk[K];
 #pragma unroll
-    for (int c = 0; c < NC; ++c) cnt[v][c] = 0u;
-  for (int ct = wave; ct * kTileN < wi.count; ct += NW) {
-    const int hcol = wi.h0 + ct * kTileN + (lane & 31);
-    // B operand: lanes 0..31 carry the digits of row 64*hcol (k = 0..7);
-    // lanes 32..63 carry k = 8..15, which are zero.
-    long B = 0;
-    if (lane < 32) {
-      const uint32_t r = (uint32_t)hcol << 6;
-      uint64_t dg = 0;
-      for (int j = 0; j < F; ++j) dg |= (uint64_t)((r >> (j * b)) & dmask) << (8 * j);
-      B = (long)dg;
-    }
-    v16i acc = {0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0};
-    acc = __builtin_amdgcn_mfma_i32_32x32x16_i8(A, B, acc, 0, 0, 0);
-    const bool hok = hcol < hend;
+    for (int q = 0; q < K; ++q) mk[q] = lut[min(max(te[q] - P, 0), r1)];
+    planes_from_masks<O>(mk, pl[v]);
 #pragma unroll
-    for (int v = 0; v < MV; ++v) {
-      const int m = 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-      uint32_t inc[NC];
-#pragma unroll
-      for (int c = 0; c < NC; ++c) inc[c] = 0u;
-      if (hok && m < ti.count) {
-        const LdsSlot& sl = s_slot[m];
-        const int P = acc[v];
-        const int r1 = sl.r1;
-        const int base = sl.base;
-        uint64_t mk[K];
-#pragma unroll
-        for (int k = 0; k < K; ++k) {
-          int c = sl.te[k] - P;
-          c = min(max(c, 0), r1);
-          mk[k] = s_lut[base + c];
-        }
-        uint64_t pl[O];
-        planes_from_masks<O>(mk, pl);
-        uint64_t* dst = a.tables + sl.woff + (uint64_t)hcol;
-#pragma unroll
-        for (int p = 0; p < O; ++p) {
-          if constexpr (NT)
-            __builtin_nontemporal_store(pl[p], dst + (uint64_t)p * (uint64_t)W);
-          else
-            dst[(uint64_t)p * (uint64_t)W] = pl[p];
-        }
-#pragma unroll
-        for (int k = 0; k < K; ++k) inc[k >> 1] += (uint32_t)__popcll(mk[k]) << (16 * (k & 1));
-      }
-#pragma unroll
-      for (int c = 0; c < NC; ++c) cnt[v][c] += inc[c];
-    }
+    for (int q = 0; q < K; ++q) cnt[q >> 1] += (uint32_t)__popcll(mk[q]) << (16 * (q & 1));
   }
-  if (want_hist) {  // uniform
+  if (aligned) {  // 16-byte runs
 #pragma unroll
-    for (int v = 0; v < MV; ++v) {
-      const int m = 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
-#pragma unroll
-      for (int c = 0; c < NC; ++c) {
-        // sum over the 32 lanes that hold neuron m (xor masks < 32 stay in the half)
-        uint32_t lo = cnt[v][c] & 0xFFFFu, hi = cnt[v][c] >> 16;
-#pragma unroll
-        for (int off = 16; off >= 1; off >>= 1) {
-          lo += (uint32_t)__shfl_xor((int)lo, off, 64);
-          hi += (uint32_t)__shfl_xor((int)hi, off, 64);
-        }
-        if ((lane & 31) == 0 && m < ti.count) {
-          if (lo) atomicAdd(&s_cnt[m * 8 + 2 * c + 1], lo);
-          if (2 * c + 1 < K && hi) atomicAdd(&s_cnt[m * 8 + 2 * c + 2], hi);
-        }
+    for (int p = 0; p < O; ++p) {
+      u64x2* q = reinterpret_cast<u64x2*>(dst + (uint64_t)p * W);
+      if constexpr (NT) {
+        __builtin_nontemporal_store(u64x2{pl[0][p], pl[1][p]}, q);
+        __builtin_nontemporal_store(u64x2{pl[2][p], pl[3][p]}, q + 64);
+      } else {
+        q[0] = u64x2{pl[0][p], pl[1][p]};
+        q[64] = u64x2{pl[2][p], pl[3][p]};
       }
     }
+  } else {
+#pragma unroll
+    for (int p = 0; p < O; ++p)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        uint64_t* d = dst + (uint64_t)p * W + (v >> 1) * 128 + (v & 1);
+        if constexpr (NT)
+          __builtin_nontemporal_store(pl[v][p], d);
+        else
+          *d = pl[v][p];
+      }
   }
 }
 
-// Work item = (tile of <= 32 neurons of one (F, b, o) group, range of words).
-// Static mode: block i takes item item_base + i.  Persistent mode: blocks
-// pull items from an atomic counter until the queue is empty.  Tiles hold at
-// most 2 * MV neurons.
-template <int NW, bool NT, int MV>
-__global__ __launch_bounds__(NW * 64) void enum_kernel(EnumArgs a) {
-  extern __shared__ uint64_t s_lut[];
-  __shared__ LdsSlot s_slot[kTileM];
-  __shared__ uint32_t s_cnt[kTileM * 8];
-  __shared__ int s_item;
+// P_hi of the 256 words from h0 on (the product described at
+// enum_wide_kernel); wv: weights with the entries past F cleared.
+__device__ __forceinline__ v4i unit_sums(uint64_t wv, int F, int b, uint32_t h0) {
   const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  for (int t = threadIdx.x; t < kTileM * 8; t += blockDim.x) s_cnt[t] = 0u;
-  int cur_tile = -1;
-  int iter = 0;
-  int prev_first = 0, prev_count = 0, prev_K = 0;
-  uint32_t prev_rows = 0;
-  for (;;) {
-    // The first barrier retires every thread's previous item (including its
-    // read of s_item and all LDS reads) before the slot and tables change.
-    __syncthreads();
-    if (a.hist && (int)threadIdx.x < prev_count) {
-      // The previous item's share of the member's histogram, from its
-      // threshold counts c_k (rows with code >= k; c_0 = the item's rows):
-      // hist[v] += c_v - c_{v+1}, in modulo-2^32 adds whose total is the
-      // histogram itself (no later pass).
-      const int m = threadIdx.x;
-      uint32_t c[9];
-      c[0] = prev_rows;
+  const uint32_t dmask = (1u << b) - 1u;
+  // lanes 0-15: the digits of the unit's row part; lanes 16-31: those of
+  // the column part (word 2 j, row 64 * 2 j)
+  const uint32_t r = lane < 16 ? (h0 + (uint32_t)(lane & 1) + ((uint32_t)(lane >> 2) << 5) +
+                                  ((uint32_t)((lane >> 1) & 1) << 7)) << 6
+                               : (uint32_t)(lane & 15) << 7;
+  uint64_t dg = 0;
+  for (int j = 0; j < F; ++j) dg |= (uint64_t)((r >> (j * b)) & dmask) << (8 * j);
+  const long A = lane < 16 ? (long)dg : (lane < 32 ? (long)wv : 0L);
+  const long B = lane < 16 ? (long)wv : (lane < 32 ? (long)dg : 0L);
+  v4i acc = {0, 0, 0, 0};
+  return __builtin_amdgcn_mfma_i32_16x16x32_i8(A, B, acc, 0, 0, 0);
+}
+
+// Sum of v over the wave, in lane 63 (DPP row shifts and broadcasts).
+__device__ __forceinline__ uint32_t wave_sum_last(uint32_t v) {
+  int x = (int)v;
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, true);   // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, true);   // row_shr:2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, true);   // row_shr:4
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, true);   // row_shr:8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);  // row_bcast:15
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);  // row_bcast:31
+  return (uint32_t)x;
+}
+
+// One neuron's tables by the `nw` waves of a block (wave `wave`; nw = 1: one
+// wave by itself), O = its output width.  lut: LDS entries the waves share.
+// Histogram in LDS rows s_cnt[wave * 8 ..] for nw > 1, else written here.
+template <int O, bool NT>
+__device__ __forceinline__ void small_tables(const SmallArgs& a, const NeuronRegs& d, int n, uint64_t* lut,
+                                             uint32_t* s_cnt, int wave, int nw) {
+  constexpr int K = (1 << O) - 1;
+  constexpr int NC = (K + 1) / 2;
+  const int lane = threadIdx.x & 63;
+  const int F = d.F, b = d.b, Fb = F * b;
+  const uint32_t dmask = (1u << b) - 1u;
+  const uint32_t W = Fb >= 6 ? 1u << (Fb - 6) : 1u;
+  const LowSums ls = low_sums(d);
+  int te[7];
 #pragma unroll
-      for (int k = 1; k < 8; ++k) {
-        c[k] = k <= prev_K ? s_cnt[m * 8 + k] : 0u;
-        s_cnt[m * 8 + k] = 0u;
+  for (int k = 0; k < K; ++k) te[k] = folded_threshold(thr_uniform(d, k), d, ls.vmin);
+  uint64_t* tab = a.tables + d.word_off;
+  uint32_t c[K + 2];  // rows whose code is at least k (wave-uniform)
+  c[0] = Fb >= 6 ? W << 6 : 1u << Fb;
+  c[K + 1] = 0u;
+  // P_hi of word `h`, one word per lane
+  auto sum_of_word = [&](uint32_t h) {
+    int P = 0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (j < F && (j + 1) * b > 6) P += weight_at(d.wv, j) * (int)(((h << 6) >> (j * b)) & dmask);
+    return P;
+  };
+  if (W <= kDirectWords) {
+    // a compare per threshold and word, at most 8 K: fewer instructions than
+    // a mask table's entries (3 each, typically 25 to 35) plus the lookups
+    const int ph = sum_of_word((uint32_t)lane);
+    uint64_t out[O];
+#pragma unroll
+    for (int p = 0; p < O; ++p) out[p] = 0ull;
+#pragma unroll
+    for (int k = 1; k <= K; ++k) c[k] = 0u;
+    for (int h = 0; h < (int)W; ++h) {
+      const int P = __builtin_amdgcn_readlane(ph, h);
+      uint64_t mk[K], pl[O];
+#pragma unroll
+      for (int k = 0; k < K; ++k) {
+        mk[k] = __ballot(ls.pv >= te[k] - P);  // lanes without a row hold INT_MIN
+        c[k + 1] += (uint32_t)__popcll(mk[k]);
       }
-      c[8] = 0u;
-      uint32_t* h = a.hist + (size_t)a.tile_neuron[prev_first + m] * 8;
+      planes_from_masks<O>(mk, pl);
 #pragma unroll
-      for (int v = 0; v < 8; ++v)
-        if (v <= prev_K && c[v] != c[v + 1]) atomicAdd(h + v, c[v] - c[v + 1]);
+      for (int p = 0; p < O; ++p) out[p] = lane == h ? pl[p] : out[p];
     }
-    if (threadIdx.x == 0) {
-      // the first item is the block's own (the queue would hand out items
-      // 0 .. grid - 1 first anyway); later ones come from the queue, which
-      // counts from the grid size
-      int it;
-      if (a.persistent)
-        it = iter == 0 ? (int)blockIdx.x
-                       : ((int)gridDim.x >= a.n_items ? a.n_items : (int)gridDim.x + (int)atomicAdd(a.queue, 1u));
-      else
-        it = iter == 0 ? a.item_base + (int)blockIdx.x : a.n_items;
-      s_item = it;
-    }
-    __syncthreads();
-    const int item = s_item;
-    if (item >= a.n_items) break;
-    ++iter;
-    const WorkItem wi = a.items[item];
-    const TileInfo& ti = wi.t;
-    if (wi.tile != cur_tile) {
-      // the members' slot records and their mask tables: two contiguous
-      // copies issued together (no dependent loads)
-      const uint32_t* ssrc = reinterpret_cast<const uint32_t*>(a.slots + ti.first);
-      uint32_t* sdst = reinterpret_cast<uint32_t*>(s_slot);
-      constexpr int kSlotDw = (int)(sizeof(LdsSlot) / 4);
-      for (int e = threadIdx.x; e < ti.count * kSlotDw; e += blockDim.x) sdst[e] = ssrc[e];
-      const uint64_t* lsrc = a.lut + (((uint64_t)ti.lut_base_hi << 32) | ti.lut_base_lo);
-      for (int e = threadIdx.x; e < ti.lut_total; e += blockDim.x) s_lut[e] = lsrc[e];
+    if (lane < (int)W)
+#pragma unroll
+      for (int p = 0; p < O; ++p) tab[(uint32_t)p * W + (uint32_t)lane] = out[p];
+  } else {
+    const int r1 = ls.range + 1;
+    for (int e0 = 64 * wave; e0 <= r1; e0 += 64 * nw) mask_chunk(lut, ls.pv, e0, r1);
+    if (nw > 1)
       __syncthreads();
-      cur_tile = wi.tile;
+    else
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    uint32_t cnt[NC];
+#pragma unroll
+    for (int q = 0; q < NC; ++q) cnt[q] = 0u;
+    if (W >= 256) {
+      const uint64_t wm = F < 8 ? d.wv & ((1ull << (8 * F)) - 1ull) : d.wv;
+      for (uint32_t h0 = 256u * (uint32_t)wave; h0 < W; h0 += 256u * (uint32_t)nw)
+        unit_words<O, NT>(unit_sums(wm, F, b, h0), te, r1, lut, tab + h0 + 2u * (uint32_t)lane, W,
+                          (d.word_off & 1ull) == 0, cnt);
+    } else {
+      for (uint32_t h = 64u * (uint32_t)wave + (uint32_t)lane; h < W; h += 64u * (uint32_t)nw) {
+        const int P = sum_of_word(h);
+        uint64_t mk[K], pl[O];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+          mk[k] = lut[min(max(te[k] - P, 0), r1)];
+          cnt[k >> 1] += (uint32_t)__popcll(mk[k]) << (16 * (k & 1));
+        }
+        planes_from_masks<O>(mk, pl);
+#pragma unroll
+        for (int p = 0; p < O; ++p) {
+          uint64_t* q = tab + (uint32_t)p * W + h;
+          if constexpr (NT)
+            __builtin_nontemporal_store(pl[p], q);
+          else
+            *q = pl[p];
+        }
+      }
     }
-    prev_first = ti.first;
-    prev_count = ti.count;
-    prev_K = (1 << ti.o) - 1;
-    {
-      const int Fb = (int)ti.F * (int)ti.b;
-      prev_rows = (uint32_t)wi.count * (Fb >= 6 ? 64u : (1u << Fb));
+    if (!a.hist) return;
+    // the wave's rows number at most 2^16 - 64 per packed half (tables of
+    // 1024 words are shared by at least two waves)
+#pragma unroll
+    for (int q = 0; q < NC; ++q) {
+      const uint32_t t = (uint32_t)__builtin_amdgcn_readlane((int)wave_sum_last(cnt[q]), 63);
+      c[2 * q + 1] = t & 0xFFFFu;
+      if (2 * q + 2 <= K) c[2 * q + 2] = t >> 16;
     }
-    // A operand: lanes 0..31 carry the weights of tile neuron `lane` (k = 0..7).
-    const long A = (lane < 32 && lane < ti.count) ? (long)s_slot[lane].wv : 0L;
-    switch (ti.o) {
-      case 1: enum_item<1, NW, NT, MV>(a, wi, ti, s_slot, s_lut, s_cnt, A, lane, wave); break;
-      case 2: enum_item<2, NW, NT, MV>(a, wi, ti, s_slot, s_lut, s_cnt, A, lane, wave); break;
-      default: enum_item<3, NW, NT, MV>(a, wi, ti, s_slot, s_lut, s_cnt, A, lane, wave); break;
+    if (nw > 1) {
+#pragma unroll
+      for (int k = 1; k <= K; ++k)
+        if (lane == k) s_cnt[wave * 8 + k] = c[k];
+      return;  // the block adds them up
     }
   }
+  if (a.hist && lane < 8) {
+    uint32_t v = 0u;
+#pragma unroll
+    for (int k = 0; k <= K; ++k)
+      if (lane == k) v = c[k] - c[k + 1];
+    a.hist[(size_t)n * 8 + lane] = v;
+  }
+}
+
+template <bool NT>
+__device__ __forceinline__ void small_neuron(const SmallArgs& a, const NeuronRegs& d, int n, uint64_t* lut,
+                                             uint32_t* s_cnt, int wave, int nw) {
+  switch (d.o) {
+    case 1: small_tables<1, NT>(a, d, n, lut, s_cnt, wave, nw); break;
+    case 2: small_tables<2, NT>(a, d, n, lut, s_cnt, wave, nw); break;
+    default: small_tables<3, NT>(a, d, n, lut, s_cnt, wave, nw); break;
+  }
+}
+
+// Support of eight neurons whose sums span fewer than 64 values, lane 8 s + j
+// deciding digit j of the s-th (the rule of tiny_support_wave, which spends
+// a whole wave on one neuron: here the eight lanes of a neuron build their
+// sets side by side and walk its thresholds in turn).
+__device__ __forceinline__ void tiny_support_lanes(const tt_neuron* dp, bool live, uint8_t* support) {
+  const int lane = threadIdx.x & 63, j = lane & 7;
+  const uint64_t* q = reinterpret_cast<const uint64_t*>(dp);
+  const uint64_t wv = live ? q[0] : 0ull;
+  int32_t thr[7];
+#pragma unroll
+  for (int k = 0; k < 7; ++k) thr[k] = live ? dp->thr[k] : 0;
+  const int bias = live ? dp->bias : 0, F = live ? dp->F : 0, b = live ? dp->b : 1;
+  const int K = live ? (1 << dp->o) - 1 : 0, relu = live && dp->act == TT_ACT_RELU;
+  const int n = live ? (int)dp->reserved : 0;
+  const int dmax = (1 << b) - 1;
+  uint64_t S = 1ull;
+  int base = bias, wj = 0;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int wi = i < F ? weight_at(wv, i) : 0;
+    const int aw = wi < 0 ? -wi : wi;
+    if (i == j) wj = wi;
+    const bool other = i != j && wi != 0;
+    if (other && wi < 0) base += wi * dmax;
+    // every shift stays below 64: |w_i| 2^m is at most the range
+#pragma unroll
+    for (int m = 0; m < 4; ++m)
+      if (other && m < b) S |= S << ((aw << m) & 63);
+  }
+  const int D = (wj < 0 ? -wj : wj) * dmax;
+  bool hit = false;
+#pragma unroll
+  for (int k = 0; k < 7; ++k) {
+    // sums lie within 2^16 of zero: a threshold beyond 2^20 is out of reach
+    const int t = min(max(thr[k], -(1 << 20)), 1 << 20);
+    if (k < K && wj != 0 && !(relu && t < 1)) {
+      const int lo = max((wj > 0 ? t - D : t) - base, 0), hi = min((wj > 0 ? t - 1 : t + D - 1) - base, 63);
+      if (lo <= hi) hit = hit || ((S >> lo) << (63 - hi + lo)) != 0ull;
+    }
+  }
+  const uint64_t bal = __ballot(hit);
+  if (live && j == 0) support[n] = (uint8_t)(bal >> (lane & 56));
+}
+
+// Tables of fewer than 2^kWideMinLog2 words per plane (in fact at most 2^10:
+// F b <= 16), histogram and, when asked, support of the neurons whose sums
+// span fewer than 512 values, all in one launch and with no workspace: a
+// neuron belongs to one wave, or to one block when its tables have 512 words
+// or more (or a mask table beyond a wave's share of LDS), so its mask table
+// is built where it is used, its histogram is stored and not added up across
+// blocks, and nothing has to be cleared first.  Bound by VALU issue and, for
+// few neurons, by the launch and one wave's chain: 8192 uneven neurons (17 MB
+// of tables) take 11.5 us, 64 neurons of 4096 rows 4.4 us.  (A prep pass that
+// wrote the mask tables to memory and a second kernel of tiles of up to 32
+// neurons took 12 + 49 us and 5.7 + 12.7 us, most of it latency of their
+// chains of loads and, in the tiles, lanes without a word.)  Blocks, in order: neurons of
+// a block each, the support of neurons whose sums span 64 to 511 values (a
+// wave each), neurons of a wave each, the support of the others (eight to a
+// wave); the host lists the longest work first in each class.
+template <bool NT>
+__global__ __launch_bounds__(64 * kSmallWaves) void enum_small_kernel(SmallArgs a) {
+  extern __shared__ uint64_t s_lut[];
+  __shared__ uint32_t s_cnt[kSmallWaves * 8];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  int blk = (int)blockIdx.x;
+  if (blk < a.n_block) {
+    const NeuronRegs d = load_neuron(a.desc + blk);
+    const int n = __builtin_amdgcn_readlane((int)d.raw, 14);
+    small_neuron<NT>(a, d, n, s_lut, s_cnt, wave, kSmallWaves);
+    if (!a.hist) return;
+    __syncthreads();
+    const int k = threadIdx.x, K = (1 << d.o) - 1;
+    if (k < 8) {
+      const int Fb = d.F * d.b;
+      uint32_t ck = k == 0 ? 1u << Fb : 0u, cn = 0u;
+#pragma unroll
+      for (int w = 0; w < kSmallWaves; ++w) {
+        if (k >= 1 && k <= K) ck += s_cnt[w * 8 + k];
+        if (k < K) cn += s_cnt[w * 8 + k + 1];
+      }
+      a.hist[(size_t)n * 8 + k] = ck - cn;
+    }
+    return;
+  }
+  blk -= a.n_block;
+  if (a.support) {
+    const int mid_blocks = (a.n_mid + kSmallWaves - 1) / kSmallWaves;
+    if (blk < mid_blocks) {
+      const int i = blk * kSmallWaves + wave;
+      if (i >= a.n_mid) return;
+      const NeuronRegs d = load_neuron(a.desc + __builtin_amdgcn_readfirstlane(a.mid[i]));
+      const uint32_t sup = small_support_wave(d, neuron_sum_range(d));
+      if (lane == 0) a.support[__builtin_amdgcn_readlane((int)d.raw, 14)] = (uint8_t)sup;
+      return;
+    }
+    blk -= mid_blocks;
+  }
+  const int wave_blocks = (a.n_wave + kSmallWaves - 1) / kSmallWaves;
+  if (blk < wave_blocks) {
+    const int i = blk * kSmallWaves + wave;
+    if (i >= a.n_wave) return;
+    const NeuronRegs d = load_neuron(a.desc + a.n_block + i);
+    small_neuron<NT>(a, d, __builtin_amdgcn_readlane((int)d.raw, 14), s_lut + wave * a.wave_lds, s_cnt, 0, 1);
+    return;
+  }
+  blk -= wave_blocks;
+  const int i = (blk * kSmallWaves + wave) * 8 + (lane >> 3);
+  const bool live = i < a.n_tiny;
+  tiny_support_lanes(a.desc + (live ? a.tiny[i] : 0), live, a.support);
 }
 
 // Wide tables (at least 2^kWideMinLog2 words per plane), one (F, b, o) group
@@ -457,46 +577,7 @@ __global__ __launch_bounds__(NW * 64) void enum_wide_kernel(EnumArgs a) {
     }
     v4i acc = {0, 0, 0, 0};
     acc = __builtin_amdgcn_mfma_i32_16x16x32_i8(A, B, acc, 0, 0, 0);
-    uint64_t pl[4][O];
-#pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int P = acc[v];
-      uint64_t mk[K];
-#pragma unroll
-      for (int q = 0; q < K; ++q) {
-        int c = pr.te[q] - P;
-        c = min(max(c, 0), pr.r1);
-        mk[q] = s_lut[c];
-      }
-      planes_from_masks<O>(mk, pl[v]);
-#pragma unroll
-      for (int q = 0; q < K; ++q) cnt[q >> 1] += (uint32_t)__popcll(mk[q]) << (16 * (q & 1));
-    }
-    uint64_t* dst = a.tables + woff + h0 + 2u * (uint32_t)lane;
-    if ((woff & 1ull) == 0) {  // uniform: 16-byte aligned runs
-#pragma unroll
-      for (int p = 0; p < O; ++p) {
-        u64x2* q = reinterpret_cast<u64x2*>(dst + (uint64_t)p * W);
-        if constexpr (NT) {
-          __builtin_nontemporal_store(u64x2{pl[0][p], pl[1][p]}, q);
-          __builtin_nontemporal_store(u64x2{pl[2][p], pl[3][p]}, q + 64);
-        } else {
-          q[0] = u64x2{pl[0][p], pl[1][p]};
-          q[64] = u64x2{pl[2][p], pl[3][p]};
-        }
-      }
-    } else {
-#pragma unroll
-      for (int p = 0; p < O; ++p)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-          uint64_t* d = dst + (uint64_t)p * W + (v >> 1) * 128 + (v & 1);
-          if constexpr (NT)
-            __builtin_nontemporal_store(pl[v][p], d);
-          else
-            *d = pl[v][p];
-        }
-    }
+    unit_words<O, NT>(acc, pr.te, pr.r1, s_lut, a.tables + woff + h0 + 2u * (uint32_t)lane, W, (woff & 1ull) == 0, cnt);
   }
   if (a.hist) {  // uniform
     // a lane counts at most 4 * 64 * upw <= 2^13 rows per threshold, so the
@@ -541,28 +622,19 @@ hipError_t launch_prep(const EnumArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-template <int NW, bool NT, int MV>
-static hipError_t launch_enum_t(const EnumArgs& a, int grid, hipStream_t s) {
-  // LDS for the largest tile's mask tables only: small tables leave room for
-  // more resident blocks
-  const int entries = a.tile_lut_max > 0 && a.tile_lut_max < kLutLdsEntries ? a.tile_lut_max : kLutLdsEntries;
-  const size_t lds = sizeof(uint64_t) * (size_t)entries;
-  hipLaunchKernelGGL((enum_kernel<NW, NT, MV>), dim3(grid), dim3(64 * NW), lds, s, a);
-  return hipGetLastError();
-}
-
-template <int MV>
-static hipError_t launch_enum_mv(const EnumArgs& a, int grid, int waves, int nontemporal, hipStream_t s) {
-  if (waves == 8)
-    return nontemporal ? launch_enum_t<8, true, MV>(a, grid, s) : launch_enum_t<8, false, MV>(a, grid, s);
-  return nontemporal ? launch_enum_t<4, true, MV>(a, grid, s) : launch_enum_t<4, false, MV>(a, grid, s);
-}
-
-hipError_t launch_enum(const EnumArgs& a, int grid, int waves, int nontemporal, int tile_neurons, hipStream_t s) {
+hipError_t launch_enum_small(const SmallArgs& a, int nontemporal, hipStream_t s) {
+  const long per = kSmallWaves;
+  long grid = (long)a.n_block + (a.n_wave + per - 1) / per;
+  if (a.support) grid += (a.n_mid + per - 1) / per + (a.n_tiny + 8 * per - 1) / (8 * per);
   if (grid <= 0) return hipSuccess;
-  if (tile_neurons <= 8) return launch_enum_mv<4>(a, grid, waves, nontemporal, s);
-  if (tile_neurons <= 16) return launch_enum_mv<8>(a, grid, waves, nontemporal, s);
-  return launch_enum_mv<16>(a, grid, waves, nontemporal, s);
+  if (a.wave_lds < 0 || a.wave_lds > kSmallWaveLut || a.block_lds < 0 || a.block_lds > kMaxLutCap)
+    return hipErrorInvalidValue;
+  const size_t lds = sizeof(uint64_t) * (size_t)std::max(kSmallWaves * a.wave_lds, a.block_lds);
+  if (nontemporal)
+    hipLaunchKernelGGL(enum_small_kernel<true>, dim3((unsigned)grid), dim3(64 * kSmallWaves), lds, s, a);
+  else
+    hipLaunchKernelGGL(enum_small_kernel<false>, dim3((unsigned)grid), dim3(64 * kSmallWaves), lds, s, a);
+  return hipGetLastError();
 }
 
 template <int NW, bool NT>

@@ -10,12 +10,12 @@
 
 namespace tt {
 
-// Enumeration tiles: 32 neurons (the M side of a 32x32x16 int8 MFMA) share a
-// work item; the N side is 32 consecutive 64-row table words.
-constexpr int kTileM = 32;
-constexpr int kTileN = 32;
-// Per-tile budget of LDS mask-table entries (uint64 each): 48 KiB.
-constexpr int kLutLdsEntries = 6144;
+// Tables of fewer than 2^kWideMinLog2 words per plane (enum_small_kernel):
+// waves per block, mask-table entries (uint64 each) a wave's own neuron may
+// take, and the words up to which a table is compared row by row instead.
+constexpr int kSmallWaves = 4;
+constexpr int kSmallWaveLut = 256;
+constexpr int kDirectWords = 8;
 // Largest mask table of one neuron: the low six row bits span at most
 // 18 * 128 + 1 distinct sums (b = 4: 15*|w0| + 3*|w1|, int8 weights down to
 // -128), plus the all-zero sentinel entry.
@@ -32,60 +32,17 @@ struct NeuronParams {
   int32_t te[7];
 };
 
-// A tile: neurons of one (F, b, o) group (host built).  Its members' mask
-// tables lie back to back in the pool from lut_base, in member order, so the
-// LDS copy of a tile is one contiguous read.
-struct TileInfo {
-  int32_t first;     // offset into the tile-neuron list (multiple of kTileM)
-  int32_t count;     // neurons in the tile, 1..32
-  int32_t W;         // words per plane
-  int32_t lut_total; // LDS mask entries used by the tile
-  uint8_t F, b, o, pad;
-  uint32_t lut_base_lo, lut_base_hi;  // first pool entry of the tile's mask tables
-  int32_t pad2;
-};
-
-// What the tile kernel keeps in LDS for each member of its current tile,
-// written by the prep kernel at the member's tile position (56 bytes).
-struct LdsSlot {
-  int32_t r1, te[7];  // as NeuronParams
-  int32_t base, W;    // LDS entry of the member's mask table; words per plane
-  uint64_t woff;      // word_off of plane 0
-  uint64_t wv;        // weights, entries j >= F zeroed
-};
-
-// A work item carries a copy of its tile's record, so a block fetches both
-// with one load.
-struct WorkItem {
-  int32_t tile;
-  int32_t h0;     // first word
-  int32_t count;  // words
-  int32_t pad;
-  TileInfo t;     // == tiles[tile]
-};
-
-// Everything the enumeration kernels read, all in one plan workspace.
+// What the wide kernel and its prep pass read, all in one plan workspace.
 struct EnumArgs {
   const tt_neuron* desc;       // [n]
   const uint64_t* lut_off;     // [n] offset of each neuron's mask table in lut
   const int32_t* lut_cap;      // [n] entries reserved for it (range + 2)
   NeuronParams* params;        // [n]
   uint64_t* lut;               // mask-table pool
-  const TileInfo* tiles;       // [n_tiles]
-  const int32_t* tile_neuron;  // [n_tiles * 32], -1 padded
-  const int32_t* tile_lds;     // [n] LDS entry base of each tile member's mask table
-  const int32_t* tile_pos;     // [n] position of the neuron in the tile-neuron list, -1: none
-  LdsSlot* slots;              // [n_tiles * 32] per tile position, written by the prep kernel
-  int32_t tile_lut_max;        // largest lut_total of any tile (LDS entries the tile kernel needs)
   uint8_t* support;            // prep kernel: support of the small-range neurons (NULL: none)
-  const WorkItem* items;       // [n_items]
-  uint32_t* queue;             // persistent work counter
-  const int32_t* prep_list;    // neurons to prepare (NULL: 0..prep_count-1)
+  const int32_t* prep_list;    // the wide neurons
   int32_t prep_count;
   int32_t prep_waves;          // waves per neuron in the prep kernel (>= 1; see prep_kernel)
-  int32_t n_items;
-  int32_t item_base;           // static mode: first item of this launch
-  int32_t persistent;
   uint64_t* tables;
   uint32_t* hist;              // [n * 8] histogram, accumulated by the kernels (NULL: none)
   const int32_t* wide_list;    // launch_enum_wide: the neurons of one wide group
@@ -93,6 +50,21 @@ struct EnumArgs {
   int32_t wide_wb;             // log2 of its words per plane (>= kWideMinLog2)
   int32_t wide_upw;            // 256-word units per wave (power of two, waves * upw <= W / 256)
   int32_t wide_lds;            // LDS mask entries: the group's largest table
+};
+
+// The other neurons (enum_small_kernel): descriptors in the order the blocks
+// take them, the neuron's own index in `reserved`.
+struct SmallArgs {
+  const tt_neuron* desc;  // [n_block + n_wave]
+  int32_t n_block;        // neurons that take a block each, first in desc
+  int32_t n_wave;         // neurons that take a wave each
+  const int32_t* mid;     // places in desc of the neurons whose sums span 64..511 values
+  const int32_t* tiny;    // and fewer than 64
+  int32_t n_mid, n_tiny;
+  int32_t wave_lds, block_lds;  // the largest mask table of each class, entries
+  uint64_t* tables;
+  uint32_t* hist;     // [n * 8] or NULL
+  uint8_t* support;   // [n] or NULL: the neurons of mid and tiny
 };
 
 // Groups with at least 2^kWideMinLog2 words per plane are enumerated by the
@@ -350,7 +322,7 @@ __device__ __forceinline__ uint32_t small_support_wave(const NeuronRegs& d, int 
 
 // Launchers (tt_enum.hip / tt_support.hip); return hipError_t.
 hipError_t launch_prep(const EnumArgs& a, hipStream_t s);
-hipError_t launch_enum(const EnumArgs& a, int grid, int waves, int nontemporal, int tile_neurons, hipStream_t s);
+hipError_t launch_enum_small(const SmallArgs& a, int nontemporal, hipStream_t s);
 hipError_t launch_enum_wide(const EnumArgs& a, int o, int waves, int nontemporal, hipStream_t s);
 hipError_t launch_support_params(const tt_neuron* desc, const int32_t* list, int n, uint8_t* support,
                                  hipStream_t s);

@@ -174,6 +174,49 @@ def test_large_rows_sampled():
     assert not np.any(sp & zero_bits)
 
 
+# (F, b) and weight bound at the small kernel's edges: fewer rows than a word,
+# the last table compared row by row (8 words) and the first looked up (16),
+# one lane per word up to 128 words, one 256-word unit, blocks of two and four
+# units, and mask tables beyond a wave's share of LDS (full int8 weights).
+SMALL_EDGES = [(1, 1, 7), (5, 1, 7), (2, 3, 127), (3, 3, 7), (3, 3, 127), (5, 2, 7), (5, 2, 60), (5, 2, 127),
+               (3, 4, 7), (3, 4, 127), (6, 2, 7), (7, 2, 7), (7, 2, 127), (5, 3, 7), (5, 3, 127), (8, 2, 7),
+               (4, 4, 7), (4, 4, 127), (8, 2, 1)]
+
+
+@pytest.mark.parametrize("n", [1, 5])
+def test_small_kernel_edges(n):
+    """Every class of the small kernel with every output width and both
+    activations, n neurons of each (n = 1 and 5: partial blocks and partial
+    support groups), tables, histogram and support in one step; then without
+    histogram and without support."""
+    ns = concat([random_neurons(seed=900 + 10 * i + o, n=n, F=(F, F), b=(b, b), o=(o, o), max_fb=16, wmax=w,
+                                bias_max=20)
+                 for i, (F, b, w) in enumerate(SMALL_EDGES) for o in (1, 2, 3)])
+    ns.w[0], ns.w[1 % len(ns)] = 0, 0  # nothing but the bias
+    desc = tt.descriptors(ns)
+    total = tt.layout(desc)
+    ref = oracle.enumerate(ns)
+    tables = device_tables(total)
+    hist = torch.zeros(len(ns) * 8, dtype=torch.int32, device="cuda")
+    sup = torch.zeros(len(ns), dtype=torch.uint8, device="cuda")
+    note(f"small kernel edges n={n}")
+    with tt.Plan(desc, total, flags=tt.TT_PLAN_PERSISTENT | tt.TT_PLAN_GRAPH) as plan:
+        assert plan.info()["wide_neurons"] == 0
+        for h, s in ((hist, sup), (None, sup), (hist, None)):
+            tables[:total].fill_(-3)
+            hist.fill_(7)
+            sup.fill_(0xEE)
+            torch.cuda.synchronize()
+            plan.step(tables, h, s)
+            torch.cuda.synchronize()
+            assert np.array_equal(host_u64(tables, 0, total), ref["planes"])
+            if h is not None:
+                assert np.array_equal(h.cpu().numpy().reshape(-1, 8).astype(np.uint32), ref["hist"])
+            if s is not None:
+                assert np.array_equal(s.cpu().numpy(), ref["support"])
+    check_canary(tables, total)
+
+
 def test_largest_neurons():
     """The largest tables the ABI allows with F <= 8, b <= 4: F = 7, b = 4
     (2^28 rows, 2^22 words per plane), 1- and 3-bit outputs, through a plan
