@@ -1320,13 +1320,29 @@ int tt_cnf_create(const int32_t* h_lits, const int32_t* h_clause_off, const int3
   const size_t off_vof = take(sizeof(int32_t) * n_inst);
   const size_t off_nv = take(sizeof(int32_t) * n_inst);
   const size_t off_ord = take(sizeof(int32_t) * n_inst);
-  // blocks take instances longest first (a stable sort by clause count), so
-  // the last waves to finish are short ones
+  const size_t upload = o;
+  // instances longest first (a stable sort by clause count), so the last
+  // waves to finish are short ones and the eight of a wave alike; those that
+  // fit the kernel of eight instances a wave before the others
   std::vector<int32_t> order(n_inst);
-  for (int t = 0; t < n_inst; ++t) order[t] = t;
+  std::vector<uint8_t> slow(n_inst, 0);
+  int fast_vars = 0;
+  for (int t = 0; t < n_inst; ++t) {
+    order[t] = t;
+    const int c1 = h_inst_off[t + 1];
+    slow[t] = c1 - h_inst_off[t] > 0xFFFF || h_n_vars[t] >= kCnfFastVarBytes;
+    for (int c = h_inst_off[t]; c < c1 && !slow[t]; ++c) slow[t] = dcoff[c + 1] - dcoff[c] > kCnfFastClause;
+    if (!slow[t]) {
+      ++h->args.n_fast;
+      fast_vars = std::max(fast_vars, h_n_vars[t]);
+    }
+  }
+  h->args.cls_stride = (fast_vars + 1 + 3) / 4 * 4;
   std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) {
+    if (slow[x] != slow[y]) return slow[x] < slow[y];
     return h_inst_off[x + 1] - h_inst_off[x] > h_inst_off[y + 1] - h_inst_off[y];
   });
+  const size_t off_rec = take(16 * (size_t)(h->args.n_fast > 0 ? n_clauses : 0));
   if (st == TT_OK) {
     const hipError_t e = hipMalloc((void**)&h->ws, o);
     if (e != hipSuccess) {
@@ -1336,7 +1352,7 @@ int tt_cnf_create(const int32_t* h_lits, const int32_t* h_clause_off, const int3
     }
   }
   if (st == TT_OK) {
-    auto* blob = new std::vector<uint8_t>(o, 0);
+    auto* blob = new std::vector<uint8_t>(upload, 0);
     if (n_dlits > 0) std::memcpy(blob->data() + off_lit, dlits.data(), sizeof(int32_t) * n_dlits);
     if (n_clauses > 0) std::memcpy(blob->data() + off_cof, dcoff.data(), sizeof(int32_t) * (n_clauses + 1));
     std::memcpy(blob->data() + off_iof, h_inst_off, sizeof(int32_t) * (n_inst + 1));
@@ -1346,6 +1362,30 @@ int tt_cnf_create(const int32_t* h_lits, const int32_t* h_clause_off, const int3
     std::memcpy(blob->data() + off_ord, order.data(), sizeof(int32_t) * n_inst);
     st = upload_async(h->ws, blob, (hipStream_t)stream);
   }
+  if (st == TT_OK) {
+    tt::CnfArgs& a = h->args;
+    a.lits = reinterpret_cast<const int32_t*>(h->ws + off_lit);
+    a.clause_off = reinterpret_cast<const int32_t*>(h->ws + off_cof);
+    a.inst_off = reinterpret_cast<const int32_t*>(h->ws + off_iof);
+    a.clause_reach = reinterpret_cast<const int32_t*>(h->ws + off_rch);
+    a.var_off = reinterpret_cast<const int32_t*>(h->ws + off_vof);
+    a.n_vars = reinterpret_cast<const int32_t*>(h->ws + off_nv);
+    a.order = reinterpret_cast<const int32_t*>(h->ws + off_ord);
+    a.clause_rec = reinterpret_cast<const uint4*>(h->ws + off_rec);
+    a.n_inst = n_inst;
+    for (int t = 0; t < n_inst && n_clauses > 0; ++t) {
+      a.stage_clauses = std::max(a.stage_clauses, h_inst_off[t + 1] - h_inst_off[t]);
+      a.stage_lits = std::max(a.stage_lits, dcoff[h_inst_off[t + 1]] - dcoff[h_inst_off[t]]);
+    }
+    if (a.n_fast > 0) {
+      const hipError_t e = tt::launch_cnf_clauses(a, n_clauses, reinterpret_cast<uint4*>(h->ws + off_rec),
+                                                  (hipStream_t)stream);
+      if (e != hipSuccess) {
+        g_last_hip = (int)e;
+        st = TT_EHIP;
+      }
+    }
+  }
   if (st != TT_OK) {
     if (h->ws) {
       (void)hipStreamSynchronize((hipStream_t)stream);
@@ -1353,19 +1393,6 @@ int tt_cnf_create(const int32_t* h_lits, const int32_t* h_clause_off, const int3
     }
     delete h;
     return st;
-  }
-  tt::CnfArgs& a = h->args;
-  a.lits = reinterpret_cast<const int32_t*>(h->ws + off_lit);
-  a.clause_off = reinterpret_cast<const int32_t*>(h->ws + off_cof);
-  a.inst_off = reinterpret_cast<const int32_t*>(h->ws + off_iof);
-  a.clause_reach = reinterpret_cast<const int32_t*>(h->ws + off_rch);
-  a.var_off = reinterpret_cast<const int32_t*>(h->ws + off_vof);
-  a.n_vars = reinterpret_cast<const int32_t*>(h->ws + off_nv);
-  a.order = reinterpret_cast<const int32_t*>(h->ws + off_ord);
-  a.n_inst = n_inst;
-  for (int t = 0; t < n_inst && n_clauses > 0; ++t) {
-    a.stage_clauses = std::max(a.stage_clauses, h_inst_off[t + 1] - h_inst_off[t]);
-    a.stage_lits = std::max(a.stage_lits, dcoff[h_inst_off[t + 1]] - dcoff[h_inst_off[t]]);
   }
   *out = h;
   return TT_OK;

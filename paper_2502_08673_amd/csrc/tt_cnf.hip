@@ -1,6 +1,7 @@
 // tt_cnf.hip -- the CNF-to-circuit transformation (Section "Transformation
-// Algorithm", Algorithm 1) on packed truth tables, one wave per CNF instance
-// (gfx950).
+// Algorithm", Algorithm 1) on packed truth tables (gfx950): eight instances a
+// wave while SC stays within five variables (cnf_fast_kernel), else one wave
+// per instance (cnf_transform_kernel), as follows.
 //
 // A wave walks its instance's clauses in order, growing the sub-clause list
 // SC (a contiguous clause range, since SC is emptied whenever an expression
@@ -15,6 +16,8 @@
 // differs: a shifted XOR inside a word for j < 6, a lane exchange for
 // j >= 6).  An SC with no output whose variables occur in no later clause
 // becomes an auxiliary output constrained to 1 (the conjunction of SC).
+#include <algorithm>
+
 #include "tt_internal.h"
 
 namespace tt {
@@ -22,6 +25,7 @@ namespace tt {
 namespace {
 
 constexpr uint8_t kClsPI = 1, kClsIV = 2, kClsPO = 4;
+constexpr int kCnfSweep = 8192;  // a round of one-wave blocks: 32 per CU
 
 // rows whose digit j is 1, for j < 6 (inside one 64-row word)
 __device__ __forceinline__ uint64_t digit_pattern(int j) {
@@ -68,13 +72,307 @@ __device__ uint32_t table_support(uint64_t t, int k, int W, uint64_t valid) {
 
 }  // namespace
 
+namespace {
+
+// ---------------------------------------------------- eight instances a wave
+// SC of at most kCnfFastVars variables (the gate encodings of circuits put a
+// gate and its inputs in one SC: four or so): every table fits one 32-bit
+// word, so a wave per instance would leave 63 lanes without a table word.
+// Here eight lanes take an instance.  They read a clause's literals side by
+// side, find each one's digit (the order of first use in SC) in a byte per
+// variable in LDS and combine their patterns into the clause's word; a word
+// over fewer variables is independent of the other digits, so appending a
+// variable changes no word.  Lane q also is SC's q-th variable: with A the
+// conjunction of SC's clauses and N and P those of the clauses holding the
+// variable negated and plain, every lane tests its own variable as the
+// output after each clause: f = N at v = 1 and g = P at v = 0 drop v's own
+// literals, and v is the output when they differ in every row.  What is
+// found goes to a list in LDS in this form.  When the list is full the
+// block's second wave takes it, while the first goes on with another one:
+// one lane per entry sorts the digits by variable (a sorting network, each
+// exchange a swap of two digits of the word) and the wave writes the records
+// in whole lines.
+constexpr int kCnfFastVars = 5;
+static_assert(kCnfFastVars == kCnfFastClause, "a clause's literals are distinct variables");
+constexpr int kCnfList = 64;
+constexpr int kCnfPending = -1;  // status of an instance left to the wave kernel
+constexpr uint32_t kNoVar = 0x8000u;
+// A variable's byte in LDS: its class bits, and its digit in SC plus one
+// (zero: not in SC) from bit 3 up.
+constexpr int kDigitShift = 3;
+constexpr uint32_t kClassBits = (1u << kDigitShift) - 1u;
+
+struct CnfList {
+  uint32_t tab[kCnfList];        // f (v's digit dropped) or SC's conjunction
+  uint16_t var[kCnfList][8];     // variable of digit q; kNoVar: none, or v
+  int32_t rec[kCnfList], first[kCnfList], last[kCnfList], out[kCnfList];
+  int32_t count, more;           // entries; whether another list follows
+};
+
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, true);
+}
+// over the eight lanes of a group: quad permutes by 1 and 2, then the mirror
+// of half a row
+__device__ __forceinline__ uint32_t or8(uint32_t x) {
+  x |= dpp<0xB1>(x);
+  x |= dpp<0x4E>(x);
+  x |= dpp<0x141>(x);
+  return x;
+}
+__device__ __forceinline__ uint32_t max8(uint32_t x) {
+  x = max(x, dpp<0xB1>(x));
+  x = max(x, dpp<0x4E>(x));
+  x = max(x, dpp<0x141>(x));
+  return x;
+}
+
+__device__ __forceinline__ uint32_t digit_pattern32(int j) { return (uint32_t)digit_pattern(j); }
+
+// digits A < B of the table and their variables exchanged when out of order
+template <int A, int B>
+__device__ __forceinline__ void order_digits(uint32_t (&v)[kCnfFastVars], uint32_t& t) {
+  const uint32_t m = digit_pattern32(A) & ~digit_pattern32(B);
+  uint32_t x = (t ^ (t >> ((1 << B) - (1 << A)))) & m;
+  x = v[A] > v[B] ? x : 0u;
+  t ^= x | (x << ((1 << B) - (1 << A)));
+  const uint32_t lo = min(v[A], v[B]), hi = max(v[A], v[B]);
+  v[A] = lo;
+  v[B] = hi;
+}
+
+// The list's records to memory, by one wave; heads: 80 bytes of LDS a record.
+__device__ __forceinline__ void cnf_flush(CnfList& L, uint4 (*heads)[5], tt_cnf_expr* expr) {
+  const int lane = threadIdx.x & 63;
+  const int count = __builtin_amdgcn_readfirstlane(L.count);
+  if (lane < count) {
+    const uint4 vv = *reinterpret_cast<const uint4*>(&L.var[lane][0]);
+    uint32_t v[kCnfFastVars] = {vv.x & 0xFFFFu, vv.x >> 16, vv.y & 0xFFFFu, vv.y >> 16, vv.z & 0xFFFFu};
+    uint32_t t = L.tab[lane];
+    order_digits<0, 3>(v, t);
+    order_digits<1, 4>(v, t);
+    order_digits<0, 2>(v, t);
+    order_digits<1, 3>(v, t);
+    order_digits<0, 1>(v, t);
+    order_digits<2, 4>(v, t);
+    order_digits<1, 2>(v, t);
+    order_digits<3, 4>(v, t);
+    order_digits<2, 3>(v, t);
+    uint32_t k = 0, sup = 0;
+#pragma unroll
+    for (int j = 0; j < kCnfFastVars; ++j) {
+      const bool used = v[j] != kNoVar;
+      k += used ? 1u : 0u;
+      // t does not depend on the digits past its variables
+      if (((t ^ (t >> (1 << j))) & ~digit_pattern32(j)) != 0u) sup |= 1u << j;
+      v[j] = used ? v[j] : 0u;
+    }
+    const uint32_t out = (uint32_t)L.out[lane];
+    const uint32_t kind = out == 0u ? TT_CNF_AUX : (t == 0u || t == ~0u) ? TT_CNF_PO : TT_CNF_IV;
+    L.tab[lane] = k >= 5u ? t : t & ((1u << (1u << k)) - 1u);
+    heads[lane][0] = make_uint4(out, kind, (uint32_t)L.first[lane], (uint32_t)L.last[lane]);
+    heads[lane][1] = make_uint4(k, sup, v[0], v[1]);
+    heads[lane][2] = make_uint4(v[2], v[3], v[4], 0u);
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  // heads: eight lanes a record, 16 bytes each (the unused bytes as zeros, so
+  // that whole lines are written)
+#pragma unroll 2
+  for (int e0 = 0; e0 < count; e0 += 8) {
+    const int e = e0 + (lane >> 3), p = lane & 7;
+    if (e < count)
+      reinterpret_cast<uint4*>(expr + L.rec[e])[p] = p < 3 ? heads[e][p] : make_uint4(0u, 0u, 0u, 0u);
+  }
+  // tables: half a wave a record; word 0 holds the rows, the others are zero
+#pragma unroll 4
+  for (int e0 = 0; e0 < count; e0 += 2) {
+    const int e = e0 + (lane >> 5), p = lane & 31;
+    if (e < count)
+      reinterpret_cast<uint4*>(expr[L.rec[e]].table)[p] = make_uint4(p == 0 ? L.tab[e] : 0u, 0u, 0u, 0u);
+  }
+}
+
+}  // namespace
+
+// A clause as eight 16-bit values: its literals (zero past the last) in 0 ..
+// 4, and in 6 the last clause of its instance that uses any of its variables.
+__global__ __launch_bounds__(256) void cnf_clause_kernel(const int32_t* lits, const int32_t* clause_off,
+                                                         const int32_t* reach, int n_clauses, uint4* rec) {
+  const int c = blockIdx.x * 256 + threadIdx.x;
+  if (c >= n_clauses) return;
+  const int p = clause_off[c], len = clause_off[c + 1] - p;
+  uint32_t v[8];
+#pragma unroll
+  for (int t = 0; t < 8; ++t) v[t] = t < kCnfFastClause && t < len ? (uint32_t)lits[p + t] & 0xFFFFu : 0u;
+  v[6] = (uint32_t)reach[c] & 0xFFFFu;
+  rec[c] = make_uint4(v[0] | (v[1] << 16), v[2] | (v[3] << 16), v[4] | (v[5] << 16), v[6] | (v[7] << 16));
+}
+
+// The first n_fast instances of the order (no clause above kCnfFastClause
+// literals, fewer than 2^16 clauses, few variables): eight to a block of two
+// waves, the first walking, the second writing.  An instance whose SC
+// outgrows kCnfFastVars variables stops with status kCnfPending and is taken
+// again, from its start, by cnf_transform_kernel.  Bound by the chain of the
+// longest instances' clauses, about 200 instructions and 0.55 us each:
+// 20000 circuits of 8 to 64 gates take 0.158 ms, 16 of them 0.14 ms (a wave
+// each: 1.38 and 0.47 ms); without its stores, 0.5 GB, it takes 0.150 ms.
+__global__ __launch_bounds__(128) void cnf_fast_kernel(CnfArgs a) {
+  __shared__ CnfList lists[2];
+  __shared__ uint4 heads[kCnfList][5];
+  __shared__ uint16_t s_sc[8][8];     // per instance: SC's variables by digit
+  __shared__ uint4 s_rec[8][8];       // per instance: the clauses i .. i + 7
+  extern __shared__ uint8_t s_cls[];  // a byte per variable, [8][cls_stride]
+  const int lane = threadIdx.x & 63, q = lane & 7, g = lane >> 3;
+  if (__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) == 1) {
+    // the writer: list k when the walker has filled it (barrier k); the
+    // walker fills the other one meanwhile
+    for (int k = 0;; ++k) {
+      __syncthreads();
+      CnfList& L = lists[k & 1];
+      const bool more = __builtin_amdgcn_readfirstlane(L.more) != 0;
+      cnf_flush(L, heads, a.expr);
+      if (!more) return;
+    }
+  }
+  const int slot = blockIdx.x * 8 + g;
+  const bool live = slot < a.n_fast;
+  const int inst = live ? a.order[slot] : 0;
+  const int nvar = live ? a.n_vars[inst] : -1;
+  const int c0 = live ? a.inst_off[inst] : 0;
+  const int nc = live ? a.inst_off[inst + 1] - c0 : 0;
+  uint8_t* cls = s_cls + g * a.cls_stride;
+  for (int x = q; x <= nvar; x += 8) cls[x] = 0;
+  const uint32_t pat = digit_pattern32(q < kCnfFastVars ? q : kCnfFastVars - 1);
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  // eight clauses at a time, one a lane, in LDS; the next eight in registers
+  // (loaded eight clauses ahead)
+  const uint4* rec = a.clause_rec + c0;
+  uint4 ahead = q < nc ? rec[q] : make_uint4(0u, 0u, 0u, 0u);
+  uint32_t A = ~0u, N = ~0u, P = ~0u;
+  uint32_t blocked = 0;  // not zero: SC's q-th variable is a primary input or intermediate
+  int nsc = 0, start = 0, nexpr = 0, reach = -1;
+  int listed = 0, filled = 0;  // entries of the list being filled, lists handed over
+  bool run = live && nc > 0, pending = false;
+  int word = 0, creach = 0;  // lane q's 16 bits of the clause (literal q), and its reach
+  auto fetch = [&](int i) {
+    if ((i & 7) == 0) {
+      s_rec[g][q] = ahead;
+      if (i + 8 + q < nc) ahead = rec[i + 8 + q];
+    }
+    const uint16_t* cl = reinterpret_cast<const uint16_t*>(&s_rec[g][i & 7]);
+    word = (int)(int16_t)cl[q];
+    creach = (int)cl[6];
+  };
+  fetch(0);
+  for (int i = 0; __any(run); ++i) {
+    const int lit = run && q < kCnfFastClause ? word : 0;
+    const int here = creach;
+    // the literals' digits; variables new to SC take the next ones
+    const int x = lit < 0 ? -lit : lit;
+    const uint32_t byte = cls[x];
+    fetch(i + 1);  // in flight with the byte
+    const uint32_t have = byte >> kDigitShift;
+    const bool add = lit != 0 && have == 0u;
+    const uint32_t adds = (uint32_t)(__ballot(add) >> (lane & 56)) & 0xFFu;
+    const int digit = add ? nsc + __popc(adds & ((1u << q) - 1u)) : (int)have - 1;
+    nsc += __popc(adds);
+    if (run && nsc > kCnfFastVars) {
+      pending = true;
+      run = false;
+    }
+    const bool use = run && lit != 0;
+    if (use && add) {
+      cls[x] = (uint8_t)(byte | (uint32_t)(digit + 1) << kDigitShift);
+      s_sc[g][digit] = (uint16_t)x;
+    }
+    // lane q's variable and its byte, wanted if something is found: read
+    // here, so that they arrive while the words are combined
+    const bool mine = run && q < nsc;
+    const uint32_t my = mine ? s_sc[g][q] : 0u;
+    const uint32_t my_cls = cls[my] & kClassBits;
+    const uint32_t lp = digit & 4 ? 0xFFFF0000u
+                                  : (digit & 2 ? (digit & 1 ? 0xFF00FF00u : 0xF0F0F0F0u)
+                                               : (digit & 1 ? 0xCCCCCCCCu : 0xAAAAAAAAu));
+    const uint32_t C = or8(use ? lp ^ (uint32_t)(lit >> 31) : 0u);
+    // bits of the clause's variables: plain, negated, and (new ones) blocked
+    uint32_t bits = use ? (lit > 0 ? 1u : 0x100u) : 0u;
+    bits |= use && add && (byte & (kClsPI | kClsIV)) ? 0x10000u : 0u;
+    bits = or8(bits << (digit & 7)) >> q;
+    if (run) {
+      A &= C;
+      N &= C | (((bits >> 8) & 1u) - 1u);
+      P &= C | ((bits & 1u) - 1u);
+      blocked |= bits & 0x10000u;
+      reach = max(reach, here);
+    }
+    // the candidates, each its own variable; the largest that passes
+    const bool ok = mine && blocked == 0u && (((N >> (1 << q)) ^ P) | pat) == ~0u;
+    const bool any_ok = ((uint32_t)(__ballot(ok) >> (lane & 56)) & 0xFFu) != 0u;
+    const bool found = any_ok || (run && reach <= i);
+    // one entry a group that found something
+    const uint64_t who = __ballot(found && q == 0);
+    run = run && i + 1 < nc;
+    if (who == 0ull) continue;
+    CnfList& L = lists[filled & 1];
+    const int at = listed + __popcll(who & ((1ull << (lane & 56)) - 1ull));
+    const uint32_t v = max8(ok ? my : 0u);
+    if (found) {
+      const bool win = mine && my == v;
+      const uint32_t n1 = N & pat;
+      const uint32_t f = any_ok ? n1 | (n1 >> (1 << q)) : A;
+      if (any_ok ? win : q == 0) {
+        L.tab[at] = f;
+        L.rec[at] = c0 + nexpr;
+        L.first[at] = start;
+        L.last[at] = i;
+        L.out[at] = (int32_t)v;
+      }
+      L.var[at][q] = (uint16_t)(mine && !win ? my : kNoVar);
+      if (mine) {
+        const uint32_t mark = win ? (f == 0u || f == ~0u ? kClsPO : kClsIV) : (my_cls & kClsIV ? 0u : kClsPI);
+        cls[my] = (uint8_t)(my_cls | mark);
+      }
+      ++nexpr;
+      start = i + 1;
+      reach = -1;
+      nsc = 0;
+      blocked = 0;
+      A = N = P = ~0u;
+    }
+    listed += __popcll(who);
+    if (listed > kCnfList - 8) {
+      if (lane == 0) {
+        L.count = listed;
+        L.more = 1;
+      }
+      __syncthreads();  // the writer has this list now and is done with the other
+      ++filled;
+      listed = 0;
+    }
+  }
+  if (lane == 0) {
+    lists[filled & 1].count = listed;
+    lists[filled & 1].more = 0;
+  }
+  __syncthreads();
+  if (!live) return;
+  if (!pending)
+    for (int x = q; x <= nvar; x += 8) a.var_class[a.var_off[inst] + x] = cls[x];
+  if (q == 0) {
+    a.n_expr[inst] = nexpr;
+    a.status[inst] = pending ? kCnfPending : 0;
+  }
+}
+
 // STAGED: the instance's clause offsets, literals and clause reaches are
 // copied into LDS first (every later read is an LDS read), when the largest
 // instance of the batch fits; else they are read from global memory.
 template <bool STAGED>
-__global__ __launch_bounds__(64) void cnf_transform_kernel(CnfArgs a) {
-  extern __shared__ int32_t smem[];  // [staged clause offsets, reaches, literals] then the class bytes
-  const int inst = a.order[blockIdx.x], lane = threadIdx.x;  // longest instances first
+__device__ __forceinline__ void cnf_transform_wave(const CnfArgs& a, int inst, int32_t* smem) {
+  const int lane = threadIdx.x;
   const int nvar = a.n_vars[inst];
   const int c0 = a.inst_off[inst], nc = a.inst_off[inst + 1] - c0;
   const int32_t* coff;   // clause c of the instance: literals lits[coff[c] .. coff[c + 1] - 1]
@@ -233,16 +531,60 @@ __global__ __launch_bounds__(64) void cnf_transform_kernel(CnfArgs a) {
     a.n_expr[inst] = nexpr;
     a.status[inst] = status;
   }
+  __syncthreads();  // the next instance overwrites smem
 }
 
-hipError_t launch_cnf_transform(const CnfArgs& a, int max_vars, hipStream_t s) {
-  if (a.n_inst <= 0) return hipSuccess;
+// One wave per instance.  The instances past n_fast in the order, one block
+// each, longest first; then blocks that look through the first n_fast for
+// those cnf_fast_kernel left pending: lane k of the b-th checks instance
+// b + k G of G blocks (one each up to kCnfSweep instances), so that a batch
+// with many is still spread over the chip.
+template <bool STAGED>
+__global__ __launch_bounds__(64) void cnf_transform_kernel(CnfArgs a) {
+  extern __shared__ int32_t smem[];  // [staged clause offsets, reaches, literals] then the class bytes
+  const int n_slow = a.n_inst - a.n_fast;
+  const int blk = (int)blockIdx.x;
+  if (blk < n_slow) {
+    cnf_transform_wave<STAGED>(a, a.order[a.n_fast + blk], smem);
+    return;
+  }
+  const int G = (int)gridDim.x - n_slow;
+  for (long base = blk - n_slow; base < a.n_fast; base += 64L * G) {
+    const long slot = base + (long)threadIdx.x * G;
+    const int inst = slot < a.n_fast ? a.order[slot] : -1;
+    uint64_t todo = __ballot(inst >= 0 && a.status[inst] == kCnfPending);
+    while (todo) {
+      const int l = __ffsll((unsigned long long)todo) - 1;
+      todo &= todo - 1ull;
+      cnf_transform_wave<STAGED>(a, __builtin_amdgcn_readlane(inst, l), smem);
+    }
+  }
+}
+
+hipError_t launch_cnf_clauses(const CnfArgs& a, int n_clauses, uint4* rec, hipStream_t s) {
+  if (n_clauses <= 0) return hipSuccess;
+  hipLaunchKernelGGL(cnf_clause_kernel, dim3((unsigned)((n_clauses + 255) / 256)), dim3(256), 0, s, a.lits,
+                     a.clause_off, a.clause_reach, n_clauses, rec);
+  return hipGetLastError();
+}
+
+hipError_t launch_cnf_transform(const CnfArgs& args, int max_vars, hipStream_t s) {
+  if (args.n_inst <= 0) return hipSuccess;
+  CnfArgs a = args;
+  if ((uintptr_t)a.expr % 16) a.n_fast = 0;  // its records go out in 16-byte pieces
+  if (a.n_fast > 0) {
+    hipLaunchKernelGGL(cnf_fast_kernel, dim3((unsigned)((a.n_fast + 7) / 8)), dim3(128), (size_t)8 * a.cls_stride, s,
+                       a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  const unsigned grid = (unsigned)(a.n_inst - a.n_fast + std::min(a.n_fast, kCnfSweep));
   const size_t cls_bytes = ((size_t)max_vars + 1 + 3) / 4 * 4;
   const size_t staged = 4 * (2 * (size_t)a.stage_clauses + 1 + (size_t)a.stage_lits) + cls_bytes;
   if (staged <= 64 * 1024)
-    hipLaunchKernelGGL(cnf_transform_kernel<true>, dim3((unsigned)a.n_inst), dim3(64), staged, s, a);
+    hipLaunchKernelGGL(cnf_transform_kernel<true>, dim3(grid), dim3(64), staged, s, a);
   else
-    hipLaunchKernelGGL(cnf_transform_kernel<false>, dim3((unsigned)a.n_inst), dim3(64), cls_bytes, s, a);
+    hipLaunchKernelGGL(cnf_transform_kernel<false>, dim3(grid), dim3(64), cls_bytes, s, a);
   return hipGetLastError();
 }
 

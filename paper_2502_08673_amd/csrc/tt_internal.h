@@ -413,7 +413,11 @@ struct CnfArgs {
   const int32_t* clause_reach;  // global clause -> last clause (instance-local) using any of its variables
   const int32_t* var_off;       // instance -> first class byte
   const int32_t* n_vars;
-  const int32_t* order;         // block -> instance, by decreasing clause count (long walks start first)
+  const int32_t* order;         // instances: the first n_fast fit cnf_fast_kernel, then the others, each part
+                                // by decreasing clause count (long walks start first)
+  const uint4* clause_rec;      // global clause index -> its literals and reach in 16 bytes (cnf_clause_kernel)
+  int32_t n_fast;
+  int32_t cls_stride;           // class bytes of an instance of cnf_fast_kernel, in LDS
   uint8_t* var_class;
   tt_cnf_expr* expr;
   int32_t* n_expr;
@@ -421,6 +425,9 @@ struct CnfArgs {
   int32_t n_inst;
   int32_t stage_clauses, stage_lits;  // the largest instance's clause and literal counts
 };
+constexpr int kCnfFastClause = 5;      // literals of a clause, at most, for cnf_fast_kernel
+constexpr int kCnfFastVarBytes = 2048; // its class bytes per instance, at most (16 KiB a block)
+hipError_t launch_cnf_clauses(const CnfArgs& a, int n_clauses, uint4* rec, hipStream_t s);
 hipError_t launch_cnf_transform(const CnfArgs& a, int max_vars, hipStream_t s);
 
 // Learned screen: BF16 MLP (tt_mlp.hip).

@@ -168,3 +168,46 @@ def test_repeated_literals_count_once():
     for t, (n, cl) in enumerate(inst):
         check_instance(t, cl, n, var_class, recs, n_expr, status, ioff, voff)
         voff += n + 1
+
+
+def _and(ins, f):
+    return [[f] + [-x for x in ins]] + [[-f, x] for x in ins]
+
+
+@pytest.mark.parametrize("n_inst,offset", [(1, 0), (9, 0), (70, 0), (9, 8)])
+def test_variable_order_and_sc_sizes_around_the_eight_lane_form(n_inst, offset):
+    """Instances whose SC reaches 2 to 8 variables (the eight-lane form holds
+    five, its clauses five literals; the others go to a wave each, before or
+    after they started in eight lanes), in shuffled variable names so that no
+    order of first use is the sorted one, with partial groups of eight (1, 9,
+    70 instances) and with records at an 8-byte offset."""
+    rng = np.random.default_rng(n_inst + offset)
+    inst = []
+    for t in range(n_inst):
+        nv, cl = tseitin_instances(seed=1000 + t, n_inst=1)[0]
+        k = 2 + t % 7
+        cl = cl + _and(list(range(nv + 1, nv + k)), nv + k)  # SC of k variables, clause of k literals
+        m = nv + k
+        k = 2 + (t // 2) % 7  # an auxiliary SC of k variables in binary clauses
+        cl = cl + [[x, x + 1] for x in range(m + 1, m + k)] + [[-(m + 1), -(m + k)]]
+        m += k
+        name = rng.permutation(m) + 1
+        inst.append((m, [[int(np.sign(L)) * int(name[abs(L) - 1]) for L in c] for c in cl]))
+    lits, coff, ioff, nv = tt.cnf_csr(inst)
+    n_cl = int(ioff[-1])
+    var_class = torch.full((int((nv + 1).sum()),), 0xEE, dtype=torch.uint8, device="cuda")
+    buf = torch.zeros((n_cl * 640 + 16,), dtype=torch.uint8, device="cuda")
+    expr = buf[offset: offset + n_cl * 640]
+    n_expr = torch.full((n_inst,), -1, dtype=torch.int32, device="cuda")
+    status = torch.full((n_inst,), -1, dtype=torch.int32, device="cuda")
+    note(f"cnf shuffled instances={n_inst} offset={offset}")
+    tt.cnf_transform(lits, coff, ioff, nv, var_class, expr, n_expr, status)
+    torch.cuda.synchronize()
+    assert (status.cpu().numpy() == 0).all()
+    recs = expr.cpu().numpy().view(tt.CNF_EXPR_DTYPE)
+    vc, ne = var_class.cpu().numpy(), n_expr.cpu().numpy()
+    voff = 0
+    for t, (n, cl) in enumerate(inst):
+        check_instance(t, cl, n, vc, recs, ne, status.cpu().numpy(), ioff, voff)
+        voff += n + 1
+    assert not buf[: offset].any() and not buf[offset + n_cl * 640:].any()
