@@ -642,6 +642,37 @@ int tt_adam_step_multi(int count, float* const* h_d_p, const float* const* h_d_g
                        float* const* h_d_v, uint16_t* const* h_d_p_bf16, const size_t* h_n, float lr, float beta1,
                        float beta2, float eps, int step, void* stream);
 
+/* The device buffers of the screening network 32 -> 256 -> 256 -> 256 -> 12
+ * in training, index = layer: bf16 weights w[l] ([out][in]), fp32 masters of
+ * weights and biases, their gradients and Adam moments, the hidden layers'
+ * activations and gradients act, dh ([batch][256] bf16), logits z and dL/dz
+ * dz ([batch][12]), the loss, and scratch of tt_mlp_train_scratch_floats(
+ * batch) floats. */
+typedef struct tt_mlp_train_state {
+  uint16_t* w[4];
+  float *pw[4], *pb[4], *gw[4], *gb[4], *mw[4], *mb[4], *vw[4], *vb[4];
+  uint16_t *act[3], *dh[3];
+  float* z;
+  uint16_t* dz;
+  float* loss;
+  float* scratch;
+  size_t scratch_floats;
+} tt_mlp_train_state;
+
+/* Scratch floats of tt_mlp_train_step (0 when batch is not positive). */
+size_t tt_mlp_train_scratch_floats(int batch);
+
+/* One training step on a batch (x[batch][32] bf16, targets y, m, h as
+ * tt_screen_labels writes them): the results of tt_mlp_forward through the
+ * layers, tt_mlp_loss, tt_mlp_backward and tt_adam_step_multi on the state's
+ * buffers, in three launches (the loss adds its terms in another fixed
+ * order).  Every pointer must be 16-byte
+ * aligned.  TT_EINVAL for NULL or misaligned pointers, batch < 1 or
+ * step < 1; TT_ERANGE for a scratch that is too small. */
+int tt_mlp_train_step(const tt_mlp_train_state* h_state, const uint16_t* d_x, const float* d_y, const float* d_m,
+                      const float* d_h, int batch, float lr, float beta1, float beta2, float eps, int step,
+                      void* stream);
+
 /* y = x rounded to bf16 (nearest, ties to even), n elements. */
 int tt_cast_bf16(const float* d_x, uint16_t* d_y, size_t n, void* stream);
 

@@ -53,6 +53,14 @@ class TTTune(ctypes.Structure):
         return {k: getattr(self, k) for k, _ in self._fields_}
 
 
+class TTMlpTrainState(ctypes.Structure):
+    _fields_ = ([("w", ctypes.c_void_p * 4)] +
+                [(k, ctypes.c_void_p * 4) for k in ("pw", "pb", "gw", "gb", "mw", "mb", "vw", "vb")] +
+                [(k, ctypes.c_void_p * 3) for k in ("act", "dh")] +
+                [(k, ctypes.c_void_p) for k in ("z", "dz", "loss", "scratch")] +
+                [("scratch_floats", ctypes.c_size_t)])
+
+
 _LIB = None
 
 
@@ -136,6 +144,9 @@ def lib():
         L.tt_adam_step.argtypes = [vp, vp, vp, vp, vp, sz, fl, fl, fl, fl, i32, vp]
         L.tt_adam_step_multi.argtypes = [i32, vp, vp, vp, vp, vp, vp, fl, fl, fl, fl, i32, vp]
         L.tt_cast_bf16.argtypes = [vp, vp, sz, vp]
+        L.tt_mlp_train_scratch_floats.argtypes = [i32]
+        L.tt_mlp_train_scratch_floats.restype = sz
+        L.tt_mlp_train_step.argtypes = [ctypes.POINTER(TTMlpTrainState), vp, vp, vp, vp, i32, fl, fl, fl, fl, i32, vp]
         L.tt_screen_work_bytes.argtypes = [i32]
         L.tt_screen_work_bytes.restype = sz
         L.tt_screen_run.argtypes = [vp, i32, vp, fl, vp, vp, u64, vp, vp, vp, vp, vp, vp, vp]
@@ -148,7 +159,7 @@ def lib():
                      "tt_lutnet_destroy", "tt_lutnet_sample", "tt_cnf_transform",
                      "tt_cnf_create", "tt_cnf_run", "tt_cnf_destroy", "tt_gd_create", "tt_gd_inputs", "tt_gd_input_vars", "tt_simplify",
                      "tt_gd_run", "tt_gd_run_from", "tt_gd_sample_unique", "tt_gd_unique", "tt_gd_kernel", "tt_gd_set_kernel", "tt_gd_destroy", "tt_sop_minimize", "tt_kmap_text", "tt_mlp_backward", "tt_mlp_loss",
-                     "tt_adam_step", "tt_adam_step_multi", "tt_cast_bf16",
+                     "tt_adam_step", "tt_adam_step_multi", "tt_cast_bf16", "tt_mlp_train_step",
                      "tt_screen_run", "tt_screen_infer", "tt_screen_expand"):
             getattr(L, name).restype = i32
         _LIB = L
@@ -645,6 +656,16 @@ class AdamGroup:
     def step(self, lr, beta1, beta2, eps, step, stream=None) -> None:
         check(lib().tt_adam_step_multi(self.count, self._p, self._g, self._m, self._v, self._pb, self._n, lr, beta1,
                                        beta2, eps, step, _stream(stream)), "tt_adam_step_multi")
+
+
+def mlp_train_scratch_floats(batch) -> int:
+    return int(lib().tt_mlp_train_scratch_floats(int(batch)))
+
+
+def mlp_train_step(state: TTMlpTrainState, x, y, m, h, batch, lr, beta1, beta2, eps, step, stream=None) -> None:
+    """One training step of the screening network (tt_mlp_train_step)."""
+    check(lib().tt_mlp_train_step(ctypes.byref(state), _ptr(x), _ptr(y), _ptr(m), _ptr(h), batch, lr, beta1, beta2,
+                                  eps, step, _stream(stream)), "tt_mlp_train_step")
 
 
 def cast_bf16(x, y, stream=None) -> None:

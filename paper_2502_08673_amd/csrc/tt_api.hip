@@ -2152,6 +2152,53 @@ int tt_adam_step(float* d_p, const float* d_g, float* d_m, float* d_v, uint16_t*
   return TT_OK;
 }
 
+size_t tt_mlp_train_scratch_floats(int batch) { return tt::train_scratch_floats(batch); }
+
+int tt_mlp_train_step(const tt_mlp_train_state* st, const uint16_t* d_x, const float* d_y, const float* d_m,
+                      const float* d_h, int batch, float lr, float beta1, float beta2, float eps, int step,
+                      void* stream) {
+  if (!st || batch < 1 || step < 1) return TT_EINVAL;
+  tt::TrainArgs a{};
+  bool ok = true;
+  auto take = [&](auto& to, auto* from) {
+    ok = ok && from && (uintptr_t)from % 16 == 0;
+    to = from;
+  };
+  take(a.x, d_x);
+  take(a.y, d_y);
+  take(a.m, d_m);
+  take(a.h, d_h);
+  for (int l = 0; l < 4; ++l) {
+    take(a.wb[l], st->w[l]);
+    a.w[l] = st->w[l];
+    take(a.p[l], st->pw[l]);
+    take(a.p[4 + l], st->pb[l]);
+    a.b[l] = st->pb[l];
+    take(a.g[l], st->gw[l]);
+    take(a.g[4 + l], st->gb[l]);
+    take(a.am[l], st->mw[l]);
+    take(a.am[4 + l], st->mb[l]);
+    take(a.av[l], st->vw[l]);
+    take(a.av[4 + l], st->vb[l]);
+    if (l < 3) {
+      take(a.act[l], st->act[l]);
+      take(a.dh[l], st->dh[l]);
+    }
+  }
+  take(a.z, st->z);
+  take(a.dz, st->dz);
+  take(a.loss, st->loss);
+  float* scratch = nullptr;
+  take(scratch, st->scratch);
+  if (!ok) return TT_EINVAL;
+  if (st->scratch_floats < tt::train_scratch_floats(batch)) return TT_ERANGE;
+  a.batch = batch;
+  const float bc1 = 1.0f - (float)std::pow((double)beta1, (double)step);
+  const float bc2 = 1.0f - (float)std::pow((double)beta2, (double)step);
+  TT_HIPCALL(tt::train_step(a, scratch, lr, beta1, beta2, eps, bc1, bc2, (hipStream_t)stream));
+  return TT_OK;
+}
+
 namespace {
 struct ScreenWork {
   size_t res, mask, mode, accept, list, count, total;

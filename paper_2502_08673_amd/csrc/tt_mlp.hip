@@ -1124,6 +1124,458 @@ hipError_t mlp_infer_gated_list(const tt_neuron* desc, int n, const uint16_t* co
   return hipGetLastError();
 }
 
+// ------------------------------------------------------------ training step
+// One step of the network's training in three launches: train_rows_kernel
+// (forward, loss, input gradients of 32 rows a block), train_dw_kernel
+// (weight and bias gradients, all layers, split over the batch) and
+// train_update_kernel (their sums in a fixed order, Adam).  The layers'
+// products are the ones the per-layer kernels make, in the same order of k,
+// and the gradients' partial sums their sums in the same order, so only the
+// loss adds its fp32 terms in other groups.
+// A step of 4096 rows takes 34 us: 17, 10 and 6 us (nineteen launches, layer
+// by layer: 174 us).  The rows kernel is bound by the chain of its layers,
+// 2 us each of 256 x 256 (every wave reads all 32 rows' activations and
+// passes its weights through LDS; with fragments loaded straight from the
+// weights' rows, half a line at a time, it took 20 us).
+constexpr int kTrainRows = 32;
+// a wave's patch of LDS: 32 weight rows of 64 elements, or 64 of 32, the
+// rows padded to spread the banks
+constexpr int kTrainRowPatch = 64 + 8, kTrainColPatch = 32 + 16;
+constexpr int kTrainPatch = 64 * kTrainColPatch;
+static_assert(32 * kTrainRowPatch <= kTrainPatch, "one patch serves both");
+constexpr size_t kTrainLds = sizeof(uint16_t) * (5 * kTrainRows * kActRow + 12 * kActRow + kTrainRows * (40 + 24) +
+                                                 8 * kTrainPatch) +
+                             sizeof(float) * (4 * 256 + kTrainRows * 12 + 8);
+static_assert(kTrainLds <= 160 * 1024, "a block fits a CU's LDS");
+
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+
+// Four elements of a column of a row-major 16-bit tile in LDS, as the lanes
+// of a group of sixteen pass the 8-byte pieces of a 4 x 16 block: lane 4 r + c
+// points at row r, columns 4 c .. 4 c + 3 and receives rows 0 .. 3 of column
+// (lane % 16).
+__device__ __forceinline__ s16x4 lds_column4(const uint16_t* p) {
+  return __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(p));
+}
+// The MFMA fragment of 32 columns x 16 rows of such a tile: elements
+// 8 (l / 32) + t, t = 0 .. 7, of column l % 32; `tile` points at row 0 of the
+// first column, rows `stride` elements apart.
+__device__ __forceinline__ bf16x8 lds_columns(const uint16_t* tile, int stride) {
+  const int lane = threadIdx.x & 63, g = lane >> 4;
+  const uint16_t* p = tile + (8 * (g >> 1) + ((lane & 15) >> 2)) * stride + 16 * (g & 1) + 4 * (lane & 3);
+  const s16x4 lo = lds_column4(p), hi = lds_column4(p + 4 * stride);
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+__device__ __forceinline__ f32x16 zero16() {
+  f32x16 z;
+#pragma unroll
+  for (int v = 0; v < 16; ++v) z[v] = 0.f;
+  return z;
+}
+__device__ __forceinline__ uint2 pack4_bf16(float a, float b, float c, float d) {
+  const f32x2 lo = {a, b}, hi = {c, d};
+  return make_uint2(__builtin_bit_cast(uint32_t, __builtin_convertvector(lo, bf16x2)),
+                    __builtin_bit_cast(uint32_t, __builtin_convertvector(hi, bf16x2)));
+}
+
+// A block: 32 rows through the network and back, their activations and
+// gradients in LDS (H, D: bf16 rows of 264; the first layer's gradients take
+// its activations' place), wave w holding columns 32 w .. 32 w + 31 of every
+// hidden layer.  A product is computed transposed (weight rows as the MFMA's
+// A operand), so a lane ends up with runs of four columns of one row.  Each
+// layer's weights are loaded while the layer before is computed, in whole
+// lines of the wave's own part, and pass through the wave's patch of LDS
+// (no barrier) on their way to fragments: rows as they are forward, columns
+// turned around backward.  Nothing is stored before the last load is issued
+// (a wait for a load also waits for the stores before it).
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(1, 2))) void train_rows_kernel(TrainArgs a) {
+  extern __shared__ uint16_t lds[];
+  constexpr int kLayer = kTrainRows * kActRow;
+  uint16_t* H = lds;                     // [3][32][kActRow] activations; [0] later dL/dh of the first layer
+  uint16_t* D = H + 3 * kLayer;          // [2][32][kActRow] dL/dh of the second and third
+  uint16_t* W4 = D + 2 * kLayer;         // [12][kActRow]
+  uint16_t* X = W4 + 12 * kActRow;       // [32][40] features
+  uint16_t* Z = X + kTrainRows * 40;     // [32][24] dL/dz, columns 12 .. 15 zero
+  uint16_t* S = Z + kTrainRows * 24;     // [8][kTrainPatch] the waves' patches
+  float* Bs = reinterpret_cast<float*>(S + 8 * kTrainPatch);  // [4][256] biases
+  float* Zf = Bs + 4 * 256;              // [32][12] logits
+  float* Ls = Zf + kTrainRows * 12;      // [8] loss of each wave's rows
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int m0 = blockIdx.x * kTrainRows, rows = min(kTrainRows, a.batch - m0);
+  const int n0 = 32 * wave, hk = 8 * (lane >> 5), ln = lane & 31;
+  uint16_t* patch = S + wave * kTrainPatch;
+  // the first loads: features, the first layer, biases, the output layer,
+  // the second layer, this thread's targets (row tid / 16, column tid % 16)
+  uint4 xv = make_uint4(0u, 0u, 0u, 0u), w4v = xv;
+  if (tid < 128 && (tid >> 2) < rows)
+    xv = *reinterpret_cast<const uint4*>(a.x + (int64_t)(m0 + (tid >> 2)) * 32 + 8 * (tid & 3));
+  bf16x8 f1[2];
+#pragma unroll
+  for (int st = 0; st < 2; ++st) f1[st] = *reinterpret_cast<const bf16x8*>(a.w[0] + (n0 + ln) * 32 + 16 * st + hk);
+  float bv[4];
+#pragma unroll
+  for (int l = 0; l < 4; ++l) bv[l] = tid < (l < 3 ? 256 : 12) ? a.b[l][tid] : 0.f;
+  if (tid < 384) w4v = *reinterpret_cast<const uint4*>(a.w[3] + (tid >> 5) * 256 + 8 * (tid & 31));
+  // pieces of the wave's 32 rows of a layer: piece 4 c + i holds rows 8 i +
+  // lane / 8 of columns 64 c .. 64 c + 63 (whole lines)
+  auto row_piece = [&](const uint16_t* w, int p) {
+    return *reinterpret_cast<const uint4*>(w + (n0 + 8 * (p & 3) + (lane >> 3)) * 256 + 64 * (p >> 2) + 8 * (lane & 7));
+  };
+  // and of its 32 columns: piece p holds rows 16 p + lane / 4
+  auto col_piece = [&](const uint16_t* w, int p) {
+    return *reinterpret_cast<const uint4*>(w + (16 * p + (lane >> 2)) * 256 + n0 + 8 * (lane & 3));
+  };
+  uint4 r2[16], r3[16], c3[16], c2[16];
+#pragma unroll
+  for (int p = 0; p < 16; ++p) r2[p] = row_piece(a.w[1], p);
+  const int lr = tid >> 4, lc = tid & 15;
+  float ty = 0.f, tm = 0.f;
+  if (lr < rows && lc < 12) {
+    const int64_t m = m0 + lr;
+    ty = lc < 8 ? a.y[m * 8 + lc] : a.h[m * 4 + lc - 8];
+    if (lc < 8) tm = a.m[m * 8 + lc];
+  }
+  if (tid < 128) *reinterpret_cast<uint4*>(&X[(tid >> 2) * 40 + 8 * (tid & 3)]) = xv;
+  if (tid < 256) {
+#pragma unroll
+    for (int l = 0; l < 4; ++l) Bs[256 * l + tid] = bv[l];
+  }
+  if (tid < 384) *reinterpret_cast<uint4*>(&W4[(tid >> 5) * kActRow + 8 * (tid & 31)]) = w4v;
+  __syncthreads();
+  // register v of lane l: column n0 + 8 (v / 4) + 4 (l / 32) + v % 4 of row l % 32
+  auto store_act = [&](const f32x16& acc, int l) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int n = n0 + 8 * q + 4 * (lane >> 5);
+      const float4 b = *reinterpret_cast<const float4*>(Bs + 256 * l + n);
+      *reinterpret_cast<uint2*>(&H[l * kLayer + ln * kActRow + n]) =
+          pack4_bf16(fmaxf(acc[4 * q] + b.x, 0.f), fmaxf(acc[4 * q + 1] + b.y, 0.f), fmaxf(acc[4 * q + 2] + b.z, 0.f),
+                     fmaxf(acc[4 * q + 3] + b.w, 0.f));
+    }
+  };
+  auto row16 = [&](const uint16_t* h, int stride, int st) {
+    return *reinterpret_cast<const bf16x8*>(h + ln * stride + 16 * st + hk);
+  };
+  f32x16 acc = zero16();
+#pragma unroll
+  for (int st = 0; st < 2; ++st) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f1[st], row16(X, 40, st), acc, 0, 0, 0);
+  store_act(acc, 0);
+#pragma unroll
+  for (int p = 0; p < 16; ++p) r3[p] = row_piece(a.w[2], p);
+  __syncthreads();
+  auto forward = [&](const uint4 (&r)[16], int l) {  // H[l] from H[l - 1] through W[l]
+    acc = zero16();
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        *reinterpret_cast<uint4*>(patch + (8 * i + (lane >> 3)) * kTrainRowPatch + 8 * (lane & 7)) = r[4 * c + i];
+#pragma unroll
+      for (int st = 0; st < 4; ++st)
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(row16(patch, kTrainRowPatch, st),
+                                                      row16(H + (l - 1) * kLayer, kActRow, 4 * c + st), acc, 0, 0, 0);
+    }
+    store_act(acc, l);
+  };
+  forward(r2, 1);
+#pragma unroll
+  for (int p = 0; p < 16; ++p) c3[p] = col_piece(a.w[2], p);
+  __syncthreads();
+  forward(r3, 2);
+#pragma unroll
+  for (int p = 0; p < 16; ++p) c2[p] = col_piece(a.w[1], p);
+  __syncthreads();
+  // rows of a buffer to memory, 16 bytes a thread, by the threads from t0 on
+  auto rows_out = [&](const uint16_t* src, uint16_t* dst, int t, int threads) {
+    for (; t < kTrainRows * 32; t += threads)
+      if ((t >> 5) < rows)
+        *reinterpret_cast<uint4*>(dst + (int64_t)(m0 + (t >> 5)) * 256 + 8 * (t & 31)) =
+            *reinterpret_cast<const uint4*>(src + (t >> 5) * kActRow + 8 * (t & 31));
+  };
+  if (wave == 0) {
+    // logits: lane l holds columns 4 (l / 32) .. + 3 (and, below 32, columns
+    // 8 .. 11) of row l % 32
+    acc = zero16();
+    const bf16x8 none = {};
+#pragma unroll
+    for (int st = 0; st < 16; ++st) {
+      const bf16x8 w = ln < 12 ? *reinterpret_cast<const bf16x8*>(&W4[ln * kActRow + 16 * st + hk]) : none;
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, row16(H + 2 * kLayer, kActRow, st), acc, 0, 0, 0);
+    }
+    const int c = 4 * (lane >> 5);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) Zf[ln * 12 + c + e] = acc[e] + Bs[768 + c + e];
+    if (lane < 32) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) Zf[ln * 12 + 8 + e] = acc[4 + e] + Bs[768 + 8 + e];
+    }
+  } else {
+    for (int l = 0; l < 3; ++l) rows_out(H + l * kLayer, a.act[l], tid - 64, 448);
+  }
+  __syncthreads();
+  {  // loss and dL/dz, an element a thread
+    const float inv = 1.0f / (float)a.batch;
+    float z = 0.f, loss = 0.f, dz = 0.f;
+    const bool live = lr < rows && lc < 12;
+    if (live) {
+      z = Zf[lr * 12 + lc];
+      if (lc < 8) {
+        const float sp = fmaxf(z, 0.f) + log1pf(expf(-fabsf(z)));
+        loss = tm * (sp - ty * z);
+        const float sg = 1.f / (1.f + expf(-z));
+        dz = tm * (sg - ty) * inv;
+      } else {
+        const float d = z - ty;
+        loss = d * d;
+        dz = 2.f * d * inv;
+      }
+    }
+    const uint16_t db = f32_to_bf16(dz);
+    Z[lr * 24 + lc] = db;
+    if (lr < rows) {
+      const int64_t m = m0 + lr;
+      a.dzp[m * 16 + lc] = db;
+      if (lc < 12) {
+        a.z[m * 12 + lc] = z;
+        a.dz[m * 12 + lc] = db;
+      }
+    }
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) loss += __shfl_xor(loss, off, 64);
+    if (lane == 0) Ls[wave] = loss;
+  }
+  __syncthreads();
+  // kept where the layer's activation is positive
+  auto store_grad = [&](const f32x16& g, const uint16_t* h, uint16_t* d) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int at = ln * kActRow + n0 + 8 * q + 4 * (lane >> 5);
+      const uint2 x = *reinterpret_cast<const uint2*>(h + at);
+      auto on = [](uint32_t v) { return v != 0u && (v & 0x8000u) == 0u; };
+      *reinterpret_cast<uint2*>(d + at) =
+          pack4_bf16(on(x.x & 0xFFFFu) ? g[4 * q] : 0.f, on(x.x >> 16) ? g[4 * q + 1] : 0.f,
+                     on(x.y & 0xFFFFu) ? g[4 * q + 2] : 0.f, on(x.y >> 16) ? g[4 * q + 3] : 0.f);
+    }
+  };
+  if (tid == 0)
+    a.loss_part[blockIdx.x] = ((Ls[0] + Ls[1]) + (Ls[2] + Ls[3])) + ((Ls[4] + Ls[5]) + (Ls[6] + Ls[7]));
+  {  // through the output layer: 12 of 16 rows of W4
+    bf16x8 w;
+#pragma unroll
+    for (int t = 0; t < 8; ++t)
+      w[t] = __builtin_bit_cast(__bf16, hk + t < 12 ? W4[(hk + t) * kActRow + n0 + ln] : (uint16_t)0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, *reinterpret_cast<const bf16x8*>(&Z[ln * 24 + hk]), zero16(), 0, 0, 0);
+    store_grad(acc, H + 2 * kLayer, D + kLayer);
+  }
+  __syncthreads();
+  auto back = [&](const uint4 (&c)[16], const uint16_t* dy) {  // dL/dh before a layer from dL/dh behind it
+    acc = zero16();
+#pragma unroll
+    for (int s4 = 0; s4 < 4; ++s4) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        *reinterpret_cast<uint4*>(patch + (16 * i + (lane >> 2)) * kTrainColPatch + 8 * (lane & 3)) = c[4 * s4 + i];
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_columns(patch + 16 * i * kTrainColPatch, kTrainColPatch),
+                                                      row16(dy, kActRow, 4 * s4 + i), acc, 0, 0, 0);
+    }
+  };
+  back(c3, D + kLayer);
+  store_grad(acc, H + kLayer, D);
+  __syncthreads();
+  back(c2, D);
+  store_grad(acc, H, H);
+  __syncthreads();
+  rows_out(H, a.dh[0], tid, 512);
+  rows_out(D, a.dh[1], tid, 512);
+  rows_out(D + kLayer, a.dh[2], tid, 512);
+}
+
+// Weight and bias gradients of all layers, dW = dY^T X over slices of the
+// batch (the slices of gemm_dw_kernel, so that every partial sum is the
+// same): a block takes 64 outputs x 64 inputs of one layer and slice, its
+// four waves 32 x 32 each.  Both operands are row-major over the batch;
+// chunks of 64 rows go through LDS as they are, the next chunk's loads in
+// flight, and the MFMA fragments (eight batch rows of a column) are read
+// transposed.
+__global__ __launch_bounds__(256) void train_dw_kernel(TrainArgs a) {
+  __shared__ __align__(16) uint16_t As[64][kDwRow];  // dY[k][m0 + i]
+  __shared__ __align__(16) uint16_t Bs[64][kDwRow];  // X[k][n0 + j]
+  __shared__ float s_col[4][64];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // blocks in layer order 2, 1 (16 tiles a slice), 0, 3 (4 tiles a slice)
+  int t = blockIdx.x, l = 2;
+  if (t >= 16 * a.slices[2]) {
+    t -= 16 * a.slices[2];
+    l = 1;
+    if (t >= 16 * a.slices[1]) {
+      t -= 16 * a.slices[1];
+      l = 0;
+      if (t >= 4 * a.slices[0]) {
+        t -= 4 * a.slices[0];
+        l = 3;
+      }
+    }
+  }
+  const bool square = l == 1 || l == 2;
+  const int tile = t & (square ? 15 : 3), sl = t >> (square ? 4 : 2);
+  const int mt = square ? tile >> 2 : (l == 0 ? tile : 0), nt = square ? tile & 3 : (l == 0 ? 0 : tile);
+  const int M = l == 3 ? 12 : 256, N = l == 0 ? 32 : 256, sy = l == 3 ? 16 : 256;
+  const uint16_t* dy = l == 3 ? a.dzp : a.dh[l];
+  const uint16_t* x = l == 0 ? a.x : a.act[l - 1];
+  const int m0 = 64 * mt, n0 = 64 * nt;
+  const int kb = sl * a.kslice[l], ke = min(a.batch, kb + a.kslice[l]);
+  const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
+  const bool want_db = nt == 0;
+  float col = 0.f;
+  f32x16 acc = zero16();
+  // two 8-element pieces per thread and operand: rows tid / 8 and + 32,
+  // columns 8 (tid % 8) ..
+  const int pr = tid >> 3, pc = 8 * (tid & 7);
+  const bool ya = m0 + pc < sy, xa = n0 + pc < N;
+  uint4 av[2], bv[2];
+  auto fetch = [&](int k0) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int k = k0 + pr + 32 * h;
+      av[h] = bv[h] = make_uint4(0u, 0u, 0u, 0u);
+      if (k < ke && ya) av[h] = *reinterpret_cast<const uint4*>(dy + (int64_t)k * sy + m0 + pc);
+      if (k < ke && xa) bv[h] = *reinterpret_cast<const uint4*>(x + (int64_t)k * N + n0 + pc);
+    }
+  };
+  fetch(kb);
+  for (int k0 = kb; k0 < ke; k0 += 64) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      *reinterpret_cast<uint4*>(&As[pr + 32 * h][pc]) = av[h];
+      *reinterpret_cast<uint4*>(&Bs[pr + 32 * h][pc]) = bv[h];
+    }
+    if (k0 + 64 < ke) fetch(k0 + 64);
+    __syncthreads();
+    if (want_db) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) col += bf16_to_f32(As[wave * 16 + r][lane]);
+    }
+#pragma unroll
+    for (int st = 0; st < 4; ++st)
+      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_columns(&As[16 * st][wm], kDwRow), lds_columns(&Bs[16 * st][wn], kDwRow),
+                                                    acc, 0, 0, 0);
+    __syncthreads();
+  }
+  if (want_db) {
+    s_col[wave][lane] = col;
+    __syncthreads();
+    if (tid < 64 && m0 + tid < M)
+      a.dbp[l][sl * M + m0 + tid] = (s_col[0][tid] + s_col[1][tid]) + (s_col[2][tid] + s_col[3][tid]);
+  }
+  // register v of lane l: row wm + 8 (v / 4) + 4 (l / 32) + v % 4, column wn + l % 32
+  float* part = a.part[l] + (int64_t)sl * M * N;
+  const int n = n0 + wn + (lane & 31);
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    const int m = m0 + wm + 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3);
+    if (m < M && n < N) part[m * N + n] = acc[v];
+  }
+}
+
+// The gradients (partial sums in the order of dw_reduce_kernel), Adam, and
+// the loss.
+__global__ __launch_bounds__(256) void train_update_kernel(TrainArgs a, float lr, float b1, float b2, float eps,
+                                                           float bc1, float bc2) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (blockIdx.x == 0 && threadIdx.x < 64) {
+    float s = 0.f;
+    for (int k = threadIdx.x; k < a.row_blocks; k += 64) s += a.loss_part[k];
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
+    if (threadIdx.x == 0) a.loss[0] = s / (float)a.batch;
+  }
+  if (i >= kTrainParams) return;
+  // tensor and element: weights of the four layers, then biases
+  int t, j;
+  float gi;
+  if (i < kTrainWeights) {
+    t = (i >= 8192) + (i >= 8192 + 65536) + (i >= 8192 + 2 * 65536);
+    j = i - (t == 0 ? 0 : 8192 + 65536 * (t - 1));
+    const int MN = t == 0 ? 8192 : t == 3 ? 3072 : 65536, S = a.slices[t];
+    const float* p = a.part[t] + j;
+    float c[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    int s = 0;
+    for (; s + 8 <= S; s += 8) {
+#pragma unroll
+      for (int k = 0; k < 8; ++k) c[k] += p[(int64_t)(s + k) * MN];
+    }
+#pragma unroll
+    for (int k = 0; k < 8; ++k)
+      if (s + k < S) c[k] += p[(int64_t)(s + k) * MN];
+    gi = ((c[0] + c[1]) + (c[2] + c[3])) + ((c[4] + c[5]) + (c[6] + c[7]));
+  } else {
+    const int l = (i - kTrainWeights) >> 8;
+    t = 4 + l;
+    j = (i - kTrainWeights) & 255;
+    const int M = l == 3 ? 12 : 256;
+    gi = 0.f;
+#pragma unroll 8
+    for (int s = 0; s < a.slices[l]; ++s) gi += a.dbp[l][s * M + j];
+  }
+  a.g[t][j] = gi;
+  const float mi = b1 * a.am[t][j] + (1.f - b1) * gi;
+  const float vi = b2 * a.av[t][j] + (1.f - b2) * gi * gi;
+  a.am[t][j] = mi;
+  a.av[t][j] = vi;
+  const float upd = lr * (mi / bc1) / (sqrtf(vi / bc2) + eps);
+  const float pi = a.p[t][j] - upd;
+  a.p[t][j] = pi;
+  if (t < 4) a.wb[t][j] = f32_to_bf16(pi);
+}
+
+// Places of the partial sums and of dL/dz in the scratch; returns its floats.
+static size_t train_layout(TrainArgs& a, float* scratch) {
+  size_t o = 0;
+  auto take = [&](size_t floats) {
+    float* at = scratch + o;
+    o += (floats + 3) / 4 * 4;
+    return at;
+  };
+  a.row_blocks = (a.batch + kTrainRows - 1) / kTrainRows;
+  for (int l = 0; l < 4; ++l) {
+    const int M = l == 3 ? 12 : 256, N = l == 0 ? 32 : 256;
+    const DwSplit sp = dw_split(a.batch, M, N);
+    a.slices[l] = sp.S;
+    a.kslice[l] = sp.kslice;
+    a.part[l] = take((size_t)sp.S * M * N);
+    a.dbp[l] = take((size_t)sp.S * M);
+  }
+  a.loss_part = take(a.row_blocks);
+  a.dzp = reinterpret_cast<uint16_t*>(take((size_t)a.batch * 8));
+  return o;
+}
+
+size_t train_scratch_floats(int batch) {
+  if (batch <= 0) return 0;
+  TrainArgs a{};
+  a.batch = batch;
+  return train_layout(a, nullptr);
+}
+
+hipError_t train_step(TrainArgs a, float* scratch, float lr, float b1, float b2, float eps, float bc1, float bc2,
+                      hipStream_t s) {
+  train_layout(a, scratch);
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&train_rows_kernel),
+                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)kTrainLds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(train_rows_kernel, dim3((unsigned)a.row_blocks), dim3(512), kTrainLds, s, a);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  const int tiles = 16 * (a.slices[1] + a.slices[2]) + 4 * (a.slices[0] + a.slices[3]);
+  hipLaunchKernelGGL(train_dw_kernel, dim3((unsigned)tiles), dim3(256), 0, s, a);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  hipLaunchKernelGGL(train_update_kernel, dim3((kTrainParams + 255) / 256), dim3(256), 0, s, a, lr, b1, b2, eps, bc1,
+                     bc2);
+  return hipGetLastError();
+}
+
 hipError_t mlp_forward(const uint16_t* x, int Bn, int in, const uint16_t* w, const float* bias, int out, int relu,
                        uint16_t* yb, float* yf, hipStream_t s) {
   GemmArgs g{};

@@ -15,6 +15,7 @@ import numpy as np
 
 from . import (  # noqa: F401
     AdamGroup,
+    TTMlpTrainState,
     adam_step,
     cast_bf16,
     descriptors,
@@ -26,6 +27,8 @@ from . import (  # noqa: F401
     mlp_infer,
     mlp_loss,
     mlp_scratch_floats,
+    mlp_train_scratch_floats,
+    mlp_train_step,
     screen_expand,
     screen_features,
     screen_labels,
@@ -66,13 +69,22 @@ class ScreenNet:
         self.z = torch.empty((B, DIMS[-1]), dtype=torch.float32, device=device)
         self.dz = torch.empty((B, DIMS[-1]), dtype=torch.int16, device=device)
         self.dh = [torch.empty((B, d), dtype=torch.int16, device=device) for d in DIMS[1:-1]]
-        self.scratch = torch.empty(max(mlp_scratch_floats(B, max(DIMS)), 64), dtype=torch.float32, device=device)
+        floats = max(mlp_scratch_floats(B, max(DIMS)), mlp_train_scratch_floats(B), 64)
+        self.scratch = torch.empty(floats, dtype=torch.float32, device=device)
         self.loss = torch.zeros(1, dtype=torch.float32, device=device)
         self.steps = 0
         self.infer_work = None  # the gated inference's candidate list
         # one Adam launch for all eight parameter tensors
         self.adam = AdamGroup(self.W32 + self.b32, self.gW + self.gb, self.mW + self.mb, self.vW + self.vb,
                               self.Wb + [None] * 4)
+        # the same buffers for the step in one call
+        self.state = TTMlpTrainState(scratch_floats=self.scratch.numel(), z=self.z.data_ptr(), dz=self.dz.data_ptr(),
+                                     loss=self.loss.data_ptr(), scratch=self.scratch.data_ptr())
+        for name, ts in (("w", self.Wb), ("pw", self.W32), ("pb", self.b32), ("gw", self.gW), ("gb", self.gb),
+                         ("mw", self.mW), ("mb", self.mb), ("vw", self.vW), ("vb", self.vb), ("act", self.acts),
+                         ("dh", self.dh)):
+            for l, t in enumerate(ts):
+                getattr(self.state, name)[l] = t.data_ptr()
 
     def forward(self, X, B: int):
         """Logits [B, 12] (fp32) for bf16 features X [B, 32]."""
@@ -120,6 +132,11 @@ class ScreenNet:
             g = dx
 
     def train_step(self, X, y, m, h, B: int, lr: float, beta1=0.9, beta2=0.999, eps=1e-8):
+        if 0 < B <= self.max_batch and not any(t.data_ptr() % 16 for t in (X, y, m, h)):
+            mlp_train_step(self.state, X, y, m, h, B, lr, beta1, beta2, eps, self.steps + 1)
+            self.steps += 1
+            return self.loss
+        # an unaligned batch: layer by layer
         self.forward(X, B)
         mlp_loss(self.z, B, y, m, h, self.dz, self.loss, self.scratch)
         self.backward(X, B)

@@ -408,3 +408,74 @@ def test_device_descriptor_enumerate_and_support():
     tt.enumerate_device(dbad, c.n, tables2, status=status)
     torch.cuda.synchronize()
     assert status.item() & 1
+
+
+@pytest.mark.parametrize("B", [1, 31, 33, 64, 65, 1000, 4097])
+def test_train_step_in_one_call_matches_the_layer_calls(B):
+    """tt_mlp_train_step against tt_mlp_forward / loss / backward / Adam on
+    the same state, batches around the 32-row blocks, the 64-row chunks and
+    the batch slices.  Products are the same sums in the same order of k:
+    bf16 buffers may differ in at most one value in a thousand, by one
+    rounding (2^-7).  Gradients and loss are fp32 sums of the same terms in
+    two orders: each order is off by at most (terms + 64) 2^-24 of the sum of
+    the terms' sizes.  Adam from the step's own gradients: the same formula,
+    1e-6."""
+    sc = tt.screen
+    rng = np.random.default_rng(B)
+    params = [(w, rng.uniform(-0.1, 0.1, size=b.shape).astype(np.float32)) for w, b in mlp_init(20250212 + 900 + B)]
+    X = torch.from_numpy(rng.normal(0, 0.7, size=(B, 32)).astype(np.float32)).cuda().to(torch.bfloat16)
+    X = X.view(torch.int16)
+    y = torch.from_numpy((rng.random((B, 8)) < 0.6).astype(np.float32)).cuda()
+    m = torch.from_numpy((rng.random((B, 8)) < 0.8).astype(np.float32)).cuda()
+    h = torch.from_numpy(rng.random((B, 4)).astype(np.float32)).cuda()
+    one, ref = sc.ScreenNet(params, max_batch=B), sc.ScreenNet(params, max_batch=B)
+    note(f"train step B={B}")
+    one.train_step(X, y, m, h, B, 2e-3)
+    ref.forward(X, B)
+    tt.mlp_loss(ref.z, B, y, m, h, ref.dz, ref.loss, ref.scratch)
+    ref.backward(X, B)
+    # Adam on the reference's state from the one-call gradients
+    before = [t.clone() for t in ref.W32 + ref.b32]
+    tt.AdamGroup(ref.W32 + ref.b32, one.gW + one.gb, ref.mW + ref.mb, ref.vW + ref.vb, ref.Wb + [None] * 4).step(
+        2e-3, 0.9, 0.999, 1e-8, 1)
+    torch.cuda.synchronize()
+    val = lambda t: t.view(torch.bfloat16).double()
+    for a, b in zip(one.acts + one.dh + [one.dz], ref.acts + ref.dh + [ref.dz]):
+        assert float((a != b).double().mean()) <= 1e-3
+        assert bool(((val(a) - val(b)).abs() <= 2.0 ** -7 * val(b).abs() + 1e-30).all())
+    assert torch.allclose(one.z, ref.z, rtol=1e-5, atol=1e-5)
+    eps = (B + 64) * 2.0 ** -24
+    ins, outs = [val(X)] + [val(t) for t in ref.acts], [val(t) for t in ref.dh] + [val(ref.dz)]
+    for l in range(4):
+        size = outs[l].abs().cpu().T @ ins[l].abs().cpu()
+        assert bool(((one.gW[l] - ref.gW[l]).double().cpu().abs() <= 2 * eps * size + 1e-3 * 2.0 ** -7 * size).all())
+        size = outs[l].abs().sum(0)
+        assert bool(((one.gb[l] - ref.gb[l]).double().abs() <= 2 * eps * size + 1e-3 * 2.0 ** -7 * size).all())
+    assert abs(float(one.loss) - float(ref.loss)) <= 2 * (12 * B + 64) * 2.0 ** -24 * abs(float(ref.loss)) + 1e-6
+    for a, b, p in zip(one.W32 + one.b32, ref.W32 + ref.b32, before):
+        assert torch.allclose(a, b, rtol=1e-6, atol=1e-6)
+        assert not torch.equal(a, p)
+    for a, b in zip(one.mW + one.vW + one.mb + one.vb, ref.mW + ref.vW + ref.mb + ref.vb):
+        assert torch.allclose(a, b, rtol=1e-6, atol=1e-12)
+    for w, wb in zip(one.W32, one.Wb):
+        assert torch.equal(w.to(torch.bfloat16).view(torch.int16), wb)
+
+
+def test_train_step_arguments_and_unaligned_batches():
+    """An unaligned batch takes the layer calls; the one-call form refuses it,
+    a scratch that is too small, and missing pointers."""
+    B = 70
+    net = tt.screen.ScreenNet(mlp_init(20250212 + 990), max_batch=B)
+    X = torch.zeros(B * 32 + 4, dtype=torch.int16, device="cuda")[4:].view(B, 32)  # 8 bytes off
+    y, m = (torch.zeros((B, 8), device="cuda") for _ in range(2))
+    h = torch.zeros((B, 4), device="cuda")
+    with pytest.raises(tt.TTError) as e:
+        tt.mlp_train_step(net.state, X, y, m, h, B, 1e-3, 0.9, 0.999, 1e-8, 1)
+    assert e.value.status == tt.TT_EINVAL
+    net.train_step(X, y, m, h, B, 1e-3)
+    assert net.steps == 1
+    net.state.scratch_floats = tt.mlp_train_scratch_floats(B) - 1
+    with pytest.raises(tt.TTError) as e:
+        tt.mlp_train_step(net.state, X.clone(), y, m, h, B, 1e-3, 0.9, 0.999, 1e-8, 1)
+    assert e.value.status == tt.TT_ERANGE
+    torch.cuda.synchronize()
