@@ -1845,35 +1845,38 @@ int tt_pack(const tt_neuron* h_desc, int n, const uint8_t* d_codes, uint64_t tot
   if (!d_codes || !d_tables) return TT_EINVAL;
   TT_TRY(validate_ranges(h_desc, n, total_words));
   hipStream_t s = (hipStream_t)stream;
-  std::vector<uint64_t> code_off(n);
-  std::vector<int32_t> item_neuron, item_h0;
+  // offsets of the codes; records by number of rows, largest first
   uint64_t acc = 0;
+  int count[TT_MAX_FB + 1] = {0};
   for (int i = 0; i < n; ++i) {
-    code_off[i] = acc;
-    acc += 1ull << (h_desc[i].F * h_desc[i].b);
-    const uint64_t W = words_of(h_desc[i].F, h_desc[i].b);
-    for (uint64_t h0 = 0; h0 < W; h0 += 64) {
-      item_neuron.push_back(i);
-      item_h0.push_back((int32_t)h0);
-    }
+    const int fb = h_desc[i].F * h_desc[i].b;
+    acc += 1ull << fb;
+    ++count[fb];
   }
-  if (acc > total_codes) return TT_ERANGE;
+  if (acc > total_codes || acc >> 62) return TT_ERANGE;
   TT_TRY(device_info(nullptr));
-  size_t o = 0;
-  auto take = [&](size_t bytes) {
-    const size_t at = o;
-    o = align_up(o + bytes);
-    return at;
-  };
-  const size_t off_desc = take(sizeof(tt_neuron) * n);
-  const size_t off_code = take(sizeof(uint64_t) * n);
-  const size_t off_in = take(sizeof(int32_t) * item_neuron.size());
-  const size_t off_ih = take(sizeof(int32_t) * item_h0.size());
-  auto* blob = new std::vector<uint8_t>(o, 0);
-  std::memcpy(blob->data() + off_desc, h_desc, sizeof(tt_neuron) * n);
-  std::memcpy(blob->data() + off_code, code_off.data(), sizeof(uint64_t) * n);
-  std::memcpy(blob->data() + off_in, item_neuron.data(), sizeof(int32_t) * item_neuron.size());
-  std::memcpy(blob->data() + off_ih, item_h0.data(), sizeof(int32_t) * item_h0.size());
+  PackArgs pa{};
+  int at[TT_MAX_FB + 1], first = 0;
+  int64_t items = 0;
+  for (int fb = TT_MAX_FB; fb >= 0; --fb) {
+    at[fb] = first;
+    if (count[fb] == 0) continue;
+    const int k = pa.n_classes++;
+    pa.fb[k] = fb;
+    pa.rec_begin[k] = first;
+    first += count[fb];
+    items += (int64_t)count[fb] << std::max(0, fb - kPackRowsLog2);
+    pa.item_end[k] = items;
+  }
+  const size_t o = sizeof(PackRec) * (size_t)n;
+  auto* blob = new std::vector<uint8_t>(o);
+  auto* rec = reinterpret_cast<PackRec*>(blob->data());
+  acc = 0;
+  for (int i = 0; i < n; ++i) {
+    const int fb = h_desc[i].F * h_desc[i].b;
+    rec[at[fb]++] = PackRec{h_desc[i].word_off, acc | (uint64_t)h_desc[i].o << 62};
+    acc += 1ull << fb;
+  }
   uint8_t* ws = nullptr;
   hipError_t e = hipMallocAsync((void**)&ws, o, s);
   if (e != hipSuccess) {
@@ -1883,14 +1886,8 @@ int tt_pack(const tt_neuron* h_desc, int n, const uint8_t* d_codes, uint64_t tot
   }
   int st = upload_async(ws, blob, s);
   if (st == TT_OK) {
-    PackArgs pa{};
-    pa.desc = reinterpret_cast<const tt_neuron*>(ws + off_desc);
+    pa.rec = reinterpret_cast<const PackRec*>(ws);
     pa.codes = d_codes;
-    pa.code_off = reinterpret_cast<const uint64_t*>(ws + off_code);
-    pa.item_neuron = reinterpret_cast<const int32_t*>(ws + off_in);
-    pa.item_h0 = reinterpret_cast<const int32_t*>(ws + off_ih);
-    pa.n_items = (int)item_neuron.size();
-    pa.words_per_item = 64;
     pa.tables = d_tables;
     e = launch_pack(pa, s);
     if (e != hipSuccess) {

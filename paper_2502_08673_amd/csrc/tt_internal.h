@@ -85,15 +85,22 @@ struct SupportArgs {
 };
 constexpr int kSmallTableWords = 16;  // tables up to 2^10 rows: one lane each
 
+// Packing of row codes: neurons sorted by their number of rows, largest
+// first, a class per number; a neuron takes one work item per kPackRows rows
+// (at least one).
+constexpr int kPackRowsLog2 = 12;
+struct PackRec {
+  uint64_t word_off;
+  uint64_t code;  // offset of its codes, the output bits in the top two bits
+};
 struct PackArgs {
-  const tt_neuron* desc;
+  const PackRec* rec;
   const uint8_t* codes;
-  const uint64_t* code_off;  // [n]
-  const int32_t* item_neuron;
-  const int32_t* item_h0;    // first word of the item
-  int32_t n_items;
-  int32_t words_per_item;    // words per item (64 per wave)
   uint64_t* tables;
+  int32_t n_classes;
+  int32_t fb[TT_MAX_FB];         // log2 rows of each class
+  int32_t rec_begin[TT_MAX_FB];  // its first record
+  int64_t item_end[TT_MAX_FB];   // items of the classes up to and with it
 };
 
 // Bits l of a 64-row word whose partner l + 2^i differs in row bit i only

@@ -388,6 +388,33 @@ def test_pack_matches_oracle_planes():
     assert np.array_equal(hist.cpu().numpy().reshape(-1, 8).astype(np.uint32), ref2["hist"])
 
 
+@pytest.mark.parametrize("skew", [0, 1, 7])
+def test_pack_row_counts_and_code_alignment(skew):
+    """Every number of rows from 2 (less than a 16-byte load) over 64, 1024
+    and 4096 (a wave's loads and items) to 2^14, every o, in shuffled order,
+    with the codes at an odd address: neighbours of two rows leave every
+    following neuron's codes unaligned as well."""
+    rng = np.random.default_rng(40 + skew)
+    shapes = [(1, 1), (2, 1), (3, 1), (4, 1), (5, 1), (3, 2), (7, 1), (8, 1), (3, 3), (5, 2), (4, 3), (6, 2), (7, 2)]
+    ns = concat([random_neurons(seed=700 + 10 * i + o, n=2, F=(F, F), b=(b, b), o=(o, o), max_fb=14)
+                 for i, (F, b) in enumerate(shapes) for o in (1, 2, 3)])
+    ns = subset(ns, rng.permutation(len(ns)))
+    rows = sum(1 << (int(F) * int(b)) for F, b in zip(ns.F, ns.b))
+    codes = rng.integers(0, 256, size=rows, dtype=np.uint8)
+    ref = oracle.from_codes(ns, codes)
+    desc = tt.descriptors(ns)
+    total = tt.layout(desc)
+    tables = device_tables(total)
+    tables[:total].fill_(-1)
+    buf = torch.full((rows + 64,), 255, dtype=torch.uint8, device="cuda")
+    buf[skew: skew + rows] = torch.from_numpy(codes).cuda()
+    note(f"pack skew={skew}")
+    tt.pack(desc, buf[skew: skew + rows], tables)
+    torch.cuda.synchronize()
+    check_canary(tables, total)
+    assert np.array_equal(host_u64(tables, 0, total), ref["planes"])
+
+
 def test_autotune_returns_valid_config(tmp_path):
     ns = cfg2(n=800)
     desc = tt.descriptors(ns)
