@@ -93,12 +93,19 @@ int validate_all(const tt_neuron* h, int n) {
 
 // Every neuron's o*W words inside [0, total_words), and no two overlap.
 int validate_ranges(const tt_neuron* h, int n, uint64_t total_words) {
-  std::vector<std::pair<uint64_t, uint64_t>> r(n);
+  // in ascending order (as tt_layout places them) neighbours decide
+  uint64_t end = 0;
+  bool ascending = true;
   for (int i = 0; i < n; ++i) {
     const uint64_t len = (uint64_t)h[i].o * words_of(h[i].F, h[i].b);
     if (h[i].word_off > total_words || len > total_words - h[i].word_off) return TT_ERANGE;
-    r[i] = {h[i].word_off, h[i].word_off + len};
+    ascending = ascending && h[i].word_off >= end;
+    end = h[i].word_off + len;
   }
+  if (ascending) return TT_OK;
+  std::vector<std::pair<uint64_t, uint64_t>> r(n);
+  for (int i = 0; i < n; ++i)
+    r[i] = {h[i].word_off, h[i].word_off + (uint64_t)h[i].o * words_of(h[i].F, h[i].b)};
   std::sort(r.begin(), r.end());
   for (int i = 1; i < n; ++i)
     if (r[i].first < r[i - 1].second) return TT_EINVAL;
@@ -130,7 +137,8 @@ struct PlanHost {
   uint64_t total_words = 0;
   tt_tune tune{};
   unsigned flags = 0;
-  std::vector<tt_neuron> desc;
+  const tt_neuron* desc = nullptr;  // [n]: the caller's, or (a plan's) own
+  std::vector<tt_neuron> own;
   // wide neurons (empty arrays when there are none)
   std::vector<uint64_t> lut_off;  // [n]
   std::vector<int32_t> lut_cap;   // [n]
@@ -138,8 +146,7 @@ struct PlanHost {
   int lut_chunks = 1;  // the largest mask table in 64-entry chunks
   std::vector<Group> groups;
   std::vector<int32_t> group_neurons;
-  // the others, in the order their kernel takes them (reserved = index)
-  std::vector<tt_neuron> small;
+  std::vector<int32_t> small;         // the others, in the order their kernel takes them
   int n_block = 0;                    // how many take a block each
   int wave_lds = 0, block_lds = 0;    // largest mask table of each class
   std::vector<int32_t> mid, tiny;     // places in small by the span of their sums
@@ -265,9 +272,7 @@ void build_plan(PlanHost& P) {
   P.small.resize(at[kKeys]);
   for (int i = 0; i < n; ++i) {
     if (key[i] < 0) continue;
-    tt_neuron& d = P.small[at[key[i]]++];
-    d = P.desc[i];
-    d.reserved = (uint64_t)i;
+    P.small[at[key[i]]++] = i;
   }
   P.groups.clear();
   P.group_neurons.clear();
@@ -306,7 +311,7 @@ void build_plan(PlanHost& P) {
 void build_support_lists(PlanHost& P) {
   build_large_list(P);
   for (size_t k = 0; k < P.small.size(); ++k) {
-    const int R = sum_range_of(P.small[k]);
+    const int R = sum_range_of(P.desc[P.small[k]]);
     if (R < 512) (R < 64 ? P.tiny : P.mid).push_back((int32_t)k);
   }
 }
@@ -328,7 +333,7 @@ Layout layout_of(const PlanHost& P, bool with_desc = true) {
     o = align_up(o + bytes);
     return at;
   };
-  const size_t nd = with_desc ? P.desc.size() : 0;
+  const size_t nd = with_desc ? (size_t)P.n : 0;
   L.desc = take(sizeof(tt_neuron) * nd);
   L.small = take(sizeof(tt_neuron) * P.small.size());
   L.lut_off = take(sizeof(uint64_t) * P.lut_off.size());
@@ -339,7 +344,7 @@ Layout layout_of(const PlanHost& P, bool with_desc = true) {
   L.mid = take(sizeof(int32_t) * P.mid.size());
   L.tiny = take(sizeof(int32_t) * P.tiny.size());
   L.upload_bytes = o;
-  L.params = take(P.lut_off.empty() ? 0 : sizeof(NeuronParams) * P.desc.size());
+  L.params = take(P.lut_off.empty() ? 0 : sizeof(NeuronParams) * (size_t)P.n);
   const size_t sup = P.sup_lists.size();  // the support kernels' scratch
   L.found = take(sizeof(uint32_t) * sup);
   L.sup_list = take(sizeof(int32_t) * sup);  // neurons still pending a support check
@@ -349,13 +354,17 @@ Layout layout_of(const PlanHost& P, bool with_desc = true) {
   return L;
 }
 
-std::vector<uint8_t>* make_upload(const PlanHost& P, const Layout& L, bool with_desc = true) {
-  auto* blob = new std::vector<uint8_t>(L.upload_bytes, 0);
+// The uploaded part of the workspace (Layout::upload_bytes at dst).
+void write_upload(const PlanHost& P, const Layout& L, uint8_t* dst, bool with_desc = true) {
   auto put = [&](size_t at, const void* src, size_t bytes) {
-    if (bytes) std::memcpy(blob->data() + at, src, bytes);
+    if (bytes) std::memcpy(dst + at, src, bytes);
   };
-  if (with_desc) put(L.desc, P.desc.data(), sizeof(tt_neuron) * P.desc.size());
-  put(L.small, P.small.data(), sizeof(tt_neuron) * P.small.size());
+  if (with_desc) put(L.desc, P.desc, sizeof(tt_neuron) * (size_t)P.n);
+  auto* small = reinterpret_cast<tt_neuron*>(dst + L.small);
+  for (size_t k = 0; k < P.small.size(); ++k) {
+    small[k] = P.desc[P.small[k]];
+    small[k].reserved = (uint64_t)P.small[k];
+  }
   put(L.lut_off, P.lut_off.data(), sizeof(uint64_t) * P.lut_off.size());
   put(L.lut_cap, P.lut_cap.data(), sizeof(int32_t) * P.lut_cap.size());
   put(L.group_neurons, P.group_neurons.data(), sizeof(int32_t) * P.group_neurons.size());
@@ -363,6 +372,11 @@ std::vector<uint8_t>* make_upload(const PlanHost& P, const Layout& L, bool with_
   put(L.sup_lists, P.sup_lists.data(), sizeof(int32_t) * P.sup_lists.size());
   put(L.mid, P.mid.data(), sizeof(int32_t) * P.mid.size());
   put(L.tiny, P.tiny.data(), sizeof(int32_t) * P.tiny.size());
+}
+
+std::vector<uint8_t>* make_upload(const PlanHost& P, const Layout& L, bool with_desc = true) {
+  auto* blob = new std::vector<uint8_t>(L.upload_bytes);
+  write_upload(P, L, blob->data(), with_desc);
   return blob;
 }
 
@@ -390,6 +404,118 @@ int upload_async(void* dst, std::vector<uint8_t>* blob, hipStream_t s) {
     return TT_EHIP;
   }
   return TT_OK;
+}
+
+// Pinned staging buffers of the one-shot calls: from pageable memory a copy
+// first waits for the stream, and the host callback that frees it costs as
+// much as the launches (45 us a call in all, 20 with these).  Per device at
+// most kStageSlots buffers of at most kStageBytes; a call holds one until it
+// has queued its work, and the next user of the buffer waits for the event
+// recorded behind that work.  Inputs that are larger, and streams under
+// capture (a graph reads its source again on every replay), take the
+// pageable path.
+constexpr size_t kStageBytes = 1u << 20;
+constexpr int kStageSlots = 8;
+struct StageSlot {
+  uint8_t* host = nullptr;
+  size_t cap = 0;
+  hipEvent_t done = nullptr;
+  bool busy = false, pending = false;
+};
+std::mutex g_stage_mu;
+std::map<int, std::vector<StageSlot*>> g_stage;
+
+// A buffer of `bytes` for a call on `s`; *slot is NULL when the pageable path
+// has to be taken.
+int stage_acquire(size_t bytes, hipStream_t s, StageSlot** slot) {
+  *slot = nullptr;
+  if (bytes == 0 || bytes > kStageBytes) return TT_OK;
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cs) != hipSuccess) {
+    (void)hipGetLastError();
+    return TT_OK;
+  }
+  if (cs != hipStreamCaptureStatusNone) return TT_OK;
+  int dev = 0;
+  TT_HIP(hipGetDevice(&dev));
+  StageSlot* got = nullptr;
+  {
+    std::lock_guard<std::mutex> lk(g_stage_mu);
+    auto& slots = g_stage[dev];
+    StageSlot* waits = nullptr;  // the first that only its event keeps
+    for (size_t k = 0; k < slots.size() && !got; ++k) {
+      StageSlot* c = slots[k];
+      if (c->busy) continue;
+      if (!c->pending || hipEventQuery(c->done) == hipSuccess)
+        got = c;
+      else if (!waits)
+        waits = c;
+    }
+    if (!got && slots.size() < (size_t)kStageSlots) {
+      got = new (std::nothrow) StageSlot();
+      if (got) slots.push_back(got);
+    }
+    if (!got) got = waits;
+    if (!got) return TT_OK;  // every buffer is in a call right now
+    got->busy = true;
+    // the order of use: the buffer goes to the end, so that the one waited
+    // for is the oldest
+    slots.erase(std::find(slots.begin(), slots.end(), got));
+    slots.push_back(got);
+  }
+  hipError_t e = hipSuccess;
+  if (got->pending) e = hipEventSynchronize(got->done);
+  got->pending = false;
+  if (e == hipSuccess && !got->done) e = hipEventCreateWithFlags(&got->done, hipEventDisableTiming);
+  if (e == hipSuccess && got->cap < bytes) {
+    size_t cap = 1u << 16;
+    while (cap < bytes) cap *= 2;
+    if (got->host) (void)hipHostFree(got->host);
+    got->host = nullptr;
+    got->cap = 0;
+    e = hipHostMalloc((void**)&got->host, cap, hipHostMallocDefault);
+    if (e == hipSuccess) got->cap = cap;
+  }
+  if (e != hipSuccess) {
+    std::lock_guard<std::mutex> lk(g_stage_mu);
+    got->busy = false;
+    (void)hipGetLastError();
+    return TT_OK;
+  }
+  *slot = got;
+  return TT_OK;
+}
+
+// The call has queued (on s) everything that reads the buffer.
+int stage_release(StageSlot* slot, hipStream_t s) {
+  hipError_t e = hipEventRecord(slot->done, s);
+  const bool recorded = e == hipSuccess;
+  if (!recorded) (void)hipStreamSynchronize(s);
+  std::lock_guard<std::mutex> lk(g_stage_mu);
+  slot->pending = recorded;
+  slot->busy = false;
+  if (!recorded) {
+    g_last_hip = (int)e;
+    return TT_EHIP;
+  }
+  return TT_OK;
+}
+
+// `bytes` written by fill(host pointer) to device memory dst, in stream order.
+template <typename Fill>
+int upload_filled(uint8_t* dst, size_t bytes, hipStream_t s, Fill fill) {
+  StageSlot* slot = nullptr;
+  TT_TRY(stage_acquire(bytes, s, &slot));
+  if (!slot) {
+    auto* blob = new std::vector<uint8_t>(bytes);
+    fill(blob->data());
+    return upload_async(dst, blob, s);
+  }
+  fill(slot->host);
+  const hipError_t e = hipMemcpyAsync(dst, slot->host, bytes, hipMemcpyHostToDevice, s);
+  if (e != hipSuccess) g_last_hip = (int)e;
+  const int st = stage_release(slot, s);
+  return e != hipSuccess ? TT_EHIP : st;
 }
 
 EnumArgs enum_args(const Layout& L, uint8_t* ws, uint64_t* tables) {
@@ -532,7 +658,7 @@ int plan_oneshot(const tt_neuron* h_desc, int n, const uint64_t* d_tables, uint6
   P->total_words = total_words;
   P->tune = default_tune();
   P->flags = 0;
-  P->desc.assign(h_desc, h_desc + n);
+  P->desc = h_desc;
   build_plan(*P);
   return TT_OK;
 }
@@ -548,9 +674,10 @@ size_t noalloc_counted_bytes(const PlanHost& P) {
     int count = 0, entries = 0;
   };
   std::map<std::tuple<int, int, int>, Open> open;
-  const size_t n = P.desc.size();
+  const size_t n = (size_t)P.n;
   size_t tiles = 0, items = 0, large = 0, entries = 0;
-  for (const tt_neuron& d : P.desc) {
+  for (size_t i = 0; i < n; ++i) {
+    const tt_neuron& d = P.desc[i];
     const uint64_t W = words_of(d.F, d.b);
     const int cap = lut_cap_of(d);
     entries += (size_t)cap;
@@ -889,13 +1016,25 @@ int tt_enumerate(const tt_neuron* h_desc, int n, uint64_t* d_tables, uint64_t to
   hipStream_t s = (hipStream_t)stream;
   const bool with_desc = !P.groups.empty();
   const Layout L = layout_of(P, with_desc);
+  if (!with_desc) {
+    // one launch whose waves read a descriptor once: straight from the
+    // staging buffer, no copy and no workspace
+    StageSlot* slot = nullptr;
+    TT_TRY(stage_acquire(L.upload_bytes, s, &slot));
+    if (slot) {
+      write_upload(P, L, slot->host, false);
+      const int st = enqueue_plan(P, L, slot->host, d_tables, d_hist, cus, s);
+      const int st2 = stage_release(slot, s);
+      return st != TT_OK ? st : st2;
+    }
+  }
   uint8_t* ws = nullptr;
   hipError_t e = hipMallocAsync((void**)&ws, L.total, s);
   if (e != hipSuccess) {
     g_last_hip = (int)e;
     return TT_ENOMEM;
   }
-  int st = upload_async(ws, make_upload(P, L, with_desc), s);
+  int st = upload_filled(ws, L.upload_bytes, s, [&](uint8_t* to) { write_upload(P, L, to, with_desc); });
   if (st == TT_OK) st = enqueue_plan(P, L, ws, d_tables, d_hist, cus, s);
   e = hipFreeAsync(ws, s);
   if (st == TT_OK && e != hipSuccess) {
@@ -938,7 +1077,8 @@ int tt_plan_create(const tt_neuron* h_desc, int n, uint64_t total_words, const t
   p->host.total_words = total_words;
   p->host.tune = t;
   p->host.flags = flags;
-  p->host.desc.assign(h_desc, h_desc + n);
+  p->host.own.assign(h_desc, h_desc + n);
+  p->host.desc = p->host.own.data();
   build_plan(p->host);
   build_support_lists(p->host);
   p->layout = layout_of(p->host);
@@ -1129,7 +1269,7 @@ int tt_support(const tt_neuron* h_desc, int n, const uint64_t* d_tables, uint64_
   hipStream_t s = (hipStream_t)stream;
   PlanHost P;
   P.n = n;
-  P.desc.assign(h_desc, h_desc + n);
+  P.desc = h_desc;
   build_large_list(P);
   const Layout L = layout_of(P);
   uint8_t* ws = nullptr;
@@ -1138,7 +1278,7 @@ int tt_support(const tt_neuron* h_desc, int n, const uint64_t* d_tables, uint64_
     g_last_hip = (int)e;
     return TT_ENOMEM;
   }
-  int st = upload_async(ws, make_upload(P, L), s);
+  int st = upload_filled(ws, L.upload_bytes, s, [&](uint8_t* to) { write_upload(P, L, to); });
   if (st == TT_OK) st = enqueue_support(P, L, ws, d_tables, d_support, d_hist, s);
   e = hipFreeAsync(ws, s);
   if (st == TT_OK && e != hipSuccess) {
@@ -1869,22 +2009,21 @@ int tt_pack(const tt_neuron* h_desc, int n, const uint8_t* d_codes, uint64_t tot
     pa.item_end[k] = items;
   }
   const size_t o = sizeof(PackRec) * (size_t)n;
-  auto* blob = new std::vector<uint8_t>(o);
-  auto* rec = reinterpret_cast<PackRec*>(blob->data());
-  acc = 0;
-  for (int i = 0; i < n; ++i) {
-    const int fb = h_desc[i].F * h_desc[i].b;
-    rec[at[fb]++] = PackRec{h_desc[i].word_off, acc | (uint64_t)h_desc[i].o << 62};
-    acc += 1ull << fb;
-  }
   uint8_t* ws = nullptr;
   hipError_t e = hipMallocAsync((void**)&ws, o, s);
   if (e != hipSuccess) {
-    delete blob;
     g_last_hip = (int)e;
     return TT_ENOMEM;
   }
-  int st = upload_async(ws, blob, s);
+  int st = upload_filled(ws, o, s, [&](uint8_t* to) {
+    auto* rec = reinterpret_cast<PackRec*>(to);
+    uint64_t code = 0;
+    for (int i = 0; i < n; ++i) {
+      const int fb = h_desc[i].F * h_desc[i].b;
+      rec[at[fb]++] = PackRec{h_desc[i].word_off, code | (uint64_t)h_desc[i].o << 62};
+      code += 1ull << fb;
+    }
+  });
   if (st == TT_OK) {
     pa.rec = reinterpret_cast<const PackRec*>(ws);
     pa.codes = d_codes;
