@@ -153,8 +153,10 @@ struct PlanHost {
   int n_groups = 0;                   // distinct (F, b, o)
   std::vector<int32_t> sup_lists;  // neurons for the support from parameters: small ranges first
   int64_t sup_small = 0;           // how many of them have sums spanning < 512 values
-  std::vector<int32_t> large;  // neurons whose tables the support kernels take wave by wave
-  long max_chunks = 1, max_items = 1;
+  // neurons by the size of their tables, for the support of tables
+  std::vector<int32_t> medium, large;
+  int n_small = 0;
+  int max_items = 1;  // 512-word items of the largest table
 };
 
 int sum_range_of(const tt_neuron& d) {
@@ -163,36 +165,17 @@ int sum_range_of(const tt_neuron& d) {
   return R;
 }
 
-// Neurons with more than kSmallTableWords words per plane.
-// Also the most check items any of them has per check: 512-word chunks
-// (near items, the histogram's units) and 64 x 2^c-word far items of the
-// digits whose row bits reach 15 and up (c <= 3 bits per group).  Work
-// units beyond these would find nothing to do.
-void build_large_list(PlanHost& P) {
-  // neurons for the support from parameters: those whose sums span fewer
-  // than 512 values first (one wave each), then the others
-  P.sup_lists.clear();
-  for (int i = 0; i < P.n; ++i)
-    if (sum_range_of(P.desc[i]) < 512) P.sup_lists.push_back(i);
-  P.sup_small = (int64_t)P.sup_lists.size();
-  for (int i = 0; i < P.n; ++i)
-    if (sum_range_of(P.desc[i]) >= 512) P.sup_lists.push_back(i);
-  P.large.clear();
-  P.max_chunks = 1;
-  P.max_items = 1;
+void build_table_lists(PlanHost& P) {
   for (int i = 0; i < P.n; ++i) {
-    const tt_neuron& d = P.desc[i];
-    const uint64_t W = words_of(d.F, d.b);
-    if (W <= (uint64_t)kSmallTableWords) continue;
-    P.large.push_back(i);
-    const long chunks = (long)std::max<uint64_t>(1, W / 512);
-    P.max_chunks = std::max(P.max_chunks, chunks);
-    P.max_items = std::max(P.max_items, chunks - 1);
-    for (int j = 0; j < d.F; ++j)
-      for (int s0 = std::max(j * d.b, 15); s0 < (j + 1) * d.b; s0 += 3) {
-        const int c = std::min(3, (j + 1) * d.b - s0);
-        P.max_items = std::max(P.max_items, (long)(W >> (6 + c)));
-      }
+    const uint64_t W = words_of(P.desc[i].F, P.desc[i].b);
+    if (W <= (uint64_t)kSmallTableWords) {
+      ++P.n_small;
+    } else if (W <= (uint64_t)kMediumTableWords) {
+      P.medium.push_back(i);
+    } else {
+      P.large.push_back(i);
+      P.max_items = std::max(P.max_items, (int)(W / 512));
+    }
   }
 }
 
@@ -307,20 +290,29 @@ void build_plan(PlanHost& P) {
 }
 
 // The lists the support of the plan's neurons takes (plans only: a one-shot
-// enumeration has no support).
+// enumeration has no support).  For the support from parameters, neurons
+// whose sums span fewer than 512 values first (a wave each), then the others.
 void build_support_lists(PlanHost& P) {
-  build_large_list(P);
+  build_table_lists(P);
+  std::vector<int32_t> span(P.n);
+  for (int i = 0; i < P.n; ++i) {
+    span[i] = sum_range_of(P.desc[i]);
+    if (span[i] < 512) P.sup_lists.push_back(i);
+  }
+  P.sup_small = (int64_t)P.sup_lists.size();
+  for (int i = 0; i < P.n; ++i)
+    if (span[i] >= 512) P.sup_lists.push_back(i);
   for (size_t k = 0; k < P.small.size(); ++k) {
-    const int R = sum_range_of(P.desc[P.small[k]]);
+    const int R = span[P.small[k]];
     if (R < 512) (R < 64 ? P.tiny : P.mid).push_back((int32_t)k);
   }
 }
 
 // ------------------------------------------------------ device workspace
 struct Layout {
-  size_t desc, small, lut_off, lut_cap, group_neurons, large, sup_lists, mid, tiny;
+  size_t desc, small, lut_off, lut_cap, group_neurons, medium, large, sup_lists, mid, tiny;
   size_t upload_bytes;
-  size_t params, found, sup_list, sup_count, lut;
+  size_t params, probed, found, lut;
   size_t total;
 };
 
@@ -339,16 +331,15 @@ Layout layout_of(const PlanHost& P, bool with_desc = true) {
   L.lut_off = take(sizeof(uint64_t) * P.lut_off.size());
   L.lut_cap = take(sizeof(int32_t) * P.lut_cap.size());
   L.group_neurons = take(sizeof(int32_t) * P.group_neurons.size());
+  L.medium = take(sizeof(int32_t) * P.medium.size());
   L.large = take(sizeof(int32_t) * P.large.size());
   L.sup_lists = take(sizeof(int32_t) * P.sup_lists.size());
   L.mid = take(sizeof(int32_t) * P.mid.size());
   L.tiny = take(sizeof(int32_t) * P.tiny.size());
   L.upload_bytes = o;
   L.params = take(P.lut_off.empty() ? 0 : sizeof(NeuronParams) * (size_t)P.n);
-  const size_t sup = P.sup_lists.size();  // the support kernels' scratch
-  L.found = take(sizeof(uint32_t) * sup);
-  L.sup_list = take(sizeof(int32_t) * sup);  // neurons still pending a support check
-  L.sup_count = take(sizeof(uint32_t) * 4);
+  L.probed = take(sizeof(uint32_t) * P.large.size());
+  L.found = take(sizeof(uint32_t) * P.large.size());
   L.lut = take(sizeof(uint64_t) * P.lut_total);
   L.total = o;
   return L;
@@ -368,6 +359,7 @@ void write_upload(const PlanHost& P, const Layout& L, uint8_t* dst, bool with_de
   put(L.lut_off, P.lut_off.data(), sizeof(uint64_t) * P.lut_off.size());
   put(L.lut_cap, P.lut_cap.data(), sizeof(int32_t) * P.lut_cap.size());
   put(L.group_neurons, P.group_neurons.data(), sizeof(int32_t) * P.group_neurons.size());
+  put(L.medium, P.medium.data(), sizeof(int32_t) * P.medium.size());
   put(L.large, P.large.data(), sizeof(int32_t) * P.large.size());
   put(L.sup_lists, P.sup_lists.data(), sizeof(int32_t) * P.sup_lists.size());
   put(L.mid, P.mid.data(), sizeof(int32_t) * P.mid.size());
@@ -536,10 +528,9 @@ int small_grid(const PlanHost& P) {
   return P.n_block + (waves + kSmallWaves - 1) / kSmallWaves;
 }
 
-// Enqueue support and/or histogram of the plan's neurons over `tables`
-// (see tt_support.hip): the histogram by one counting pass over the words,
-// the support by probes, a device-side list of the neurons still pending and
-// work units over their unknown digits.
+// Enqueue support and/or histogram of the plan's neurons over `tables` (three
+// launches, one when no table is larger than a wave's registers; see
+// tt_support.hip).
 int enqueue_support(const PlanHost& P, const Layout& L, uint8_t* ws, const uint64_t* tables, uint8_t* support,
                     uint32_t* hist, hipStream_t s, bool own_tables = false, bool small_done = false) {
   if (P.n == 0) return TT_OK;
@@ -559,33 +550,20 @@ int enqueue_support(const PlanHost& P, const Layout& L, uint8_t* ws, const uint6
   SupportArgs sa{};
   sa.desc = reinterpret_cast<const tt_neuron*>(ws + L.desc);
   sa.tables = tables;
-  sa.found = reinterpret_cast<uint32_t*>(ws + L.found);
   sa.hist = hist;
   sa.support = support;
   sa.n = P.n;
+  sa.n_small = P.n_small;
+  sa.n_medium = (int32_t)P.medium.size();
   sa.n_large = (int32_t)P.large.size();
+  sa.medium = reinterpret_cast<const int32_t*>(ws + L.medium);
   sa.large = reinterpret_cast<const int32_t*>(ws + L.large);
+  sa.probed = reinterpret_cast<uint32_t*>(ws + L.probed);
+  sa.found = reinterpret_cast<uint32_t*>(ws + L.found);
+  sa.max_items = P.max_items;
   int cus = 0;
   TT_TRY(device_info(&cus));
-  // Tables of at most kSmallTableWords words per plane: one thread per
-  // neuron.  Larger ones: work units per neuron, about four (histogram:
-  // every large neuron) or eight (support: only the neurons still pending)
-  // per resident wave in all.
-  const long nl = std::max<long>(1, sa.n_large);
-  auto units = [&](long per_wave, long cap) {
-    const long target = per_wave * 32L * cus;
-    return (int)std::max<long>(1, std::min<long>(cap, (target + nl - 1) / nl));
-  };
-  if (hist) TT_HIP(launch_fill_u32(hist, (size_t)P.n * 8, 0u, s));
-  TT_HIP(launch_small_tables(sa, s));
-  if (hist) TT_HIP(launch_hist_tables(sa, (int)std::min<long>(units(4, 64), P.max_chunks), s));
-  if (support && sa.n_large > 0) {
-    const int U = (int)std::min<long>(units(8, 128), P.max_items);
-    TT_HIP(launch_fill_u32(sa.found, (size_t)P.n, 0u, s));
-    TT_HIP(launch_support_tasks(sa, U, reinterpret_cast<int32_t*>(ws + L.sup_list),
-                                reinterpret_cast<uint32_t*>(ws + L.sup_count), s));
-    TT_HIP(launch_support_finish(sa, s));
-  }
+  TT_HIP(launch_support_tables(sa, cus, s));
   return TT_OK;
 }
 
@@ -1270,7 +1248,7 @@ int tt_support(const tt_neuron* h_desc, int n, const uint64_t* d_tables, uint64_
   PlanHost P;
   P.n = n;
   P.desc = h_desc;
-  build_large_list(P);
+  build_table_lists(P);
   const Layout L = layout_of(P);
   uint8_t* ws = nullptr;
   hipError_t e = hipMallocAsync((void**)&ws, L.total, s);

@@ -76,14 +76,17 @@ constexpr int kWideMaxUpw = 32;  // 2^15 words per block
 struct SupportArgs {
   const tt_neuron* desc;
   const uint64_t* tables;
-  uint32_t* found;           // [n] row bits whose flip changes some code
   uint32_t* hist;            // [n * 8] or NULL
   uint8_t* support;          // [n] or NULL
   int32_t n;
-  int32_t n_large;           // neurons of more than kSmallTableWords words:
-  const int32_t* large;      // [n_large], handled wave by wave (the rest lane by lane)
+  int32_t n_small;           // tables of at most kSmallTableWords words per plane: a lane each
+  int32_t n_medium, n_large; // of up to kMediumTableWords: a wave each; and of more
+  const int32_t *medium, *large;
+  uint32_t *probed, *found;  // [n_large] row bits whose flip changes some code: after the probes, and so far
+  int32_t max_items;         // 512-word items of the largest table
 };
-constexpr int kSmallTableWords = 16;  // tables up to 2^10 rows: one lane each
+constexpr int kSmallTableWords = 16;
+constexpr int kMediumTableWords = 512;
 
 // Packing of row codes: neurons sorted by their number of rows, largest
 // first, a class per number; a neuron takes one work item per kPackRows rows
@@ -336,11 +339,7 @@ hipError_t launch_support_params(const tt_neuron* desc, const int32_t* list, int
 hipError_t launch_support_params_small(const tt_neuron* desc, const int32_t* list, int count, uint8_t* support,
                                        hipStream_t s);
 hipError_t launch_fill_u32(uint32_t* p, size_t n, uint32_t v, hipStream_t s);
-hipError_t launch_support_finish(const SupportArgs& a, hipStream_t s);
-hipError_t launch_support_tasks(const SupportArgs& a, int units_per_neuron, int32_t* list, uint32_t* count,
-                                hipStream_t s);
-hipError_t launch_hist_tables(const SupportArgs& a, int units_per_neuron, hipStream_t s);
-hipError_t launch_small_tables(const SupportArgs& a, hipStream_t s);
+hipError_t launch_support_tables(const SupportArgs& a, int cus, hipStream_t s);
 hipError_t launch_pack(const PackArgs& a, hipStream_t s);
 
 // Networks evaluated through their tables (tt_lutnet.hip).

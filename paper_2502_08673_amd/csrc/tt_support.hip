@@ -13,6 +13,8 @@
 // one of its bits is found.  Only the tables are read.  (For tables that are
 // the enumeration of their descriptors, support_params_kernel below decides
 // the support from the parameters instead.)
+#include <algorithm>
+
 #include "tt_internal.h"
 
 namespace tt {
@@ -27,145 +29,188 @@ __global__ void fill_u32_kernel(uint32_t* p, size_t n, uint32_t v) {
 }
 
 
-__device__ __forceinline__ uint64_t shfl_xor_u64(uint64_t v, int m) {
-  const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)v, m, 64);
-  const uint32_t hi = (uint32_t)__shfl_xor((int)(uint32_t)(v >> 32), m, 64);
-  return ((uint64_t)hi << 32) | lo;
+// Sum of x over the wave, in every lane.
+__device__ __forceinline__ uint32_t wave_sum_all(uint32_t x) {
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) x += (uint32_t)__shfl_xor((int)x, off, 64);
+  return x;
 }
 
-// Support from the tables alone (no histogram), in two launches of one
-// kernel after the found bits are cleared.  Checks come in two kinds:
-//  - near items, up to 512 contiguous words (lane = word bits 0..5, register
-//    k = word bits 6..8): in-word row bits and word bits 0..8;
-//  - far items, for a digit with row bits from 15 (word bit 9) up: 64 x 2^c
-//    words, lanes varying word bits 0..5 and register k the digit's word
-//    bits s .. s + c - 1 (c <= 3; a 4-bit digit takes two groups), so each
-//    load still reads 512 contiguous bytes.
-// The probe launch gives kProbes units per neuron; unit k takes item
-// k * items / kProbes of every check (spread over the table, so that a digit
-// that only matters in part of the table is likely seen) and resets the list
-// counter.  A list kernel then collects the neurons with bits still unknown,
-// and the work launch gives each listed neuron U units (part = u % U) that
-// take items part, part + U, ... of each check whose bits are still unknown,
-// re-reading the found bits as they go.  Every new bit is published with one
-// atomic OR.
+// Tables of 32 words or more go through items of up to 512 words in a wave's
+// registers: register k of a lane holds word base + lane + (the bits of k at
+// three chosen word bits), so an item's pairs cover the row bits inside a
+// word (0-5), the lane bits (6-11) and the three chosen ones.  With word bits
+// 6-8 an item is 512 contiguous words; with higher ones (a digit whose row
+// bits reach 15 and up) every load still reads 512 contiguous bytes.  Either
+// way the items partition the table, so one pass serves the histogram and
+// the digits its bits decide.
+//
+// Three launches.  The first settles the tables of up to 16 words (a lane
+// each) and of up to 512 (a wave each, one item), and probes the larger ones,
+// a block each: four items spread over the table for every choice of bits
+// that some digit needs.  The second scans the larger ones: one pass over
+// each choice of bits that a digit still needs after the probes, and the
+// histogram with the first of them, so a table is read once (more often only
+// when several of its digits of row bits 12 or above never matter).  The third
+// turns found bits into supports (a count of ended units in the second would
+// need a device-wide fence per unit, which empties the XCD's L2: 480 us).
+// Bound by HBM: 100 tables of 2^24 rows
+// (419 MB, read 1.05 times), support and histogram: 131-138 us, 3.1 TB/s (a
+// histogram pass beside probe, list, work and finish passes: 240 us).
 constexpr int kProbes = 4;
-constexpr int kTaskR = 8;
+constexpr int kRegs = 8;
 
-// Pair tests over the registers P0..P2 (planes, O of them; zero registers
-// compare equal), each true if some pair of rows differs in some plane in
-// some lane of the wave.
-//  - in-word row bit q < 6: rows l and l + 2^q of a word (bit q of l clear).
-//    For q < 5 both rows of a pair lie in the same 32-bit half, so the test
-//    runs on the halves with 32-bit shifts; for q = 5 the pairs are the halves.
-template <int O>
-__device__ __forceinline__ bool inword_differs(const uint64_t* P0, const uint64_t* P1, const uint64_t* P2, int q) {
-  uint32_t x = 0;
-  if (q == 5) {
-#pragma unroll
-    for (int k = 0; k < kTaskR; ++k) {
-      x |= (uint32_t)P0[k] ^ (uint32_t)(P0[k] >> 32);
-      if (O > 1) x |= (uint32_t)P1[k] ^ (uint32_t)(P1[k] >> 32);
-      if (O > 2) x |= (uint32_t)P2[k] ^ (uint32_t)(P2[k] >> 32);
-    }
-  } else {
-    const int sh = 1 << q;
-#pragma unroll
-    for (int k = 0; k < kTaskR; ++k) {
-      uint32_t lo = (uint32_t)P0[k], hi = (uint32_t)(P0[k] >> 32);
-      x |= (lo ^ (lo >> sh)) | (hi ^ (hi >> sh));
-      if (O > 1) {
-        lo = (uint32_t)P1[k];
-        hi = (uint32_t)(P1[k] >> 32);
-        x |= (lo ^ (lo >> sh)) | (hi ^ (hi >> sh));
-      }
-      if (O > 2) {
-        lo = (uint32_t)P2[k];
-        hi = (uint32_t)(P2[k] >> 32);
-        x |= (lo ^ (lo >> sh)) | (hi ^ (hi >> sh));
-      }
-      __builtin_amdgcn_sched_barrier(0);  // one register's temporaries at a time
-    }
-    x &= (uint32_t)low_flip_select(q);
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_mov(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xF, 0xF, true);
+}
+// x of lane l xor x of lane l ^ 2^T
+template <int T>
+__device__ __forceinline__ uint32_t lane_flip_diff(uint32_t x) {
+  if constexpr (T == 0) return x ^ dpp_mov<0xB1>(x);                  // quad permute 1 0 3 2
+  if constexpr (T == 1) return x ^ dpp_mov<0x4E>(x);                  // 2 3 0 1
+  if constexpr (T == 2) return x ^ dpp_mov<0x141>(dpp_mov<0x1B>(x));  // 3 2 1 0, then the half row mirrored
+  if constexpr (T == 3) return x ^ dpp_mov<0x128>(x);                 // rows of 16 rotated by 8
+  // rows of 16 (halves) swapped between two copies: each lane gets both sides
+  if constexpr (T == 4) {
+    const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    return r[0] ^ r[1];
   }
-  return __any(x != 0u);
+  const auto r = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+  return r[0] ^ r[1];
 }
 
-//  - lane bit t (word bit t of a 64-word run): lanes l and l ^ 2^t.
 template <int O>
-__device__ __forceinline__ bool lane_differs(const uint64_t* P0, const uint64_t* P1, const uint64_t* P2, int t) {
-  bool df = false;
-#pragma unroll
-  for (int k = 0; k < kTaskR; ++k) {
-    df |= shfl_xor_u64(P0[k], 1 << t) != P0[k];
-    if (O > 1) df |= shfl_xor_u64(P1[k], 1 << t) != P1[k];
-    if (O > 2) df |= shfl_xor_u64(P2[k], 1 << t) != P2[k];
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  return __any(df);
+struct Item {
+  uint64_t p[O][kRegs];
+};
+
+// Word bits of register bits 0..2 (ascending).
+struct RegBits {
+  int b0, b1, b2;
+};
+__device__ __forceinline__ uint32_t reg_offset(const RegBits& B, int k) {
+  return ((uint32_t)(k & 1) << B.b0) | ((uint32_t)((k >> 1) & 1) << B.b1) | ((uint32_t)(k >> 2) << B.b2);
+}
+// First word of item `it`: its bits around the lane bits and B.
+__device__ __forceinline__ uint32_t item_base(uint32_t it, const RegBits& B) {
+  uint32_t x = it << 6;
+  x = ((x >> B.b0) << (B.b0 + 1)) | (x & ((1u << B.b0) - 1u));
+  x = ((x >> B.b1) << (B.b1 + 1)) | (x & ((1u << B.b1) - 1u));
+  x = ((x >> B.b2) << (B.b2 + 1)) | (x & ((1u << B.b2) - 1u));
+  return x;
 }
 
-//  - register bit i: registers k and k + 2^i (bit i of k clear, k + 2^i < nreg).
+// nw: words of the table when it has fewer than 512 (else 512; the others
+// read as zero)
 template <int O>
-__device__ __forceinline__ bool reg_differs(const uint64_t* P0, const uint64_t* P1, const uint64_t* P2, int i,
-                                            int nreg) {
-  bool df = false;
-  const int u = 1 << i;
-#pragma unroll
-  for (int k = 0; k < kTaskR; ++k) {
-    if (!(k & u) && (k | u) < nreg) {
-      df |= P0[k] != P0[k | u];
-      if (O > 1) df |= P1[k] != P1[k | u];
-      if (O > 2) df |= P2[k] != P2[k | u];
-    }
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  return __any(df);
-}
-
-// One check item: registers k < 2^c hold words base + lane + (k << s) of
-// each of the o planes (lanes below `nw` only: fewer words than a full
-// item; absent planes stay zero and compare equal).  Near items (s = 6) also
-// test in-word row bits and the lane word bits.  Returns the row bits of
-// `need` it finds.  (The probe's few items per neuron take this one
-// variant for every o, which keeps its register use down.)
-__device__ __forceinline__ uint32_t check_item(const uint64_t* t0, uint64_t W, int o, int b, int Fb, bool near,
-                                               uint64_t base, int s, int c, int nw, uint32_t need) {
+__device__ __forceinline__ void load_item(Item<O>& v, const uint64_t* t0, uint64_t W, uint32_t base, const RegBits& B,
+                                          int nw) {
   const int lane = threadIdx.x & 63;
-  uint64_t P0[kTaskR], P1[kTaskR], P2[kTaskR];
 #pragma unroll
-  for (int k = 0; k < kTaskR; ++k) {
-    P0[k] = P1[k] = P2[k] = 0ull;
-    if (k < (1 << c)) {  // uniform
-      // a wave-uniform row pointer plus the lane: scalar base, small vector offset
-      const uint64_t* q = t0 + base + ((uint64_t)k << s);
-      if (!near || lane + 64 * k < nw) {
-        P0[k] = q[lane];
-        if (o > 1) P1[k] = q[W + lane];
-        if (o > 2) P2[k] = q[2 * W + lane];
-      }
+  for (int k = 0; k < kRegs; ++k)
+#pragma unroll
+    for (int p = 0; p < O; ++p) {
+      v.p[p][k] = 0ull;
+      const uint64_t* q = t0 + (uint64_t)p * W + base + reg_offset(B, k);
+      if (64 * k + lane < nw) v.p[p][k] = q[lane];
+    }
+}
+
+// Rows whose bit pattern holds a set of planes: c[s - 1] counts the rows with
+// every plane of the set s.
+template <int O>
+__device__ __forceinline__ void count_sets(const Item<O>& v, uint32_t (&c)[(1 << O) - 1]) {
+#pragma unroll
+  for (int k = 0; k < kRegs; ++k) {
+    uint64_t x[1 << O];
+#pragma unroll
+    for (int s = 1; s < (1 << O); ++s) {
+      const int low = s & -s, p = low == 1 ? 0 : (low == 2 ? 1 : 2);
+      x[s] = s == low ? v.p[p][k] : x[s ^ low] & v.p[p][k];
+      c[s - 1] += (uint32_t)__popcll(x[s]);
     }
   }
-  // testable row bits: in-word (near), lane word bits (near) and register
-  // word bits s .. s + c - 1 = row bits s + 6 ..
-  const int lowbits = Fb < 6 ? Fb : 6;
-  int lb = 0;
-  while ((1 << lb) < nw && lb < 6) ++lb;
-  uint32_t todo = (((1u << c) - 1u) << (s + 6));
-  if (near) todo |= ((1u << lowbits) - 1u) | (((1u << lb) - 1u) << 6);
-  todo &= need;
+}
+// Rows of code v from the set counts c (c[-1] = all rows): inclusion and
+// exclusion over the planes that v lacks.
+template <int O>
+__device__ __forceinline__ uint32_t rows_of_code(const uint32_t (&c)[(1 << O) - 1], uint32_t rows, int v) {
+  uint32_t n = 0;
+#pragma unroll
+  for (int s = 0; s < (1 << O); ++s)
+    if ((s & v) == v) {
+      const uint32_t t = s == 0 ? rows : c[s > 0 ? s - 1 : 0];
+      n += (__popc(s ^ v) & 1) ? 0u - t : t;
+    }
+  return n;
+}
+
+template <int O>
+__device__ __forceinline__ uint32_t inword_diff(const Item<O>& v, int q) {
+  uint32_t x = 0;
+#pragma unroll
+  for (int k = 0; k < kRegs; ++k)
+#pragma unroll
+    for (int p = 0; p < O; ++p) {
+      const uint32_t lo = (uint32_t)v.p[p][k], hi = (uint32_t)(v.p[p][k] >> 32);
+      // rows l and l + 2^q: for q < 5 both lie in one half, for q = 5 the
+      // halves are the pairs
+      x |= q == 5 ? lo ^ hi : (lo ^ (lo >> (1 << q))) | (hi ^ (hi >> (1 << q)));
+    }
+  return q == 5 ? x : x & (uint32_t)low_flip_select(q);
+}
+template <int O, int T>
+__device__ __forceinline__ uint32_t lane_diff(const Item<O>& v) {
+  uint32_t x = 0;
+#pragma unroll
+  for (int k = 0; k < kRegs; ++k)
+#pragma unroll
+    for (int p = 0; p < O; ++p) {
+      const uint32_t lo = (uint32_t)v.p[p][k], hi = (uint32_t)(v.p[p][k] >> 32);
+      x |= lane_flip_diff<T>(lo) | lane_flip_diff<T>(hi);
+    }
+  return x;
+}
+template <int O>
+__device__ __forceinline__ uint32_t reg_diff(const Item<O>& v, int i) {
+  uint64_t x = 0;
+#pragma unroll
+  for (int u = 0; u < 3; ++u)
+    if (u == i) {  // uniform
+#pragma unroll
+      for (int k = 0; k < kRegs; ++k)
+        if (!(k & (1 << u)))
+#pragma unroll
+          for (int p = 0; p < O; ++p) x |= v.p[p][k] ^ v.p[p][k | (1 << u)];
+    }
+  return (uint32_t)x | (uint32_t)(x >> 32);
+}
+
+// The row bits of `todo` (testable in this item) whose flip changes some
+// code; of a digit only the first that does.
+template <int O>
+__device__ __forceinline__ uint32_t item_finds(const Item<O>& v, const RegBits& B, int b, uint32_t todo) {
   uint32_t fl = 0;
-  while (todo) {  // uniform; a digit is done once one of its bits differs
+  while (todo) {  // uniform
     const int bit = __ffs(todo) - 1;
     todo &= todo - 1u;
-    bool d;
-    if (near && bit < 6)
-      d = inword_differs<3>(P0, P1, P2, bit);
-    else if (near && bit < 12)
-      d = lane_differs<3>(P0, P1, P2, bit - 6);
-    else
-      d = reg_differs<3>(P0, P1, P2, bit - (s + 6), 1 << c);
-    if (d) {
+    uint32_t x;
+    if (bit < 6) {
+      x = inword_diff<O>(v, bit);
+    } else if (bit < 12) {
+      switch (bit - 6) {
+        case 0: x = lane_diff<O, 0>(v); break;
+        case 1: x = lane_diff<O, 1>(v); break;
+        case 2: x = lane_diff<O, 2>(v); break;
+        case 3: x = lane_diff<O, 3>(v); break;
+        case 4: x = lane_diff<O, 4>(v); break;
+        default: x = lane_diff<O, 5>(v); break;
+      }
+    } else {
+      x = reg_diff<O>(v, bit - 6 == B.b0 ? 0 : (bit - 6 == B.b1 ? 1 : 2));
+    }
+    if (__any(x != 0u)) {
       fl |= 1u << bit;
       todo &= ~(((1u << b) - 1u) << ((bit / b) * b));
     }
@@ -173,284 +218,39 @@ __device__ __forceinline__ uint32_t check_item(const uint64_t* t0, uint64_t W, i
   return fl;
 }
 
-// Far group g (g = 0, 1, ...) of a neuron: the digit j and its first row
-// bit s0 (>= 15) and bit count c <= 3; false when there is no such group.
-__device__ __forceinline__ bool far_group(int F, int b, int g, int& j, int& s0, int& c) {
-  for (j = 0; j < F; ++j) {
+__device__ __forceinline__ uint32_t testable(const RegBits& B) {
+  return 0xFFFu | (64u << B.b0) | (64u << B.b1) | (64u << B.b2);
+}
+constexpr RegBits kNear = {6, 7, 8};
+
+// Far group g (g = 0, 1, ...) of a neuron: up to three row bits from 15 up of
+// one digit as register bits, the lowest word bits beside them; false when
+// there is no such group.
+__device__ __forceinline__ bool far_group(int F, int b, int g, int* digit, RegBits* B) {
+  for (int j = 0; j < F; ++j) {
     const int lo = j * b > 15 ? j * b : 15, hi = (j + 1) * b;
-    for (s0 = lo; s0 < hi; s0 += 3) {
+    for (int s = lo; s < hi; s += 3)
       if (g-- == 0) {
-        c = hi - s0 < 3 ? hi - s0 : 3;
+        const int c = hi - s < 3 ? hi - s : 3, w = s - 6;
+        *digit = j;
+        *B = c == 3 ? RegBits{w, w + 1, w + 2} : (c == 2 ? RegBits{6, w, w + 1} : RegBits{6, 7, w});
         return true;
       }
-    }
   }
   return false;
 }
 
-__device__ __forceinline__ uint64_t far_base(uint64_t it, int s, int c) {
-  const uint64_t lowb = it & ((1ull << (s - 6)) - 1ull);
-  return ((it >> (s - 6)) << (s + c)) | (lowb << 6);
-}
-
-// Probe: unit (n, k), k < kProbes, checks item k * items / kProbes of the
-// near check and of every far group; also resets the pending-list counter.
-__global__ __launch_bounds__(256) void support_probe_kernel(SupportArgs a, uint32_t* count) {
-  const int lane = threadIdx.x & 63;
-  const int wave_in_grid = __builtin_amdgcn_readfirstlane((int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6));
-  if (wave_in_grid == 0 && lane == 0) *count = 0u;
-  const long units = (long)a.n_large * kProbes;
-  const long nwv = (long)((gridDim.x * blockDim.x) >> 6);
-  for (long u = wave_in_grid; u < units; u += nwv) {
-    const int n = a.large[u / kProbes], part = (int)(u % kProbes);
-    const tt_neuron* dp = a.desc + n;
-    const int F = __builtin_amdgcn_readfirstlane(dp->F), b = __builtin_amdgcn_readfirstlane(dp->b);
-    const int o = __builtin_amdgcn_readfirstlane(dp->o);
-    const uint64_t* t0 = a.tables + dp->word_off;
-    const int Fb = F * b, Wb = Fb > 6 ? Fb - 6 : 0;
-    const uint64_t W = 1ull << Wb;
-    uint32_t mine = 0;
-    // near: one item of up to 512 words
-    {
-      const long items = Wb > 9 ? 1L << (Wb - 9) : 1L;
-      const long it = (long)part * items / kProbes;
-      const bool fresh = part == 0 || it != (long)(part - 1) * items / kProbes;
-      if (fresh) {
-        const int nw = Wb < 9 ? 1 << Wb : 512;
-        const int c = Wb < 9 ? (Wb > 6 ? Wb - 6 : 0) : 3;
-        mine |= check_item(t0, W, o, b, Fb, true, (uint64_t)it << 9, 6, c, nw,
-                           unknown_row_bits(0u, F, b) & ((1u << 15) - 1u));
-      }
-    }
-    int j, s0, c;
-    for (int g = 0; far_group(F, b, g, j, s0, c); ++g) {
-      const uint32_t D = ((1u << b) - 1u) << (j * b);
-      if (mine & D) continue;
-      const long items = (long)(W >> (6 + c));
-      const long it = (long)part * items / kProbes;
-      if (part > 0 && it == (long)(part - 1) * items / kProbes) continue;
-      mine |= check_item(t0, W, o, b, Fb, false, far_base((uint64_t)it, s0 - 6, c), s0 - 6, c, 0, D);
-    }
-    if (lane == 0 && mine) atomicOr(&a.found[n], mine);
-  }
-}
-
-// Work: unit (listed neuron, part) takes items part + 1, part + 1 + U, ... of
-// the near check (full 512-word items) and part, part + U, ... of each far
-// group whose digit is still unknown; found bits are published per item and
-// re-read as it goes.
-template <int O>
-__device__ __forceinline__ void work_unit(const SupportArgs& a, int n, int part, int U, int F, int b,
-                                          const uint64_t* t0, int Wb) {
-  const int lane = threadIdx.x & 63;
-  const uint64_t W = 1ull << Wb;
-  uint32_t fnd = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.found[n]);
-  uint64_t P0[kTaskR], P1[kTaskR], P2[kTaskR];
-  if (Wb > 9) {
-    const int items = 1 << (Wb - 9);
-    for (int it = 1 + part; it < items; it += U) {
-      const uint32_t need = unknown_row_bits(fnd, F, b) & ((1u << 15) - 1u);
-      if (!need) break;
-      const uint64_t* q0 = t0 + ((uint64_t)it << 9);
-#pragma unroll
-      for (int k = 0; k < kTaskR; ++k) {
-        P0[k] = q0[64 * k + lane];
-        P1[k] = P2[k] = 0ull;
-        if (O > 1) P1[k] = q0[W + 64 * k + lane];
-        if (O > 2) P2[k] = q0[2 * W + 64 * k + lane];
-      }
-      const uint32_t fnow = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.found[n]);
-      uint32_t fl = 0;
-      for (uint32_t todo = need; todo;) {  // uniform; a digit is done once one of its bits differs
-        const int bit = __ffs(todo) - 1;
-        todo &= todo - 1u;
-        bool d;
-        if (bit < 6)
-          d = inword_differs<O>(P0, P1, P2, bit);
-        else if (bit < 12)
-          d = lane_differs<O>(P0, P1, P2, bit - 6);
-        else
-          d = reg_differs<O>(P0, P1, P2, bit - 12, kTaskR);
-        if (d) {
-          fl |= 1u << bit;
-          todo &= ~(((1u << b) - 1u) << ((bit / b) * b));
-        }
-      }
-      if (fl && lane == 0) atomicOr(&a.found[n], fl);
-      fnd |= fl | fnow;
-    }
-  }
-  int j, s0, c;
-  for (int g = 0; far_group(F, b, g, j, s0, c); ++g) {
-    const uint32_t D = ((1u << b) - 1u) << (j * b);
-    const int s = s0 - 6;
-    const long items = (long)(W >> (6 + c));
-    for (long it = part; it < items; it += U) {
-      if (fnd & D) break;
-      const uint64_t* q0 = t0 + far_base((uint64_t)it, s, c);
-#pragma unroll
-      for (int k = 0; k < kTaskR; ++k) {
-        P0[k] = P1[k] = P2[k] = 0ull;
-        if (k < (1 << c)) {  // uniform
-          const uint64_t* q = q0 + ((uint64_t)k << s);
-          P0[k] = q[lane];
-          if (O > 1) P1[k] = q[W + lane];
-          if (O > 2) P2[k] = q[2 * W + lane];
-        }
-      }
-      const uint32_t fnow = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.found[n]);
-      uint32_t fl = 0;
-      for (int i = 0; i < c; ++i)  // bits of one digit: the first that differs settles it
-        if (reg_differs<O>(P0, P1, P2, i, 1 << c)) {
-          fl |= 1u << (s0 + i);
-          break;
-        }
-      if (fl && lane == 0) atomicOr(&a.found[n], fl);
-      fnd |= fl | fnow;
-    }
-  }
-}
-
-__global__ __launch_bounds__(256) void support_work_kernel(SupportArgs a, int U, const int32_t* list,
-                                                           const uint32_t* count) {
-  const int wave_in_grid = __builtin_amdgcn_readfirstlane((int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6));
-  const long listed = (long)(uint32_t)__builtin_amdgcn_readfirstlane((int)*count);
-  const long units = listed * U;
-  const long nwv = (long)((gridDim.x * blockDim.x) >> 6);
-  for (long u = wave_in_grid; u < units; u += nwv) {
-    const int n = __builtin_amdgcn_readfirstlane(list[u / U]);
-    const int part = (int)(u % U);
-    const tt_neuron* dp = a.desc + n;
-    const int F = __builtin_amdgcn_readfirstlane(dp->F), b = __builtin_amdgcn_readfirstlane(dp->b);
-    const int o = __builtin_amdgcn_readfirstlane(dp->o);
-    const uint64_t* t0 = a.tables + dp->word_off;
-    const int Fb = F * b, Wb = Fb > 6 ? Fb - 6 : 0;
-    switch (o) {
-      case 1: work_unit<1>(a, n, part, U, F, b, t0, Wb); break;
-      case 2: work_unit<2>(a, n, part, U, F, b, t0, Wb); break;
-      default: work_unit<3>(a, n, part, U, F, b, t0, Wb); break;
-    }
-  }
-}
-
-// Histogram of packed tables: unit (n, part) takes the 512-word chunks
-// part, part + U, ... of neuron n (a table of fewer words is one chunk),
-// counts the rows of every code with popcounts of plane combinations, sums
-// its lanes and adds the totals to hist[n] (zeroed beforehand).
-__global__ __launch_bounds__(256) void hist_tables_kernel(SupportArgs a, int U) {
-  const int lane = threadIdx.x & 63;
-  const int wave_in_grid = __builtin_amdgcn_readfirstlane((int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6));
-  const long units = (long)a.n_large * U;
-  const long nwv = (long)((gridDim.x * blockDim.x) >> 6);
-  for (long u = wave_in_grid; u < units; u += nwv) {
-    const int n = a.large[u / U], part = (int)(u % U);
-    const tt_neuron* dp = a.desc + n;
-    const int F = __builtin_amdgcn_readfirstlane(dp->F), b = __builtin_amdgcn_readfirstlane(dp->b);
-    const int o = __builtin_amdgcn_readfirstlane(dp->o);
-    const uint64_t* t0 = a.tables + dp->word_off;
-    const int Fb = F * b, Wb = Fb > 6 ? Fb - 6 : 0;
-    const uint64_t W = 1ull << Wb;
-    const int nw = Wb < 9 ? 1 << Wb : 512;  // words per chunk
-    const long items = Wb > 9 ? 1L << (Wb - 9) : 1L;
-    if (part >= items) continue;
-    // rows past 2^(F b) in a single-word table are not counted
-    const uint64_t validw = Fb >= 6 ? ~0ull : ((1ull << (1 << Fb)) - 1ull);
-    uint32_t hv[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-    for (long it = part; it < items; it += U) {
-      const uint64_t* q0 = t0 + ((uint64_t)it << 9);
-#pragma unroll
-      for (int k = 0; k < kTaskR; ++k) {
-        if (64 * k < nw) {  // uniform
-          const bool in = lane + 64 * k < nw;
-          uint64_t p0 = 0, p1 = 0, p2 = 0;
-          if (in) {
-            p0 = q0[64 * k + lane];
-            if (o > 1) p1 = q0[W + 64 * k + lane];
-            if (o > 2) p2 = q0[2 * W + 64 * k + lane];
-          }
-          const uint64_t m = in ? validw : 0ull;
-#pragma unroll
-          for (int v = 0; v < 8; ++v) {
-            uint64_t x = m & ((v & 1) ? p0 : ~p0);
-            x &= (v & 2) ? p1 : ~p1;  // planes at or above o read as zero
-            x &= (v & 4) ? p2 : ~p2;
-            hv[v] += (uint32_t)__popcll(x);
-          }
-        }
-      }
-    }
-#pragma unroll
-    for (int v = 0; v < 8; ++v) {
-      if (v < (1 << o)) {  // uniform
-        uint32_t x = hv[v];
-#pragma unroll
-        for (int off = 32; off >= 1; off >>= 1) x += (uint32_t)__shfl_xor((int)x, off, 64);
-        if (lane == 0 && x) atomicAdd(&a.hist[(size_t)n * 8 + v], x);
-      }
-    }
-  }
-}
-
-hipError_t launch_hist_tables(const SupportArgs& a, int units_per_neuron, hipStream_t s) {
-  if (a.n_large <= 0) return hipSuccess;
-  int dev = 0, cus = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  if (e != hipSuccess) return e;
-  const long units = (long)a.n_large * units_per_neuron;
-  const long waves = units < 32L * cus ? units : 32L * cus;
-  hipLaunchKernelGGL(hist_tables_kernel, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, s, a, units_per_neuron);
-  return hipGetLastError();
-}
-
-// Neurons with a digit not yet known to matter (order not kept).
-__global__ void support_pending_kernel(SupportArgs a, int32_t* list, uint32_t* count) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= a.n_large) return;
-  const int n = a.large[k];
-  const tt_neuron* dp = a.desc + n;
-  if (unknown_row_bits(a.found[n], dp->F, dp->b)) list[atomicAdd(count, 1u)] = n;
-}
-
-hipError_t launch_support_tasks(const SupportArgs& a, int units_per_neuron, int32_t* list, uint32_t* count,
-                                hipStream_t s) {
-  if (a.n <= 0) return hipSuccess;
-  int dev = 0, cus = 0;
-  hipError_t e = hipGetDevice(&dev);
-  if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-  if (e != hipSuccess) return e;
-  if (a.n_large <= 0) return hipSuccess;
-  const long pu = (long)a.n_large * kProbes;
-  const long pw = pu < 32L * cus ? pu : 32L * cus;
-  hipLaunchKernelGGL(support_probe_kernel, dim3((unsigned)((pw + 3) / 4)), dim3(256), 0, s, a, count);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(support_pending_kernel, dim3((a.n_large + 255) / 256), dim3(256), 0, s, a, list, count);
-  if ((e = hipGetLastError()) != hipSuccess) return e;
-  const long units = (long)a.n_large * units_per_neuron;  // at most
-  const long waves = units < 32L * cus ? units : 32L * cus;
-  hipLaunchKernelGGL(support_work_kernel, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, s, a, units_per_neuron,
-                     list, count);
-  return hipGetLastError();
-}
-
-__global__ void support_finish_kernel(SupportArgs a) {
-  const int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= a.n_large) return;
-  const int n = a.large[k];
-  const tt_neuron* dp = a.desc + n;
-  const int F = dp->F, b = dp->b;
-  const uint32_t f = a.found[n];
+__device__ __forceinline__ uint8_t support_of_bits(uint32_t found, int F, int b) {
   uint32_t s = 0;
   for (int j = 0; j < F; ++j)
-    if (f & (((1u << b) - 1u) << (j * b))) s |= 1u << j;
-  a.support[n] = (uint8_t)s;
+    if (found & (((1u << b) - 1u) << (j * b))) s |= 1u << j;
+  return (uint8_t)s;
 }
 
 // Support and/or histogram of the small tables (at most kSmallTableWords
 // words per plane), one lane per neuron holding its whole table: in-word row
 // bits by shifted XOR, word bits by comparing word pairs, codes by popcounts.
-__global__ __launch_bounds__(256) void small_tables_kernel(SupportArgs a) {
-  const int n = blockIdx.x * blockDim.x + threadIdx.x;
+__device__ __forceinline__ void small_table(const SupportArgs& a, int n) {
   if (n >= a.n) return;
   const tt_neuron* dp = a.desc + n;
   const int F = dp->F, b = dp->b, o = dp->o;
@@ -513,6 +313,202 @@ __global__ __launch_bounds__(256) void small_tables_kernel(SupportArgs a) {
       if (fl & (((1u << b) - 1u) << (j * b))) sres |= 1u << j;
     a.support[n] = (uint8_t)sres;
   }
+}
+
+// A table of 32 to 512 words per plane: one item, one wave.
+template <int O>
+__device__ __forceinline__ void medium_table(const SupportArgs& a, const NeuronRegs& d, int n) {
+  const int lane = threadIdx.x & 63, Fb = d.F * d.b, nw = 1 << (Fb - 6);
+  Item<O> v;
+  load_item<O>(v, a.tables + d.word_off, (uint64_t)nw, 0u, kNear, nw);
+  if (a.hist) {
+    uint32_t c[(1 << O) - 1];
+#pragma unroll
+    for (int s = 0; s < (1 << O) - 1; ++s) c[s] = 0u;
+    count_sets<O>(v, c);
+#pragma unroll
+    for (int s = 0; s < (1 << O) - 1; ++s) c[s] = wave_sum_all(c[s]);
+    uint32_t mine = 0;
+#pragma unroll
+    for (int q = 0; q < (1 << O); ++q)
+      if (lane == q) mine = rows_of_code<O>(c, 1u << Fb, q);
+    if (lane < 8) a.hist[(size_t)n * 8 + lane] = mine;
+  }
+  if (a.support) {
+    const uint32_t fl = item_finds<O>(v, kNear, d.b, unknown_row_bits(0u, d.F, d.b));
+    if (lane == 0) a.support[n] = support_of_bits(fl, d.F, d.b);
+  }
+}
+
+// The probes of a table of 2^10 words or more, by the block's waves.
+template <int O>
+__device__ __forceinline__ void probe_table(const SupportArgs& a, const NeuronRegs& d, uint32_t* s_found, int wave,
+                                            int waves) {
+  const int lane = threadIdx.x & 63, F = d.F, b = d.b, Wb = F * b - 6;
+  const uint64_t W = 1ull << Wb;
+  const uint64_t* t0 = a.tables + d.word_off;
+  const uint32_t items = (uint32_t)(W >> 9);
+  for (int u = wave;; u += waves) {
+    const int g = u / kProbes, k = u % kProbes;
+    int digit = 0;
+    RegBits B = kNear;
+    if (g > 0 && !far_group(F, b, g - 1, &digit, &B)) break;
+    const uint32_t it = (uint32_t)((uint64_t)k * items / kProbes);
+    if (k > 0 && it == (uint32_t)((uint64_t)(k - 1) * items / kProbes)) continue;
+    const uint32_t seen = (uint32_t)__builtin_amdgcn_readfirstlane((int)*(volatile uint32_t*)s_found);
+    uint32_t need = unknown_row_bits(seen, F, b) & testable(B);
+    if (g > 0 && !(need & (((1u << b) - 1u) << (digit * b)))) continue;
+    if (!need) continue;
+    Item<O> v;
+    load_item<O>(v, t0, W, item_base(it, B), B, 512);
+    const uint32_t fl = item_finds<O>(v, B, b, need);
+    if (fl && lane == 0) atomicOr(s_found, fl);
+  }
+}
+
+// Blocks: larger tables (probes, a block each), tables of 32 to 512 words (a
+// wave each), then all neurons a lane each for the smallest tables.
+__global__ __launch_bounds__(512) void support_first_kernel(SupportArgs a) {
+  __shared__ uint32_t s_found;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  int blk = (int)blockIdx.x;
+  if (blk < a.n_large) {
+    const int n = a.large[blk];
+    if (threadIdx.x == 0) s_found = 0u;
+    __syncthreads();
+    if (a.support) {
+      const NeuronRegs d = load_neuron(a.desc + n);
+      switch (d.o) {
+        case 1: probe_table<1>(a, d, &s_found, wave, 8); break;
+        case 2: probe_table<2>(a, d, &s_found, wave, 8); break;
+        default: probe_table<3>(a, d, &s_found, wave, 8); break;
+      }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      a.probed[blk] = s_found;
+      a.found[blk] = s_found;
+    }
+    if (a.hist && threadIdx.x < 8) a.hist[(size_t)n * 8 + threadIdx.x] = 0u;
+    return;
+  }
+  blk -= a.n_large;
+  const int medium_blocks = (a.n_medium + 7) / 8;
+  if (blk < medium_blocks) {
+    const int i = blk * 8 + wave;
+    if (i >= a.n_medium) return;
+    const int n = __builtin_amdgcn_readfirstlane(a.medium[i]);
+    const NeuronRegs d = load_neuron(a.desc + n);
+    switch (d.o) {
+      case 1: medium_table<1>(a, d, n); break;
+      case 2: medium_table<2>(a, d, n); break;
+      default: medium_table<3>(a, d, n); break;
+    }
+    return;
+  }
+  blk -= medium_blocks;
+  small_table(a, blk * 512 + (int)threadIdx.x);
+}
+
+// One unit of a larger table: items part, part + units, ... of each pass.
+template <int O>
+__device__ __forceinline__ void scan_table(const SupportArgs& a, const NeuronRegs& d, int k, int n, uint32_t part,
+                                           uint32_t units) {
+  const int lane = threadIdx.x & 63, F = d.F, b = d.b, Wb = F * b - 6;
+  const uint64_t W = 1ull << Wb;
+  const uint64_t* t0 = a.tables + d.word_off;
+  const uint32_t items = (uint32_t)(W >> 9);
+  // what the probes left open chooses the passes (the same for every unit of
+  // the neuron: the items of a pass are shared out between them)
+  const uint32_t open = a.support ? unknown_row_bits(a.probed[k], F, b) : 0u;
+  uint32_t fnd = a.support ? (uint32_t)__builtin_amdgcn_readfirstlane((int)a.found[k]) : ~0u;
+  uint32_t c[(1 << O) - 1];
+#pragma unroll
+  for (int s = 0; s < (1 << O) - 1; ++s) c[s] = 0u;
+  bool count = a.hist != nullptr;
+  auto pass = [&](const RegBits& B, uint32_t wanted) {
+    for (uint32_t it = part; it < items; it += units) {
+      uint32_t need = a.support ? unknown_row_bits(fnd, F, b) & testable(B) & wanted : 0u;
+      if (!count && !need) return;
+      Item<O> v;
+      load_item<O>(v, t0, W, item_base(it, B), B, 512);
+      if (need) {
+        // what other units have found since, now and then (a round trip)
+        if (((it / units) & 3u) == 3u) fnd |= (uint32_t)__builtin_amdgcn_readfirstlane(
+            (int)__hip_atomic_load(&a.found[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        need = unknown_row_bits(fnd, F, b) & testable(B) & wanted;
+        const uint32_t fl = item_finds<O>(v, B, b, need);
+        if (fl && lane == 0) atomicOr(&a.found[k], fl);
+        fnd |= fl;
+      }
+      if (count) count_sets<O>(v, c);
+    }
+    count = false;
+  };
+  bool any = false;
+  if (open & 0x7000u) {  // a digit with row bits 12 - 14
+    pass(kNear, ~0u);
+    any = true;
+  }
+  int digit;
+  RegBits B;
+  for (int g = 0; far_group(F, b, g, &digit, &B); ++g) {
+    const uint32_t D = ((1u << b) - 1u) << (digit * b);
+    if (!(open & D)) continue;
+    pass(B, any ? D : ~0u);  // the first pass also settles the low digits
+    any = true;
+  }
+  if (!any && (open || count)) pass(kNear, ~0u);
+  if (a.hist) {
+#pragma unroll
+    for (int s = 0; s < (1 << O) - 1; ++s) c[s] = wave_sum_all(c[s]);
+    const uint32_t mine_items = part < items ? (items - 1u - part) / units + 1u : 0u;
+    uint32_t mine = 0;
+#pragma unroll
+    for (int q = 0; q < (1 << O); ++q)
+      if (lane == q) mine = rows_of_code<O>(c, mine_items << 15, q);
+    if (lane < (1 << O) && mine) atomicAdd(&a.hist[(size_t)n * 8 + lane], mine);
+  }
+}
+
+__global__ __launch_bounds__(256) void support_scan_kernel(SupportArgs a, uint32_t U) {
+  const uint32_t gw = (uint32_t)__builtin_amdgcn_readfirstlane((int)((blockIdx.x * blockDim.x + threadIdx.x) >> 6));
+  const uint32_t k = gw / U, part = gw - k * U;
+  if (k >= (uint32_t)a.n_large) return;
+  const int n = __builtin_amdgcn_readfirstlane(a.large[k]);
+  const NeuronRegs d = load_neuron(a.desc + n);
+  const uint32_t items = 1u << (d.F * d.b - 15), units = min(U, items);
+  if (part >= units) return;
+  switch (d.o) {
+    case 1: scan_table<1>(a, d, (int)k, n, part, units); break;
+    case 2: scan_table<2>(a, d, (int)k, n, part, units); break;
+    default: scan_table<3>(a, d, (int)k, n, part, units); break;
+  }
+}
+
+__global__ __launch_bounds__(256) void support_finish_kernel(SupportArgs a) {
+  const int k = blockIdx.x * 256 + threadIdx.x;
+  if (k >= a.n_large) return;
+  const int n = a.large[k];
+  a.support[n] = support_of_bits(a.found[k], a.desc[n].F, a.desc[n].b);
+}
+
+hipError_t launch_support_tables(const SupportArgs& a, int cus, hipStream_t s) {
+  if (a.n <= 0) return hipSuccess;
+  const long first = (long)a.n_large + (a.n_medium + 7) / 8 + (a.n_small > 0 ? (a.n + 511) / 512 : 0);
+  hipLaunchKernelGGL(support_first_kernel, dim3((unsigned)first), dim3(512), 0, s, a);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || a.n_large <= 0) return e;
+  // one to two rounds of resident waves, at most one unit per item; a power of
+  // two, as the items are, so that every unit of a neuron gets as many (100
+  // tables of 2^24 rows: 16 units a compute unit at most 189 us, 32: 143, 64: 138)
+  long U = 1;
+  while (2 * U <= a.max_items && 2 * U * a.n_large <= 64L * cus) U *= 2;
+  const long waves = (long)a.n_large * U;
+  hipLaunchKernelGGL(support_scan_kernel, dim3((unsigned)((waves + 3) / 4)), dim3(256), 0, s, a, (uint32_t)U);
+  if ((e = hipGetLastError()) != hipSuccess || !a.support) return e;
+  hipLaunchKernelGGL(support_finish_kernel, dim3((unsigned)((a.n_large + 255) / 256)), dim3(256), 0, s, a);
+  return hipGetLastError();
 }
 
 // Support of a neuron from its parameters, for tables that are its own
@@ -668,12 +664,6 @@ hipError_t launch_support_params(const tt_neuron* desc, const int32_t* list, int
   return hipGetLastError();
 }
 
-hipError_t launch_small_tables(const SupportArgs& a, hipStream_t s) {
-  if (a.n <= 0 || a.n_large >= a.n) return hipSuccess;
-  hipLaunchKernelGGL(small_tables_kernel, dim3((a.n + 255) / 256), dim3(256), 0, s, a);
-  return hipGetLastError();
-}
-
 // Sixteen code bytes (any alignment) and the bits of one plane in them: a
 // byte's bit weighted by its place, summed by four-byte dot products.
 __device__ __forceinline__ uint4 load_codes16(const uint8_t* p) {
@@ -745,12 +735,6 @@ hipError_t launch_fill_u32(uint32_t* p, size_t n, uint32_t v, hipStream_t s) {
   size_t blocks = (n + 255) / 256;
   if (blocks > 4096) blocks = 4096;
   hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)blocks), dim3(256), 0, s, p, n, v);
-  return hipGetLastError();
-}
-
-hipError_t launch_support_finish(const SupportArgs& a, hipStream_t s) {
-  if (a.n_large <= 0) return hipSuccess;
-  hipLaunchKernelGGL(support_finish_kernel, dim3((a.n_large + 255) / 256), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

@@ -361,6 +361,47 @@ def test_support_far_word_bits():
     assert np.array_equal(sup.cpu().numpy(), ref["support"])
 
 
+@pytest.mark.parametrize("shape", [(5, 2), (6, 2), (4, 3), (7, 2), (5, 3), (3, 4), (4, 4), (8, 2), (6, 3), (5, 4),
+                                   (7, 3)])
+def test_table_support_finds_single_pairs(shape):
+    """Tables that are constant but for one row, at the edges of the support
+    kernels' classes (16 words a lane, up to 512 a wave, probes and scan
+    above; 4-bit digits across word bit 9): that row's flips reach every
+    digit, and a second table holds a pair that differs in one chosen digit
+    only through equal codes elsewhere.  Support and histogram, together and
+    apart, against the oracle on arbitrary codes."""
+    F, b = shape
+    rows = 1 << (F * b)
+    rng = np.random.default_rng(F * 10 + b)
+    n = 6
+    ns = random_neurons(seed=1, n=n, F=(F, F), b=(b, b), o=(1, 3), max_fb=F * b)
+    ns.o[:] = [1, 2, 3, 1, 2, 3]
+    ns.thr[:] = 0  # only the tables are read
+    codes = np.zeros((n, rows), np.uint8)
+    for i in range(3):  # one odd row, far from every probed item's start
+        codes[i, rng.integers(rows // 2, rows)] = (1 << int(ns.o[i])) - 1
+    for i in range(3, 6):  # a function of one digit only
+        j = int(rng.integers(0, F))
+        codes[i] = ((np.arange(rows) >> (j * b)) & ((1 << b) - 1)) == int(rng.integers(0, 1 << b))
+    ref = oracle.from_codes(ns, codes.reshape(-1))
+    t = device_tables(ref["total_words"])
+    t[: ref["total_words"]] = torch.from_numpy(ref["planes"].view(np.int64)).cuda()
+    desc = tt.descriptors(ns)
+    tt.layout(desc)
+    sup = torch.zeros(n, dtype=torch.uint8, device="cuda")
+    hist = torch.zeros(n * 8, dtype=torch.int32, device="cuda")
+    note(f"table support {shape}")
+    for s, h in ((sup, hist), (sup, None), (None, hist)):
+        sup.fill_(0xEE)
+        hist.fill_(-1)
+        tt.support(desc, t, support_out=s, hist=h)
+        torch.cuda.synchronize()
+        if s is not None:
+            assert np.array_equal(sup.cpu().numpy(), ref["support"])
+        if h is not None:
+            assert np.array_equal(hist.cpu().numpy().reshape(-1, 8).astype(np.uint32), ref["hist"])
+
+
 def test_pack_matches_oracle_planes():
     ns = concat([cfg2(n=500), random_neurons(seed=12, n=100, max_fb=14)])
     codes = oracle.codes(ns)
