@@ -270,7 +270,7 @@ int tt_autotune(const tt_neuron* h_desc, int n, uint64_t* d_tables, uint64_t tot
  * are uint8 [batch][n_inputs] and outputs uint8 [batch][n] (codes < 2^o),
  * both device memory.  Evaluated level by level (a level reads only the
  * inputs and earlier levels): one launch for the whole network, with each
- * block's 64 samples' codes in LDS, when n_inputs + n is at most 1019; else
+ * block's samples' codes in LDS, when n_inputs + n is at most 1019; else
  * one launch per level.
  * --------------------------------------------------------------------- */
 typedef struct tt_lutnet tt_lutnet;
@@ -278,8 +278,8 @@ typedef struct tt_lutnet tt_lutnet;
 /* Build a reusable handle for a network: validates the descriptors and the
  * fan-in, groups the neurons by level and stages everything the kernels read
  * into a device workspace owned by the handle (in the single-launch form
- * this includes a copy of the tables with the planes interleaved, made on
- * stream).  d_tables must hold the tables when stream reaches this call and
+ * this includes a copy of the tables with each row's code in adjacent bits,
+ * made on stream).  d_tables must hold the tables when stream reaches this call and
  * must not change while the handle exists.  TT_EINVAL for bad descriptors,
  * fan-in out of range or NULL pointers; TT_ERANGE for tables beyond
  * total_words; TT_ENOMEM when the workspace cannot be allocated. */

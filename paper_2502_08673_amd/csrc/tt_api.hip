@@ -748,6 +748,7 @@ struct tt_gd {
 struct tt_lutnet {
   int n = 0, n_inputs = 0, depth = 0;
   long stride = 0;      // > 0: the single-launch form
+  int cus = 0;
   uint8_t* ws = nullptr;
   bool ws_async = false;  // allocated in stream order (freed the same way)
   tt::NetArgs na{};
@@ -785,7 +786,7 @@ int lutnet_setup(const tt_neuron* h_desc, int n, const int32_t* h_fanin, int n_i
   if (n == 0 || check_only) return TT_OK;
   if (!d_tables) return TT_EINVAL;
   TT_TRY(validate_ranges(h_desc, n, total_words));
-  TT_TRY(device_info(nullptr));
+  TT_TRY(device_info(&L->cus));
   // neurons grouped by level
   std::vector<int32_t> order;
   L->level_begin.assign(depth + 1, 0);
@@ -805,25 +806,39 @@ int lutnet_setup(const tt_neuron* h_desc, int n, const int32_t* h_fanin, int n_i
   const long stride = tt::lutnet_fused_stride(n_inputs, n);
   L->stride = stride;
   std::vector<uint8_t>* blob = nullptr;
-  size_t off_rec = 0, off_lvb = 0, off_inm = 0, off_rep = 0, off_il = 0;
+  size_t off_rec = 0, off_lvb = 0, off_inm = 0, off_rep = 0, off_il = 0, off_slot = 0;
   size_t off_desc = 0, off_fan = 0, off_ord = 0;
-  int fmax = 1, omax = 1;
+  int fmax = 1, omax = 1, lw = 0, rounds = 0;
+  auto pack_rounds = [](int count) { return (count + tt::kPackWaves - 1) / tt::kPackWaves; };
   bool need_mask = false;
   if (stride > 0) {
     for (int i = 0; i < n; ++i) {
       fmax = std::max(fmax, (int)h_desc[i].F);
       omax = std::max(omax, (int)h_desc[i].o);
     }
-    const int G = tt::net_group(omax);
+    lw = tt::net_code_shift(omax);
+    auto dwords_of = [&](const tt_neuron& d) {
+      const int bits = d.F * d.b + lw;
+      return bits > 5 ? 1u << (bits - 5) : 1u;
+    };
     uint64_t il_dwords = 0;
+    uint32_t largest = 0;
+    bool one_b = true;
     for (int i = 0; i < n; ++i) {
-      const int Fb = h_desc[i].F * h_desc[i].b;
-      il_dwords += (uint64_t)G * (Fb > 5 ? 1ull << (Fb - 5) : 1ull);
+      il_dwords += std::max(dwords_of(h_desc[i]), 4u);
+      largest = std::max(largest, dwords_of(h_desc[i]));
+      one_b = one_b && h_desc[i].b == h_desc[0].b;
+    }
+    // the packed form: tables of at most 1 KiB, digits of one width
+    if (one_b && 4 * largest <= tt::kPackTable && tt::net_pack_lds(n_inputs + n) <= tt::kPackMaxLds) {
+      for (int lv = 0; lv < depth; ++lv) rounds += pack_rounds(L->level_begin[lv + 1] - L->level_begin[lv]);
+      rounds = (rounds + tt::kPackRounds - 1) / tt::kPackRounds * tt::kPackRounds;
     }
     off_rec = take(sizeof(tt::NetRec) * n);
     off_lvb = take(sizeof(int32_t) * (depth + 1));
     off_inm = take((size_t)n_inputs);
     off_rep = take(sizeof(tt::RepackItem) * n);
+    if (rounds > 0) off_slot = take(sizeof(tt::NetSlot) * tt::kPackWaves * (rounds + tt::kPackRounds));
     const size_t blob_bytes = o;
     off_il = take(4 * il_dwords);
     blob = new std::vector<uint8_t>(blob_bytes, 0);
@@ -833,16 +848,30 @@ int lutnet_setup(const tt_neuron* h_desc, int n, const int32_t* h_fanin, int n_i
     for (int k = 0; k < n; ++k) {
       const int i = order[k];
       const tt_neuron& d = h_desc[i];
-      const int Fb = d.F * d.b;
-      const uint32_t groups = Fb > 5 ? 1u << (Fb - 5) : 1u;
       tt::NetRec& R = rec[k];
       R.tab = at;
       R.out = (uint32_t)(n_inputs + i);
       R.mask = (1u << d.b) - 1u;
       R.b = d.b;
       for (int j = 0; j < 8; ++j) R.sig[j] = (uint32_t)(j < d.F ? h_fanin[8 * (size_t)i + j] : n_inputs + n);
-      rep[k] = tt::RepackItem{d.word_off, at, (uint32_t)words_of(d.F, d.b), d.o, groups, 0u};
-      at += (uint64_t)G * groups;
+      rep[k] = tt::RepackItem{d.word_off, at, (uint32_t)words_of(d.F, d.b), d.o, dwords_of(d), 0u};
+      at += std::max(dwords_of(d), 4u);
+    }
+    if (rounds > 0) {
+      auto* slot = reinterpret_cast<tt::NetSlot*>(blob->data() + off_slot);
+      for (int lv = 0; lv < depth; ++lv) {
+        const int k0 = L->level_begin[lv], count = L->level_begin[lv + 1] - k0;
+        for (int k = 0; k < count; ++k) {
+          const tt::NetRec& R = rec[k0 + k];
+          slot[k].tab = (uint32_t)(4 * R.tab);  // at most 1019 tables of 1 KiB
+          slot[k].last_unit = ((dwords_of(h_desc[order[k0 + k]]) + 3) / 4 - 1) * 16;
+          slot[k].out = tt::net_row(R.out);
+          slot[k].flags = 1;
+          for (int j = 0; j < 8; ++j) slot[k].sig[j] = tt::net_row(R.sig[j]);
+        }
+        slot += (size_t)tt::kPackWaves * pack_rounds(count);
+        for (int w = 1; w <= tt::kPackWaves; ++w) slot[-w].flags |= 2;
+      }
     }
     std::memcpy(blob->data() + off_lvb, L->level_begin.data(), sizeof(int32_t) * (depth + 1));
     // An input whose readers all take b digits is staged as its low b bits;
@@ -894,8 +923,12 @@ int lutnet_setup(const tt_neuron* h_desc, int n, const int32_t* h_fanin, int n_i
     na.mask = need_mask ? 1 : 0;
     na.in_mask = L->ws + off_inm;
     na.tables = reinterpret_cast<const uint32_t*>(L->ws + off_il);
-    TT_HIP(tt::launch_lutnet_repack(reinterpret_cast<const tt::RepackItem*>(L->ws + off_rep), n,
-                                    tt::net_group(omax), d_tables, reinterpret_cast<uint32_t*>(L->ws + off_il), s));
+    na.lw = lw;
+    na.slots = rounds > 0 ? reinterpret_cast<const tt::NetSlot*>(L->ws + off_slot) : nullptr;
+    na.rounds = rounds;
+    na.digit = h_desc[0].b;
+    TT_HIP(tt::launch_lutnet_repack(reinterpret_cast<const tt::RepackItem*>(L->ws + off_rep), n, lw, d_tables,
+                                    reinterpret_cast<uint32_t*>(L->ws + off_il), s));
   } else {
     tt::LutnetArgs& la = L->la;
     la.desc = reinterpret_cast<const tt_neuron*>(L->ws + off_desc);
@@ -915,7 +948,15 @@ int lutnet_enqueue(const tt_lutnet& L, const uint8_t* d_inputs, int batch, uint8
     na.inputs = d_inputs;
     na.out = d_out;
     na.sample = 0;
-    TT_HIP(tt::launch_lutnet_fused(na, tt::NetSample{}, s));
+    // The packed form's blocks take eight times the samples, so it pays once
+    // the other one has three blocks of 64 samples for each compute unit: 448
+    // neurons, F = 6, b = 2: 48000 samples 28.5 against 27.3 us, 64000 40.7
+    // against 28.1, 16000 15.3 against 25.3; F = 4, b = 1, 480 neurons: 48000
+    // 26.3 against 30.7, 250000 141 against 86.
+    if (na.slots && batch >= 192 * L.cus)
+      TT_HIP(tt::launch_lutnet_packed(na, s));
+    else
+      TT_HIP(tt::launch_lutnet_fused(na, tt::NetSample{}, s));
     return TT_OK;
   }
   tt::LutnetArgs la = L.la;

@@ -366,15 +366,28 @@ struct NetRec {
   uint32_t sig[8];  // fan-in bytes in a signal row; past F, the row's zero byte
 };
 static_assert(sizeof(NetRec) == 64, "NetRec is one 64-byte scalar load");
-// The single-launch form reads a copy of the tables with the planes
-// interleaved: dword g of every plane side by side, G = 1, 2 or 4 dwords per
-// group for a network whose largest o is 1, 2 or 3 (planes past a neuron's o
-// are zero), so that one load returns a row's bit of every plane.
+// The single-launch forms read a copy of the tables with a row's code in
+// 1, 2 or 4 adjacent bits (2^lw; for a network whose largest o is 1, 2 or 3;
+// planes past a neuron's o are zero), so that one dword returns every plane.
 struct RepackItem {
   uint64_t src_word;   // the neuron's word_off
   uint64_t dst_dword;  // its NetRec::tab
-  uint32_t W, o, groups, pad;
+  uint32_t W, o, dwords, pad;
 };
+// A neuron of a round of the packed form: round t's neuron of wave w at
+// [t][w], a level's neurons filling whole rounds.
+constexpr int kPackWaves = 16;
+constexpr int kPackRounds = 4;  // rounds are padded with empty ones to a multiple of it, and as many follow
+constexpr uint32_t kPackTable = 1024;  // most bytes of a table
+struct NetSlot {
+  uint32_t tab;        // byte of the neuron's table in the copy
+  uint32_t last_unit;  // byte of its last 16 bytes within it
+  uint32_t out;        // LDS byte of its signal row
+  uint32_t flags;      // 1: a neuron (else an empty place), 2: the round ends a level
+  uint32_t pad[4];
+  uint32_t sig[8];     // LDS bytes of its fan-in's signal rows; past F, the zero row's
+};
+static_assert(sizeof(NetSlot) == 64, "a wave loads a NetSlot as a dword per lane of a row of 16");
 struct NetArgs {
   const NetRec* rec;          // [n] in level order
   const int32_t* level_begin; // [depth + 1]
@@ -383,7 +396,11 @@ struct NetArgs {
   int32_t fmax, omax;         // largest F and o of the network
   int32_t mask;               // readers mask codes to their digits (else every code already fits)
   const uint8_t* in_mask;     // [n_inputs] (8-byte aligned): input code masks applied when staging
-  const uint32_t* tables;     // the interleaved copy
+  const uint32_t* tables;     // the copy, a row's code in 2^lw bits, tables 16-byte aligned
+  int32_t lw;
+  const NetSlot* slots;       // [rounds + kPackRounds][kPackWaves], NULL when the packed form does not fit
+  int32_t rounds;
+  int32_t digit;              // the neurons' common b
   const uint8_t* inputs;      // [batch][n_inputs]
   uint8_t* out;               // [batch][n]
   int32_t sample;             // draw the inputs and keep the draws that meet the targets (NetSample)
@@ -402,13 +419,22 @@ struct NetSample {
   uint16_t tsig[kNetMaxTargets];
   uint8_t tval[kNetMaxTargets];
 };
-inline int net_group(int omax) { return omax <= 1 ? 1 : omax == 2 ? 2 : 4; }
+inline int net_code_shift(int omax) { return omax <= 1 ? 0 : omax == 2 ? 1 : 2; }
+// The packed form: LDS byte of a signal's row, the rows' and the whole size.
+__host__ __device__ inline uint32_t net_row(uint32_t sig) { return 132u * sig + 4u * (sig >> 6); }
+constexpr long kPackMaxLds = 160 * 1024;
+// rows: the signals' and one of zeros; then a table per wave
+inline long net_pack_tables_at(int signals) {
+  return ((long)net_row((uint32_t)signals) + 132 + kPackTable - 1) / kPackTable * kPackTable;
+}
+inline long net_pack_lds(int signals) { return net_pack_tables_at(signals) + (long)kPackWaves * kPackTable; }
 // LDS row stride of the single-launch form, 0 when the network's signals do
 // not fit (then one launch per level)
 long lutnet_fused_stride(int n_inputs, int n);
-hipError_t launch_lutnet_repack(const RepackItem* items, int n, int G, const uint64_t* tables, uint32_t* il,
+hipError_t launch_lutnet_repack(const RepackItem* items, int n, int lw, const uint64_t* tables, uint32_t* il,
                                 hipStream_t s);
 hipError_t launch_lutnet_fused(const NetArgs& a, const NetSample& smp, hipStream_t s);
+hipError_t launch_lutnet_packed(const NetArgs& a, hipStream_t s);
 
 // CNF transformation (tt_cnf.hip).
 constexpr int kCnfMaxVars = TT_CNF_MAX_VARS;

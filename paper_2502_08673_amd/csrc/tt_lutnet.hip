@@ -4,11 +4,13 @@
 // Signals 0 .. n_inputs - 1 are primary input codes (uint8 per sample), and
 // signal n_inputs + i is the output code of neuron i.  A neuron gathers its
 // F input codes, forms the row r from their low b bits, and reads bit
-// r % 64 of word r / 64 of each of its o planes.  Two forms: the whole
+// r % 64 of word r / 64 of each of its o planes.  Three forms: the whole
 // network per block with the samples' signals in LDS (when a few dozen
-// samples' signals fit), else one launch per level (a level reads only the
-// primary inputs and earlier levels) with the signals in global memory.
+// samples' signals fit), bytes for 64 samples or packed for 256 or 512, else
+// one launch per level (a level reads only the primary inputs and earlier
+// levels) with the signals in global memory.
 #include <algorithm>
+#include <utility>
 
 #include "tt_internal.h"
 
@@ -46,9 +48,9 @@ __global__ __launch_bounds__(256) void lutnet_level_kernel(LutnetArgs a) {
 // kNetStep neurons at a time: their records are wave-uniform (scalar loads,
 // no chain of dependent loads), each lane reads the fan-in codes from its
 // own row (FMAX reads, unused slots pointing at the zero byte, so no branch
-// on F), and one load per lane returns the row's group of interleaved plane
-// dwords, all inside the neuron's table, which stays in cache.  The block
-// writes its output rows at the end.
+// on F), and one load per lane returns the dword that holds the row's code,
+// inside the neuron's table, which stays in cache.  The block writes its
+// output rows at the end.
 constexpr int kNetSamples = 64;
 constexpr int kNetStep = 8;
 constexpr int kNetThreads = 512;
@@ -182,35 +184,20 @@ __global__ __launch_bounds__(kNetThreads) void lutnet_fused_kernel(NetArgs a, co
       for (int u = 0; u < kNetStep; ++u)
 #pragma unroll
         for (int j = 0; j < FMAX; ++j) c[u][j] = sig[rowb + R[u]->sig[j]];
-      constexpr int G = OMAX <= 1 ? 1 : OMAX == 2 ? 2 : 4;
-      uint32_t r[kNetStep], d[kNetStep][G];
+      constexpr int LW = OMAX <= 1 ? 0 : OMAX == 2 ? 1 : 2;
+      uint32_t r[kNetStep], d[kNetStep];
 #pragma unroll
       for (int u = 0; u < kNetStep; ++u) {
         const uint32_t mask = R[u]->mask, b = R[u]->b;
         uint32_t x = 0;
 #pragma unroll
         for (int j = 0; j < FMAX; ++j) x |= (MASK ? c[u][j] & mask : c[u][j]) << (j * b);
-        r[u] = x;
-        const uint32_t* tb = a.tables + R[u]->tab;  // group x >> 5 holds bit x & 31 of every plane
-        if constexpr (G == 1) {
-          d[u][0] = tb[x >> 5];
-        } else if constexpr (G == 2) {
-          const uint2 v = reinterpret_cast<const uint2*>(tb)[x >> 5];
-          d[u][0] = v.x;
-          d[u][G - 1] = v.y;
-        } else {
-          const uint4 v = reinterpret_cast<const uint4*>(tb)[x >> 5];
-          d[u][0] = v.x;
-          d[u][1 % G] = v.y;
-          d[u][2 % G] = v.z;
-        }
+        r[u] = x << LW;
+        d[u] = a.tables[R[u]->tab + (x >> (5 - LW))];
       }
 #pragma unroll
       for (int u = 0; u < kNetStep; ++u) {
-        const uint32_t sh = r[u] & 31u;
-        uint32_t q = (d[u][0] >> sh) & 1u;
-#pragma unroll
-        for (int p = 1; p < OMAX; ++p) q |= ((d[u][p] >> sh) & 1u) << p;
+        const uint32_t q = __builtin_amdgcn_ubfe(d[u], r[u], 1u << LW);
         // unconditional: a repeated neuron writes the value its first copy
         // writes, and lanes past the batch write rows that are never read out
         sig[rowb + R[u]->out] = (uint8_t)q;
@@ -245,23 +232,344 @@ __global__ __launch_bounds__(kNetThreads) void lutnet_fused_kernel(NetArgs a, co
     lds_to_rows<uint8_t>(sig + a.n_inputs, a.stride, ns, a.n, a.out + s0 * a.n);
 }
 
-__global__ __launch_bounds__(256) void lutnet_repack_kernel(const RepackItem* items, int n, int G,
+// The packed form, for large batches: signals of BITS (2 or 4) bits, a signal
+// row of 128 bytes in LDS for 1024 / BITS samples (33 dwords and one more
+// every 64 rows: the 64 rows that a wave's lanes touch at one place while
+// staging lie in 64 banks).  A wave takes a neuron for all of the block's
+// samples, a lane 16 bits of each fan-in row: the rows of the table of its 8
+// or 4 samples come from a few operations on all of them at once, and the
+// neuron's table (at most 1 KiB, loaded two rounds ahead) is looked up in
+// LDS.  The form above loads each code by itself and gathers from the cache,
+// one address at a time per compute unit, which bounds it.  Here the bound is
+// the LDS (eight gathers of 64 lanes in 64 banks, 54 of a neuron's 95 cycles)
+// and the vector unit beside it (75 instructions a neuron and 512 samples);
+// while all blocks load or write at once, HBM.  256 inputs, 448 neurons, F = 6,
+// b = 2, 250001 samples: 73 us (that form: 133); 480 neurons of F = 4, b = 1:
+// 86 (141); 60 of them: 12.6 (38.5).  Four waves that only write and load
+// beside twelve that look up, with the next samples' inputs on the way: 73.
+constexpr int kPackThreads = 64 * kPackWaves;
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// LDS by its address: a pointer into the dynamic array costs an addition of
+// its base (0) at every access
+template <typename T>
+__device__ __forceinline__ T lds_load(uint32_t byte) {
+  return *(T __attribute__((address_space(3)))*)(uintptr_t)byte;
+}
+template <typename T>
+__device__ __forceinline__ void lds_store(uint32_t byte, T v) {
+  *(T __attribute__((address_space(3)))*)(uintptr_t)byte = v;
+}
+
+// bytes of four dwords transposed: out[t] = byte t of w[0], .. w[3]
+__device__ __forceinline__ void transpose_bytes(const uint32_t (&w)[4], uint32_t (&out)[4]) {
+  const uint32_t l01 = __builtin_amdgcn_perm(w[1], w[0], 0x05010400u), l23 = __builtin_amdgcn_perm(w[3], w[2], 0x05010400u);
+  const uint32_t h01 = __builtin_amdgcn_perm(w[1], w[0], 0x07030602u), h23 = __builtin_amdgcn_perm(w[3], w[2], 0x07030602u);
+  out[0] = __builtin_amdgcn_perm(l23, l01, 0x05040100u);
+  out[1] = __builtin_amdgcn_perm(l23, l01, 0x07060302u);
+  out[2] = __builtin_amdgcn_perm(h23, h01, 0x05040100u);
+  out[3] = __builtin_amdgcn_perm(h23, h01, 0x07060302u);
+}
+
+// m ? x : y, bit by bit (as the instruction: from the expression the compiler
+// makes three where it knows some of the bits)
+__device__ __forceinline__ uint32_t select_bits(uint32_t m, uint32_t x, uint32_t y) {
+  uint32_t r;
+  asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(r) : "s"(m), "v"(x), "v"(y));
+  return r;
+}
+
+// The block's `left` rows of n codes into the signal rows 0, 1, ...; samples
+// past the batch read its last row.  A thread takes a dword of samples of
+// four signals (one signal, when a row is not made of aligned dwords): one
+// dword per row.  A signal's dword holds row J k + j, J = 8 / BITS, in bits
+// 8 k + BITS j.
+template <int BITS>
+__device__ __forceinline__ void pack_load(int n, const uint8_t* rows, uint32_t left) {
+  constexpr int J = 8 / BITS, R = 4 * J;
+  constexpr uint32_t kCode = (1u << BITS) - 1u, kCodes = 0x01010101u * kCode;
+  const bool quads = (n & 3) == 0 && ((uintptr_t)rows & 3) == 0;
+  const uint32_t cols = quads ? n / 4 : n;
+  if (cols == 0) return;
+  uint32_t g = threadIdx.x / cols, c = threadIdx.x - g * cols;
+  const uint32_t dg = kPackThreads / cols, dc = kPackThreads - dg * cols;
+  while (g < 32) {
+    if (quads) {
+      uint32_t d[R], v[4], t[4];
+      if (left == 1024u / BITS) {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+          d[r] = *reinterpret_cast<const uint32_t*>(rows + (long)r * n + (__umul24(R * g, (uint32_t)n) + 4 * c));
+      } else {
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+          d[r] = *reinterpret_cast<const uint32_t*>(rows + (__umul24(min(R * g + r, left - 1), (uint32_t)n) + 4 * c));
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        v[k] = d[J * k + J - 1];
+#pragma unroll
+        for (int j = J - 2; j >= 0; --j) v[k] = select_bits(kCodes, d[J * k + j], v[k] << BITS);
+      }
+      transpose_bytes(v, t);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) lds_store<uint32_t>(net_row(4 * c + q) + 4 * g, t[q]);
+    } else {
+      uint32_t v = 0;
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        v |= ((uint32_t)rows[__umul24(min(R * g + r, left - 1), (uint32_t)n) + c] & kCode) << (BITS * r);
+      lds_store<uint32_t>(net_row(c) + 4 * g, v);
+    }
+    g += dg;
+    c += dc;
+    if (c >= cols) {
+      c -= cols;
+      ++g;
+    }
+  }
+}
+
+// The reverse: the n signal rows from sig0 on into the block's `left` rows
+// (FULL: all of them) of codes.
+template <int BITS, bool FULL>
+__device__ __forceinline__ void pack_store(int sig0, int n, uint8_t* rows, uint32_t left) {
+  constexpr int J = 8 / BITS, R = 4 * J;
+  constexpr uint32_t kCode = (1u << BITS) - 1u, kCodes = 0x01010101u * kCode;
+  const bool quads = (n & 3) == 0 && ((uintptr_t)rows & 3) == 0;
+  const uint32_t cols = quads ? n / 4 : n;
+  uint32_t g = threadIdx.x / cols, c = threadIdx.x - g * cols;
+  const uint32_t dg = kPackThreads / cols, dc = kPackThreads - dg * cols;
+  while (g < 32) {
+    const uint32_t r0 = R * g;
+    if (quads) {
+      uint32_t v[4], t[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) v[q] = lds_load<uint32_t>(net_row(sig0 + 4 * c + q) + 4 * g);
+      transpose_bytes(v, t);
+      const uint32_t at = __umul24(r0, (uint32_t)n) + 4 * c;
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        if (FULL || r0 + r < left)
+          *reinterpret_cast<uint32_t*>(rows + (long)r * n + at) = (t[r / J] >> (BITS * (r % J))) & kCodes;
+    } else {
+      const uint32_t v = lds_load<uint32_t>(net_row(sig0 + c) + 4 * g), at = __umul24(r0, (uint32_t)n) + c;
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+        if (FULL || r0 + r < left) rows[(long)r * n + at] = (uint8_t)((v >> (BITS * r)) & kCode);
+    }
+    g += dg;
+    c += dc;
+    if (c >= cols) {
+      c -= cols;
+      ++g;
+    }
+  }
+}
+
+// dword i of a NetSlot held one dword a lane in each row of 16 lanes
+__device__ __forceinline__ uint32_t slot_word(uint32_t rec, int i) {
+  return (uint32_t)__builtin_amdgcn_readlane((int)rec, i);
+}
+template <int I>
+__device__ __forceinline__ uint32_t slot_bcast(uint32_t rec) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)rec, 0x150 + I, 0xF, 0xF, true);  // row_newbcast
+}
+
+// Rows x[4] of the table from four samples' nibbles: a holds index words 0
+// and 2 (16 bits each), c words 1 and 3; a sample's nibbles side by side.
+__device__ __forceinline__ void join_nibbles(uint32_t a, uint32_t c, bool wide, uint32_t& x0, uint32_t& x1,
+                                             uint32_t& x2, uint32_t& x3) {
+  const uint32_t e = select_bits(0x0F0F0F0Fu, a, c << 4), o = select_bits(0xF0F0F0F0u, c, a >> 4);
+  if (wide) {
+    x0 = __builtin_amdgcn_perm(0u, e, 0x0C0C0200u);
+    x1 = __builtin_amdgcn_perm(0u, o, 0x0C0C0200u);
+    x2 = __builtin_amdgcn_perm(0u, e, 0x0C0C0301u);
+    x3 = __builtin_amdgcn_perm(0u, o, 0x0C0C0301u);
+  } else {
+    x0 = e & 255u;
+    x1 = o & 255u;
+    x2 = e >> 8;
+    x3 = o >> 8;
+  }
+}
+
+// the lane's 16 bits of each fan-in row
+template <int N, int... I>
+__device__ __forceinline__ void load_fanin(uint32_t rec, uint32_t lane2, uint32_t (&u)[N],
+                                           std::integer_sequence<int, I...>) {
+  ((u[I] = lds_load<uint16_t>(slot_bcast<8 + I>(rec) + lane2)), ...);
+}
+
+// Rows of the table of the lane's 16 / BITS samples (its 16 bits of each
+// fan-in row): the digits, 4 / B a nibble, joined within the M index words
+// of all samples first, then the nibbles of each sample.
+template <int BITS, int B, int M>
+__device__ __forceinline__ void pack_index(uint32_t rec, uint32_t lane2, uint32_t (&x)[16 / BITS]) {
+  constexpr int K = B == 1 ? 4 : B == 2 ? 2 : 1;
+  uint32_t u[K * M];
+  load_fanin(rec, lane2, u, std::make_integer_sequence<int, K * M>{});
+  if constexpr (BITS == 4) {
+    constexpr uint32_t kDigit = 0x1111u * ((1u << B) - 1u);
+    uint32_t P[4] = {0, 0, 0, 0};
+#pragma unroll
+    for (int i = 0; i < M; ++i)
+#pragma unroll
+      for (int k = 0; k < K; ++k) P[i] |= (u[i * K + k] & kDigit) << (k * B);
+    if constexpr (B == 3) {
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        x[s] = 0;
+#pragma unroll
+        for (int i = 0; i < M; ++i) x[s] |= ((P[i] >> (4 * s)) & 7u) << (3 * i);
+      }
+    } else {
+      join_nibbles(P[0] | P[2] << 16, P[1] | P[3] << 16, M > 2, x[0], x[1], x[2], x[3]);
+    }
+  } else {
+    // two-bit digits first: even and odd samples' nibbles from pairs of them
+    uint32_t w[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+#pragma unroll
+    for (int i = 0; i < 2 * M; ++i) w[i] = B == 2 ? u[i] : select_bits(0x5555u, u[2 * i], u[2 * i + 1] << 1) & 0xFFFFu;
+    const uint32_t a = w[0] | w[4] << 16, b = w[1] | w[5] << 16, c = w[2] | w[6] << 16, d = w[3] | w[7] << 16;
+    join_nibbles(select_bits(0x33333333u, a, b << 2), select_bits(0x33333333u, c, d << 2), M > 2, x[0], x[2], x[4],
+                 x[6]);
+    join_nibbles(select_bits(0xCCCCCCCCu, b, a >> 2), select_bits(0xCCCCCCCCu, d, c >> 2), M > 2, x[1], x[3], x[5],
+                 x[7]);
+  }
+}
+
+template <int BITS, int B, int M, int LW>
+__global__ __launch_bounds__(kPackThreads, 8) void lutnet_packed_kernel(NetArgs a, uint32_t tables_at) {
+  // dynamic LDS, from byte 0 on: signal rows, then a table per wave
+  constexpr int kAhead = kPackRounds / 2;  // tables on the way; records on the way: twice as many
+  constexpr int S = 16 / BITS;
+  constexpr uint32_t kRows = 1024 / BITS;
+  const int lane = threadIdx.x & 63;
+  const uint32_t lane2 = 2 * lane, lane16 = 16 * lane;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const long s0 = (long)blockIdx.x * kRows;
+  const uint32_t left = (uint32_t)min((long)kRows, (long)a.batch - s0);
+  const uint32_t tab = tables_at + wave * kPackTable;
+  const uint32_t* slots = reinterpret_cast<const uint32_t*>(a.slots + wave) + (lane & 15);
+  const uint8_t* tables = reinterpret_cast<const uint8_t*>(a.tables);
+  uint32_t recs[kPackRounds];
+  u32x4 ahead[kAhead];
+  auto fetch = [&](uint32_t rec) {
+    return *reinterpret_cast<const u32x4*>(tables + (slot_bcast<0>(rec) + min(lane16, slot_bcast<1>(rec))));
+  };
+#pragma unroll
+  for (int u = 0; u < kPackRounds; ++u) recs[u] = slots[u * (kPackWaves * 16)];
+#pragma unroll
+  for (int u = 0; u < kAhead; ++u) ahead[u] = fetch(recs[u]);
+  pack_load<BITS>(a.n_inputs, a.inputs + s0 * a.n_inputs, left);
+  if (threadIdx.x < 32) lds_store<uint32_t>(net_row(a.n_inputs + a.n) + 4 * threadIdx.x, 0u);
+  __syncthreads();
+  for (int t = 0; t < a.rounds; t += kPackRounds) {
+    slots += kPackRounds * kPackWaves * 16;
+#pragma unroll
+    for (int u = 0; u < kPackRounds; ++u) {
+      const uint32_t rec = recs[u], flags = slot_word(rec, 3);
+      const u32x4 table = ahead[u % kAhead];
+      ahead[u % kAhead] = fetch(recs[(u + kAhead) % kPackRounds]);
+      if (flags & 1u) {
+        lds_store<u32x4>(tab + lane16, table);
+        __builtin_amdgcn_wave_barrier();
+        uint32_t x[S], d[S], q = 0;
+        pack_index<BITS, B, M>(rec, lane2, x);
+#pragma unroll
+        for (int s = 0; s < S; ++s) d[s] = lds_load<uint32_t>(select_bits(kPackTable - 4u, x[s] >> (3 - LW), tab));
+#pragma unroll
+        for (int s = 0; s < S; ++s) q |= __builtin_amdgcn_ubfe(d[s], x[s] << LW, 1u << LW) << (BITS * s);
+        lds_store<uint16_t>(slot_bcast<2>(rec) + lane2, (uint16_t)q);
+        __builtin_amdgcn_wave_barrier();
+      }
+      recs[u] = slots[u * (kPackWaves * 16)];
+      if (flags & 2u) __syncthreads();
+    }
+  }
+  if (left == kRows)
+    pack_store<BITS, true>(a.n_inputs, a.n, a.out + s0 * a.n, left);
+  else
+    pack_store<BITS, false>(a.n_inputs, a.n, a.out + s0 * a.n, left);
+}
+
+// Dword g of the copy: the codes of rows (32 >> lw) g and on, bit p of a code
+// from plane p (bits of a plane spread 2^lw apart).
+__device__ __forceinline__ uint32_t code_dword(const uint32_t* src, uint64_t plane, uint32_t g, int o, int lw) {
+  if (lw == 0) return src[g];
+  uint32_t v = 0;
+  for (int p = 0; p < o; ++p) {
+    const uint32_t w = src[p * plane + (g >> lw)];
+    uint32_t x = lw == 1 ? (w >> (16 * (g & 1u))) & 0xFFFFu : (w >> (8 * (g & 3u))) & 0xFFu;
+    if (lw == 1) {
+      x = (x | x << 8) & 0x00FF00FFu;
+      x = (x | x << 4) & 0x0F0F0F0Fu;
+      x = (x | x << 2) & 0x33333333u;
+      x = (x | x << 1) & 0x55555555u;
+    } else {
+      x = (x | x << 12) & 0x000F000Fu;
+      x = (x | x << 6) & 0x03030303u;
+      x = (x | x << 3) & 0x11111111u;
+    }
+    v |= x << p;
+  }
+  return v;
+}
+
+__global__ __launch_bounds__(256) void lutnet_repack_kernel(const RepackItem* items, int n, int lw,
                                                             const uint64_t* tables, uint32_t* il) {
   for (int k = blockIdx.x; k < n; k += gridDim.x) {
     const RepackItem it = items[k];
     const uint32_t* src = reinterpret_cast<const uint32_t*>(tables + it.src_word);
-    for (uint32_t g = threadIdx.x; g < it.groups; g += blockDim.x)
-      for (int p = 0; p < G; ++p)
-        il[it.dst_dword + (uint64_t)g * G + p] = p < (int)it.o ? src[(uint64_t)p * 2 * it.W + g] : 0u;
+    for (uint32_t g = threadIdx.x; g < it.dwords; g += blockDim.x)
+      il[it.dst_dword + g] = code_dword(src, 2ull * it.W, g, (int)it.o, lw);
   }
 }
 
-hipError_t launch_lutnet_repack(const RepackItem* items, int n, int G, const uint64_t* tables, uint32_t* il,
+hipError_t launch_lutnet_repack(const RepackItem* items, int n, int lw, const uint64_t* tables, uint32_t* il,
                                 hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  hipLaunchKernelGGL(lutnet_repack_kernel, dim3((unsigned)std::min(n, 4096)), dim3(256), 0, s, items, n, G, tables,
+  hipLaunchKernelGGL(lutnet_repack_kernel, dim3((unsigned)std::min(n, 4096)), dim3(256), 0, s, items, n, lw, tables,
                      il);
   return hipGetLastError();
+}
+
+template <int BITS, int B, int M, int LW>
+hipError_t launch_packed(const NetArgs& a, hipStream_t s) {
+  const int samples = 1024 / BITS;
+  const unsigned blocks = (unsigned)(((long)a.batch + samples - 1) / samples);
+  const uint32_t tables_at = (uint32_t)net_pack_tables_at(a.n_inputs + a.n);
+  const size_t lds = (size_t)net_pack_lds(a.n_inputs + a.n);
+  const auto kernel = lutnet_packed_kernel<BITS, B, M, LW>;
+  if (lds > 65536) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kPackThreads), lds, s, a, tables_at);
+  return hipGetLastError();
+}
+
+hipError_t launch_lutnet_packed(const NetArgs& a, hipStream_t s) {
+  if (a.batch <= 0) return hipSuccess;
+  // two bits a signal where the codes and digits have at most two
+  if (a.omax <= 2 && a.digit <= 2) {
+    const bool one = a.lw == 0;
+    if (a.digit == 1) return one ? launch_packed<2, 1, 2, 0>(a, s) : launch_packed<2, 1, 2, 1>(a, s);
+    if (a.fmax <= 4) return one ? launch_packed<2, 2, 2, 0>(a, s) : launch_packed<2, 2, 2, 1>(a, s);
+    return one ? launch_packed<2, 2, 3, 0>(a, s) : launch_packed<2, 2, 3, 1>(a, s);
+  }
+  switch (a.digit * 4 + a.lw) {
+    case 6: return launch_packed<4, 1, 2, 2>(a, s);
+    case 10: return launch_packed<4, 2, 3, 2>(a, s);
+    case 12: return launch_packed<4, 3, 4, 0>(a, s);
+    case 13: return launch_packed<4, 3, 4, 1>(a, s);
+    case 14: return launch_packed<4, 3, 4, 2>(a, s);
+    case 16: return launch_packed<4, 4, 3, 0>(a, s);
+    case 17: return launch_packed<4, 4, 3, 1>(a, s);
+    default: return launch_packed<4, 4, 3, 2>(a, s);
+  }
 }
 
 long lutnet_fused_stride(int n_inputs, int n) {

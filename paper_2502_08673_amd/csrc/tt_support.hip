@@ -370,7 +370,7 @@ __device__ __forceinline__ void probe_table(const SupportArgs& a, const NeuronRe
 // wave each), then all neurons a lane each for the smallest tables.
 __global__ __launch_bounds__(512) void support_first_kernel(SupportArgs a) {
   __shared__ uint32_t s_found;
-  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   int blk = (int)blockIdx.x;
   if (blk < a.n_large) {
     const int n = a.large[blk];

@@ -299,3 +299,48 @@ def test_ragged_batch_lanes_stay_inside_the_tables(batch, P):
         torch.cuda.synchronize()
     assert int(count.item()) == batch
     assert sorted(draw.cpu().tolist()) == list(range(batch))
+
+
+@pytest.mark.parametrize("F,b,o,P,n,extra,offset",
+                         [((1, 8), 1, (1, 1), 92, 60, 0, 0), ((1, 5), 1, (1, 2), 93, 53, 1, 0),
+                          ((1, 4), 2, (1, 1), 40, 64, 511, 0), ((5, 6), 2, (1, 2), 64, 33, 513, 0),
+                          ((1, 6), 2, (2, 2), 700, 96, 255, 1), ((1, 8), 1, (3, 3), 13, 20, 7, 0),
+                          ((1, 5), 2, (1, 3), 36, 40, 257, 0), ((1, 4), 3, (1, 1), 36, 40, 1, 0),
+                          ((2, 4), 3, (1, 2), 21, 44, 256, 0), ((1, 3), 3, (3, 3), 8, 41, 3, 2),
+                          ((1, 3), 4, (1, 1), 24, 40, 5, 0), ((1, 2), 4, (1, 3), 20, 36, 0, 1)])
+def test_large_batches_take_the_packed_form(F, b, o, P, n, extra, offset):
+    """Batches from three blocks of 64 samples per compute unit on: every form
+    of the packed kernel (bits a signal, digits, code widths), codes wider
+    than the reader's digits, levels that do not fill a round of waves, rows
+    of odd byte counts and buffers of odd addresses, ragged last blocks.  The
+    first and the last samples against the oracle, all of them against the
+    same handle on pieces below the limit."""
+    batch = 192 * torch.cuda.get_device_properties(0).multi_processor_count + extra
+    ns = random_neurons(seed=700 + P + n, n=n, F=F, b=(b, b), o=o, max_fb=16, wmax=20, bias_max=30)
+    rng = np.random.default_rng(P + extra)
+    fanin = np.full((n, 8), -1, np.int32)
+    for i in range(n):
+        f = int(ns.F[i])
+        fanin[i, :f] = rng.integers(0, P + i, size=f)
+    inputs = rng.integers(0, 256, size=(batch, P)).astype(np.uint8)
+    desc = tt.descriptors(ns)
+    total = tt.layout(desc)
+    tables = device_tables(total)
+    tt.enumerate(desc, tables, total_words=total)
+    x = torch.zeros(offset + batch * P, dtype=torch.uint8, device="cuda")[offset:].view(batch, P)
+    x.copy_(torch.from_numpy(inputs))
+    out = torch.full((offset + batch * n + 64,), 0xEE, dtype=torch.uint8, device="cuda")
+    y = out[offset: offset + batch * n].view(batch, n)
+    pieces = torch.empty((batch, n), dtype=torch.uint8, device="cuda")
+    note(f"lutnet packed F={F} b={b} o={o} P={P} n={n} batch={batch}")
+    with tt.Lutnet(desc, fanin, P, tables, total) as net:
+        net.run(x, y)
+        step = (batch + 3) // 4
+        for s in range(0, batch, step):
+            net.run(x[s: s + step].contiguous(), pieces[s: s + step])
+        torch.cuda.synchronize()
+    assert torch.equal(y, pieces)
+    assert (out[:offset] == 0xEE).all() and (out[offset + batch * n:] == 0xEE).all()
+    rows = np.r_[0:200, batch - 700:batch]
+    want = lutnet.evaluate(ns, [fanin[i, :int(ns.F[i])] for i in range(n)], P, inputs[rows])
+    assert np.array_equal(y[torch.from_numpy(rows).cuda()].cpu().numpy(), want)
