@@ -181,6 +181,66 @@ def test_batch_edges_iterations_and_rate(batch, iters, lr):
                 assert np.array_equal(bit.astype(bool), Vg[:, q] > 0), kernel
 
 
+def test_logits_whose_sigmoid_leaves_the_reciprocal_range():
+    """Logits whose 1 + e^-v is above 2^126 or infinite (the compiled kernel
+    divides there), beside ordinary ones in the same sample and in others,
+    and logits whose sigmoid is 1: both kernels against the oracle."""
+    n_vars, clauses = tseitin_instances(seed=305, n_inst=1, n_gates=(20, 40))[0]
+    recs, cls = transform_on_gpu(n_vars, clauses)
+    R = T.transform(clauses)
+    with tt.GdSampler(clauses, n_vars, recs, cls) as gd:
+        rng = np.random.default_rng(77)
+        V0 = rng.normal(0, 1, (600, gd.n_pi)).astype(np.float32)
+        odd = np.float32([-np.inf, -1e30, -200, -100, -88.8, -88.7, -88, -87.4, -87.3, -87, 17, 87, 89, 1e30, np.inf])
+        put = rng.random(V0.shape) < 0.4
+        put[::3] = False
+        V0[put] = rng.choice(odd, size=int(put.sum()))
+        with np.errstate(over="ignore"):
+            Vo, ok, _ = G.sample(clauses, R, V0.astype(np.float64), lr=10.0, iters=2)
+        for kernel in (tt.TT_GD_COMPILED, tt.TT_GD_INTERPRETED):
+            gd.kernel = kernel
+            V = torch.from_numpy(V0.copy()).cuda()
+            valid = torch.zeros((600,), dtype=torch.uint8, device="cuda")
+            sol = torch.zeros((600, gd.words), dtype=torch.int64, device="cuda")
+            note(f"gd_sample kernel={kernel} extreme logits")
+            gd.run(V, 10.0, 2, valid, sol)
+            torch.cuda.synchronize()
+            Vg = V.cpu().numpy()
+            assert np.allclose(Vg, Vo, atol=ATOL, rtol=RTOL), kernel
+            clear = (np.abs(Vo) > CLEAR).all(axis=1)
+            assert np.array_equal(valid.cpu().numpy()[clear].astype(bool), ok[clear]), kernel
+
+
+@pytest.mark.parametrize("k", range(4))
+def test_clauses_that_the_gates_do_not_imply(k):
+    """Clauses over a gate's own variables, some of them with a literal
+    flipped, beside the clauses that the circuit was recovered from: those
+    that the gate implies and those that it does not, on every sample, with
+    and without steps."""
+    n_vars, clauses = tseitin_instances(seed=310 + k, n_inst=1, n_gates=(20, 40))[0]
+    recs, cls = transform_on_gpu(n_vars, clauses)
+    R = T.transform(clauses)
+    rng = np.random.default_rng(k)
+    for c in rng.permutation(len(clauses) - 1)[:3]:
+        more = [int(x) for x in clauses[c]]
+        more[int(rng.integers(len(more)))] *= -1
+        clauses = clauses + [more]
+    with tt.GdSampler(clauses, n_vars, recs, cls) as gd:
+        V0 = np.random.default_rng(k).normal(0, 1, (500, gd.n_pi)).astype(np.float32)
+        for iters in (0, 5):
+            Vo, ok, _ = G.sample(clauses, R, V0.astype(np.float64), lr=10.0, iters=iters)
+            for kernel in (tt.TT_GD_COMPILED, tt.TT_GD_INTERPRETED):
+                gd.kernel = kernel
+                V = torch.from_numpy(V0.copy()).cuda()
+                valid = torch.zeros((500,), dtype=torch.uint8, device="cuda")
+                sol = torch.zeros((500, gd.words), dtype=torch.int64, device="cuda")
+                note(f"gd_sample kernel={kernel} extra clauses k={k} iters={iters}")
+                gd.run(V, 10.0, iters, valid, sol)
+                torch.cuda.synchronize()
+                clear = (np.abs(Vo) > CLEAR).all(axis=1)
+                assert np.array_equal(valid.cpu().numpy()[clear].astype(bool), ok[clear]), (kernel, iters)
+
+
 @pytest.mark.parametrize("big", [False, True])
 def test_run_from_matches_in_place(big):
     """tt_gd_run_from on both kernels: with the final logits not kept (null)
