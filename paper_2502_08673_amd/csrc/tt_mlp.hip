@@ -761,8 +761,8 @@ __global__ void labels_kernel(const tt_neuron* desc, int n, const uint8_t* suppo
 
 // ------------------------------------------------------------- launchers
 // Whole-network inference, 32 -> 256 -> 256 -> 256 -> 12: a block of eight
-// waves takes 128 rows and keeps their activations in LDS from layer to
-// layer (one buffer of 128 rows x (256 + 8) bf16, overwritten in place: a
+// waves takes up to 160 rows and keeps their activations in LDS from layer to
+// layer (one buffer of 160 rows x (256 + 8) bf16, overwritten in place: a
 // layer's outputs stay in registers until every wave has finished reading
 // its inputs), so only the features come from HBM and only the logits go
 // back.  Weights: every thread loads its share of a whole hidden layer
@@ -770,14 +770,15 @@ __global__ void labels_kernel(const tt_neuron* desc, int n, const uint8_t* suppo
 // layer finishes, and the chunks pass through two LDS buffers, one barrier
 // each; a block reads every weight from L2 once.  The biases and the output
 // layer's weights sit in LDS from the start.  Wave w computes output
-// columns 64 (w % 4) .. + 63 of rows 64 (w / 4) .. + 63: per 16-k step two
-// weight fragments (MFMA A operand, rows = output columns) and two
-// activation fragments (B operand, columns = rows) give four
-// v_mfma_f32_32x32x16_bf16.  The 12-column output layer: waves 0-3 take
-// 32 rows each, one weight fragment (rows 12-31 zero).  Rounding as in the
-// layer-by-layer path: fp32 accumulation, bias, ReLU, round to nearest even
-// bf16 between layers (v_cvt_pk_bf16_f32).
-constexpr int kInferRows = 128;
+// columns 64 (w % 4) .. + 63 of the first or the second half of the tiles of
+// 32 rows (w / 4): per 16-k step two weight fragments (MFMA A operand, rows =
+// output columns) and one activation fragment per tile (B operand, columns =
+// rows) give two v_mfma_f32_32x32x16_bf16 a tile.  The 12-column output
+// layer: a wave takes a tile, one weight fragment (rows 12-31 zero).
+// Rounding as in the layer-by-layer path: fp32 accumulation, bias, ReLU,
+// round to nearest even bf16 between layers (v_cvt_pk_bf16_f32).
+constexpr int kInferRows = 128;     // rows of a pass over a candidate list
+constexpr int kInferMostRows = 160;  // rows of any pass
 constexpr int kActRow = 256 + 8;
 constexpr int kWChunk = 32;
 constexpr int kWRow = kWChunk + 8;
@@ -801,31 +802,37 @@ struct InferArgs {
   int nspans;
 };
 
-// One 32-k chunk of a hidden layer: two 16-k steps of four MFMAs on the
-// chunk in LDS buffer `buf` and the matching columns of H.
-__device__ __forceinline__ void infer_chunk(const uint16_t* H, const uint16_t* Wc, int buf, int c, f32x16 (&acc)[2][2],
-                                            int lane, int cg, int rg, int hk) {
+// One 32-k chunk of a hidden layer: two 16-k steps of 2 NT MFMAs on the
+// chunk in LDS buffer `buf` and the matching columns of H.  The layer's first
+// chunk adds to the constant zero instead of cleared registers.
+template <int NT, bool FIRST>
+__device__ __forceinline__ void infer_chunk(const uint16_t* H, const uint16_t* Wc, int buf, int c,
+                                            f32x16 (&acc)[NT][2], int lane, int cg, int r0, int hk) {
 #pragma unroll
   for (int st = 0; st < kWChunk / 16; ++st) {
-    bf16x8 wf[2], hf[2];
+    bf16x8 wf[2], hf[NT];
 #pragma unroll
     for (int j = 0; j < 2; ++j)
       wf[j] = *reinterpret_cast<const bf16x8*>(&Wc[(buf * 256 + 64 * cg + 32 * j + (lane & 31)) * kWRow + 16 * st + hk]);
 #pragma unroll
-    for (int r = 0; r < 2; ++r)
-      hf[r] = *reinterpret_cast<const bf16x8*>(&H[(64 * rg + 32 * r + (lane & 31)) * kActRow + c * kWChunk + 16 * st + hk]);
+    for (int r = 0; r < NT; ++r)
+      hf[r] = *reinterpret_cast<const bf16x8*>(&H[(r0 + 32 * r + (lane & 31)) * kActRow + c * kWChunk + 16 * st + hk]);
 #pragma unroll
-    for (int r = 0; r < 2; ++r)
+    for (int r = 0; r < NT; ++r)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) acc[r][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[j], hf[r], acc[r][j], 0, 0, 0);
+      for (int j = 0; j < 2; ++j) {
+        const f32x16 zero = {};
+        acc[r][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wf[j], hf[r], FIRST && st == 0 ? zero : acc[r][j], 0, 0, 0);
+      }
   }
 }
 
-// Bias (from LDS), ReLU, bf16: a hidden layer's outputs (registers) into H,
-// then zeroed accumulators for the next layer.  Register v of lane l:
-// column 64 cg + 32 j + 8 (v / 4) + 4 (l / 32) + v % 4 of row 64 rg + 32 r + l % 32.
-__device__ __forceinline__ void infer_epilogue(f32x16 (&acc)[2][2], const float* bias, uint16_t* H, int lane, int cg,
-                                               int rg) {
+// Bias (from LDS), ReLU, bf16: a hidden layer's outputs (registers) into H.
+// Register v of lane l: column 64 cg + 32 j + 8 (v / 4) + 4 (l / 32) + v % 4 of
+// row r0 + 32 r + l % 32.
+template <int NT>
+__device__ __forceinline__ void infer_epilogue(f32x16 (&acc)[NT][2], const float* bias, uint16_t* H, int lane, int cg,
+                                               int r0) {
 #pragma unroll
   for (int j = 0; j < 2; ++j) {
 #pragma unroll
@@ -833,8 +840,8 @@ __device__ __forceinline__ void infer_epilogue(f32x16 (&acc)[2][2], const float*
       const int n = 64 * cg + 32 * j + 8 * qq + 4 * (lane >> 5);
       const float4 bn = *reinterpret_cast<const float4*>(bias + n);
 #pragma unroll
-      for (int r = 0; r < 2; ++r) {
-        const int m = 64 * rg + 32 * r + (lane & 31);
+      for (int r = 0; r < NT; ++r) {
+        const int m = r0 + 32 * r + (lane & 31);
         const f32x2 lo = {fmaxf(acc[r][j][4 * qq + 0] + bn.x, 0.f), fmaxf(acc[r][j][4 * qq + 1] + bn.y, 0.f)};
         const f32x2 hi = {fmaxf(acc[r][j][4 * qq + 2] + bn.z, 0.f), fmaxf(acc[r][j][4 * qq + 3] + bn.w, 0.f)};
         *reinterpret_cast<uint2*>(&H[m * kActRow + n]) =
@@ -843,12 +850,6 @@ __device__ __forceinline__ void infer_epilogue(f32x16 (&acc)[2][2], const float*
       }
     }
   }
-#pragma unroll
-  for (int r = 0; r < 2; ++r)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[r][j][v] = 0.f;
 }
 
 // The weight pieces of one hidden layer held by this thread: rows n0 and
@@ -863,7 +864,7 @@ __device__ __forceinline__ void infer_epilogue(f32x16 (&acc)[2][2], const float*
   *reinterpret_cast<uint4*>(&Wc[((buf) * 256 + n0) * kWRow + kq]) = P##a##c;       \
   *reinterpret_cast<uint4*>(&Wc[((buf) * 256 + n0 + 128) * kWRow + kq]) = P##b##c;
 #define TT_W_STEP(P, c, next)                                \
-  infer_chunk(H, Wc, (c) & 1, c, acc, lane, cg, rg, hk);     \
+  infer_chunk<NT, (c) == 0>(H, Wc, (c) & 1, c, acc, lane, cg, r0, hk); \
   TT_W_STORE(P, ((c) + 1) & 1, next)                         \
   __syncthreads();
 #define TT_W_LAYER256(P)                                                                                  \
@@ -871,33 +872,83 @@ __device__ __forceinline__ void infer_epilogue(f32x16 (&acc)[2][2], const float*
   __syncthreads(); /* chunk 0, and the layer's inputs in H */                                             \
   TT_W_STEP(P, 0, 1) TT_W_STEP(P, 1, 2) TT_W_STEP(P, 2, 3) TT_W_STEP(P, 3, 4) TT_W_STEP(P, 4, 5)         \
   TT_W_STEP(P, 5, 6) TT_W_STEP(P, 6, 7)                                                                   \
-  infer_chunk(H, Wc, 1, 7, acc, lane, cg, rg, hk);                                                        \
+  infer_chunk<NT, false>(H, Wc, 1, 7, acc, lane, cg, r0, hk);                                             \
+  __syncthreads(); /* every wave is done with H and the chunk buffers */
+// the same while loading the next layer's pieces Q of W into the registers
+// that each stored chunk leaves
+#define TT_W_LAYER256_LOAD(P, Q, W)                                                     \
+  TT_W_STORE(P, 0, 0)                                                                   \
+  TT_W_LOAD(Q, W, 256, 0)                                                               \
+  __syncthreads(); /* chunk 0, and the layer's inputs in H */                           \
+  TT_W_STEP(P, 0, 1) TT_W_LOAD(Q, W, 256, 1) TT_W_STEP(P, 1, 2) TT_W_LOAD(Q, W, 256, 2) \
+  TT_W_STEP(P, 2, 3) TT_W_LOAD(Q, W, 256, 3) TT_W_STEP(P, 3, 4) TT_W_LOAD(Q, W, 256, 4) \
+  TT_W_STEP(P, 4, 5) TT_W_LOAD(Q, W, 256, 5) TT_W_STEP(P, 5, 6) TT_W_LOAD(Q, W, 256, 6) \
+  TT_W_STEP(P, 6, 7) TT_W_LOAD(Q, W, 256, 7)                                            \
+  infer_chunk<NT, false>(H, Wc, 1, 7, acc, lane, cg, r0, hk);                           \
   __syncthreads(); /* every wave is done with H and the chunk buffers */
 
-// One pass of the network over rows 0 .. rows - 1 (at most kInferRows) of
-// the block: row r is candidate cand[r] (gated and list modes) or base + r.
+// The hidden layers on a wave's NT tiles of 32 rows from row r0 on (NT may
+// differ between the block's waves; every wave meets the same barriers).
+// Starts with layer 1's inputs in H and its weights in chunk buffer 0, ends
+// with layer 3's outputs in H.
+template <int NT>
+__device__ __forceinline__ void infer_layers(const InferArgs& a, uint16_t* H, uint16_t* Wc, const float* Bs, int r0) {
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int cg = (tid >> 6) & 3, hk = 8 * (lane >> 5);
+  const int n0 = tid >> 2, kq = 8 * (tid & 3);
+  f32x16 acc[NT][2];
+  if constexpr (NT <= 2) {
+    TT_W_LOAD8(L2, a.w[1])  // layer 2's weights, in flight during layer 1
+    infer_chunk<NT, true>(H, Wc, 0, 0, acc, lane, cg, r0, hk);  // layer 1: 32 inputs, one chunk
+    __syncthreads();  // every wave is done with H and chunk buffer 0
+    infer_epilogue<NT>(acc, Bs, H, lane, cg, r0);
+    TT_W_LAYER256_LOAD(L2, L3, a.w[2])
+    infer_epilogue<NT>(acc, Bs + 256, H, lane, cg, r0);
+    TT_W_LAYER256(L3)
+  } else {
+    // three tiles leave no registers for weights ahead of the products
+    infer_chunk<NT, true>(H, Wc, 0, 0, acc, lane, cg, r0, hk);
+    TT_W_LOAD8(L2, a.w[1])
+    __syncthreads();
+    infer_epilogue<NT>(acc, Bs, H, lane, cg, r0);
+    TT_W_LAYER256(L2)
+    TT_W_LOAD8(L3, a.w[2])
+    infer_epilogue<NT>(acc, Bs + 256, H, lane, cg, r0);
+    TT_W_LAYER256(L3)
+  }
+  infer_epilogue<NT>(acc, Bs + 512, H, lane, cg, r0);
+  __syncthreads();  // the last hidden layer's outputs are in H
+}
+
+// One pass of the network over rows 0 .. rows - 1 (at most MOST) of the
+// block: row r is candidate cand[r] (gated and list modes) or base + r.
 // Ends with a barrier (the next pass overwrites H, the weight buffers and
 // the biases).
+template <int MOST>
 __device__ __forceinline__ void infer_pass(const InferArgs& a, uint16_t* H, uint16_t* Wc, uint16_t* W4s, float* Bs,
                                            const int32_t* cand, int base, int rows) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int cg = wave & 3, rg = wave >> 2;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = MOST == kInferRows ? tid >> 6 : __builtin_amdgcn_readfirstlane(tid >> 6);
   const int hk = 8 * (lane >> 5);  // k offset of this lane's 8 elements in a 16-k step
   const int n0 = tid >> 2, kq = 8 * (tid & 3);
-  // features (one 16-byte piece per thread; rows past the block's are
-  // zero), output-layer weights, biases and the first layer's weights: all
-  // loads issued at once
-  uint4 xv = make_uint4(0u, 0u, 0u, 0u), w4v = make_uint4(0u, 0u, 0u, 0u);
+  const int tiles = MOST == kInferRows ? 4 : (rows + 31) / 32;
+  // features (16-byte pieces; rows past the block's are zero), output-layer
+  // weights, biases and the first layer's weights: all loads issued at once
+  uint4 xv[2] = {make_uint4(0u, 0u, 0u, 0u), make_uint4(0u, 0u, 0u, 0u)}, w4v = make_uint4(0u, 0u, 0u, 0u);
+  const bool more = a.x && tid < 4 * (MOST - 128);
   if (a.x && (tid >> 2) < rows)
-    xv = *reinterpret_cast<const uint4*>(a.x + (int64_t)(base + (tid >> 2)) * 32 + 8 * (tid & 3));
+    xv[0] = *reinterpret_cast<const uint4*>(a.x + (int64_t)(base + (tid >> 2)) * 32 + 8 * (tid & 3));
+  if (more && 128 + (tid >> 2) < rows)
+    xv[1] = *reinterpret_cast<const uint4*>(a.x + (int64_t)(base + 128 + (tid >> 2)) * 32 + 8 * (tid & 3));
   if (tid < 384) w4v = *reinterpret_cast<const uint4*>(a.w[3] + (tid >> 5) * 256 + 8 * (tid & 31));
   float bv[4];
 #pragma unroll
   for (int l = 0; l < 4; ++l) bv[l] = (a.b[l] && tid < (l < 3 ? 256 : 12)) ? a.b[l][tid] : 0.f;
   TT_W_LOAD(L1, a.w[0], 32, 0)
   if (a.x) {
-    *reinterpret_cast<uint4*>(&H[(tid >> 2) * kActRow + 8 * (tid & 3)]) = xv;
-  } else if (tid < kInferRows) {  // one thread per row computes its features
+    *reinterpret_cast<uint4*>(&H[(tid >> 2) * kActRow + 8 * (tid & 3)]) = xv[0];
+    if (more) *reinterpret_cast<uint4*>(&H[(128 + (tid >> 2)) * kActRow + 8 * (tid & 3)]) = xv[1];
+  } else if (tid < MOST) {  // one thread per row computes its features
     uint32_t pk[16] = {};
     if (tid < rows) neuron_features(a.desc + (cand ? cand[tid] : base + tid), pk);
 #pragma unroll
@@ -912,24 +963,20 @@ __device__ __forceinline__ void infer_pass(const InferArgs& a, uint16_t* H, uint
   }
   TT_W_STORE(L1, 0, 0)
   __syncthreads();
-  f32x16 acc[2][2];
-#pragma unroll
-  for (int r = 0; r < 2; ++r)
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) acc[r][j][v] = 0.f;
-  infer_chunk(H, Wc, 0, 0, acc, lane, cg, rg, hk);  // layer 1: 32 inputs, one chunk
-  TT_W_LOAD8(L2, a.w[1])  // layer 2's weights, in flight during layer 1's epilogue
-  __syncthreads();        // every wave is done with H and chunk buffer 0
-  infer_epilogue(acc, Bs, H, lane, cg, rg);
-  TT_W_LAYER256(L2)
-  TT_W_LOAD8(L3, a.w[2])
-  infer_epilogue(acc, Bs + 256, H, lane, cg, rg);
-  TT_W_LAYER256(L3)
-  infer_epilogue(acc, Bs + 512, H, lane, cg, rg);
-  __syncthreads();  // the last hidden layer's outputs are in H
-  if (wave < 4) {
+  if constexpr (MOST == kInferRows) {
+    infer_layers<2>(a, H, Wc, Bs, 64 * (wave >> 2));
+  } else {
+    // waves w and w + 4 share a SIMD, so an odd tile costs it one tile, not two
+    // (a single tile is computed by both halves, with the same values)
+    const int tiles0 = (tiles + 1) / 2, mine = wave < 4 ? tiles0 : max(tiles - tiles0, 1);
+    const int r0 = wave < 4 ? 0 : 32 * (tiles - mine);
+    switch (mine) {
+      case 1: infer_layers<1>(a, H, Wc, Bs, r0); break;
+      case 2: infer_layers<2>(a, H, Wc, Bs, r0); break;
+      default: infer_layers<3>(a, H, Wc, Bs, r0); break;
+    }
+  }
+  if (wave < tiles) {
     const int mb = 32 * wave;
     const int wr = lane & 31;  // weight row = output column; rows 12.. are zero
     f32x16 o;
@@ -955,14 +1002,25 @@ __device__ __forceinline__ void infer_pass(const InferArgs& a, uint16_t* H, uint
   __syncthreads();  // the next pass overwrites H, the weight buffers and the biases
 }
 
+// Blocks of kInferRows rows (or of candidates), or, SHARED, the tiles of 32
+// rows shared out over the blocks, at most five each.
+template <bool SHARED>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(1, 2))) void mlp_infer_kernel(InferArgs a) {
+  constexpr int kMost = SHARED ? kInferMostRows : kInferRows;
   extern __shared__ uint16_t lds[];
   __shared__ int32_t s_list[2 * kInferRows];  // gated: this block's candidates
   __shared__ int32_t s_wcnt[4];
-  uint16_t* H = lds;                                            // [128][kActRow]
-  uint16_t* Wc = lds + kInferRows * kActRow;                    // [2][256][kWRow]
+  uint16_t* H = lds;                                            // [kMost][kActRow]
+  uint16_t* Wc = lds + kMost * kActRow;                         // [2][256][kWRow]
   uint16_t* W4s = Wc + 2 * 256 * kWRow;                         // [12][kActRow]: output-layer weights
   float* Bs = reinterpret_cast<float*>(W4s + 12 * kActRow);     // [4][256]: biases (zero where NULL)
+  if constexpr (SHARED) {
+    const long tiles = ((long)a.n + 31) / 32;
+    const int first = (int)(32 * (blockIdx.x * tiles / gridDim.x));
+    const int end = (int)min(32 * ((blockIdx.x + 1) * tiles / gridDim.x), (long)a.n);
+    infer_pass<kMost>(a, H, Wc, W4s, Bs, nullptr, first, end - first);
+    return;
+  }
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   if (a.list) {
     // list mode: the spans' counts to prefix sums (at most 8 spans per
@@ -1014,7 +1072,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(1, 2))) voi
         s_list[tid] = a.list[(size_t)lo * kGateSpan + (g - s_pre[lo])];
       }
       __syncthreads();
-      infer_pass(a, H, Wc, W4s, Bs, s_list, 0, rows);
+      infer_pass<kMost>(a, H, Wc, W4s, Bs, s_list, 0, rows);
     }
     return;
   }
@@ -1038,25 +1096,35 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(1, 2))) voi
   }
   if (cnt <= 0) return;  // block-uniform
   for (int p = 0; p < cnt; p += kInferRows)
-    infer_pass(a, H, Wc, W4s, Bs, a.gated ? s_list + p : nullptr, base + p, min(kInferRows, cnt - p));
+    infer_pass<kMost>(a, H, Wc, W4s, Bs, a.gated ? s_list + p : nullptr, base + p, min(kInferRows, cnt - p));
 }
 
+#undef TT_W_LAYER256_LOAD
 #undef TT_W_LAYER256
 #undef TT_W_STEP
 #undef TT_W_STORE
 #undef TT_W_LOAD8
 #undef TT_W_LOAD
 
+size_t infer_lds(int rows) {
+  return sizeof(uint16_t) * ((size_t)rows * kActRow + 2 * 256 * kWRow + 12 * kActRow) + sizeof(float) * 4 * 256;
+}
+
+// more than 64 KiB of dynamic LDS: allowed per launch (cheap host call, no
+// per-process state to keep consistent across devices or threads)
+template <bool SHARED>
+hipError_t launch_infer(const InferArgs& a, long blocks, hipStream_t s) {
+  const size_t lds = infer_lds(SHARED ? kInferMostRows : kInferRows);
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&mlp_infer_kernel<SHARED>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(mlp_infer_kernel<SHARED>, dim3((unsigned)blocks), dim3(512), lds, s, a);
+  return hipGetLastError();
+}
+
 hipError_t mlp_infer(const uint16_t* x, int n, const uint16_t* const* w, const float* const* b, float* logits,
                      hipStream_t s, const tt_neuron* desc, int gated) {
   if (n <= 0) return hipSuccess;
-  const size_t lds =
-      sizeof(uint16_t) * ((size_t)kInferRows * kActRow + 2 * 256 * kWRow + 12 * kActRow) + sizeof(float) * 4 * 256;
-  // more than 64 KiB of dynamic LDS: allowed per launch (cheap host call, no
-  // per-process state to keep consistent across devices or threads)
-  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&mlp_infer_kernel),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  if (e != hipSuccess) return e;
   InferArgs a{};
   a.x = x;
   a.n = n;
@@ -1067,9 +1135,20 @@ hipError_t mlp_infer(const uint16_t* x, int n, const uint16_t* const* w, const f
   a.logits = logits;
   a.desc = desc;
   a.gated = desc && gated ? 1 : 0;
-  const int per_block = a.gated ? 2 * kInferRows : kInferRows;
-  hipLaunchKernelGGL(mlp_infer_kernel, dim3((unsigned)((n + per_block - 1) / per_block)), dim3(512), lds, s, a);
-  return hipGetLastError();
+  if (a.gated) return launch_infer<false>(a, ((long)n + 2 * kInferRows - 1) / (2 * kInferRows), s);
+  // One block fits a compute unit.  Blocks of up to five tiles where they
+  // save a round (99 999 rows as 782 blocks of four took a fourth round for
+  // 14 of them: 45.6 us; as 768 of four or five: 37.5), and where they have
+  // three or fewer (20 000 rows: 12.3 and 11.4 us, 41 000: 23.4 and 21.3);
+  // else four (60 000 rows: 23.8 us, 24.2 in the other kernel).
+  int dev = 0, cus = 0;
+  hipError_t e = hipGetDevice(&dev);
+  if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+  if (e != hipSuccess) return e;
+  const long tiles = ((long)n + 31) / 32;
+  const long rounds4 = (tiles + 4 * cus - 1) / (4 * cus), rounds5 = (tiles + 5 * cus - 1) / (5 * cus);
+  if (rounds5 < rounds4 || tiles <= 3 * rounds5 * cus) return launch_infer<true>(a, std::min(tiles, rounds5 * cus), s);
+  return launch_infer<false>(a, (tiles + 3) / 4, s);
 }
 
 // The wave pass's candidates, compacted span by span: block b scans
@@ -1102,11 +1181,6 @@ hipError_t mlp_infer_gated_list(const tt_neuron* desc, int n, const uint16_t* co
   int32_t* list = work;
   int32_t* cnt = work + (size_t)nspans * kGateSpan;
   hipLaunchKernelGGL(infer_gate_list_kernel, dim3((unsigned)nspans), dim3(kGateSpan), 0, s, desc, n, list, cnt);
-  const size_t lds =
-      sizeof(uint16_t) * ((size_t)kInferRows * kActRow + 2 * 256 * kWRow + 12 * kActRow) + sizeof(float) * 4 * 256;
-  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&mlp_infer_kernel),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-  if (e != hipSuccess) return e;
   InferArgs a{};
   a.n = n;
   for (int l = 0; l < 4; ++l) {
@@ -1120,8 +1194,7 @@ hipError_t mlp_infer_gated_list(const tt_neuron* desc, int n, const uint16_t* co
   a.cnt = cnt;
   a.nspans = nspans;
   const int grid = (int)std::min<long>(blocks, ((long)n + kInferRows - 1) / kInferRows);
-  hipLaunchKernelGGL(mlp_infer_kernel, dim3((unsigned)grid), dim3(512), lds, s, a);
-  return hipGetLastError();
+  return launch_infer<false>(a, grid, s);
 }
 
 // ------------------------------------------------------------ training step

@@ -281,6 +281,22 @@ def test_training_learns_support():
     assert acc["bit_accuracy"] > 0.95, acc
 
 
+@pytest.mark.parametrize("tiles,rows", [(1, -31), (1, 0), (2, -1), (3, -17), (4, 0), (5, -1)])
+def test_inference_tiles_per_block(tiles, rows):
+    """Rows for every number of 32-row tiles that a block of tt_mlp_infer can
+    take (one round of blocks, and one row more than whole rounds): bit for
+    bit the logits of the same rows in calls of 128."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    net = tt.screen.ScreenNet(mlp_init(37, mlp_ref.DIMS), max_batch=64)
+    X = bf16_bits(rnd((32 * tiles * cus + 1, 32), 38))
+    for n in (32 * tiles * cus + rows, 32 * tiles * cus + 1, 32 * tiles + rows):
+        note(f"inference n={n}")
+        got = net.infer(X, n).clone()
+        want = torch.cat([net.infer(X[k: min(k + 128, n)].contiguous(), min(128, n - k)).clone()
+                          for k in range(0, n, 128)])
+        assert torch.equal(got, want)
+
+
 def test_screen_infer_from_descriptors_matches_feature_path():
     """tt_screen_infer (features computed in the inference kernel) gives the
     logits of tt_screen_features + tt_mlp_infer bit for bit; gated, it writes
