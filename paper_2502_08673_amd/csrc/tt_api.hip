@@ -3,6 +3,7 @@
 // autotuner and the one-shot entry points declared in include/tt.h.
 #include <algorithm>
 #include <chrono>
+#include <climits>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -759,12 +760,19 @@ struct tt_lutnet {
 
 namespace {
 
+// The packed form's blocks take eight times the samples, so it pays once the
+// other one has three blocks of 64 samples for each compute unit: 448 neurons,
+// F = 6, b = 2: 48000 samples 28.5 against 27.3 us, 64000 40.7 against 28.1,
+// 16000 15.3 against 25.3; F = 4, b = 1, 480 neurons: 48000 26.3 against 30.7,
+// 250000 141 against 86.
+int pack_min_batch(int cus) { return 192 * cus; }
+
 // Validate a network, group it by level and build its workspace (records,
 // interleaved tables and input masks for the single-launch form; descriptors,
-// fan-in and level order for the per-level form).  check_only: stop after
-// the argument checks.
+// fan-in and level order for the per-level form) for batches of up to
+// most_batch samples (0: stop after the argument checks).
 int lutnet_setup(const tt_neuron* h_desc, int n, const int32_t* h_fanin, int n_inputs, const uint64_t* d_tables,
-                 uint64_t total_words, hipStream_t s, bool async_ws, tt_lutnet* L, bool check_only = false) {
+                 uint64_t total_words, hipStream_t s, bool async_ws, tt_lutnet* L, int most_batch = INT_MAX) {
   TT_TRY(validate_all(h_desc, n));
   if (n_inputs < 0 || (n > 0 && !h_fanin)) return TT_EINVAL;
   // fan-in: signals below n_inputs + i (topological order); levels from it
@@ -783,7 +791,7 @@ int lutnet_setup(const tt_neuron* h_desc, int n, const int32_t* h_fanin, int n_i
   L->n = n;
   L->n_inputs = n_inputs;
   L->depth = depth;
-  if (n == 0 || check_only) return TT_OK;
+  if (n == 0 || most_batch == 0) return TT_OK;
   if (!d_tables) return TT_EINVAL;
   TT_TRY(validate_ranges(h_desc, n, total_words));
   TT_TRY(device_info(&L->cus));
@@ -830,7 +838,8 @@ int lutnet_setup(const tt_neuron* h_desc, int n, const int32_t* h_fanin, int n_i
       one_b = one_b && h_desc[i].b == h_desc[0].b;
     }
     // the packed form: tables of at most 1 KiB, digits of one width
-    if (one_b && 4 * largest <= tt::kPackTable && tt::net_pack_lds(n_inputs + n) <= tt::kPackMaxLds) {
+    if (most_batch >= pack_min_batch(L->cus) && one_b && 4 * largest <= tt::kPackTable &&
+        tt::net_pack_lds(n_inputs + n) <= tt::kPackMaxLds) {
       for (int lv = 0; lv < depth; ++lv) rounds += pack_rounds(L->level_begin[lv + 1] - L->level_begin[lv]);
       rounds = (rounds + tt::kPackRounds - 1) / tt::kPackRounds * tt::kPackRounds;
     }
@@ -948,12 +957,7 @@ int lutnet_enqueue(const tt_lutnet& L, const uint8_t* d_inputs, int batch, uint8
     na.inputs = d_inputs;
     na.out = d_out;
     na.sample = 0;
-    // The packed form's blocks take eight times the samples, so it pays once
-    // the other one has three blocks of 64 samples for each compute unit: 448
-    // neurons, F = 6, b = 2: 48000 samples 28.5 against 27.3 us, 64000 40.7
-    // against 28.1, 16000 15.3 against 25.3; F = 4, b = 1, 480 neurons: 48000
-    // 26.3 against 30.7, 250000 141 against 86.
-    if (na.slots && batch >= 192 * L.cus)
+    if (na.slots && batch >= pack_min_batch(L.cus))
       TT_HIP(tt::launch_lutnet_packed(na, s));
     else
       TT_HIP(tt::launch_lutnet_fused(na, tt::NetSample{}, s));
@@ -1395,7 +1399,7 @@ int tt_lutnet_eval(const tt_neuron* h_desc, int n, const int32_t* h_fanin, int n
   hipStream_t s = (hipStream_t)stream;
   tt_lutnet L;
   // with nothing to evaluate only the arguments are checked
-  int st = lutnet_setup(h_desc, n, h_fanin, n_inputs, d_tables, total_words, s, true, &L, batch == 0);
+  int st = lutnet_setup(h_desc, n, h_fanin, n_inputs, d_tables, total_words, s, true, &L, batch);
   if (st == TT_OK && n > 0 && batch > 0) st = lutnet_enqueue(L, d_inputs, batch, d_out, s);
   const int st2 = lutnet_release(&L, s);
   return st != TT_OK ? st : st2;
