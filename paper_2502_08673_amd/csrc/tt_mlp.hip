@@ -897,7 +897,7 @@ __device__ __forceinline__ void infer_layers(const InferArgs& a, uint16_t* H, ui
   const int cg = (tid >> 6) & 3, hk = 8 * (lane >> 5);
   const int n0 = tid >> 2, kq = 8 * (tid & 3);
   f32x16 acc[NT][2];
-  if constexpr (NT <= 2) {
+  if constexpr (NT == 2) {
     TT_W_LOAD8(L2, a.w[1])  // layer 2's weights, in flight during layer 1
     infer_chunk<NT, true>(H, Wc, 0, 0, acc, lane, cg, r0, hk);  // layer 1: 32 inputs, one chunk
     __syncthreads();  // every wave is done with H and chunk buffer 0
@@ -966,15 +966,11 @@ __device__ __forceinline__ void infer_pass(const InferArgs& a, uint16_t* H, uint
   if constexpr (MOST == kInferRows) {
     infer_layers<2>(a, H, Wc, Bs, 64 * (wave >> 2));
   } else {
-    // waves w and w + 4 share a SIMD, so an odd tile costs it one tile, not two
-    // (a single tile is computed by both halves, with the same values)
-    const int tiles0 = (tiles + 1) / 2, mine = wave < 4 ? tiles0 : max(tiles - tiles0, 1);
-    const int r0 = wave < 4 ? 0 : 32 * (tiles - mine);
-    switch (mine) {
-      case 1: infer_layers<1>(a, H, Wc, Bs, r0); break;
-      case 2: infer_layers<2>(a, H, Wc, Bs, r0); break;
-      default: infer_layers<3>(a, H, Wc, Bs, r0); break;
-    }
+    // waves w and w + 4 share a SIMD, so a fifth tile costs it one tile, not two
+    if (wave < 4 && tiles > 4)
+      infer_layers<3>(a, H, Wc, Bs, 0);
+    else
+      infer_layers<2>(a, H, Wc, Bs, wave < 4 ? 0 : 32 * (tiles - 2));
   }
   if (wave < tiles) {
     const int mb = 32 * wave;
@@ -1003,7 +999,7 @@ __device__ __forceinline__ void infer_pass(const InferArgs& a, uint16_t* H, uint
 }
 
 // Blocks of kInferRows rows (or of candidates), or, SHARED, the tiles of 32
-// rows shared out over the blocks, at most five each.
+// rows shared out over the blocks, four or five each.
 template <bool SHARED>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(1, 2))) void mlp_infer_kernel(InferArgs a) {
   constexpr int kMost = SHARED ? kInferMostRows : kInferRows;
@@ -1136,18 +1132,18 @@ hipError_t mlp_infer(const uint16_t* x, int n, const uint16_t* const* w, const f
   a.desc = desc;
   a.gated = desc && gated ? 1 : 0;
   if (a.gated) return launch_infer<false>(a, ((long)n + 2 * kInferRows - 1) / (2 * kInferRows), s);
-  // One block fits a compute unit.  Blocks of up to five tiles where they
-  // save a round (99 999 rows as 782 blocks of four took a fourth round for
-  // 14 of them: 45.6 us; as 768 of four or five: 37.5), and where they have
-  // three or fewer (20 000 rows: 12.3 and 11.4 us, 41 000: 23.4 and 21.3);
-  // else four (60 000 rows: 23.8 us, 24.2 in the other kernel).
+  // One block fits a compute unit.  Blocks of four and five tiles where they
+  // save a round of at least three (99 999 rows as 782 blocks of four took a
+  // fourth round for 14 of them: 45.6 us; as 768 of four or five: 37.5); a
+  // single round (33 000 rows: 23.0 and 13.4) gains less than the larger code
+  // costs when it is cold (67 and 114 us).
   int dev = 0, cus = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (e != hipSuccess) return e;
   const long tiles = ((long)n + 31) / 32;
   const long rounds4 = (tiles + 4 * cus - 1) / (4 * cus), rounds5 = (tiles + 5 * cus - 1) / (5 * cus);
-  if (rounds5 < rounds4 || tiles <= 3 * rounds5 * cus) return launch_infer<true>(a, std::min(tiles, rounds5 * cus), s);
+  if (rounds5 < rounds4 && rounds5 > 1) return launch_infer<true>(a, rounds5 * cus, s);
   return launch_infer<false>(a, (tiles + 3) / 4, s);
 }
 

@@ -281,11 +281,12 @@ def test_training_learns_support():
     assert acc["bit_accuracy"] > 0.95, acc
 
 
-@pytest.mark.parametrize("tiles,rows", [(1, -31), (1, 0), (2, -1), (3, -17), (4, 0), (5, -1)])
+@pytest.mark.parametrize("tiles,rows", [(1, -31), (4, 0), (5, -1), (8, 1), (9, -17), (10, 0)])
 def test_inference_tiles_per_block(tiles, rows):
-    """Rows for every number of 32-row tiles that a block of tt_mlp_infer can
-    take (one round of blocks, and one row more than whole rounds): bit for
-    bit the logits of the same rows in calls of 128."""
+    """Row counts at which tt_mlp_infer shares 32-row tiles out over whole
+    rounds of blocks (more than eight and up to ten tiles per compute unit),
+    just beside them, and below: bit for bit the logits of the same rows in
+    calls of 128."""
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     net = tt.screen.ScreenNet(mlp_init(37, mlp_ref.DIMS), max_batch=64)
     X = bf16_bits(rnd((32 * tiles * cus + 1, 32), 38))
