@@ -647,7 +647,7 @@ int tt_adam_step_multi(int count, float* const* h_d_p, const float* const* h_d_g
  * weights and biases, their gradients and Adam moments, the hidden layers'
  * activations and gradients act, dh ([batch][256] bf16), logits z and dL/dz
  * dz ([batch][12]), the loss, and scratch of tt_mlp_train_scratch_floats(
- * batch) floats. */
+ * largest batch) floats. */
 typedef struct tt_mlp_train_state {
   uint16_t* w[4];
   float *pw[4], *pb[4], *gw[4], *gb[4], *mw[4], *mb[4], *vw[4], *vb[4];
@@ -659,7 +659,8 @@ typedef struct tt_mlp_train_state {
   size_t scratch_floats;
 } tt_mlp_train_state;
 
-/* Scratch floats of tt_mlp_train_step (0 when batch is not positive). */
+/* Scratch floats that serve tt_mlp_train_step on every batch up to `batch`
+ * (0 when batch is not positive). */
 size_t tt_mlp_train_scratch_floats(int batch);
 
 /* One training step on a batch (x[batch][32] bf16, targets y, m, h as

@@ -2311,7 +2311,7 @@ int tt_adam_step(float* d_p, const float* d_g, float* d_m, float* d_v, uint16_t*
   return TT_OK;
 }
 
-size_t tt_mlp_train_scratch_floats(int batch) { return tt::train_scratch_floats(batch); }
+size_t tt_mlp_train_scratch_floats(int batch) { return tt::train_scratch_floats(batch, true); }
 
 int tt_mlp_train_step(const tt_mlp_train_state* st, const uint16_t* d_x, const float* d_y, const float* d_m,
                       const float* d_h, int batch, float lr, float beta1, float beta2, float eps, int step,
@@ -2350,7 +2350,7 @@ int tt_mlp_train_step(const tt_mlp_train_state* st, const uint16_t* d_x, const f
   float* scratch = nullptr;
   take(scratch, st->scratch);
   if (!ok) return TT_EINVAL;
-  if (st->scratch_floats < tt::train_scratch_floats(batch)) return TT_ERANGE;
+  if (st->scratch_floats < tt::train_scratch_floats(batch, false)) return TT_ERANGE;
   a.batch = batch;
   const float bc1 = 1.0f - (float)std::pow((double)beta1, (double)step);
   const float bc2 = 1.0f - (float)std::pow((double)beta2, (double)step);

@@ -57,7 +57,8 @@ struct TrainArgs {
   int slices[4], kslice[4];
   float *part[4], *dbp[4];
 };
-size_t train_scratch_floats(int batch);
+// scratch of a step on `batch` rows; most: of one on any batch up to it
+size_t train_scratch_floats(int batch, bool most);
 hipError_t train_step(TrainArgs a, float* scratch, float lr, float b1, float b2, float eps, float bc1, float bc2,
                       hipStream_t s);
 

@@ -578,13 +578,19 @@ __global__ void dw_reduce_kernel(const float* part, const float* dbp, int S, int
 struct DwSplit {
   int S, kslice;
 };
-static DwSplit dw_split(int Bn, int M, int N) {
+// the most slices that a batch of up to Bn rows is split into
+static int dw_most_slices(int Bn, int M, int N) {
   const int tiles = ((M + 63) / 64) * ((N + 63) / 64);
   const int chunks = (Bn + kDwKC - 1) / kDwKC;
-  int S = std::max(1, std::min(chunks, std::min(kDwMaxSlices, (512 + tiles - 1) / tiles)));
+  return std::max(1, std::min(chunks, std::min(kDwMaxSlices, (512 + tiles - 1) / tiles)));
+}
+// whole chunks a slice: a larger batch may take fewer slices (2048 rows of a
+// 256 x 256 layer 32, 2112 rows 17)
+static DwSplit dw_split(int Bn, int M, int N) {
+  const int chunks = (Bn + kDwKC - 1) / kDwKC;
+  const int S = dw_most_slices(Bn, M, N);
   const int per = (chunks + S - 1) / S;
-  S = (chunks + per - 1) / per;
-  return {S, per * kDwKC};
+  return {(chunks + per - 1) / per, per * kDwKC};
 }
 
 // Loss and dL/dz for logits z [B, 12] (row stride 12).
@@ -1600,8 +1606,9 @@ __global__ __launch_bounds__(256) void train_update_kernel(TrainArgs a, float lr
   if (t < 4) a.wb[t][j] = f32_to_bf16(pi);
 }
 
-// Places of the partial sums and of dL/dz in the scratch; returns its floats.
-static size_t train_layout(TrainArgs& a, float* scratch) {
+// Places of the partial sums and of dL/dz in the scratch; returns its floats
+// (`most`: room for every batch up to a.batch).
+static size_t train_layout(TrainArgs& a, float* scratch, bool most = false) {
   size_t o = 0;
   auto take = [&](size_t floats) {
     float* at = scratch + o;
@@ -1612,21 +1619,22 @@ static size_t train_layout(TrainArgs& a, float* scratch) {
   for (int l = 0; l < 4; ++l) {
     const int M = l == 3 ? 12 : 256, N = l == 0 ? 32 : 256;
     const DwSplit sp = dw_split(a.batch, M, N);
+    const size_t S = most ? dw_most_slices(a.batch, M, N) : sp.S;
     a.slices[l] = sp.S;
     a.kslice[l] = sp.kslice;
-    a.part[l] = take((size_t)sp.S * M * N);
-    a.dbp[l] = take((size_t)sp.S * M);
+    a.part[l] = take(S * M * N);
+    a.dbp[l] = take(S * M);
   }
   a.loss_part = take(a.row_blocks);
   a.dzp = reinterpret_cast<uint16_t*>(take((size_t)a.batch * 8));
   return o;
 }
 
-size_t train_scratch_floats(int batch) {
+size_t train_scratch_floats(int batch, bool most) {
   if (batch <= 0) return 0;
   TrainArgs a{};
   a.batch = batch;
-  return train_layout(a, nullptr);
+  return train_layout(a, nullptr, most);
 }
 
 hipError_t train_step(TrainArgs a, float* scratch, float lr, float b1, float b2, float eps, float bc1, float bc2,

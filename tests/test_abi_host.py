@@ -295,3 +295,12 @@ def test_gd_and_sop_argument_checks():
                              ctypes.byref(ex)) == tt.TT_OK and nt.value == 0
     buf = ctypes.create_string_buffer(64)
     assert L.tt_kmap_text(plane.ctypes.data, buf, 64) == tt.TT_EINVAL
+
+
+def test_training_scratch_serves_every_smaller_batch():
+    """A step needs more scratch on 2048 rows (32 slices of a 256 x 256
+    layer) than on 2112 (17): the size asked for must cover every batch up to
+    the one it is asked for."""
+    sizes = [tt.mlp_train_scratch_floats(b) for b in range(0, 9001)]
+    assert sizes[0] == 0 and sizes[1] > 0
+    assert all(a <= b for a, b in zip(sizes, sizes[1:]))

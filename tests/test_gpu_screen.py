@@ -496,3 +496,37 @@ def test_train_step_arguments_and_unaligned_batches():
         tt.mlp_train_step(net.state, X.clone(), y, m, h, B, 1e-3, 0.9, 0.999, 1e-8, 1)
     assert e.value.status == tt.TT_ERANGE
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("most", [2112, 5000])
+def test_train_steps_below_the_largest_batch(most):
+    """One net's scratch serves every batch up to max_batch, those that split
+    into more slices than max_batch does among them.  Two steps per batch
+    size, bit for bit the layer calls' gradients, weights and moments (the
+    products and the partial sums are the same ones in the same order); the
+    loss, whose terms are added in other groups, within the bound of two
+    orders of one sum."""
+    sc = tt.screen
+    params = mlp_init(20250212 + most)
+    one, ref = sc.ScreenNet(params, max_batch=most), sc.ScreenNet(params, max_batch=most)
+    rng = np.random.default_rng(most)
+    for B in [b for b in (1, 2048, 4096, most) if b <= most]:
+        X = torch.from_numpy(rng.normal(0, 0.7, size=(B, 32)).astype(np.float32)).cuda().to(torch.bfloat16)
+        X = X.view(torch.int16)
+        y = torch.from_numpy((rng.random((B, 8)) < 0.6).astype(np.float32)).cuda()
+        m = torch.from_numpy((rng.random((B, 8)) < 0.8).astype(np.float32)).cuda()
+        h = torch.from_numpy(rng.random((B, 4)).astype(np.float32)).cuda()
+        note(f"train step max_batch={most} B={B}")
+        for _ in range(2):
+            one.train_step(X, y, m, h, B, 2e-3)
+            ref.forward(X, B)
+            tt.mlp_loss(ref.z, B, y, m, h, ref.dz, ref.loss, ref.scratch)
+            ref.backward(X, B)
+            ref.steps += 1
+            ref.adam.step(2e-3, 0.9, 0.999, 1e-8, ref.steps)
+            torch.cuda.synchronize()
+            for name in ("gW", "gb", "W32", "b32", "Wb", "mW", "mb", "vW", "vb"):
+                for l, (a, b) in enumerate(zip(getattr(one, name), getattr(ref, name))):
+                    assert torch.equal(a, b), (B, name, l)
+            bound = 2 * (12 * B + 64) * 2.0 ** -24 * abs(float(ref.loss)) + 1e-6
+            assert abs(float(one.loss) - float(ref.loss)) <= bound
