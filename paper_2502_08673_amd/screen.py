@@ -8,6 +8,7 @@ PyTorch supplies device memory, the batch shuffle and the stream.
 from __future__ import annotations
 
 import math
+import struct
 import time
 from dataclasses import dataclass
 
@@ -77,14 +78,16 @@ class ScreenNet:
         # one Adam launch for all eight parameter tensors
         self.adam = AdamGroup(self.W32 + self.b32, self.gW + self.gb, self.mW + self.mb, self.vW + self.vb,
                               self.Wb + [None] * 4)
-        # the same buffers for the step in one call
-        self.state = TTMlpTrainState(scratch_floats=self.scratch.numel(), z=self.z.data_ptr(), dz=self.dz.data_ptr(),
-                                     loss=self.loss.data_ptr(), scratch=self.scratch.data_ptr())
-        for name, ts in (("w", self.Wb), ("pw", self.W32), ("pb", self.b32), ("gw", self.gW), ("gb", self.gb),
-                         ("mw", self.mW), ("mb", self.mb), ("vw", self.vW), ("vb", self.vb), ("act", self.acts),
-                         ("dh", self.dh)):
-            for l, t in enumerate(ts):
-                getattr(self.state, name)[l] = t.data_ptr()
+        self.state = TTMlpTrainState()
+        self._point_state()
+
+    def _point_state(self):
+        """The state of the step in one call: the buffers that the net holds
+        now (a program may have put others in their place)."""
+        ts = (*self.Wb, *self.W32, *self.b32, *self.gW, *self.gb, *self.mW, *self.mb, *self.vW, *self.vb, *self.acts,
+              *self.dh, self.z, self.dz, self.loss, self.scratch)  # in the order of tt_mlp_train_state
+        struct.pack_into("=%dQ" % len(ts), self.state, 0, *[t.data_ptr() for t in ts])
+        self.state.scratch_floats = self.scratch.numel()
 
     def forward(self, X, B: int):
         """Logits [B, 12] (fp32) for bf16 features X [B, 32]."""
@@ -133,6 +136,7 @@ class ScreenNet:
 
     def train_step(self, X, y, m, h, B: int, lr: float, beta1=0.9, beta2=0.999, eps=1e-8):
         if 0 < B <= self.max_batch and not any(t.data_ptr() % 16 for t in (X, y, m, h)):
+            self._point_state()
             mlp_train_step(self.state, X, y, m, h, B, lr, beta1, beta2, eps, self.steps + 1)
             self.steps += 1
             return self.loss
