@@ -418,6 +418,15 @@ struct StageSlot {
 std::mutex g_stage_mu;
 std::map<int, std::vector<StageSlot*>> g_stage;
 
+// While it lives, the thread's calls are no part of a capture that is open on
+// some other stream: asking for an event or allocating host memory would end
+// that capture with an error.
+struct OutsideCapture {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  OutsideCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  ~OutsideCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
 // A buffer of `bytes` for a call on `s`; *slot is NULL when the pageable path
 // has to be taken.
 int stage_acquire(size_t bytes, hipStream_t s, StageSlot** slot) {
@@ -431,6 +440,7 @@ int stage_acquire(size_t bytes, hipStream_t s, StageSlot** slot) {
   if (cs != hipStreamCaptureStatusNone) return TT_OK;
   int dev = 0;
   TT_HIP(hipGetDevice(&dev));
+  const OutsideCapture outside;
   StageSlot* got = nullptr;
   {
     std::lock_guard<std::mutex> lk(g_stage_mu);

@@ -637,3 +637,33 @@ def test_weight_minus_128_largest_mask_tables():
     check_canary(tables, total)
     assert int(status.item()) == 0
     assert np.array_equal(host_u64(tables, 0, total), sref["planes"])
+
+
+def test_one_shot_calls_while_another_stream_captures():
+    """A graph is recorded on one stream while one-shot calls (their first,
+    which allocate the staging buffers, and later ones, which ask for its
+    events) run on another: the graph is whole, and so are the results."""
+    ns = random_neurons(seed=77, n=40, max_fb=14)
+    desc = tt.descriptors(ns)
+    total = tt.layout(desc)
+    ref = oracle.enumerate(ns)
+    tables = device_tables(total)
+    sup = torch.zeros(len(ns), dtype=torch.uint8, device="cuda")
+    x = torch.arange(1000, device="cuda")
+    side = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    note("one-shot calls beside a capture")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        y = x + 1
+        for _ in range(3):
+            tt.enumerate(desc, tables, total_words=total, stream=side)
+            tt.support(desc, tables, support_out=sup, stream=side)
+    torch.cuda.synchronize()
+    assert np.array_equal(host_u64(tables, 0, total), ref["planes"])
+    assert np.array_equal(sup.cpu().numpy(), ref["support"])
+    for k in range(3):
+        x.fill_(k)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert (y == k + 1).all()

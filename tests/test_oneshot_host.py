@@ -1,0 +1,94 @@
+"""The host side of the one-shot calls without a GPU: how they stage their
+descriptors on streams that are busy, capturing or of another device.  Each
+case runs in a process of its own on tests/fake_hip.cpp, whose runtime calls
+take the place of the real ones."""
+import ctypes
+import os
+import subprocess
+import sys
+
+import numpy as np
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+A, B, C = 0x10, 0x20, 0x30  # streams
+
+
+class Calls:
+    """One-shot calls on n small neurons; tables and codes are never read."""
+
+    def __init__(self, tt, fake):
+        self.tt, self.L, self.fake = tt, tt.lib(), fake
+
+    def desc(self, n):
+        d = np.zeros(n, self.tt.NEURON_DTYPE)
+        d["F"], d["b"], d["o"], d["w"][:, :2] = 2, 1, 1, 1
+        return d, self.tt.layout(d)
+
+    def enumerate(self, stream, n=16):
+        d, total = self.desc(n)
+        t = np.zeros(total, np.uint64)
+        assert self.L.tt_enumerate(d.ctypes.data, n, t.ctypes.data, total, None, stream) == 0
+
+    def pack(self, stream, n=16):
+        d, total = self.desc(n)
+        t = np.zeros(total, np.uint64)
+        assert self.L.tt_pack(d.ctypes.data, n, t.ctypes.data, 4 * n, t.ctypes.data, total, stream) == 0
+
+    def support(self, stream, n=16):
+        d, total = self.desc(n)
+        t = np.zeros(total, np.uint64)
+        assert self.L.tt_support(d.ctypes.data, n, t.ctypes.data, total, t.ctypes.data, None, stream) == 0
+
+    def noalloc(self, stream, n=16):
+        d, total = self.desc(n)
+        t = np.zeros(total, np.uint64)
+        assert self.L.tt_enumerate_noalloc(d.ctypes.data, n, t.ctypes.data, total, None, stream) == 0
+
+    def all(self, stream, n=16):
+        for call in (self.enumerate, self.pack, self.support):
+            call(stream, n)
+
+
+def calls_while_another_stream_captures(c, fake):
+    """A program records a graph on one stream and makes a call on another:
+    the capture goes on, and the call is staged as ever."""
+    c.all(A)
+    fake.fake_capture(C)
+    fake.fake_block(A)
+    c.all(A)
+    c.all(B)
+    assert not fake.fake_invalidated()
+    assert fake.fake_host_allocs() >= 4 and not fake.fake_graph_host_functions()
+
+
+CASES = [calls_while_another_stream_captures]
+
+
+@pytest.fixture(scope="module")
+def fake_so(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("fake") / "libfake_hip.so")
+    src = os.path.join(os.path.dirname(os.path.abspath(__file__)), "fake_hip.cpp")
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__",
+                           "-I/opt/rocm/include", src, "-o", out])
+    return out
+
+
+@pytest.mark.parametrize("case", [f.__name__ for f in CASES])
+def test_staging(case, fake_so):
+    r = subprocess.run([sys.executable, os.path.abspath(__file__), case, fake_so], capture_output=True, text=True,
+                       timeout=120)
+    assert r.returncode == 0, r.stdout + r.stderr
+
+
+if __name__ == "__main__":
+    stand_in = ctypes.CDLL(sys.argv[2], mode=ctypes.RTLD_GLOBAL)  # first, so that libtt.so finds its symbols here
+    for name in ("fake_block", "fake_unblock", "fake_capture"):
+        getattr(stand_in, name).argtypes = [ctypes.c_void_p]
+    stand_in.fake_stream_device.argtypes = [ctypes.c_void_p, ctypes.c_int]
+    stand_in.fake_source.restype = ctypes.c_void_p
+    stand_in.fake_replay.restype = ctypes.c_long
+    sys.path.insert(0, ROOT)
+    import paper_2502_08673_amd as package
+
+    {f.__name__: f for f in CASES}[sys.argv[1]](Calls(package, stand_in), stand_in)
