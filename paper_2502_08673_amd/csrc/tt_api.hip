@@ -403,12 +403,14 @@ int upload_async(void* dst, std::vector<uint8_t>* blob, hipStream_t s) {
 // first waits for the stream, and the host callback that frees it costs as
 // much as the launches (45 us a call in all, 20 with these).  Per device at
 // most kStageSlots buffers of at most kStageBytes; a call holds one until it
-// has queued its work, and the next user of the buffer waits for the event
-// recorded behind that work.  Inputs that are larger, and streams under
-// capture (a graph reads its source again on every replay), take the
-// pageable path.
+// has queued its work, and the next user takes it once the event recorded
+// behind that work has passed.  No call waits for that: the work may be on
+// any stream, behind anything.  Inputs that are larger, calls that find no
+// buffer free, and streams under capture (a graph reads its source again on
+// every replay) take the pageable path, which waits for nothing but its own
+// stream.
 constexpr size_t kStageBytes = 1u << 20;
-constexpr int kStageSlots = 8;
+constexpr int kStageSlots = 16;
 struct StageSlot {
   uint8_t* host = nullptr;
   size_t cap = 0;
@@ -445,31 +447,19 @@ int stage_acquire(size_t bytes, hipStream_t s, StageSlot** slot) {
   {
     std::lock_guard<std::mutex> lk(g_stage_mu);
     auto& slots = g_stage[dev];
-    StageSlot* waits = nullptr;  // the first that only its event keeps
     for (size_t k = 0; k < slots.size() && !got; ++k) {
       StageSlot* c = slots[k];
-      if (c->busy) continue;
-      if (!c->pending || hipEventQuery(c->done) == hipSuccess)
-        got = c;
-      else if (!waits)
-        waits = c;
+      if (!c->busy && c->pending) c->pending = hipEventQuery(c->done) != hipSuccess;
+      if (!c->busy && !c->pending) got = c;
     }
     if (!got && slots.size() < (size_t)kStageSlots) {
       got = new (std::nothrow) StageSlot();
       if (got) slots.push_back(got);
     }
-    if (!got) got = waits;
-    if (!got) return TT_OK;  // every buffer is in a call right now
+    if (!got) return TT_OK;
     got->busy = true;
-    // the order of use: the buffer goes to the end, so that the one waited
-    // for is the oldest
-    slots.erase(std::find(slots.begin(), slots.end(), got));
-    slots.push_back(got);
   }
-  hipError_t e = hipSuccess;
-  if (got->pending) e = hipEventSynchronize(got->done);
-  got->pending = false;
-  if (e == hipSuccess && !got->done) e = hipEventCreateWithFlags(&got->done, hipEventDisableTiming);
+  hipError_t e = got->done ? hipSuccess : hipEventCreateWithFlags(&got->done, hipEventDisableTiming);
   if (e == hipSuccess && got->cap < bytes) {
     size_t cap = 1u << 16;
     while (cap < bytes) cap *= 2;

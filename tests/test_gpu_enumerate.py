@@ -667,3 +667,73 @@ def test_one_shot_calls_while_another_stream_captures():
         graph.replay()
         torch.cuda.synchronize()
         assert (y == k + 1).all()
+
+
+def test_one_shot_calls_do_not_wait_for_other_streams():
+    """Calls for every staging buffer queued behind a long kernel on one
+    stream, then a call on another: it returns while the first stream is
+    still busy (whether it also ends then depends on the hardware queues the
+    streams got), and all results are right."""
+    ns = random_neurons(seed=78, n=50, max_fb=14)
+    desc = tt.descriptors(ns)
+    total = tt.layout(desc)
+    ref = oracle.enumerate(ns)
+    busy, idle = torch.cuda.Stream(), torch.cuda.Stream()
+    late = [device_tables(total) for _ in range(16)]
+    early = device_tables(total)
+    start, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+    for _ in range(2):  # (the first launch is slow)
+        start.record()
+        torch.cuda._sleep(1_000_000)
+        end.record()
+        torch.cuda.synchronize()
+    cycles = int(500 / start.elapsed_time(end) * 1_000_000)  # half a second
+    note("one-shot calls beside a busy stream")
+    with torch.cuda.stream(busy):
+        torch.cuda._sleep(cycles)
+        for t in late:
+            tt.enumerate(desc, t, total_words=total)
+        done = busy.record_event()
+    tt.enumerate(desc, early, total_words=total, stream=idle)
+    assert not done.query()
+    torch.cuda.synchronize()
+    for t in late + [early]:
+        assert np.array_equal(host_u64(t, 0, total), ref["planes"])
+
+
+@pytest.mark.parametrize("n", [1, 3000, 20000])
+def test_one_shot_calls_from_several_threads(n):
+    """Four threads, each on a stream of its own, with different neurons on
+    every call; n = 20000 is more than a staging buffer holds."""
+    import threading
+
+    sets = []
+    for k in range(4):
+        ns = random_neurons(seed=800 + k, n=n, F=(1, 4), b=(1, 2), max_fb=7)
+        desc = tt.descriptors(ns)
+        sets.append((desc, tt.layout(desc), oracle.enumerate(ns), torch.cuda.Stream()))
+    tables = [[device_tables(sets[(k + r) % 4][1]) for r in range(12)] for k in range(4)]
+    torch.cuda.synchronize()
+    errors = []
+
+    def work(k):
+        try:
+            for r, t in enumerate(tables[k]):
+                desc, total = sets[(k + r) % 4][:2]
+                tt.enumerate(desc, t, total_words=total, stream=sets[k][3])
+        except Exception as e:
+            errors.append(e)
+
+    note(f"one-shot calls from threads n={n}")
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(4)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    assert not errors
+    for k in range(4):
+        for r, t in enumerate(tables[k]):
+            total, ref = sets[(k + r) % 4][1:3]
+            assert np.array_equal(host_u64(t, 0, total), ref["planes"])
+            check_canary(t, total)

@@ -62,7 +62,28 @@ def calls_while_another_stream_captures(c, fake):
     assert fake.fake_host_allocs() >= 4 and not fake.fake_graph_host_functions()
 
 
-CASES = [calls_while_another_stream_captures]
+def calls_never_wait_for_earlier_ones(c, fake):
+    """Twenty calls behind work that does not end, then calls on an idle
+    stream: none waits, no buffer that a queued call still reads is written
+    again, and the buffers are bounded and used again later."""
+    fake.fake_block(A)
+    for _ in range(20):
+        c.pack(A)
+    read = [fake.fake_source(k) for k in range(fake.fake_sources())]
+    assert len(read) == 20 and len(set(read)) == 20
+    for _ in range(20):
+        c.all(B)
+    assert fake.fake_waits() == 0
+    staged = fake.fake_host_allocs()
+    assert 0 < staged <= 16
+    assert not {fake.fake_source(k) for k in range(20, fake.fake_sources())} & set(read[:staged])
+    fake.fake_unblock(A)
+    for _ in range(20):
+        c.all(A)
+    assert fake.fake_host_allocs() == staged
+
+
+CASES = [calls_while_another_stream_captures, calls_never_wait_for_earlier_ones]
 
 
 @pytest.fixture(scope="module")
