@@ -402,7 +402,8 @@ int upload_async(void* dst, std::vector<uint8_t>* blob, hipStream_t s) {
 // Pinned staging buffers of the one-shot calls: from pageable memory a copy
 // first waits for the stream, and the host callback that frees it costs as
 // much as the launches (45 us a call in all, 20 with these).  Per device at
-// most kStageSlots buffers of at most kStageBytes; a call holds one until it
+// most kStageSlots buffers of kStageBytes, made whole (64 KiB take as long)
+// and never freed or grown, which would wait for the whole device; a call holds one until it
 // has queued its work, and the next user takes it once the event recorded
 // behind that work has passed.  No call waits for that: the work may be on
 // any stream, behind anything.  Inputs that are larger, calls that find no
@@ -413,7 +414,6 @@ constexpr size_t kStageBytes = 1u << 20;
 constexpr int kStageSlots = 16;
 struct StageSlot {
   uint8_t* host = nullptr;
-  size_t cap = 0;
   hipEvent_t done = nullptr;
   bool busy = false, pending = false;
 };
@@ -460,15 +460,7 @@ int stage_acquire(size_t bytes, hipStream_t s, StageSlot** slot) {
     got->busy = true;
   }
   hipError_t e = got->done ? hipSuccess : hipEventCreateWithFlags(&got->done, hipEventDisableTiming);
-  if (e == hipSuccess && got->cap < bytes) {
-    size_t cap = 1u << 16;
-    while (cap < bytes) cap *= 2;
-    if (got->host) (void)hipHostFree(got->host);
-    got->host = nullptr;
-    got->cap = 0;
-    e = hipHostMalloc((void**)&got->host, cap, hipHostMallocDefault);
-    if (e == hipSuccess) got->cap = cap;
-  }
+  if (e == hipSuccess && !got->host) e = hipHostMalloc((void**)&got->host, kStageBytes, hipHostMallocDefault);
   if (e != hipSuccess) {
     std::lock_guard<std::mutex> lk(g_stage_mu);
     got->busy = false;

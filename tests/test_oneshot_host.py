@@ -83,7 +83,18 @@ def calls_never_wait_for_earlier_ones(c, fake):
     assert fake.fake_host_allocs() == staged
 
 
-CASES = [calls_while_another_stream_captures, calls_never_wait_for_earlier_ones]
+def a_larger_call_frees_no_buffer(c, fake):
+    """A buffer that served a small call serves a large one as it is: freeing
+    it to make a larger one would wait for every stream."""
+    c.pack(B)
+    fake.fake_block(A)
+    c.pack(B, n=9000)  # 144 kB of records
+    c.enumerate(B, n=16000)
+    assert fake.fake_host_frees() == 0 and fake.fake_waits() == 0
+    assert fake.fake_host_allocs() == 1
+
+
+CASES = [calls_while_another_stream_captures, calls_never_wait_for_earlier_ones, a_larger_call_frees_no_buffer]
 
 
 @pytest.fixture(scope="module")
