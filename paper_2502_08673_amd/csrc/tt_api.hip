@@ -471,14 +471,16 @@ int stage_acquire(size_t bytes, hipStream_t s, StageSlot** slot) {
   return TT_OK;
 }
 
-// The call has queued (on s) everything that reads the buffer.
+// The call has queued (on s) everything that reads the buffer.  Without a
+// recorded event the buffer is free once the stream has ended; if that cannot
+// be said either, it stays out of use.
 int stage_release(StageSlot* slot, hipStream_t s) {
-  hipError_t e = hipEventRecord(slot->done, s);
+  const hipError_t e = hipEventRecord(slot->done, s);
   const bool recorded = e == hipSuccess;
-  if (!recorded) (void)hipStreamSynchronize(s);
+  const bool known = recorded || hipStreamSynchronize(s) == hipSuccess;
   std::lock_guard<std::mutex> lk(g_stage_mu);
   slot->pending = recorded;
-  slot->busy = false;
+  slot->busy = !known;
   if (!recorded) {
     g_last_hip = (int)e;
     return TT_EHIP;

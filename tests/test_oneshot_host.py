@@ -94,7 +94,21 @@ def a_larger_call_frees_no_buffer(c, fake):
     assert fake.fake_host_allocs() == 1
 
 
-CASES = [calls_while_another_stream_captures, calls_never_wait_for_earlier_ones, a_larger_call_frees_no_buffer]
+def a_buffer_of_unknown_state_is_not_used_again(c, fake):
+    """Where the event behind a call cannot be recorded and the stream cannot
+    be waited for, nobody knows when the call's buffer has been read."""
+    fake.fake_block(A)
+    fake.fake_fail_record(1)
+    d, total = c.desc(16)
+    t = np.zeros(total, np.uint64)
+    assert c.L.tt_pack(d.ctypes.data, 16, t.ctypes.data, 64, t.ctypes.data, total, A) == c.tt.TT_EHIP
+    for _ in range(20):
+        c.pack(B)
+    assert fake.fake_source(0) not in {fake.fake_source(k) for k in range(1, fake.fake_sources())}
+
+
+CASES = [calls_while_another_stream_captures, calls_never_wait_for_earlier_ones, a_larger_call_frees_no_buffer,
+         a_buffer_of_unknown_state_is_not_used_again]
 
 
 @pytest.fixture(scope="module")
