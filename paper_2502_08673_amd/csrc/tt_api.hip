@@ -440,8 +440,12 @@ int stage_acquire(size_t bytes, hipStream_t s, StageSlot** slot) {
     return TT_OK;
   }
   if (cs != hipStreamCaptureStatusNone) return TT_OK;
-  int dev = 0;
+  int dev = 0, home = -1;
   TT_HIP(hipGetDevice(&dev));
+  // (the events belong to the current device: a stream of another one cannot
+  // record them)
+  if (hipStreamGetDevice(s, &home) != hipSuccess) (void)hipGetLastError();
+  if (home != dev) return TT_OK;
   const OutsideCapture outside;
   StageSlot* got = nullptr;
   {

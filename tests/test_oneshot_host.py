@@ -107,8 +107,16 @@ def a_buffer_of_unknown_state_is_not_used_again(c, fake):
     assert fake.fake_source(0) not in {fake.fake_source(k) for k in range(1, fake.fake_sources())}
 
 
+def a_stream_of_another_device(c, fake):
+    """A call on a stream of a device that is not the current one succeeds."""
+    fake.fake_stream_device(B, 1)
+    c.all(A)
+    c.all(B)
+    c.all(A)
+
+
 CASES = [calls_while_another_stream_captures, calls_never_wait_for_earlier_ones, a_larger_call_frees_no_buffer,
-         a_buffer_of_unknown_state_is_not_used_again]
+         a_buffer_of_unknown_state_is_not_used_again, a_stream_of_another_device]
 
 
 @pytest.fixture(scope="module")
