@@ -147,7 +147,9 @@ int tt_enumerate(const tt_neuron* h_desc, int n, uint64_t* d_tables, uint64_t to
  *    until the process ends.  All calls on one device share it and it keeps
  *    the last call's contents (nothing in it needs to start at zero).  Calls
  *    on one stream are ordered; calls on one device that may overlap (other
- *    streams, other threads) race on the array and must not be issued. */
+ *    streams, other threads) race on the array and must not be issued.
+ *  - Under capture the graph keeps the copy of the descriptors that its
+ *    replays read; it is freed with the graph and its instances. */
 #define TT_NOALLOC_SCRATCH_BYTES (32u << 20)
 int tt_enumerate_noalloc(const tt_neuron* h_desc, int n, uint64_t* d_tables, uint64_t total_words,
                          uint32_t* d_hist, void* stream);

@@ -375,19 +375,50 @@ std::vector<uint8_t>* make_upload(const PlanHost& P, const Layout& L, bool with_
 
 void free_blob(void* p) { delete static_cast<std::vector<uint8_t>*>(p); }
 
+// The blob given to the graph that `s` is recording, if it is recording one
+// (*kept): a graph reads its sources on every replay, so the blob lives as
+// long as the graph and what was instantiated from it.
+int keep_for_graph(std::vector<uint8_t>* blob, hipStream_t s, bool* kept) {
+  *kept = false;
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  hipGraph_t graph = nullptr;
+  if (hipStreamGetCaptureInfo_v2(s, &cs, nullptr, &graph, nullptr, nullptr) != hipSuccess) {
+    (void)hipGetLastError();
+    return TT_OK;
+  }
+  if (cs != hipStreamCaptureStatusActive) return TT_OK;
+  hipUserObject_t owner = nullptr;
+  TT_HIP(hipUserObjectCreate(&owner, blob, free_blob, 1, hipUserObjectNoDestructorSync));
+  *kept = true;
+  const hipError_t e = hipGraphRetainUserObject(graph, owner, 1, hipGraphUserObjectMove);
+  if (e != hipSuccess) {
+    (void)hipUserObjectRelease(owner, 1);  // and with it the blob
+    g_last_hip = (int)e;
+    return TT_EHIP;
+  }
+  return TT_OK;
+}
+
 // Stream-ordered upload of a host blob; the blob is freed by a host callback
-// once the copy has executed.
+// once the copy has executed, or with the graph that the copy is part of.
 int upload_async(void* dst, std::vector<uint8_t>* blob, hipStream_t s) {
   if (blob->empty()) {
     delete blob;
     return TT_OK;
   }
+  bool kept = false;
+  const int st = keep_for_graph(blob, s, &kept);
+  if (st != TT_OK) {
+    if (!kept) delete blob;
+    return st;
+  }
   hipError_t e = hipMemcpyAsync(dst, blob->data(), blob->size(), hipMemcpyHostToDevice, s);
   if (e != hipSuccess) {
-    delete blob;
+    if (!kept) delete blob;
     g_last_hip = (int)e;
     return TT_EHIP;
   }
+  if (kept) return TT_OK;
   e = hipLaunchHostFunc(s, free_blob, blob);
   if (e != hipSuccess) {
     // The copy is already queued: wait for it before releasing the blob.
@@ -407,9 +438,9 @@ int upload_async(void* dst, std::vector<uint8_t>* blob, hipStream_t s) {
 // has queued its work, and the next user takes it once the event recorded
 // behind that work has passed.  No call waits for that: the work may be on
 // any stream, behind anything.  Inputs that are larger, calls that find no
-// buffer free, and streams under capture (a graph reads its source again on
-// every replay) take the pageable path, which waits for nothing but its own
-// stream.
+// buffer free, and streams under capture (a graph reads its source on every
+// replay, so it keeps one of its own) take the pageable path, which waits for
+// nothing but its own stream.
 constexpr size_t kStageBytes = 1u << 20;
 constexpr int kStageSlots = 16;
 struct StageSlot {

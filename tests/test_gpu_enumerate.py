@@ -737,3 +737,35 @@ def test_one_shot_calls_from_several_threads(n):
             total, ref = sets[(k + r) % 4][1:3]
             assert np.array_equal(host_u64(t, 0, total), ref["planes"])
             check_canary(t, total)
+
+
+def test_captured_noalloc_replays_its_own_descriptors():
+    """tt_enumerate_noalloc recorded into a graph, wide neurons among the
+    others: every replay, with the outputs poisoned, other calls and new host
+    memory in between, gives the tables of the descriptors it was recorded
+    with, which the caller has changed since."""
+    ns = concat([random_neurons(seed=91, n=60, max_fb=14), random_neurons(seed=92, n=3, F=(6, 6), b=(3, 3), max_fb=18)])
+    other = random_neurons(seed=93, n=500, max_fb=12)
+    desc, odesc = tt.descriptors(ns), tt.descriptors(other)
+    total, ototal = tt.layout(desc), tt.layout(odesc)
+    ref = oracle.enumerate(ns)
+    tables, otables = device_tables(total), device_tables(ototal)
+    hist = torch.zeros(len(ns) * 8, dtype=torch.int32, device="cuda")
+    tt.enumerate_noalloc(odesc, otables, total_words=ototal)
+    torch.cuda.synchronize()
+    note("captured tt_enumerate_noalloc")
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        tt.enumerate_noalloc(desc, tables, total_words=total, hist=hist)
+    desc["w"], desc["bias"] = 1, 0
+    for k in range(4):
+        tables[:total].fill_(-1 - k)
+        hist.fill_(-1)
+        tt.enumerate_noalloc(odesc, otables, total_words=ototal)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(host_u64(tables, 0, total), ref["planes"])
+        assert np.array_equal(hist.cpu().numpy().reshape(-1, 8).astype(np.uint32), ref["hist"])
+    del graph
+    check_canary(tables, total)

@@ -115,8 +115,26 @@ def a_stream_of_another_device(c, fake):
     c.all(A)
 
 
+def a_captured_copy_lives_as_long_as_its_graph(c, fake):
+    """A call recorded into a graph: replays read the call's own copy of its
+    descriptors, which nothing frees before the graph is destroyed."""
+    for call in (c.noalloc, c.enumerate, c.pack, c.support):
+        fake.fake_capture(A)
+        call(A)
+        fake.fake_capture(None)
+        assert fake.fake_graph_host_functions() == 0 and fake.fake_retained() == 1
+        sums = []
+        for _ in range(3):
+            sums.append(fake.fake_replay())
+            c.all(B, 100)  # host memory that was free by now is written
+        assert sums[0] > 0 and sums == sums[:1] * 3
+        fake.fake_destroy_graph()
+    assert not fake.fake_invalidated()
+
+
 CASES = [calls_while_another_stream_captures, calls_never_wait_for_earlier_ones, a_larger_call_frees_no_buffer,
-         a_buffer_of_unknown_state_is_not_used_again, a_stream_of_another_device]
+         a_buffer_of_unknown_state_is_not_used_again, a_stream_of_another_device,
+         a_captured_copy_lives_as_long_as_its_graph]
 
 
 @pytest.fixture(scope="module")
