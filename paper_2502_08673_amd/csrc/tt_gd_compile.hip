@@ -300,10 +300,17 @@ std::string gd_compiled_source(const GdProgram& P) {
   }
   w.line("const bool ok = all > 0.5f;");
   w.line("valid[s] = ok ? 1 : 0;");
+  // (an expression handed in for a primary input overwrites its hardened value)
+  std::vector<bool> written(P.n_vslots, false);
+  for (int g = 0; g < P.iv_rng[n_iv]; ++g)
+    if (P.gate[g].dst < P.n_vslots) written[P.gate[g].dst] = true;
   for (int wd = 0; wd < P.words; ++wd) {
     std::string bits = "0ull";
-    for (int b = 0; b < 64 && 64 * wd + b < npi; ++b)
-      bits += " | (v" + Writer::num(64 * wd + b) + " > 0.f ? 1ull << " + Writer::num(b) + " : 0ull)";
+    for (int b = 0; b < 64 && 64 * wd + b < npi; ++b) {
+      const int q = 64 * wd + b;
+      bits += " | (" + (written[q] ? "p" + Writer::num(q) + " > 0.5f" : "v" + Writer::num(q) + " > 0.f") + " ? 1ull << " +
+              Writer::num(b) + " : 0ull)";
+    }
     w.line("const unsigned long long sw" + Writer::num(wd) + " = " + bits + ";");
     w.line("sol[s * " + Writer::num(P.words) + "L + " + Writer::num(wd) + "] = sw" + Writer::num(wd) + ";");
   }

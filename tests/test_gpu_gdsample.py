@@ -438,3 +438,31 @@ def test_reconvergent_forms():
     PO, PI, IV, E = T.transform(cl)
     assert 4 in IV and 7 in IV
     check(9, cl, batch=600, seed=17)
+
+
+def test_an_expression_for_a_primary_input_decides_its_solution_bit():
+    """Classes that call a gate's output a primary input as well (no completed
+    transformation gives such): the gate's value is the bit of the solution,
+    in both kernels, whatever the sign of the variable's logit."""
+    n_vars, clauses = tseitin_instances(seed=320, n_inst=1, n_gates=(20, 40))[0]
+    recs, cls = transform_on_gpu(n_vars, clauses)
+    x = int(recs[recs["kind"] == 1]["out"][0])
+    cls = cls.copy()
+    cls[x] |= tt.TT_CNF_CLS_PI
+    with tt.GdSampler(clauses, n_vars, recs, cls) as gd:
+        assert gd.kernel == tt.TT_GD_COMPILED
+        col = gd.pi_vars.index(x)
+        V0 = np.random.default_rng(9).normal(0, 1, (500, gd.n_pi)).astype(np.float32)
+        got = []
+        for kernel in (tt.TT_GD_COMPILED, tt.TT_GD_INTERPRETED):
+            gd.kernel = kernel
+            V = torch.from_numpy(V0.copy()).cuda()
+            valid = torch.zeros((500,), dtype=torch.uint8, device="cuda")
+            sol = torch.zeros((500, gd.words), dtype=torch.int64, device="cuda")
+            note(f"gd_sample kernel={kernel} expression for a primary input")
+            gd.run(V, 10.0, 0, valid, sol)
+            torch.cuda.synchronize()
+            got.append((valid.cpu().numpy(), sol.cpu().numpy().view(np.uint64)))
+    assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
+    bit = (got[0][1][:, col // 64] >> np.uint64(col % 64)) & np.uint64(1)
+    assert (bit.astype(bool) != (V0[:, col] > 0)).any()
