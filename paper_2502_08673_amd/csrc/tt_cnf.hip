@@ -16,6 +16,8 @@
 // differs: a shifted XOR inside a word for j < 6, a lane exchange for
 // j >= 6).  An SC with no output whose variables occur in no later clause
 // becomes an auxiliary output constrained to 1 (the conjunction of SC).
+#include <stddef.h>
+
 #include <algorithm>
 
 #include "tt_internal.h"
@@ -102,12 +104,13 @@ constexpr uint32_t kNoVar = 0x8000u;
 constexpr int kDigitShift = 3;
 constexpr uint32_t kClassBits = (1u << kDigitShift) - 1u;
 
-struct CnfList {
+struct alignas(16) CnfList {
   uint32_t tab[kCnfList];        // f (v's digit dropped) or SC's conjunction
   uint16_t var[kCnfList][8];     // variable of digit q; kNoVar: none, or v
   int32_t rec[kCnfList], first[kCnfList], last[kCnfList], out[kCnfList];
   int32_t count, more;           // entries; whether another list follows
 };
+static_assert(sizeof(CnfList) % 16 == 0 && offsetof(CnfList, var) % 16 == 0, "var's rows are read as uint4");
 
 template <int CTRL>
 __device__ __forceinline__ uint32_t dpp(uint32_t x) {
