@@ -97,7 +97,9 @@ namespace {
 constexpr int kCnfFastVars = 5;
 static_assert(kCnfFastVars == kCnfFastClause, "a clause's literals are distinct variables");
 constexpr int kCnfList = 64;
-constexpr int kCnfPending = -1;  // status of an instance left to the wave kernel
+// Status of an instance left to the wave kernel: -1 less the clause that the
+// SC that outgrew the eight lanes began with.
+constexpr int kCnfPending = -1;
 constexpr uint32_t kNoVar = 0x8000u;
 // A variable's byte in LDS: its class bits, and its digit in SC plus one
 // (zero: not in SC) from bit 3 up.
@@ -216,8 +218,10 @@ __global__ __launch_bounds__(256) void cnf_clause_kernel(const int32_t* lits, co
 // The first n_fast instances of the order (no clause above kCnfFastClause
 // literals, fewer than 2^16 clauses, few variables): eight to a block of two
 // waves, the first walking, the second writing.  An instance whose SC
-// outgrows kCnfFastVars variables stops with status kCnfPending and is taken
-// again, from its start, by cnf_transform_kernel.  Bound by the chain of the
+// outgrows kCnfFastVars variables stops there: cnf_transform_kernel goes on
+// from the clause that this SC began with, with the classes and expressions so
+// far (from the instance's start, 20000 circuits with a seven-variable SC at
+// their end took 3.3 ms, and 2.5 ms by that kernel alone).  Bound by the chain of the
 // longest instances' clauses, about 200 instructions and 0.55 us each:
 // 20000 circuits of 8 to 64 gates take 0.158 ms, 16 of them 0.14 ms (a wave
 // each: 1.38 and 0.47 ms); without its stores, 0.5 GB, it takes 0.150 ms.
@@ -362,19 +366,20 @@ __global__ __launch_bounds__(128) void cnf_fast_kernel(CnfArgs a) {
   }
   __syncthreads();
   if (!live) return;
-  if (!pending)
-    for (int x = q; x <= nvar; x += 8) a.var_class[a.var_off[inst] + x] = cls[x];
+  for (int x = q; x <= nvar; x += 8) a.var_class[a.var_off[inst] + x] = (uint8_t)(cls[x] & kClassBits);
   if (q == 0) {
     a.n_expr[inst] = nexpr;
-    a.status[inst] = pending ? kCnfPending : 0;
+    a.status[inst] = pending ? kCnfPending - start : 0;
   }
 }
 
 // STAGED: the instance's clause offsets, literals and clause reaches are
 // copied into LDS first (every later read is an LDS read), when the largest
 // instance of the batch fits; else they are read from global memory.
+// first, nexpr: the clause to begin with and the expressions found before it
+// (first > 0: the classes so far are the instance's in var_class).
 template <bool STAGED>
-__device__ __forceinline__ void cnf_transform_wave(const CnfArgs& a, int inst, int32_t* smem) {
+__device__ __forceinline__ void cnf_transform_wave(const CnfArgs& a, int inst, int32_t* smem, int first, int nexpr) {
   const int lane = threadIdx.x;
   const int nvar = a.n_vars[inst];
   const int c0 = a.inst_off[inst], nc = a.inst_off[inst + 1] - c0;
@@ -400,7 +405,7 @@ __device__ __forceinline__ void cnf_transform_wave(const CnfArgs& a, int inst, i
     lits = a.lits;
     cls = reinterpret_cast<uint8_t*>(smem);
   }
-  for (int x = lane; x <= nvar; x += 64) cls[x] = 0;
+  for (int x = lane; x <= nvar; x += 64) cls[x] = first > 0 ? a.var_class[a.var_off[inst] + x] : (uint8_t)0;
   __syncthreads();
   // SC's variables, ascending, one per lane: lane q holds the q-th (lanes at
   // or past nsc hold INT_MAX), so finding a variable's place is one ballot
@@ -413,8 +418,8 @@ __device__ __forceinline__ void cnf_transform_wave(const CnfArgs& a, int inst, i
   // without v, which some row satisfies.  Such variables are skipped
   // without a walk.
   int occ = 0;
-  int start = 0, nexpr = 0, status = 0, reach = -1;
-  for (int i = 0; i < nc; ++i) {
+  int start = first, status = 0, reach = -1;
+  for (int i = first; i < nc; ++i) {
     reach = max(reach, creach[i]);
     const bool unit = coff[i + 1] - coff[i] == 1;
     for (int p = coff[i]; p < coff[i + 1]; ++p) {  // merge the clause's variables
@@ -548,18 +553,21 @@ __global__ __launch_bounds__(64) void cnf_transform_kernel(CnfArgs a) {
   const int n_slow = a.n_inst - a.n_fast;
   const int blk = (int)blockIdx.x;
   if (blk < n_slow) {
-    cnf_transform_wave<STAGED>(a, a.order[a.n_fast + blk], smem);
+    cnf_transform_wave<STAGED>(a, a.order[a.n_fast + blk], smem, 0, 0);
     return;
   }
   const int G = (int)gridDim.x - n_slow;
   for (long base = blk - n_slow; base < a.n_fast; base += 64L * G) {
     const long slot = base + (long)threadIdx.x * G;
     const int inst = slot < a.n_fast ? a.order[slot] : -1;
-    uint64_t todo = __ballot(inst >= 0 && a.status[inst] == kCnfPending);
+    const int left = inst >= 0 ? a.status[inst] : 0;
+    uint64_t todo = __ballot(left <= kCnfPending);
     while (todo) {
       const int l = __ffsll((unsigned long long)todo) - 1;
       todo &= todo - 1ull;
-      cnf_transform_wave<STAGED>(a, __builtin_amdgcn_readlane(inst, l), smem);
+      const int which = __builtin_amdgcn_readlane(inst, l);
+      const int first = kCnfPending - __builtin_amdgcn_readlane(left, l);
+      cnf_transform_wave<STAGED>(a, which, smem, first, a.n_expr[which]);
     }
   }
 }

@@ -211,3 +211,40 @@ def test_variable_order_and_sc_sizes_around_the_eight_lane_form(n_inst, offset):
         check_instance(t, cl, n, vc, recs, ne, status.cpu().numpy(), ioff, voff)
         voff += n + 1
     assert not buf[: offset].any() and not buf[offset + n_cl * 640:].any()
+
+
+@pytest.mark.parametrize("n_inst", [1, 9, 70])
+def test_an_instance_goes_on_after_an_sc_that_outgrew_the_eight_lanes(n_inst):
+    """A circuit, an SC of six to eight variables in binary clauses, some of
+    them the circuit's inputs and outputs (their classes decide what the SC
+    can give), and a second circuit: the records before, of and after that SC
+    and the classes, also where the SC is the instance's first."""
+    rng = np.random.default_rng(n_inst)
+    inst = []
+    for t in range(n_inst):
+        nv, cl = tseitin_instances(seed=1100 + t, n_inst=1)[0] if t % 4 else (0, [])
+        k = 6 + t % 3
+        old = [int(x) for x in rng.permutation(nv)[: min(nv, t % 5)] + 1]
+        xs = [int(x) for x in rng.permutation(old + list(range(nv + 1, nv + 1 + k - len(old))))]
+        # the chain's variables occur nowhere later; the circuit before them is closed by its last output
+        chain = [[xs[i], -xs[i + 1] if i % 2 else xs[i + 1]] for i in range(k - 1)] + [[-xs[0], -xs[-1]]]
+        m = max([nv] + xs)
+        nv2, cl2 = tseitin_instances(seed=1200 + t, n_inst=1)[0]
+        cl = cl + chain + [[int(np.sign(L)) * (abs(L) + m) for L in c] for c in cl2]
+        inst.append((m + nv2, cl))
+    lits, coff, ioff, nv = tt.cnf_csr(inst)
+    var_class = torch.full((int((nv + 1).sum()),), 0xEE, dtype=torch.uint8, device="cuda")
+    expr = torch.zeros((int(ioff[-1]) * 640,), dtype=torch.uint8, device="cuda")
+    n_expr = torch.full((n_inst,), -1, dtype=torch.int32, device="cuda")
+    status = torch.full((n_inst,), -1, dtype=torch.int32, device="cuda")
+    note(f"cnf goes on after a wide SC, instances={n_inst}")
+    with tt.Cnf(lits, coff, ioff, nv) as h:
+        for _ in range(2):
+            h.run(var_class, expr, n_expr, status)
+    torch.cuda.synchronize()
+    st, recs = status.cpu().numpy(), expr.cpu().numpy().view(tt.CNF_EXPR_DTYPE)
+    vc, ne = var_class.cpu().numpy(), n_expr.cpu().numpy()
+    voff = 0
+    for t, (n, cl) in enumerate(inst):
+        check_instance(t, cl, n, vc, recs, ne, st, ioff, voff)
+        voff += n + 1
