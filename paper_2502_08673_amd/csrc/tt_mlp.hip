@@ -1611,7 +1611,7 @@ __global__ __launch_bounds__(256) void train_update_kernel(TrainArgs a, float lr
 static size_t train_layout(TrainArgs& a, float* scratch, bool most = false) {
   size_t o = 0;
   auto take = [&](size_t floats) {
-    float* at = scratch + o;
+    float* at = scratch ? scratch + o : nullptr;
     o += (floats + 3) / 4 * 4;
     return at;
   };
