@@ -1514,8 +1514,8 @@ int tt_cnf_create(const int32_t* h_lits, const int32_t* h_clause_off, const int3
   const size_t off_ord = take(sizeof(int32_t) * n_inst);
   const size_t upload = o;
   // instances longest first (a stable sort by clause count), so the last
-  // waves to finish are short ones and the eight of a wave alike; those that
-  // fit the kernel of eight instances a wave before the others
+  // waves to finish are short ones and the eight of a wave alike; those whose
+  // size fits the kernel of eight instances a wave before the others
   std::vector<int32_t> order(n_inst);
   std::vector<uint8_t> slow(n_inst, 0);
   int fast_vars = 0;
@@ -1523,7 +1523,6 @@ int tt_cnf_create(const int32_t* h_lits, const int32_t* h_clause_off, const int3
     order[t] = t;
     const int c1 = h_inst_off[t + 1];
     slow[t] = c1 - h_inst_off[t] > 0xFFFF || h_n_vars[t] >= kCnfFastVarBytes;
-    for (int c = h_inst_off[t]; c < c1 && !slow[t]; ++c) slow[t] = dcoff[c + 1] - dcoff[c] > kCnfFastClause;
     if (!slow[t]) {
       ++h->args.n_fast;
       fast_vars = std::max(fast_vars, h_n_vars[t]);
@@ -1535,6 +1534,7 @@ int tt_cnf_create(const int32_t* h_lits, const int32_t* h_clause_off, const int3
     return h_inst_off[x + 1] - h_inst_off[x] > h_inst_off[y + 1] - h_inst_off[y];
   });
   const size_t off_rec = take(16 * (size_t)(h->args.n_fast > 0 ? n_clauses : 0));
+  const size_t off_left = take(sizeof(int32_t) * (size_t)h->args.n_fast);
   if (st == TT_OK) {
     const hipError_t e = hipMalloc((void**)&h->ws, o);
     if (e != hipSuccess) {
@@ -1564,6 +1564,7 @@ int tt_cnf_create(const int32_t* h_lits, const int32_t* h_clause_off, const int3
     a.n_vars = reinterpret_cast<const int32_t*>(h->ws + off_nv);
     a.order = reinterpret_cast<const int32_t*>(h->ws + off_ord);
     a.clause_rec = reinterpret_cast<const uint4*>(h->ws + off_rec);
+    a.left = reinterpret_cast<int32_t*>(h->ws + off_left);
     a.n_inst = n_inst;
     for (int t = 0; t < n_inst && n_clauses > 0; ++t) {
       a.stage_clauses = std::max(a.stage_clauses, h_inst_off[t + 1] - h_inst_off[t]);

@@ -449,6 +449,10 @@ struct CnfArgs {
                                 // by decreasing clause count (long walks start first)
   const uint4* clause_rec;      // global clause index -> its literals and reach in 16 bytes (cnf_clause_kernel)
   int32_t n_fast;
+  // place in the order -> 0, or one more than the clause that the wave kernel
+  // goes on from (written by every run, the same values: they follow from the
+  // instances)
+  int32_t* left;
   int32_t cls_stride;           // class bytes of an instance of cnf_fast_kernel, in LDS
   uint8_t* var_class;
   tt_cnf_expr* expr;
@@ -457,7 +461,6 @@ struct CnfArgs {
   int32_t n_inst;
   int32_t stage_clauses, stage_lits;  // the largest instance's clause and literal counts
 };
-constexpr int kCnfFastClause = 5;      // literals of a clause, at most, for cnf_fast_kernel
 constexpr int kCnfFastVarBytes = 2048; // its class bytes per instance, at most (16 KiB a block)
 hipError_t launch_cnf_clauses(const CnfArgs& a, int n_clauses, uint4* rec, hipStream_t s);
 hipError_t launch_cnf_transform(const CnfArgs& a, int max_vars, hipStream_t s);

@@ -215,10 +215,12 @@ def test_variable_order_and_sc_sizes_around_the_eight_lane_form(n_inst, offset):
 
 @pytest.mark.parametrize("n_inst", [1, 9, 70])
 def test_an_instance_goes_on_after_an_sc_that_outgrew_the_eight_lanes(n_inst):
-    """A circuit, an SC of six to eight variables in binary clauses, some of
-    them the circuit's inputs and outputs (their classes decide what the SC
-    can give), and a second circuit: the records before, of and after that SC
-    and the classes, also where the SC is the instance's first."""
+    """A circuit, SCs of six to eight variables in binary clauses, some of them
+    the circuit's inputs and outputs (their classes decide what the SC can
+    give), a gate of six inputs (a clause of seven literals), and a second
+    circuit: the records before, of and after those SCs and the classes, also
+    where an SC is the instance's first, and with several in a row (the
+    instance then stays with the wave kernel)."""
     rng = np.random.default_rng(n_inst)
     inst = []
     for t in range(n_inst):
@@ -229,6 +231,12 @@ def test_an_instance_goes_on_after_an_sc_that_outgrew_the_eight_lanes(n_inst):
         # the chain's variables occur nowhere later; the circuit before them is closed by its last output
         chain = [[xs[i], -xs[i + 1] if i % 2 else xs[i + 1]] for i in range(k - 1)] + [[-xs[0], -xs[-1]]]
         m = max([nv] + xs)
+        for _ in range(t % 7 // 2):  # up to three more in a row
+            chain += [[x, x + 1] for x in range(m + 1, m + k)] + [[-(m + 1), -(m + k)]]
+            m += k
+        if t % 2:
+            chain += _and(list(range(m + 1, m + 7)), m + 7)
+            m += 7
         nv2, cl2 = tseitin_instances(seed=1200 + t, n_inst=1)[0]
         cl = cl + chain + [[int(np.sign(L)) * (abs(L) + m) for L in c] for c in cl2]
         inst.append((m + nv2, cl))
