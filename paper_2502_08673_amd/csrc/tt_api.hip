@@ -789,12 +789,28 @@ struct tt_lutnet {
 
 namespace {
 
-// The packed form's blocks take eight times the samples, so it pays once the
-// other one has three blocks of 64 samples for each compute unit: 448 neurons,
-// F = 6, b = 2: 48000 samples 28.5 against 27.3 us, 64000 40.7 against 28.1,
-// 16000 15.3 against 25.3; F = 4, b = 1, 480 neurons: 48000 26.3 against 30.7,
-// 250000 141 against 86.
-int pack_min_batch(int cus) { return 192 * cus; }
+// Whether a batch takes the packed form: from three blocks of 64 samples for
+// each compute unit on, where the other form would have k of its blocks on
+// some compute unit for each round of the packed form's, which takes about as
+// long as k of them.  k by the packed form's reads for a neuron, measured at
+// 480 neurons and 256 inputs (the other form / this one, us): two bits a
+// signal, 4: F = 4, b = 1: 49152 samples 23.8 / 26.9, 57344 30.5 / 27.5, the
+// second round's first 147456 58.5 / 55.7; four bits a signal: b = 3, F = 2,
+// 4: 65536 29.4 / 25.6, 73728 32.9 / 44.1, 131072 49.2 / 48.1; b = 4, 3:
+// 49152 22.5 / 19.5, 73728 32.9 / 34.9, 98304 40.2 / 36.2.  Above 512 neurons
+// the other form's waves take a level in more turns, 3: 700 neurons, 49152
+// samples 41.0 / 36.5.  Where two packed blocks fit a compute unit a round is
+// shorter: up to 160 signals at once (100 neurons, 60 inputs: 11.6 / 10.2), with
+// three or four bits a digit 3 (200 neurons, F = 2, b = 3: 13.6 / 12.4).
+bool takes_packed(int n_inputs, int n, int omax, int digit, int fmax, int batch, int cus) {
+  const int signals = n_inputs + n;
+  if (batch < 192 * cus) return false;
+  if (signals <= 160) return true;
+  const int samples = tt::net_pack_samples(omax, digit), two = 2 * tt::net_pack_lds(signals) <= tt::kPackMaxLds ? 2 : 1;
+  const int twice_k = n > 512 || (two == 2 && digit > 2) ? 6 : samples == 512 || digit == 3 || fmax > 4 ? 8 : digit == 2 ? 7 : 6;
+  const long round = (long)samples * two * cus, blocks = ((long)batch + 64L * cus - 1) / (64L * cus);
+  return 2 * blocks >= twice_k * (((long)batch + round - 1) / round);
+}
 
 // Validate a network, group it by level and build its workspace (records,
 // interleaved tables and input masks for the single-launch form; descriptors,
@@ -867,8 +883,8 @@ int lutnet_setup(const tt_neuron* h_desc, int n, const int32_t* h_fanin, int n_i
       one_b = one_b && h_desc[i].b == h_desc[0].b;
     }
     // the packed form: tables of at most 1 KiB, digits of one width
-    if (most_batch >= pack_min_batch(L->cus) && one_b && 4 * largest <= tt::kPackTable &&
-        tt::net_pack_lds(n_inputs + n) <= tt::kPackMaxLds) {
+    if ((most_batch == INT_MAX || takes_packed(n_inputs, n, omax, h_desc[0].b, fmax, most_batch, L->cus)) && one_b &&
+        4 * largest <= tt::kPackTable && tt::net_pack_lds(n_inputs + n) <= tt::kPackMaxLds) {
       for (int lv = 0; lv < depth; ++lv) rounds += pack_rounds(L->level_begin[lv + 1] - L->level_begin[lv]);
       rounds = (rounds + tt::kPackRounds - 1) / tt::kPackRounds * tt::kPackRounds;
     }
@@ -986,7 +1002,7 @@ int lutnet_enqueue(const tt_lutnet& L, const uint8_t* d_inputs, int batch, uint8
     na.inputs = d_inputs;
     na.out = d_out;
     na.sample = 0;
-    if (na.slots && batch >= pack_min_batch(L.cus))
+    if (na.slots && takes_packed(na.n_inputs, na.n, na.omax, na.digit, na.fmax, batch, L.cus))
       TT_HIP(tt::launch_lutnet_packed(na, s));
     else
       TT_HIP(tt::launch_lutnet_fused(na, tt::NetSample{}, s));

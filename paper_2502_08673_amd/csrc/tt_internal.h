@@ -427,6 +427,8 @@ constexpr long kPackMaxLds = 160 * 1024;
 inline long net_pack_tables_at(int signals) {
   return ((long)net_row((uint32_t)signals) + 132 + kPackTable - 1) / kPackTable * kPackTable;
 }
+// samples of a block: two bits a signal where the codes and digits have at most two, else four
+inline int net_pack_samples(int omax, int digit) { return omax <= 2 && digit <= 2 ? 512 : 256; }
 inline long net_pack_lds(int signals) { return net_pack_tables_at(signals) + (long)kPackWaves * kPackTable; }
 // LDS row stride of the single-launch form, 0 when the network's signals do
 // not fit (then one launch per level)

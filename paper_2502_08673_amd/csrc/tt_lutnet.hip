@@ -244,8 +244,9 @@ __global__ __launch_bounds__(kNetThreads) void lutnet_fused_kernel(NetArgs a, co
 // the LDS (eight gathers of 64 lanes in 64 banks, 54 of a neuron's 95 cycles)
 // and the vector unit beside it (75 instructions a neuron and 512 samples);
 // while all blocks load or write at once, HBM.  256 inputs, 448 neurons, F = 6,
-// b = 2, 250001 samples: 73 us (that form: 133); 480 neurons of F = 4, b = 1:
-// 86 (141); 60 of them: 12.6 (38.5).  Four waves that only write and load
+// b = 2, 250001 samples: 73 us (that form: 133); 480 neurons of F = 4, b = 1,
+// 262144 samples: 66.5 (98; 73 reading eight signals a neuron, as for F = 8);
+// 60 of them: 12.6 (38.5).  Four waves that only write and load
 // beside twelve that look up, with the next samples' inputs on the way: 73.
 constexpr int kPackThreads = 64 * kPackWaves;
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -553,15 +554,15 @@ hipError_t launch_packed(const NetArgs& a, hipStream_t s) {
 
 hipError_t launch_lutnet_packed(const NetArgs& a, hipStream_t s) {
   if (a.batch <= 0) return hipSuccess;
-  // two bits a signal where the codes and digits have at most two
-  if (a.omax <= 2 && a.digit <= 2) {
+  if (net_pack_samples(a.omax, a.digit) == 512) {
     const bool one = a.lw == 0;
+    if (a.digit == 1 && a.fmax <= 4) return one ? launch_packed<2, 1, 1, 0>(a, s) : launch_packed<2, 1, 1, 1>(a, s);
     if (a.digit == 1) return one ? launch_packed<2, 1, 2, 0>(a, s) : launch_packed<2, 1, 2, 1>(a, s);
     if (a.fmax <= 4) return one ? launch_packed<2, 2, 2, 0>(a, s) : launch_packed<2, 2, 2, 1>(a, s);
     return one ? launch_packed<2, 2, 3, 0>(a, s) : launch_packed<2, 2, 3, 1>(a, s);
   }
   switch (a.digit * 4 + a.lw) {
-    case 6: return launch_packed<4, 1, 2, 2>(a, s);
+    case 6: return a.fmax <= 4 ? launch_packed<4, 1, 1, 2>(a, s) : launch_packed<4, 1, 2, 2>(a, s);
     case 10: return launch_packed<4, 2, 3, 2>(a, s);
     case 12: return launch_packed<4, 3, 4, 0>(a, s);
     case 13: return launch_packed<4, 3, 4, 1>(a, s);

@@ -344,3 +344,42 @@ def test_large_batches_take_the_packed_form(F, b, o, P, n, extra, offset):
     rows = np.r_[0:200, batch - 700:batch]
     want = lutnet.evaluate(ns, [fanin[i, :int(ns.F[i])] for i in range(n)], P, inputs[rows])
     assert np.array_equal(y[torch.from_numpy(rows).cuda()].cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("F,b,o,P,n,blocks", [((1, 4), 1, (1, 1), 92, 60, 5), ((1, 4), 1, (1, 2), 300, 200, 4),
+                                              ((2, 4), 1, (1, 3), 200, 97, 3), ((1, 2), 2, (1, 2), 250, 490, 9),
+                                              ((2, 2), 3, (1, 3), 256, 480, 5), ((2, 2), 3, (1, 3), 256, 480, 8),
+                                              ((1, 2), 4, (1, 2), 256, 480, 3), ((1, 5), 2, (1, 3), 300, 400, 7)])
+def test_forms_around_the_rule_that_chooses_them(F, b, o, P, n, blocks):
+    """Batches of `blocks` blocks of 64 samples for each compute unit, less
+    and more than at which the packed form is taken, and one sample on either
+    side; narrow fan-in of one-bit digits (read four signals at a time).  The
+    first and last samples against the oracle, all of them against the same
+    handle on small pieces."""
+    limit = blocks * 64 * torch.cuda.get_device_properties(0).multi_processor_count
+    ns = random_neurons(seed=1700 + P + n, n=n, F=F, b=(b, b), o=o, max_fb=16, wmax=20, bias_max=30)
+    rng = np.random.default_rng(P + n)
+    fanin = np.full((n, 8), -1, np.int32)
+    for i in range(n):
+        f = int(ns.F[i])
+        fanin[i, :f] = rng.integers(0, P + i, size=f)
+    desc = tt.descriptors(ns)
+    total = tt.layout(desc)
+    tables = device_tables(total)
+    tt.enumerate(desc, tables, total_words=total)
+    x = torch.randint(0, 256, (limit + 1, P), dtype=torch.uint8, device="cuda")
+    pieces = torch.empty((limit + 1, n), dtype=torch.uint8, device="cuda")
+    with tt.Lutnet(desc, fanin, P, tables, total) as net:
+        for s in range(0, limit + 1, 16384):
+            net.run(x[s: s + 16384], pieces[s: s + 16384])
+        for batch in (limit - 1, limit, limit + 1):
+            note(f"lutnet forms F={F} b={b} o={o} P={P} n={n} batch={batch}")
+            y = torch.full((batch * n + 64,), 0xEE, dtype=torch.uint8, device="cuda")
+            net.run(x[:batch], y[: batch * n].view(batch, n))
+            torch.cuda.synchronize()
+            assert torch.equal(y[: batch * n].view(batch, n), pieces[:batch])
+            assert (y[batch * n:] == 0xEE).all()
+    rows = np.r_[0:100, limit - 100:limit + 1]
+    at = torch.from_numpy(rows).cuda()
+    want = lutnet.evaluate(ns, [fanin[i, :int(ns.F[i])] for i in range(n)], P, x[at].cpu().numpy())
+    assert np.array_equal(pieces[at].cpu().numpy(), want)
