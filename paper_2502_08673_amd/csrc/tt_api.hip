@@ -436,9 +436,11 @@ int upload_async(void* dst, std::vector<uint8_t>* blob, hipStream_t s) {
 // most kStageSlots buffers of kStageBytes, made whole (64 KiB take as long)
 // and never freed or grown, which would wait for the whole device; a call holds one until it
 // has queued its work, and the next user takes it once the event recorded
-// behind that work has passed.  No call waits for that: the work may be on
-// any stream, behind anything.  Inputs that are larger, calls that find no
-// buffer free, and streams under capture (a graph reads its source on every
+// behind that work has passed.  With all of them in use a call waits for the
+// oldest of its own stream (as the pageable path would for the whole stream:
+// 64 us a call where that takes 68), never for another's, whose work may be
+// behind anything.  Inputs that are larger, calls that get no buffer so, and
+// streams under capture (a graph reads its source on every
 // replay, so it keeps one of its own) take the pageable path, which waits for
 // nothing but its own stream.
 constexpr size_t kStageBytes = 1u << 20;
@@ -447,9 +449,12 @@ struct StageSlot {
   uint8_t* host = nullptr;
   hipEvent_t done = nullptr;
   bool busy = false, pending = false;
+  hipStream_t stream = nullptr;  // of the last use, which was the use-th
+  uint64_t use = 0;
 };
 std::mutex g_stage_mu;
 std::map<int, std::vector<StageSlot*>> g_stage;
+uint64_t g_stage_uses = 0;
 
 // While it lives, the thread's calls are no part of a capture that is open on
 // some other stream: asking for an event or allocating host memory would end
@@ -491,9 +496,23 @@ int stage_acquire(size_t bytes, hipStream_t s, StageSlot** slot) {
       got = new (std::nothrow) StageSlot();
       if (got) slots.push_back(got);
     }
+    // (one handle names the per-thread default streams of all threads)
+    for (size_t k = 0; k < slots.size() && s != hipStreamPerThread && (!got || got->pending); ++k) {
+      StageSlot* c = slots[k];
+      if (!c->busy && c->pending && c->stream == s && (!got || c->use < got->use)) got = c;
+    }
     if (!got) return TT_OK;
     got->busy = true;
+    got->stream = s;
+    got->use = ++g_stage_uses;
   }
+  if (got->pending && hipEventSynchronize(got->done) != hipSuccess) {
+    std::lock_guard<std::mutex> lk(g_stage_mu);
+    got->busy = false;  // and still pending
+    (void)hipGetLastError();
+    return TT_OK;
+  }
+  got->pending = false;
   hipError_t e = got->done ? hipSuccess : hipEventCreateWithFlags(&got->done, hipEventDisableTiming);
   if (e == hipSuccess && !got->host) e = hipHostMalloc((void**)&got->host, kStageBytes, hipHostMallocDefault);
   if (e != hipSuccess) {
