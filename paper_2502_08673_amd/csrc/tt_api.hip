@@ -137,6 +137,7 @@ struct PlanHost {
   int n = 0;
   uint64_t total_words = 0;
   tt_tune tune{};
+  bool tuned = false;  // the caller's setting, else the default
   unsigned flags = 0;
   const tt_neuron* desc = nullptr;  // [n]: the caller's, or (a plan's) own
   std::vector<tt_neuron> own;
@@ -182,7 +183,8 @@ void build_table_lists(PlanHost& P) {
 
 // One 256-word unit per wave and eight waves per block, streaming stores:
 // 0.33 ms for the 2 GiB of 512 neurons of 2^24 rows, where four waves of four
-// units take 0.37 ms (more blocks in flight, shorter bursts of each).
+// units take 0.37 ms (more blocks in flight, shorter bursts of each).  Groups
+// of few blocks take more units a wave (default_units).
 tt_tune default_tune() {
   tt_tune t;
   t.chunk_words = 2048;
@@ -200,6 +202,18 @@ int check_tune(const tt_tune& t) {
   if (t.waves != 4 && t.waves != 8) return TT_EINVAL;
   if (t.tile_neurons != 8 && t.tile_neurons != 16 && t.tile_neurons != 32) return TT_EINVAL;
   return TT_OK;
+}
+
+// Units a wave of a wide group where the caller has no setting: one, but more
+// where the mask table that every block loads first is as large as they get
+// (four-bit digits, weights near the int8 limits: up to 18 KiB) and the blocks
+// are a few rounds of the chip.  512 neurons of 2^20 rows, o = 3: 51.6 us with
+// one unit, 48.0 with two, 49.0 with four; o = 1: 26.0, 24.9, 24.4; 32 neurons
+// of 2^24 rows, o = 1: 22.0, 19.4, 18.8.  With weights of up to 7 two units
+// gain nothing (20.9 and 20.2, 31.2 and 31.7 us).
+int default_units(long units, int o, int lut_entries) {
+  const long blocks = units / 8;
+  return lut_entries <= 1792 || blocks < 2048 || blocks >= 8192 ? 1 : o == 1 ? 4 : 2;
 }
 
 // A neuron of the small kernel takes a block when its tables have 512 words
@@ -282,7 +296,7 @@ void build_plan(PlanHost& P) {
     // words per item: chunk_words / (256 * waves), a power of two in
     // [1, kWideMaxUpw] with waves * upw at most the neuron's units
     const int nw = P.tune.waves;
-    int upw = 1;
+    int upw = P.tuned ? 1 : default_units((long)mem.size() << (G.wide_wb - 8), G.o, G.wide_lds);
     while (upw * 2 <= P.tune.chunk_words / (256 * nw) && upw * 2 <= kWideMaxUpw) upw *= 2;
     while (upw > 1 && nw * upw > (1 << (G.wide_wb - 8))) upw /= 2;
     G.wide_upw = upw;
@@ -1163,6 +1177,7 @@ int tt_plan_create(const tt_neuron* h_desc, int n, uint64_t total_words, const t
   p->host.n = n;
   p->host.total_words = total_words;
   p->host.tune = t;
+  p->host.tuned = tune != nullptr;
   p->host.flags = flags;
   p->host.own.assign(h_desc, h_desc + n);
   p->host.desc = p->host.own.data();

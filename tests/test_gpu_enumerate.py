@@ -769,3 +769,36 @@ def test_captured_noalloc_replays_its_own_descriptors():
         assert np.array_equal(hist.cpu().numpy().reshape(-1, 8).astype(np.uint32), ref["hist"])
     del graph
     check_canary(tables, total)
+
+
+@pytest.mark.parametrize("o", [1, 2, 3])
+def test_default_units_of_the_largest_mask_tables(o):
+    """Four-bit digits with weights near the int8 limits, around the number of
+    blocks from which the default gives a wave more units (256 neurons of 2^14
+    words per plane): the plan without a setting and the one-shot call against
+    a setting of one unit, and two neurons against the oracle."""
+    one = {"chunk_words": 2048, "blocks_per_cu": 2, "waves": 8, "nontemporal": 1, "tile_neurons": 32}
+    for n in (255, 256, 300):
+        ns = random_neurons(seed=870 + o, n=n, F=(5, 5), b=(4, 4), o=(o, o), max_fb=20, wmax=127)
+        desc = tt.descriptors(ns)
+        total = tt.layout(desc)
+        got = []
+        for name, tune in (("one unit", one), ("default", None), ("one-shot", None)):
+            tables = device_tables(total)
+            hist = torch.full((n * 8,), -1, dtype=torch.int32, device="cuda")
+            note(f"default units o={o} n={n} {name}")
+            if name == "one-shot":
+                tt.enumerate(desc, tables, total_words=total, hist=hist)
+            else:
+                with tt.Plan(desc, total, tune=tune, flags=tt.TT_PLAN_PERSISTENT) as plan:
+                    plan.launch(tables, hist)
+                    torch.cuda.synchronize()
+            torch.cuda.synchronize()
+            check_canary(tables, total)
+            got.append((tables, hist))
+        for tables, hist in got[1:]:
+            assert torch.equal(tables, got[0][0]) and torch.equal(hist, got[0][1])
+        ref = oracle.enumerate(subset(ns, np.array([0, n - 1])))
+        W = o << 14
+        assert np.array_equal(host_u64(tables, 0, W), ref["planes"][:W])
+        assert np.array_equal(host_u64(tables, total - W, total), ref["planes"][W:])
