@@ -771,6 +771,33 @@ def test_captured_noalloc_replays_its_own_descriptors():
     check_canary(tables, total)
 
 
+@pytest.mark.parametrize("waves", [4, 8])
+def test_units_per_wave_of_wide_tables(waves):
+    """1 to 32 units of 256 words per wave of the wide kernel (as many as the
+    table has for the smallest), streaming stores and others, small weights
+    and the largest mask tables, against the oracle."""
+    ns = concat([random_neurons(seed=860, n=4, F=(6, 6), b=(3, 3), max_fb=18),
+                 random_neurons(seed=861, n=3, F=(7, 7), b=(3, 3), max_fb=21),
+                 random_neurons(seed=862, n=3, F=(5, 5), b=(4, 4), max_fb=20, wmax=127)])
+    desc = tt.descriptors(ns)
+    total = tt.layout(desc)
+    ref = oracle.enumerate(ns)
+    tables = device_tables(total)
+    hist = torch.zeros(len(ns) * 8, dtype=torch.int32, device="cuda")
+    for k in range(6):
+        tune = {"chunk_words": 256 * waves << k, "blocks_per_cu": 2, "waves": waves, "nontemporal": k % 2,
+                "tile_neurons": 32}
+        note(f"wide units waves={waves} per wave={1 << k}")
+        with tt.Plan(desc, total, tune=tune, flags=tt.TT_PLAN_PERSISTENT) as plan:
+            tables[:total].fill_(-1 - k)
+            hist.fill_(-1)
+            plan.launch(tables, hist)
+            torch.cuda.synchronize()
+        assert np.array_equal(host_u64(tables, 0, total), ref["planes"]), k
+        assert np.array_equal(hist.cpu().numpy().reshape(-1, 8).astype(np.uint32), ref["hist"]), k
+    check_canary(tables, total)
+
+
 @pytest.mark.parametrize("o", [1, 2, 3])
 def test_default_units_of_the_largest_mask_tables(o):
     """Four-bit digits with weights near the int8 limits, around the number of
@@ -802,3 +829,39 @@ def test_default_units_of_the_largest_mask_tables(o):
         W = o << 14
         assert np.array_equal(host_u64(tables, 0, W), ref["planes"][:W])
         assert np.array_equal(host_u64(tables, total - W, total), ref["planes"][W:])
+
+
+def test_graph_of_wide_neurons_replays_and_is_recorded_again():
+    """A plan with wide neurons launches from a recorded graph (one launch
+    alone would be made directly): replays with the same pointers, whose
+    histogram is added up from zero each time, and other pointers midway, for
+    the enumeration and for the whole step, with eager work in between."""
+    ns = concat([cfg2(n=200), random_neurons(seed=880, n=5, F=(6, 6), b=(3, 3), max_fb=18),
+                 random_neurons(seed=881, n=2, F=(7, 7), b=(3, 3), max_fb=21, wmax=40)])
+    desc = tt.descriptors(ns)
+    total = tt.layout(desc)
+    ref = oracle.enumerate(ns)
+    bufs = [(device_tables(total), torch.zeros(len(ns) * 8, dtype=torch.int32, device="cuda"),
+             torch.zeros(len(ns), dtype=torch.uint8, device="cuda")) for _ in range(2)]
+    with tt.Plan(desc, total, flags=tt.TT_PLAN_PERSISTENT | tt.TT_PLAN_GRAPH) as plan:
+        assert plan.info()["wide_neurons"] == 7
+        for call in ("launch", "step"):
+            for rep, k in enumerate((0, 0, 0, 1, 1, 0)):
+                tables, hist, sup = bufs[k]
+                note(f"graph of wide neurons {call} {rep}")
+                tables[:total].fill_(int(np.int64(rep * 7919 - 3)))
+                hist.fill_(rep + 1)
+                sup.fill_(0xEE)
+                torch.cuda.synchronize()
+                if call == "launch":
+                    plan.launch(tables, hist)
+                else:
+                    plan.step(tables, hist, sup)
+                torch.cuda.synchronize()
+                assert np.array_equal(host_u64(tables, 0, total), ref["planes"]), (call, rep)
+                assert np.array_equal(hist.cpu().numpy().reshape(-1, 8).astype(np.uint32), ref["hist"]), (call, rep)
+                if call == "step":
+                    assert np.array_equal(sup.cpu().numpy(), ref["support"]), rep
+                _ = (torch.arange(1000, device="cuda") * 3).sum().item()  # eager work between replays
+    for tables, _, _ in bufs:
+        check_canary(tables, total)
