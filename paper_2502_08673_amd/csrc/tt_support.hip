@@ -410,6 +410,14 @@ __global__ __launch_bounds__(512) void support_first_kernel(SupportArgs a) {
   small_table(a, blk * 512 + (int)threadIdx.x);
 }
 
+// The smallest tables where there are no others: a lane keeps its 48 words,
+// which the first kernel's blocks of eight waves leave it too few registers
+// for (500 tables of 16 words, two planes, support and histogram: 15.5 us there,
+// 10.8 here).
+__global__ __launch_bounds__(256) void support_small_kernel(SupportArgs a) {
+  small_table(a, (int)(blockIdx.x * 256 + threadIdx.x));
+}
+
 // One unit of a larger table: items part, part + units, ... of each pass.
 template <int O>
 __device__ __forceinline__ void scan_table(const SupportArgs& a, const NeuronRegs& d, int k, int n, uint32_t part,
@@ -495,6 +503,10 @@ __global__ __launch_bounds__(256) void support_finish_kernel(SupportArgs a) {
 
 hipError_t launch_support_tables(const SupportArgs& a, int cus, hipStream_t s) {
   if (a.n <= 0) return hipSuccess;
+  if (a.n_large == 0 && a.n_medium == 0) {
+    hipLaunchKernelGGL(support_small_kernel, dim3((unsigned)((a.n + 255) / 256)), dim3(256), 0, s, a);
+    return hipGetLastError();
+  }
   const long first = (long)a.n_large + (a.n_medium + 7) / 8 + (a.n_small > 0 ? (a.n + 511) / 512 : 0);
   hipLaunchKernelGGL(support_first_kernel, dim3((unsigned)first), dim3(512), 0, s, a);
   hipError_t e = hipGetLastError();

@@ -865,3 +865,28 @@ def test_graph_of_wide_neurons_replays_and_is_recorded_again():
                 _ = (torch.arange(1000, device="cuda") * 3).sum().item()  # eager work between replays
     for tables, _, _ in bufs:
         check_canary(tables, total)
+
+
+@pytest.mark.parametrize("n", [1, 255, 256, 257, 1000])
+def test_support_of_small_tables_alone(n):
+    """Tables of up to 16 words per plane and no others (a kernel of their
+    own), all output widths, around a block's 256 neurons: support and
+    histogram together and apart against the oracle."""
+    ns = random_neurons(seed=890 + n, n=n, F=(1, 5), b=(1, 4), max_fb=10)
+    desc = tt.descriptors(ns)
+    total = tt.layout(desc)
+    ref = oracle.enumerate(ns)
+    tables = device_tables(total)
+    tables[:total] = torch.from_numpy(ref["planes"].view(np.int64)).cuda()
+    sup = torch.zeros(n, dtype=torch.uint8, device="cuda")
+    hist = torch.zeros(n * 8, dtype=torch.int32, device="cuda")
+    note(f"support of small tables n={n}")
+    for s, h in ((sup, hist), (sup, None), (None, hist)):
+        sup.fill_(0xEE)
+        hist.fill_(-1)
+        tt.support(desc, tables, support_out=s, hist=h)
+        torch.cuda.synchronize()
+        if s is not None:
+            assert np.array_equal(sup.cpu().numpy(), ref["support"])
+        if h is not None:
+            assert np.array_equal(hist.cpu().numpy().reshape(-1, 8).astype(np.uint32), ref["hist"])
