@@ -371,13 +371,14 @@ typedef struct tt_cnf tt_cnf;
 int tt_cnf_create(const int32_t* h_lits, const int32_t* h_clause_off, const int32_t* h_inst_off, int n_inst,
                   const int32_t* h_n_vars, void* stream, tt_cnf** cnf);
 
-/* Transform the staged instances, one wave each; asynchronous on stream, no
- * allocation.  Device outputs: d_var_class, for instance t at offset
- * sum_{u<t} (h_n_vars[u] + 1), one byte per variable 0 .. n_vars of
- * TT_CNF_CLS_* bits; d_expr, instance t's expressions at d_expr[h_inst_off[t]
- * ...] in the order found (capacity: one per clause); d_n_expr[t] their
- * count; d_status[t] 0, or 1 when an SC grew past TT_CNF_MAX_VARS variables
- * (the instance stops there; what it found before is kept). */
+/* Transform the staged instances, eight to a wave while their SCs stay within
+ * five variables, else one; asynchronous on stream, no allocation.  Device
+ * outputs: d_var_class, for instance t at offset sum_{u<t} (h_n_vars[u] + 1),
+ * one byte per variable 0 .. n_vars of TT_CNF_CLS_* bits; d_expr, instance t's
+ * expressions at d_expr[h_inst_off[t] ...] in the order found (capacity: one
+ * per clause); d_n_expr[t] their count; d_status[t] 0, or 1 when an SC grew
+ * past TT_CNF_MAX_VARS variables (the instance stops there; what it found
+ * before is kept). */
 int tt_cnf_run(const tt_cnf* cnf, uint8_t* d_var_class, tt_cnf_expr* d_expr, int32_t* d_n_expr, int32_t* d_status,
                void* stream);
 

@@ -270,7 +270,8 @@ def support(desc, tables, support_out=None, hist=None, stream=None) -> None:
 
 
 class Plan:
-    """Batched enumeration plan (persistent work queue, optional hipGraph)."""
+    """Batched enumeration plan: descriptors and lists staged once, the tables of each step in one launch or a few
+    (optionally replayed from a hipGraph)."""
 
     def __init__(self, desc, total_words: int, tune: Optional[dict] = None,
                  flags: int = TT_PLAN_PERSISTENT | TT_PLAN_GRAPH):

@@ -1,6 +1,7 @@
 // tt_api.hip -- host side of libtt.so: validation, layout, the planner
-// (grouping, tiling, work queue), plan workspace, graph capture, the
-// autotuner and the one-shot entry points declared in include/tt.h.
+// (neurons by class and size), plan workspace, graph capture, the autotuner,
+// the staging of the one-shot calls and the entry points declared in
+// include/tt.h.
 #include <algorithm>
 #include <chrono>
 #include <climits>

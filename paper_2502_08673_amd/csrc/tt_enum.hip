@@ -352,8 +352,8 @@ __device__ __forceinline__ void small_tables(const SmallArgs& a, const NeuronReg
       }
     }
     if (!a.hist) return;
-    // the wave's rows number at most 2^16 - 64 per packed half (tables of
-    // 1024 words are shared by at least two waves)
+    // a wave takes at most 256 words, 2^14 rows: the packed halves hold the sums
+    static_assert((1024 / kSmallWaves) * 64 < (1 << 16), "tables of up to 2^10 words, 512 and more by a block's waves");
 #pragma unroll
     for (int q = 0; q < NC; ++q) {
       const uint32_t t = (uint32_t)__builtin_amdgcn_readlane((int)wave_sum_last(cnt[q]), 63);

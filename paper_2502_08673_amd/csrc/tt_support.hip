@@ -511,9 +511,10 @@ hipError_t launch_support_tables(const SupportArgs& a, int cus, hipStream_t s) {
   hipLaunchKernelGGL(support_first_kernel, dim3((unsigned)first), dim3(512), 0, s, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || a.n_large <= 0) return e;
-  // one to two rounds of resident waves, at most one unit per item; a power of
-  // two, as the items are, so that every unit of a neuron gets as many (100
-  // tables of 2^24 rows: 16 units a compute unit at most 189 us, 32: 143, 64: 138)
+  // up to 64 waves a compute unit (four rounds of those resident), at most one
+  // unit per item; a power of two, as the items are, so that every unit of a
+  // neuron gets as many (100 tables of 2^24 rows: 16 units a compute unit at
+  // most 189 us, 32: 143, 64: 138)
   long U = 1;
   while (2 * U <= a.max_items && 2 * U * a.n_large <= 64L * cus) U *= 2;
   const long waves = (long)a.n_large * U;
