@@ -753,9 +753,10 @@ def bench_screen(args):
     cost_learned = sc.row_cost(c, runner.mask.cpu().numpy(), runner.accept.cpu().numpy())
     accept_rate = float(runner.accept.float().mean().item())
 
-    # The host-built batched plan on the same candidates (persistent
-    # enumeration with fused histogram, then support): plain enumeration at
-    # its fastest, plan creation and tuning outside the timed region.
+    # The host-built batched plan on the same candidates, plan creation and
+    # tuning outside the timed region: enumeration with fused histogram, then
+    # the support of the tables as tables; and the whole step, whose support
+    # follows from the parameters (plain enumeration at its fastest).
     ptab = torch.empty(c.total_words, dtype=torch.int64, device="cuda")
     psup = torch.zeros(c.n, dtype=torch.uint8, device="cuda")
     phist = torch.zeros(c.n * 8, dtype=torch.int32, device="cuda")
@@ -770,6 +771,10 @@ def bench_screen(args):
     torch.cuda.synchronize()
     ok_batched = (bool(torch.equal(psup, ref_sup)) and bool(torch.equal(phist, ref_hist))
                   and bool(torch.equal(ptab, ref_tables)))
+    psup.zero_()
+    t_step = sc.timed(lambda: pplan.step(ptab, phist, psup), reps)
+    torch.cuda.synchronize()
+    ok_batched = ok_batched and bool(torch.equal(psup, ref_sup)) and bool(torch.equal(phist, ref_hist))
     pplan.close()
     rows = c.ns.total_rows()
     return {
@@ -797,6 +802,7 @@ def bench_screen(args):
             "speedup_learned_vs_plain": t_plain / t_learned, "speedup_trivial_vs_plain": t_plain / t_trivial,
             "speedup_learned_vs_trivial": t_trivial / t_learned, "speedup_ideal_vs_trivial": t_trivial / t_ideal,
             "plain_batched_plan_ms": t_batched, "speedup_learned_vs_batched_plan": t_batched / t_learned,
+            "plain_plan_step_ms": t_step, "speedup_learned_vs_plan_step": t_step / t_learned,
             "exact_batched_plan": ok_batched,
             "rows_plain": rows, "rows_trivial": cost_trivial, "rows_learned": cost_learned, "rows_ideal": cost_ideal,
             "accept_rate_learned": accept_rate,
