@@ -449,15 +449,14 @@ int upload_async(void* dst, std::vector<uint8_t>* blob, hipStream_t s) {
 // first waits for the stream, and the host callback that frees it costs as
 // much as the launches (45 us a call in all, 20 with these).  Per device at
 // most kStageSlots buffers of kStageBytes, made whole (64 KiB take as long)
-// and never freed or grown, which would wait for the whole device; a call holds one until it
-// has queued its work, and the next user takes it once the event recorded
-// behind that work has passed.  With all of them in use a call waits for the
-// oldest of its own stream (as the pageable path would for the whole stream:
-// 64 us a call where that takes 68), never for another's, whose work may be
-// behind anything.  Inputs that are larger, calls that get no buffer so, and
-// streams under capture (a graph reads its source on every
-// replay, so it keeps one of its own) take the pageable path, which waits for
-// nothing but its own stream.
+// and never freed or grown, which would wait for the whole device; a call holds
+// one until it has queued its work, and the next user takes it once the event
+// recorded behind that work has passed.  With all of them in use a call waits
+// for the oldest of its own stream (as the pageable path would for the whole
+// stream), never for another's, whose work may be behind anything.  Inputs that
+// are larger, calls that get no buffer so, and streams under capture (a graph
+// reads its source on every replay, so it keeps one of its own) take the
+// pageable path, which waits for nothing but its own stream.
 constexpr size_t kStageBytes = 1u << 20;
 constexpr int kStageSlots = 16;
 struct StageSlot {

@@ -410,10 +410,11 @@ __global__ __launch_bounds__(512) void support_first_kernel(SupportArgs a) {
   small_table(a, blk * 512 + (int)threadIdx.x);
 }
 
-// The smallest tables where there are no others: a lane keeps its 48 words,
-// which the first kernel's blocks of eight waves leave it too few registers
-// for (500 tables of 16 words, two planes, support and histogram: 15.5 us there,
-// 10.8 here).
+// The smallest tables where there are no others, in blocks of four waves: the
+// first kernel's blocks of eight put twice the waves on a CU while others idle.
+// Same instructions and registers, 2 / 4 / 8 waves a block, support and
+// histogram: 500 tables of 16 words, two planes, 9.3 / 10.6 / 15.6 us; 20000,
+// three planes, 12.1 / 14.1 / 19.4; 50000, two planes, 16.9 / 14.6 / 18.0.
 __global__ __launch_bounds__(256) void support_small_kernel(SupportArgs a) {
   small_table(a, (int)(blockIdx.x * 256 + threadIdx.x));
 }
